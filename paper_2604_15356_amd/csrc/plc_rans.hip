@@ -19,6 +19,8 @@
 // registers.
 #include "plc_device.h"
 
+#include <type_traits>
+
 namespace plc {
 namespace {
 
@@ -789,24 +791,33 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 }
 
 // ---------------------------------------------------------------------------
-// Encoder for few, long units: three wavefronts per unit
+// Encoder for few, long units: four wavefronts per unit
 // ---------------------------------------------------------------------------
-// When there are no more units than compute units, time is the length of one unit's chain of steps,
-// and a lone wavefront issues in order: an independent vector instruction every ~4.3 cycles, one that needs
-// the previous result after ~9, an LDS instruction every 8-16.  So everything that is not the state
-// recurrence moves to two helper wavefronts of the same workgroup, which run on other SIMDs of the compute
-// unit:
-//   feeder  stages the symbols (64 groups ahead, as above) and turns every (group, lane) of the next
-//           batch into its 16-byte table entry at a fixed place of an LDS ring; a lane without a symbol
-//           (ragged top group, or a step past the unit's first group) gets an identity entry;
-//   coder   per step: one LDS read of its entry, one LDS write of its state before the step, and the
-//           recurrence itself -- no ranking, no addresses to compute, no branches;
-//   packer  one batch behind, recovers from the stored states which lanes emitted (x > thr), ranks
-//           them with one ballot per two steps, packs the 16-bit words and writes them out.
-// The three meet at one workgroup barrier per batch of 16 steps.
-constexpr int kEntrySlots = 3;  // feeder writes b+1, coder reads b, packer reads b-1
-constexpr int kStateSlots = 2;  // coder writes b, packer reads b-1
-constexpr int kIdentity = PLC_MAX_BITS * 256;  // table index of the entry that leaves a state unchanged
+// When there are no more units than compute units, time is the length of one unit's chain of steps.  A lone
+// wavefront issues one instruction every 4.64 cycles whether or not it needs the result of the one before
+// (measured on gfx950, v_mul_hi_u32 and the SDWA forms included; s_nop 1 takes 8.6, ds_read_b128 11, ds_write_b32
+// 15), so a step costs its instruction count, wait states included -- and everything that is not the state
+// recurrence moves to three helper wavefronts of the same workgroup, one per SIMD of the compute unit:
+//   mover   brings the symbols from HBM to LDS (64 groups ahead) and the words from LDS to HBM;
+//   feeder  turns every (group, lane) of a batch into its 16-byte table entry at a fixed place of an LDS
+//           ring; a lane without a symbol (ragged top group, or a step past the unit's first group) gets an
+//           identity entry.  It runs two batches ahead of the coder, so that the coder can ask for the next
+//           batch's first entries before the barrier;
+//   coder   the recurrence alone: six vector instructions a step, an entry read in the wait states behind the
+//           compare, and one LDS write of the four states of four steps;
+//   packer  recovers from the stored states which lanes emitted (x > thr), ranks them with one ballot per two
+//           steps and packs the 16-bit words into an LDS region per batch.
+// They meet at one workgroup barrier per batch of 16 steps.  The coder writes its last four states of a batch in
+// the batch after (and waits for nothing at a barrier), so the packer works two batches behind it.
+// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer batch it - 4.  The mover takes in a round
+// of symbols every fourth iteration and sends the words of two batches out in each of the two after it: waiting
+// for symbols is waiting for every store before them as well (one counter), and these are then two iterations
+// old (stores in every iteration held the barrier up every round).
+constexpr int kEntrySlots = 5;  // feeder writes b + 2, coder reads b and b + 1, packer reads b - 2
+constexpr int kStateSlots = 3;  // coder writes b and the end of b - 1, packer reads b - 2
+constexpr int kListRegion = 2 * kBatchSyms + 8;  // the words of a pair of batches behind up to seven carried ones
+constexpr int kListRegions = 3;  // the packer's, and the up to two in front of it that have not left
+constexpr int kPipeThreads = 256;
 // These kernels hold two units per compute unit (LDS), 512 at a time, and a unit's time is that of its chain:
 // up to two rounds they beat the many-unit kernels (768 units: encode 1.7 against 2.8 ms, decode 3.3 against
 // 4.9 ms), at three they tie with them.
@@ -822,54 +833,75 @@ constexpr int64_t kDenseStreams = 512;
 constexpr int kCompactMaxK = 4;  // up to here four workgroups of the decoder with 4-byte entries fit a compute unit
 constexpr int kDenseMaxK = 6;  // up to here the kernel's registers (156 at k = 6) leave room for three wavefronts per SIMD
 
-template <bool LONG>
-__device__ __forceinline__ void pipe_step(uint32_t &x, const uint4 e) {
+// One step, in this order: the instructions between the compare and the select that reads its result (`fill`:
+// the caller's LDS accesses) take the place of the wait states the hardware asks for there.
+template <bool LONG, typename Fill>
+__device__ __forceinline__ void pipe_step(uint32_t &x, const u32x4 e, Fill fill) {
   const bool emit = x > e.y;
-  const uint32_t xr = emit ? x >> 16 : x;
+  PLC_PIN();
+  fill();
+  PLC_PIN();
+  const uint32_t xr = emit ? x >> 16 : x;  // one instruction: the select takes the high half as its operand
+  PLC_PIN();
   const uint32_t t1 = __umulhi(e.x, xr);
   const uint32_t q = (LONG ? t1 + xr : t1) >> (e.z >> 24);
   x = __umul24(q, e.z) + (xr + e.w);
+  PLC_PIN();
 }
 
-// One batch of the coder.  Entries are fetched kAhead steps before their use, so that the LDS round
-// trip (longer than a step while the helpers are busy on the same LDS) stays off the chain.
+// One batch of the coder.  `e` holds the entries of its first four steps on entry and those of the next
+// batch's first four (at `next`) on return.  A lane's states before steps 4 q .. 4 q + 3 leave as one 16-byte
+// vector for xb[q], behind the first compare of the four steps after them: `before` holds the last four on
+// return and `held`, where they belong, those of the batch before on entry.
 template <bool LONG>
-__device__ __forceinline__ void pipe_batch(uint32_t &x, const uint4 *eb, uint32_t *xb) {
-  constexpr int kAhead = 4;
-  uint4 e[kAhead];
+__device__ __forceinline__ void pipe_batch(uint32_t &x, u32x4 (&e)[2][4], u32x4 &before, u32x4 *&held,
+                                           const u32x4 *eb, const u32x4 *next, u32x4 *xb) {
 #pragma unroll
-  for (int j = 0; j < kAhead; ++j) e[j] = eb[j * kLanes];
-  uint32_t x_even = 0;
-#pragma unroll
-  for (int j = 0; j < kBatch; ++j) {
-    const uint4 cur = e[j % kAhead];
-    PLC_PIN();
-    if (j + kAhead < kBatch) e[j % kAhead] = eb[(j + kAhead) * kLanes];
-    if (j & 1) {  // the states before steps j - 1 and j leave in one LDS instruction
-      xb[(j - 1) * kLanes] = x_even;
-      xb[j * kLanes] = x;
-    } else {
-      x_even = x;
-    }
-    PLC_PIN();
-    pipe_step<LONG>(x, cur);
+  for (int q = 0; q < kBatch / 4; ++q) {
+    u32x4 (&cur)[4] = e[q & 1];
+    u32x4 (&nxt)[4] = e[(q & 1) ^ 1];
+    const u32x4 *src = q + 1 < kBatch / 4 ? eb + 4 * (q + 1) * kLanes : next;
+    const u32x4 done = before;
+    // the four entries were asked for two steps ago and more; all of them in one wait
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    before.x = x;
+    pipe_step<LONG>(x, cur[0], [&] {
+      *held = done;
+      PLC_PIN();
+      nxt[0] = src[0];
+    });
+    before.y = x;
+    pipe_step<LONG>(x, cur[1], [&] {
+      nxt[1] = src[kLanes];
+      PLC_PIN();
+      nxt[2] = src[2 * kLanes];
+      PLC_PIN();
+      nxt[3] = src[3 * kLanes];
+    });
+    before.z = x;
+    pipe_step<LONG>(x, cur[2], [&] {});
+    before.w = x;
+    pipe_step<LONG>(x, cur[3], [&] {});
+    held = xb + q * kLanes;
   }
 }
 
 template <bool ADAPT>  // ADAPT: one table per bit depth (the *_bucketed call)
-__global__ __launch_bounds__(192) void rans_encode_pipe_kernel(const RansArgs a) {
+__global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const RansArgs a) {
+  constexpr int kIdentity = (ADAPT ? PLC_MAX_BITS : 1) * 256;  // index of the entry that leaves a state unchanged
   __shared__ uint4 table[kIdentity + 1];
   __shared__ uint16_t table_of_group[2][kSuperGroups];  // ADAPT: table offset of each group of a staging round
   __shared__ uint4 entry_ring[kEntrySlots][kBatch][kLanes];
-  __shared__ uint32_t state_ring[kStateSlots][kBatch][kLanes];
+  __shared__ uint4 state_ring[kStateSlots][kBatch / 4][kLanes];
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
-  __shared__ __attribute__((aligned(16))) uint16_t word_stage[2 * kBatchSyms + 8 + 64];  // list, carry, idle slots
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(16))) uint16_t word_list[kListRegions + 1][kListRegion];  // + 1: spare, see below
+  __shared__ uint32_t list_fill[kListRegions];  // positions in use of each region of the list
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t unit = blockIdx.x;  // one unit per stream, one workgroup per unit
 
   bool long_form = false;
-  {  // every wavefront scans the frequencies; of a lane's four entries the coder builds one, the feeder
-     // one and the packer two
+  {  // every wavefront scans the frequencies and builds one of a lane's four entries
     const int n_tables = ADAPT ? a.n_tables : 1;
     uint32_t f[ADAPT ? PLC_MAX_BITS : 1][4], cum[ADAPT ? PLC_MAX_BITS : 1];
     for (int t = 0; t < n_tables; ++t) {
@@ -880,7 +912,7 @@ __global__ __launch_bounds__(192) void rans_encode_pipe_kernel(const RansArgs a)
     for (int t = 0; t < n_tables; ++t) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if ((r < 2 ? r : 2) == wave)
+        if (r == wave)
           table[t * 256 + lane * 4 + r] =
               long_form ? make_enc_entry<true>(f[t][r], cum[t]) : make_enc_entry<false>(f[t][r], cum[t]);
         cum[t] += f[t][r];
@@ -888,7 +920,6 @@ __global__ __launch_bounds__(192) void rans_encode_pipe_kernel(const RansArgs a)
     }
     if (threadIdx.x == 0) table[kIdentity] = make_uint4(0u, 0xffffffffu, 0u, 0u);  // never emits, x' = x
   }
-  __syncthreads();
 
   const uint32_t len = (uint32_t)a.syms_per_stream;
   const uint8_t *ubase = a.sym_in + unit * a.syms_per_stream;
@@ -906,61 +937,61 @@ __global__ __launch_bounds__(192) void rans_encode_pipe_kernel(const RansArgs a)
     return g > 0 ? g : 0;
   };
   const int32_t n_rounds = (n_batches + 3) / 4;
-
-  uint32_t x = kLow;              // coder
-  bool bad_symbol = false;        // feeder
-  bool bad_depth = false;
-  uint4 nv[kStagePieces];         // feeder: next round's symbols in flight
-  bool ntake[kStagePieces];
-  uint32_t ntog = 0;              // feeder, ADAPT: table offset of group bottom + lane of the next round
-  // packer: the word list, as in the single-wavefront encoder
+  const int32_t n_iters = n_batches + 4;
   uint16_t *wp = a.words_out + a.word_off[unit];
   const uint32_t pad = __builtin_amdgcn_readfirstlane((uint32_t)((reinterpret_cast<uintptr_t>(wp) >> 1) & 7u));
-  const uint32_t cap = a.word_cap < 0x7fffffffull ? (uint32_t)a.word_cap : 0x7fffffffu;
-  uint32_t vbase = 0, fill = pad;
 
-  auto round_load = [&](int32_t r) {
-    const int64_t lo = (int64_t)round_bottom(r) * kLanes;
-    int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
-    hi = hi < (int64_t)len ? hi : (int64_t)len;
+  if (wave == 0) {
+    // ---- coder: batch it - 2
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    uint32_t x = kLow;
+    u32x4 e[2][4], before = {0u, 0u, 0u, 0u};
+    const u32x4 *const entries = reinterpret_cast<const u32x4 *>(&entry_ring[0][0][lane & 31]);
+    u32x4 *const states = reinterpret_cast<u32x4 *>(&state_ring[0][0][lane & 31]);
+    u32x4 *held = states + (kStateSlots - 1) * (kBatch / 4) * kLanes;  // (read by nobody yet)
+    lds_barrier();  // iteration 0
 #pragma unroll
-    for (int i = 0; i < kStagePieces; ++i) {
-      const int64_t off = lo - (int64_t)mis + (int64_t)(lane + 64 * i) * 16;  // 16-byte aligned in absolute address
-      ntake[i] = r < n_rounds && off < hi;
-      if (ntake[i]) nv[i] = load16_stream(ubase + off);
+    for (int j = 0; j < 4; ++j) e[0][j] = entries[j * kLanes];
+    lds_barrier();  // iteration 1
+    auto code = [&](auto long_form_c) {  // a loop per form, and little in it besides the steps
+      constexpr bool kLong = decltype(long_form_c)::value;
+      constexpr int kEntryStep = kBatch * kLanes, kStateStep = (kBatch / 4) * kLanes;
+      int at = 0, sat = 0;  // uniform
+      const u32x4 *eb = entries;
+      for (int32_t b = 0; b < n_batches; ++b) {
+        at = at == (kEntrySlots - 1) * kEntryStep ? 0 : at + kEntryStep;
+        const u32x4 *next = entries + at;
+        pipe_batch<kLong>(x, e, before, held, eb, next, states + sat);
+        sat = sat == (kStateSlots - 1) * kStateStep ? 0 : sat + kStateStep;
+        eb = next;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();  // iteration b + 2
+        asm volatile("" ::: "memory");
+      }
+    };
+    if (long_form) {
+      code(std::true_type{});
+    } else {
+      code(std::false_type{});
     }
-    if (ADAPT) {
-      const int32_t g = round_bottom(r) + lane;
-      ntog = (r < n_rounds && g < batch_top(4 * r)) ? group_table(a, unit, 0, g, 256u, &bad_depth) : 0u;
-    }
-  };
-  auto round_store = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < kStagePieces; ++i)
-      if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
-    if (ADAPT) table_of_group[buf][lane] = (uint16_t)ntog;
-  };
-  if (wave == 1) {
-    round_load(0);
-    round_store(0);
-    round_load(1);
-  }
-
-  int eslot_feed = 0, eslot_code = 0, eslot_pack = 0, sslot_code = 0, sslot_pack = 0;
-  for (int32_t it = 0; it < n_batches + 2; ++it) {
-    if (wave == 1) {
-      // ---- feeder: entries of batch `it`
+    *held = before;  // the last four states, in place before the barrier behind them
+    for (int32_t it = n_batches + 2; it < n_iters; ++it) lds_barrier();
+    if (lane < kLanes) a.states_out[unit * kLanes + lane] = x;
+  } else if (wave == 1) {
+    // ---- feeder: entries of batch it
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    bool bad_symbol = false;
+    int slot = 0;
+    for (int32_t it = 0; it < n_iters; ++it) {
       if (it < n_batches) {
         const int32_t r = it >> 2;
-        if ((it & 3) == 0 && it > 0) {  // first batch of a new round: land it, start the one after
-          round_store(r & 1);
-          round_load(r + 1);
-        }
         const int32_t top = batch_top(it), bottom = round_bottom(r);
         const uint8_t *sb = sym_stage[r & 1];
         // lane (half h, l) serves step 2p + h of the batch: group top - 1 - 2p - h, rANS lane l
         const int half = lane >> 5, l = lane & 31;
-        uint4 *eo = &entry_ring[eslot_feed][half][l];
+        uint4 *eo = &entry_ring[slot][half][l];
         if (it > 0) {
           // 16 full groups: all symbol reads, then all table reads, then all ring writes, so that the LDS
           // round trips overlap instead of queueing one behind the other
@@ -998,106 +1029,145 @@ __global__ __launch_bounds__(192) void rans_encode_pipe_kernel(const RansArgs a)
             eo[2 * p * kLanes] = e;
           }
         }
-        eslot_feed = eslot_feed == kEntrySlots - 1 ? 0 : eslot_feed + 1;
+        slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
       }
-    } else if (wave == 0) {
-      // ---- coder: batch `it - 1`
-      if (it >= 1 && it <= n_batches) {
-        const uint4 *eb = &entry_ring[eslot_code][0][lane & 31];
-        uint32_t *xb = &state_ring[sslot_code][0][lane & 31];
-        if (long_form) {
-          pipe_batch<true>(x, eb, xb);
-        } else {
-          pipe_batch<false>(x, eb, xb);
-        }
-        eslot_code = eslot_code == kEntrySlots - 1 ? 0 : eslot_code + 1;
-        sslot_code ^= 1;
-      }
-    } else {
-      // ---- packer: batch `it - 2`
-      if (it >= 2) {
-        uint32_t top_fill = fill;  // uniform
-        // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first
-        const uint32_t *xs = &state_ring[sslot_pack][lane >> 5][31 - (lane & 31)];
-        const uint32_t *ts = &entry_ring[eslot_pack][lane >> 5][31 - (lane & 31)].y;
-        // In phases, each over all eight step pairs, so that the instructions of a phase do not wait for one
-        // another (a lone wavefront waits out the latency of every dependent instruction): reads, emit
-        // masks, ranks, list positions, stores.  A lane without a word stores into a slot of its own
-        // behind the list instead of sitting out the store.
-        uint32_t xps[kBatch / 2], thrs[kBatch / 2], rank[kBatch / 2], base[kBatch / 2];
-        uint64_t mask[kBatch / 2];
+      lds_barrier();
+    }
+    if (bad_symbol) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0
+  } else if (wave == 2) {
+    // ---- packer: batch it - 4
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    uint32_t fill = pad;  // uniform: positions of the region in use, the first of them not this pair's words
+    int slot = 0, sslot = 0, region = 0;
+    for (int32_t it = 0; it < n_iters; ++it) {
+      const int32_t b = it - 4;
+      if (b >= 0 && b < n_batches) {
+        // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
+        // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
+        const int half = lane >> 5, rl = 31 - (lane & 31);
+        const uint32_t *xs = reinterpret_cast<const uint32_t *>(&state_ring[sslot][0][rl]) + half;
+        const uint32_t *ts = &entry_ring[slot][half][rl].y;
+        uint16_t *list = word_list[region];
+        uint16_t *spare = &word_list[kListRegions][lane];
+        // In phases, each over all eight step pairs: reads, emit masks, list positions, stores.  A lane without
+        // a word stores into a slot of its own instead of sitting out the store.
+        uint32_t xps[kBatch / 2], thrs[kBatch / 2], at[kBatch / 2];
 #pragma unroll
         for (int p = 0; p < kBatch / 2; ++p) {
-          xps[p] = xs[2 * p * kLanes];
+          xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
           thrs[p] = ts[2 * p * kLanes * 4];
         }
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) mask[p] = __ballot(xps[p] > thrs[p]);
-#pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p)
-          rank[p] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[p] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[p], 0u));
-#pragma unroll
         for (int p = 0; p < kBatch / 2; ++p) {
-          base[p] = top_fill;
-          top_fill += (uint32_t)__builtin_popcountll(mask[p]);
+          const uint64_t mask = __ballot(xps[p] > thrs[p]);
+          at[p] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, fill));
+          fill += (uint32_t)__builtin_popcountll(mask);
         }
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) {
-          const bool emit = xps[p] > thrs[p];
-          word_stage[emit ? base[p] + rank[p] : (uint32_t)(2 * kBatchSyms + 8) + (uint32_t)lane] = (uint16_t)xps[p];
+        for (int p = 0; p < kBatch / 2; ++p) *(xps[p] > thrs[p] ? list + at[p] : spare) = (uint16_t)xps[p];
+        if ((b & 1) || b == n_batches - 1) {  // on to the next pair's region
+          if (lane == 0) list_fill[region] = fill;
+          region = region == kListRegions - 1 ? 0 : region + 1;
+          fill &= 7u;
         }
-        eslot_pack = eslot_pack == kEntrySlots - 1 ? 0 : eslot_pack + 1;
-        sslot_pack ^= 1;
-        fill = __builtin_amdgcn_readfirstlane(top_fill);
-        // Every second batch (the list holds two batches' words) the complete 16-byte pieces leave, up
-        // to two per lane, and the incomplete tail moves to the front.
-        if ((it & 1) || it == n_batches + 1) {
-          wave_sync();
-          const uint32_t full = fill / 8;  // at most 129 pieces
-          const bool plain = vbase >= pad && vbase + 8 * full - pad <= cap;
-          if (plain) {
-            uint16_t *dst = wp + (vbase - pad);  // 16-byte aligned
+        slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
+        sslot = sslot == kStateSlots - 1 ? 0 : sslot + 1;
+      }
+      lds_barrier();
+    }
+  } else {
+    // ---- mover: symbols of the coming round, words of batch it - 5
+    bool bad_depth = false;
+    uint4 nv[kStagePieces];         // next round's symbols in flight
+    bool ntake[kStagePieces];
+    uint32_t ntog = 0;              // ADAPT: table offset of group bottom + lane of the next round
+    auto round_load = [&](int32_t r) {
+      const int64_t lo = (int64_t)round_bottom(r) * kLanes;
+      int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
+      hi = hi < (int64_t)len ? hi : (int64_t)len;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-              if ((uint32_t)(lane + 64 * h) < full)
-                *reinterpret_cast<uint4 *>(dst + 8 * (lane + 64 * h)) =
-                    *reinterpret_cast<const uint4 *>(word_stage + 8 * (lane + 64 * h));
-            if (full > 128 && lane == 0)
-              *reinterpret_cast<uint4 *>(dst + 8 * 128) = *reinterpret_cast<const uint4 *>(word_stage + 8 * 128);
-          } else {
-            for (uint32_t q = lane; q < 8 * full; q += 64) {
-              const uint32_t v = vbase + q;
-              if (v >= pad && v - pad < cap) wp[v - pad] = word_stage[q];
-            }
-          }
-          const uint32_t rest = fill - 8 * full;
-          uint16_t carry = 0;
-          if ((uint32_t)lane < rest) carry = word_stage[8 * full + lane];
-          wave_sync();
-          if ((uint32_t)lane < rest) word_stage[lane] = carry;
-          vbase += 8 * full;
-          fill = rest;
-          wave_sync();
+      for (int i = 0; i < kStagePieces; ++i) {
+        const int64_t off = lo - (int64_t)mis + (int64_t)(lane + 64 * i) * 16;  // 16-byte aligned in absolute address
+        ntake[i] = r < n_rounds && off < hi;
+        if (ntake[i]) nv[i] = load16_stream(ubase + off);
+      }
+      if (ADAPT) {
+        const int32_t g = round_bottom(r) + lane;
+        ntog = (r < n_rounds && g < batch_top(4 * r)) ? group_table(a, unit, 0, g, 256u, &bad_depth) : 0u;
+      }
+    };
+    auto round_store = [&](int buf) {
+#pragma unroll
+      for (int i = 0; i < kStagePieces; ++i)
+        if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
+      if (ADAPT) table_of_group[buf][lane] = (uint16_t)ntog;
+    };
+    round_load(0);
+    __syncthreads();  // tables
+    round_store(0);
+    round_load(1);
+    __syncthreads();  // first symbols
+    // Words.  Position p of a region stands for the word at 16-byte-aligned address (wp - pad) + vbase + p; the
+    // first `pad` positions of the first are padding in front of the unit's first word.  The complete 16-byte
+    // pieces leave, up to two per lane; the incomplete tail (< 8 words) moves to the front of the next region, in
+    // front of the words that the packer has written or is writing there.
+    const uint32_t cap = a.word_cap < 0x7fffffffull ? (uint32_t)a.word_cap : 0x7fffffffu;  // a unit has < 2^31 symbols
+    uint32_t vbase = 0, rest = pad;
+    const int32_t n_pairs = (n_batches + 1) / 2;
+    int32_t out_pair = 0;  // the next pair of batches whose words leave
+    int region = 0;
+    auto words_out = [&]() {
+      const uint16_t *list = word_list[region];
+      const uint32_t fill = __builtin_amdgcn_readfirstlane(list_fill[region]);
+      region = region == kListRegions - 1 ? 0 : region + 1;
+      const uint32_t full = fill / 8;  // at most 128
+      rest = fill - 8 * full;
+      const uint16_t tail = list[8 * full + (lane & 7)];  // (lanes past the tail read inside the region)
+      if (vbase >= pad && vbase + 8 * full - pad <= cap) {
+        uint16_t *dst = wp + (vbase - pad);  // 16-byte aligned
+        uint4 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)  // (a lane past the last piece reads inside the region)
+          v[h] = *reinterpret_cast<const uint4 *>(list + 8 * (lane + 64 * h));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if ((uint32_t)(lane + 64 * h) < full) *reinterpret_cast<uint4 *>(dst + 8 * (lane + 64 * h)) = v[h];
+      } else {
+        for (uint32_t q = lane; q < 8 * full; q += 64) {
+          const uint32_t v = vbase + q;
+          if (v >= pad && v - pad < cap) wp[v - pad] = list[q];
         }
       }
+      vbase += 8 * full;
+      ++out_pair;
+      if ((uint32_t)lane < rest) {
+        if (out_pair < n_pairs) {
+          word_list[region][lane] = tail;
+        } else {  // the incomplete last piece
+          const uint32_t v = vbase + (uint32_t)lane;
+          if (v >= pad && v - pad < cap) wp[v - pad] = tail;
+        }
+      }
+    };
+    for (int32_t it = 0; it < n_iters; ++it) {
+      const int32_t phase = it & 3;
+      if (phase == 0 && it < n_batches) {  // the feeder has begun a round: the next one's symbols land
+        const int32_t r = it >> 2;
+        round_store((r + 1) & 1);
+        round_load(r + 2);
+      }
+      // (batch it - 5 is packed: in steady state a pair goes out at phase 1 and the next one at phase 2)
+      if ((phase == 1 || phase == 2) && 2 * out_pair + 1 <= it - 5) words_out();
+      lds_barrier();
     }
-    __syncthreads();
-  }
-
-  if (wave == 0) {
-    if (lane < kLanes) a.states_out[unit * kLanes + lane] = x;
-  } else if (wave == 1) {
-    if (bad_symbol || bad_depth) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0, or a bad depth
-  } else {
-    for (uint32_t q = lane; q < fill; q += 64) {  // the incomplete last piece
-      const uint32_t v = vbase + q;
-      if (v >= pad && v - pad < cap) wp[v - pad] = word_stage[q];
-    }
-    const uint32_t n_words = vbase + fill - pad;
+    while (out_pair < n_pairs) words_out();
+    const uint32_t n_words = vbase + rest - pad;
     if (lane == 0) {
       a.n_words_out[unit] = n_words;
       if ((uint64_t)n_words > a.word_cap) raise(a.status, PLC_ERR_CAPACITY);
     }
+    if (bad_depth) raise(a.status, PLC_ERR_INVALID);
   }
 }
 
@@ -2491,12 +2561,12 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
   {
     TraceScope trace(PLC_TRACE_RANS_ENCODE, st);
     if (a.units_per_stream == 1 && a.n_units <= kPipeMaxUnits) {
-      // few units (kPipeMaxUnits): the chain of one unit is the time, so give each unit three wavefronts
-      // (with more units, three wavefronts per unit cost more in occupancy than the shorter chain gains)
+      // few units (kPipeMaxUnits): the chain of one unit is the time, so give each unit four wavefronts
+      // (with more units, four wavefronts per unit cost more in occupancy than the shorter chain gains)
       if (a.bits) {
-        hipLaunchKernelGGL(rans_encode_pipe_kernel<true>, dim3((unsigned)a.n_units), dim3(192), 0, st, a);
+        hipLaunchKernelGGL(rans_encode_pipe_kernel<true>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       } else {
-        hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(192), 0, st, a);
+        hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       }
     } else if (a.bits) {
       dispatch_waves<LaunchEncode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);

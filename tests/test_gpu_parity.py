@@ -198,7 +198,7 @@ def test_special_values_escape_bit_exactly(oracle, dev):
 
 # --------------------------------------------------------------------------- byte-stream calls on their own
 
-BYTE_CASES = [(600, 1000, "gauss"),        # several hundred whole-stream units: the three-wavefront encoder, the chain decoder
+BYTE_CASES = [(600, 1000, "gauss"),        # several hundred whole-stream units: the four-wavefront encoder, the chain decoder
               (1500, 1000, "gauss"),       # more whole-stream units than those kernels take: the many-unit kernels, one
                                            # wavefront per workgroup (the shape of the 70B-shaped and 64-session runs)
               (1025, 700, "two"),          # an odd number of them: the last wavefront of the two-streams-per-wavefront
@@ -252,6 +252,38 @@ def test_histogram_table_rans_bit_exact(oracle, dev, n_streams, N, kind, chunk):
     o_nw = torch.from_numpy(enc["n_words"].view(np.int32)).to(dev)
     dec = torch.zeros_like(sym_t)
     plc.plc_rans_decode(freq, o_states, o_words, word_off, o_nw, n_streams, N, chunk, dec, status)
+    assert int(status.item()) == 0
+    assert torch.equal(dec, sym_t)
+
+
+@pytest.mark.parametrize("N", [31, 512, 513, 1024, 1057, 1536, 2048, 2049, 2560, 3073, 4096, 4608 + 7, 9 * 512, 21 * 512 + 33])
+def test_few_unit_coders_at_the_edges_of_their_batches(oracle, dev, N):
+    """The coders of few whole streams hand batches of 16 groups from wavefront to wavefront through LDS, symbols in
+    rounds of four batches and words in pairs: every count of batches up to twice those and what is left over,
+    on streams at every 16-byte misalignment, with words at odd addresses, nothing written behind a unit's words."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    n_streams, cap, lead = 5, (N + 7) // 8 * 8 + 5, 3
+    sym_t = random_bytes(n_streams, N, seed=N, kind="gauss", device=dev)
+    sym = sym_t.cpu().numpy()
+    freq, _ = O.build_freq(O.histogram(sym))
+    enc = O.rans_encode(sym, freq, word_cap_per_unit=cap)
+    i32, i16 = torch.int32, torch.int16
+    freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+    states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+    words = torch.zeros(lead + n_streams * cap, dtype=i16, device=dev)
+    word_off = lead + torch.arange(n_streams, dtype=torch.int64, device=dev) * cap
+    status = torch.zeros(1, dtype=i32, device=dev)
+    plc.plc_rans_encode(sym_t, n_streams, N, 0, freq_t, states, words, word_off, cap, n_words, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+    expect = np.zeros(lead + n_streams * cap, dtype=np.uint16)
+    for unit in range(n_streams):
+        nw = int(enc["n_words"][unit])
+        expect[lead + unit * cap:lead + unit * cap + nw] = enc["words"][unit * cap:unit * cap + nw]
+    assert np.array_equal(u16(words), expect)
+    dec = torch.zeros_like(sym_t)
+    plc.plc_rans_decode(freq_t, states, words, word_off, n_words, n_streams, N, 0, dec, status)
     assert int(status.item()) == 0
     assert torch.equal(dec, sym_t)
 
