@@ -1439,6 +1439,36 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   if (bad_depth) raise(a.status, PLC_ERR_INVALID);
 }
 
+// Slot tables.  Every thread of the workgroup takes every THREADS-th slot and finds its symbol -- the last one
+// whose first slot is not above it, which passes over symbols that do not occur -- in eight halvings, eight slots
+// at a time so that their LDS round trips overlap: some 4000 cycles for a table.  (Walking the symbols one after
+// the other and filling in each one's slots was a round trip and a loop per symbol, 33,000 cycles.)
+// cum_of: first slot of each symbol (of a table that sums to 4096).  put(slot, symbol, first slot, frequency).
+template <int THREADS, typename Put>
+__device__ __forceinline__ void for_each_slot(const uint32_t *cum_of, Put put) {
+  constexpr int kAtOnce = 8;
+  for (uint32_t o0 = threadIdx.x; o0 < kScale; o0 += THREADS * kAtOnce) {
+    uint32_t s[kAtOnce], lo[kAtOnce], hi[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) s[i] = 0u;
+#pragma unroll
+    for (uint32_t half = 128u; half; half >>= 1) {
+#pragma unroll
+      for (int i = 0; i < kAtOnce; ++i) s[i] += cum_of[s[i] + half] <= o0 + (uint32_t)(THREADS * i) ? half : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      lo[i] = cum_of[s[i]];
+      hi[i] = s[i] < 255u ? cum_of[s[i] < 255u ? s[i] + 1u : 255u] : kScale;
+    }
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      const uint32_t o = o0 + (uint32_t)(THREADS * i);
+      if (o < kScale) put(o, s[i], lo[i], hi[i] - lo[i]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Reconstruction inside the decoder for units coded as whole streams
 // ---------------------------------------------------------------------------
@@ -1747,25 +1777,28 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
 // ---------------------------------------------------------------------------
 // Decoder for streams coded as one unit (one wavefront per workgroup)
 // ---------------------------------------------------------------------------
-// With one unit per stream there are only as many wavefronts as streams, so what counts is the
-// length of the dependent chain of one step: a lone wavefront waits out the full latency of every
-// instruction whose result the next one needs (measured: with the table lookup replaced by arithmetic a
-// step still took 130 of its 180 cycles).  In the kernel above that chain holds two LDS round trips --
-// slot table, then, for the lanes that renormalise, the word -- and some ten dependent vector
-// instructions.  Here the round trips are folded into one and the instructions behind it cut to five.
+// With one unit per stream there are only as many wavefronts as streams, so what counts is the length of a
+// step: one LDS round trip (61-67 cycles for 8 bytes) and the instructions, 4.64 cycles each, between the arrival
+// of an entry and the read of the next.  In the kernel above that chain holds two round trips -- slot
+// table, then, for the lanes that renormalise, the word -- and some ten instructions.  Here the round trips are
+// folded into one and the instructions cut to six.
 //
 // Every entry, of the slot table and of the word ring alike, is 8 bytes
-//     .x = f | sym << 24        .y = f * w4 + slot - cum
+//     .x = f | sym << 24        .y = y | t << 16   with  y = f * w4 + slot - cum,  t = floor((2^16 - 1 - y) / f)
 // A ring entry stands for a word w = w4 << 12 | slot: it is the slot-table entry that the state will
 // select once the word has been shifted in (the state's low 12 bits are then the word's, which is all
 // they are needed for), with the word's top four bits w4 already multiplied in; in the slot table itself
 // w4 = 0.  A lane that renormalises reads its ring entry, a lane that does not reads the slot table at
 // its new state -- one read either way, at an address chosen per lane, both tables living in one LDS
-// array; the ring entries are formed when a block of words is staged, off the chain.  The state is
-// carried as xc = x >> 12 without the bits the word supplies: from the previous step's value v,
-// xc = v << 4 if the lane renormalised and v >> 12 if not (ready long before the entry arrives), so
-// that f * (x >> 12) + slot - cum = f * (xc + w4) + slot - cum = f * xc + .y: one multiply-add, whose
-// 24-bit multiplicand ignores the symbol in the top byte of .x.
+// array; the ring entries are formed when a block of words is staged, off the chain: .y + w4 * (f - 2^16), for
+// y grows by f * w4 (to at most 4096 * 15 + 4095 < 2^16) and t falls by w4 (from at least 15).  The
+// state is carried as xc = x >> 12 without the bits the word supplies, so that
+// f * (x >> 12) + slot - cum = f * (xc + w4) + slot - cum = f * xc + y: one multiply-add, whose 24-bit
+// multiplicand ignores the symbol in the top byte of .x.  Whether the lane renormalises, f * xc + y < 2^16, is
+// xc <= t and does not wait for it: the compare comes first, and the multiply-add and the mask of the slot stand
+// in the two wait states between it and the rank that reads its lanes.  The multiply-add leaves t in the upper
+// half of its result; the slot and a renormalising lane's next state do not look there, the other lanes' has it
+// taken off behind the read.
 // The ring holds RB blocks of 512 words.  Four let the helper leave its newest block on its way for a batch
 // (below); three are what the decoder strictly needs -- the block of the pointer, the one below it, and the
 // one being staged for the batch after -- and bring the workgroup's LDS from 56.6 to 52.5 KB, so that a
@@ -1778,30 +1811,36 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
 template <bool MASKED>
 __device__ __forceinline__ void dec_chain_step(uint32_t &xc, uint2 &e, const uint2 *tab, uint32_t &ring_at,
                                                uint8_t *sym_slot, bool on) {
-  const uint32_t xn = __umul24(e.x, xc) + e.y;  // f * (x >> 12) + slot - cum
-  uint32_t m32 = (uint32_t)__builtin_amdgcn_uicmp(xn, kLow, 36 /* unsigned < */);
-  bool need = xn < kLow;
-  if (MASKED) {
-    need = need && on;
-    m32 = (uint32_t)__builtin_amdgcn_ballot_w64(need);
-  }
+  // which lanes renormalise; ranks and choices are made from this one mask
+  uint64_t mask = __builtin_amdgcn_uicmp(e.y >> 16, xc, 35 /* unsigned >= */);
+  if (MASKED) mask &= __builtin_amdgcn_ballot_w64(on);
+  const uint32_t m32 = (uint32_t)mask;
+  const bool need = __builtin_amdgcn_inverse_ballot_w64(mask);
+  PLC_PIN();
+  const uint32_t xn = __umul24(e.x, xc) + e.y;  // f * (x >> 12) + slot - cum, plus t << 16
+  PLC_PIN();
+  uint32_t idx_slot = xn & (kScale - 1);
+  asm volatile("" : "+v"(idx_slot));  // in a register: the choice below is one select, not a branch
+  PLC_PIN();
   // ring entry of the rank-th word from the top (lane 0 is served first: the rank is the number of
   // renormalising lanes below this one), or slot-table entry of xn
-  uint32_t idx_ring = __builtin_amdgcn_mbcnt_lo(m32, ring_at);
-  uint32_t idx_slot = xn & (kScale - 1);
-  asm volatile("" : "+v"(idx_ring), "+v"(idx_slot));  // both in registers: the choice is one select, not a branch
+  const uint32_t idx_ring = __builtin_amdgcn_mbcnt_lo(m32, ring_at);
+  PLC_PIN();
   const uint2 en = tab[need ? idx_ring : idx_slot];
-  __builtin_amdgcn_sched_barrier(0);  // what follows is issued in the shadow of the read
-  // (the entry of the top word, uniform, kept in a vector register where the rank is added to it: a count and
-  // an add per step)
-  ring_at += (uint32_t)__builtin_popcount(m32);
-  asm volatile("" : "+v"(ring_at));
-  const uint32_t next = need ? (xn << 4) : (xn >> kScaleBits);
+  PLC_PIN();  // what follows is issued in the shadow of the read
+  // (the entry of the top word, uniform, kept in a vector register where the rank is added to it: one instruction)
+  asm volatile("v_bcnt_u32_b32 %0, %1, %0" : "+v"(ring_at) : "s"(m32));
+  uint32_t shifted = (xn & 0xffffu) << 4, kept = (xn - (e.y & 0xffff0000u)) >> kScaleBits;
+  asm volatile("" : "+v"(shifted), "+v"(kept));  // (as above)
+  PLC_PIN();
+  if (!MASKED || on) *sym_slot = (uint8_t)(e.x >> 24);
+  PLC_PIN();
+  const uint32_t next = need ? shifted : kept;
   if (!MASKED || on) {
-    *sym_slot = (uint8_t)(e.x >> 24);
     xc = next;
     e = en;
   }
+  PLC_PIN();
 }
 
 // Two wavefronts per unit.  What a step does not need stays off the decoding wavefront: a helper, on
@@ -1824,7 +1863,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   constexpr uint32_t kRing = RB * kBlockWords;  // words the ring holds: word i sits at kRing - 1 - i mod kRing
   __shared__ __attribute__((aligned(16))) uint2 tab[kScale + kRing + kRingMirror];  // slot table, then the ring
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][2 * kBatchSyms];  // second half: lanes 32..63
-  __shared__ uint32_t fc[256];
+  __shared__ uint32_t cum_of[256], most[256];  // per symbol: first slot; floor((2^16 - 1) / f) | remainder << 16
   __shared__ int32_t ptr_pub[2];  // the word pointer after batch b, in slot b mod 2
   constexpr int kThreads = RK ? 192 : 128;
   const int lane = threadIdx.x & 63;
@@ -1834,7 +1873,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   const int64_t chunk = blockIdx.x - stream * a.wgs_per_stream;
   bool bad = false;
 
-  {  // slot table: symbols one after the other, 128 slots per pass
+  {  // slot table
     uint32_t f[4], cum;
     const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
     if (total != kScale) {  // not a table: nothing can be decoded (both wavefronts leave, before any barrier)
@@ -1844,16 +1883,17 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
     if (wave == 0) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        fc[lane * 4 + r] = f[r] | (cum << 16);
+        const uint32_t fs = f[r] ? f[r] : 1u, t = 0xffffu / fs;
+        cum_of[lane * 4 + r] = cum;
+        most[lane * 4 + r] = t | ((0xffffu - t * fs) << 16);
         cum += f[r];
       }
     }
     __syncthreads();
-    for (int s = 0; s < 256; ++s) {
-      const uint32_t v = fc[s];
-      const uint32_t fs = v & 0xffffu, cs = v >> 16;
-      for (uint32_t o = threadIdx.x; o < fs; o += kThreads) tab[cs + o] = make_uint2(fs | ((uint32_t)s << 24), o);
-    }
+    for_each_slot<kThreads>(cum_of, [&](uint32_t o, uint32_t s, uint32_t cs, uint32_t fs) {
+      const uint32_t r = o - cs, m = most[s];
+      tab[o] = make_uint2(fs | (s << 24), r | (((m & 0xffffu) - (r > (m >> 16) ? 1u : 0u)) << 16));
+    });
     __syncthreads();
   }
   uint2 *ring = tab + kScale;
@@ -1910,7 +1950,10 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
 #pragma unroll
         for (int i = 0; i < 8; ++i) en[i] = tab[w[7 - i] & (kScale - 1)];  // en[i] belongs at pos + i
 #pragma unroll
-        for (int i = 0; i < 8; ++i) en[i].y += __umul24(en[i].x, w[7 - i] >> kScaleBits);  // f * w4 <= 4096 * 15
+        for (int i = 0; i < 8; ++i) {  // f * w4 onto y, w4 off t
+          const uint32_t w4 = w[7 - i] >> kScaleBits;
+          en[i].y += __umul24(en[i].x, w4) - (w4 << 16);
+        }
 #pragma unroll
         for (int i = 0; i < 8; i += 2)
           *reinterpret_cast<uint4 *>(&ring[pos + i]) = make_uint4(en[i].x, en[i].y, en[i + 1].x, en[i + 1].y);
@@ -1961,7 +2004,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
     int32_t ptr_before = hi;  // the pointer as it stood before the batch now running
     for (int32_t g0 = 0; g0 < G; g0 += kBatch) {
       stage_down_to(ptr_before - kBelow, RB == 4);
-      __syncthreads();  // barrier of this batch: its symbols are in the stage, the pointer is published
+      lds_barrier();  // barrier of this batch: its symbols are in the stage, the pointer is published
       ptr_before = ptr_pub[(g0 / kBatch) & 1];  // (its own slot: the decoder publishes the next one a batch later)
       const bool tail = g0 >= g_tail;
       const int32_t cnt_groups = tail ? tail_groups : kBatch;
@@ -1994,27 +2037,39 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   uint2 e = tab[x0 & (kScale - 1)];
   int32_t ptr = hi;
   __syncthreads();  // barrier "start": the first words are staged
-  for (int32_t g0 = 0; g0 < G; g0 += kBatch) {
-    const bool tail = g0 >= g_tail;
-    const int32_t cnt_groups = tail ? tail_groups : kBatch;
-    uint8_t *sb = &sym_stage[(g0 / kBatch) & 1][coder ? rl : kBatchSyms + rl];
-    const uint32_t q0 = kRing - 1u - (uint32_t)(ptr - 1) % kRing;  // ring position of the top word (uniform)
-    uint32_t ring_at = (uint32_t)kScale + q0;  // its entry in tab
-    asm volatile("" : "+v"(ring_at));
-    if (tail) {
-      for (int32_t j = 0; j < cnt_groups; ++j)
-        dec_chain_step<true>(xc, e, tab, ring_at, sb + kLanes * j, j != cnt_groups - 1 || top_active);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) dec_chain_step<false>(xc, e, tab, ring_at, sb + kLanes * j, true);
-    }
-    ptr -= (int32_t)((uint32_t)__builtin_amdgcn_readfirstlane(ring_at) - (uint32_t)kScale - q0);
+  // The top word's entry in tab (uniform): in a vector register where the ranks are added to it, and a scalar copy
+  // as of the batch's first step.  Everything a batch needs besides its steps is done behind the last step's read.
+  uint32_t ring_start = (uint32_t)kScale + kRing - 1u - (uint32_t)(ptr - 1) % kRing;
+  uint32_t ring_at = ring_start;
+  asm volatile("" : "+v"(ring_at));
+  uint8_t *sb = &sym_stage[0][coder ? rl : kBatchSyms + rl];
+  auto batch_done = [&](int parity) {
+    const uint32_t now = (uint32_t)__builtin_amdgcn_readfirstlane(ring_at);
+    ptr -= (int32_t)(now - ring_start);
     if (ptr < lo) {  // ran out of words: the stream is damaged
       bad = true;
       ptr = lo;
     }
-    if (lane == 0) ptr_pub[(g0 / kBatch) & 1] = ptr;
-    __syncthreads();  // barrier of this batch
+    if (lane == 0) ptr_pub[parity] = ptr;
+    ring_start = now >= (uint32_t)kScale + kRing ? now - kRing : now;
+    ring_at = ring_start;
+    asm volatile("" : "+v"(ring_at));
+    lds_barrier();  // barrier of this batch
+  };
+  int32_t g0 = 0;
+  int parity = 0;
+  for (; g0 < g_tail; g0 += kBatch) {
+    uint8_t *sbb = sb + parity * (int)sizeof(sym_stage[0]);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) dec_chain_step<false>(xc, e, tab, ring_at, sbb + kLanes * j, true);
+    batch_done(parity);
+    parity ^= 1;
+  }
+  if (tail_groups) {
+    uint8_t *sbb = sb + parity * (int)sizeof(sym_stage[0]);
+    for (int32_t j = 0; j < tail_groups; ++j)
+      dec_chain_step<true>(xc, e, tab, ring_at, sbb + kLanes * j, j != tail_groups - 1 || top_active);
+    batch_done(parity);
   }
   // integrity: every word consumed, every lane back at the initial state: x >> 12 as carried, and the entry
   // in hand that of the initial state's slot with w4 = 0 (entries of different slots differ in .y, and
@@ -2046,7 +2101,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
 //   step          multiply | add (each takes its half of the entry), compare, rank, select, shift | read:
 //                 six dependent instructions and one round trip
 // What a step costs is its dependent chain -- the round trip and six vector instructions at about eight cycles
-// each, one more than the kernel above, whose entry needs no taking apart: 134 against 104 cycles a step with
+// each, three more than the kernel above, whose entry needs no taking apart: 134 against 104 cycles a step with
 // the barrier's share -- so the decoder's uniform operands are formed once per batch, and whatever else can
 // be is left to the helper (handing on the slot itself, read by the decoder from the raw ring behind its
 // entry, was tried: 2.4 against 2.1 ms on the Llama shape).  The helper stages the
@@ -2074,6 +2129,12 @@ inline size_t depths_lds_bytes(int n_tables) {
 constexpr int depths_threads(int rk) { return rk ? 192 : 128; }
 static_assert(PLC_MAX_BITS * (kDepthTableBytes + kDepthRingBytes) / 4 <= 65536, "a word of the tables and rings in 16 bits");
 
+// A product that is to stay one: multiply and add are not contracted over this.
+__device__ __forceinline__ uint32_t keep_apart(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // LDS of the kernel in 4-byte words.  tw is the first word of the next group's slot table, ring_at the word
 // of that group's ring where the top word sits (both uniform; ring_at in a vector register), ring_step how far
 // the ring that the step after this one reads lies behind this one's: ring_at for that step is formed here,
@@ -2086,31 +2147,41 @@ __device__ __forceinline__ void dec_depth_step(uint32_t &xh, uint32_t &e, uint32
   // f * (x >> 12) + slot - cum; product and sum kept apart so that each takes its half of the entry through
   // the instruction's own operand select instead of a mask and a shift in front of a fused multiply-add
   uint32_t fx = __umul24(e & 0xffffu, xh);
-  asm volatile("" : "+v"(fx));
-  const uint32_t xn = fx + (e >> 16);
-  uint32_t m32 = (uint32_t)__builtin_amdgcn_uicmp(xn, kLow, 36 /* unsigned < */);
-  bool need = xn < kLow;
-  if (MASKED) {
-    need = need && on;
-    m32 = (uint32_t)__builtin_amdgcn_ballot_w64(need);
-  }
-  // ring entry of the rank-th word from the top, or slot-table entry of xn (tables start at multiples of 4096 words)
-  uint32_t idx_ring = __builtin_amdgcn_mbcnt_lo(m32, ring_at);
+  PLC_PIN();
+  const uint32_t xn = keep_apart(fx) + (e >> 16);
+  PLC_PIN();
+  uint64_t mask = __builtin_amdgcn_uicmp(xn, kLow, 36 /* unsigned < */);
+  if (MASKED) mask &= __builtin_amdgcn_ballot_w64(on);
+  const uint32_t m32 = (uint32_t)mask;
+  const bool need = __builtin_amdgcn_inverse_ballot_w64(mask);
+  PLC_PIN();
+  // ring entry of the rank-th word from the top, or slot-table entry of xn (tables start at multiples of 4096
+  // words); what stands between the compare and the rank takes the place of its wait states
   uint32_t idx_slot = (xn & slot_mask) | tw;  // (the mask in a register: and-or is one instruction then)
-  asm volatile("" : "+v"(idx_ring), "+v"(idx_slot));  // both in registers: the choice is one select, not a branch
+  asm volatile("" : "+v"(idx_slot));  // in a register: the choice below is one select, not a branch
+  PLC_PIN();
+  uint32_t kept = xn >> kScaleBits;
+  asm volatile("" : "+v"(kept));
+  PLC_PIN();
+  const uint32_t idx_ring = __builtin_amdgcn_mbcnt_lo(m32, ring_at);
+  PLC_PIN();
   const uint32_t at_next = need ? idx_ring : idx_slot;
   const uint32_t en = lds_words[at_next];
-  __builtin_amdgcn_sched_barrier(0);  // what follows is issued in the shadow of the read
-  ring_at += (uint32_t)__builtin_popcount(m32) + ring_step;
-  asm volatile("" : "+v"(ring_at));
-  const uint32_t next = need ? (xn << 4) : (xn >> kScaleBits);
+  PLC_PIN();  // what follows is issued in the shadow of the read
+  asm volatile("v_bcnt_u32_b32 %0, %1, %0" : "+v"(ring_at) : "s"(m32));
+  uint32_t shifted = xn << 4;
+  asm volatile("" : "+v"(shifted));
+  PLC_PIN();
+  if (!MASKED || on) *code_slot = (uint16_t)at;
+  PLC_PIN();
+  ring_at += ring_step;
+  const uint32_t next = need ? shifted : kept;
   if (!MASKED || on) {
-    *code_slot = (uint16_t)at;
     xh = next;
     e = en;
     at = at_next;
   }
-  __builtin_amdgcn_sched_barrier(0);  // all of it before the entry is waited for
+  PLC_PIN();  // all of it before the entry is waited for
 }
 
 template <int RK, int MODE = 0>  // MODE 0: a table per depth; 1: one table; 2: one table and a chosen candidate
@@ -2124,8 +2195,8 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   __shared__ __attribute__((aligned(16))) uint16_t code_stage[2][kBatchSyms];  // where the entries were read from
   __shared__ uint16_t code_spare[kBatchSyms];                                  // the same from lanes 32..63, never read
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kBatchSyms];    // symbols, for the reconstruction
-  uint32_t *const fc = reinterpret_cast<uint32_t *>(&code_stage[0][0]);        // frequencies while the tables are built
-  static_assert(sizeof(code_stage) >= 256 * sizeof(uint32_t), "room for the frequencies");
+  uint32_t *const fc = reinterpret_cast<uint32_t *>(&code_stage[0][0]);        // first slots while the tables are built
+  static_assert(sizeof(code_stage) >= 256 * sizeof(uint32_t), "room for the first slots");
   __shared__ uint32_t tables_of_batch[4];  // batch b mod 4: the tables of groups 16 b + 1 .. 16 b + 16, two bits each
   __shared__ uint32_t first_table;
   __shared__ int32_t ptr_pub[2];  // the word pointer after batch b, in slot b mod 2
@@ -2153,7 +2224,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
     if (wave == 0) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        fc[lane * 4 + r] = f[r] | (cum << 16);
+        fc[lane * 4 + r] = cum;
         cum += f[r];
       }
     }
@@ -2162,14 +2233,10 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
     uint8_t *ts = reinterpret_cast<uint8_t *>(depth_lds + symtab_off + (size_t)t * kDepthSymBytes);
     if (total == kScale) {
       used |= 1u << t;
-      for (int sy = 0; sy < 256; ++sy) {
-        const uint32_t v = fc[sy];
-        const uint32_t fs = v & 0xffffu, cs = v >> 16;
-        for (uint32_t o = threadIdx.x; o < fs; o += kThreads) {
-          tt[cs + o] = fs | (o << 16);
-          ts[cs + o] = (uint8_t)sy;
-        }
-      }
+      for_each_slot<kThreads>(fc, [&](uint32_t o, uint32_t sy, uint32_t cs, uint32_t fs) {
+        tt[o] = fs | ((o - cs) << 16);
+        ts[o] = (uint8_t)sy;
+      });
     } else {
       for (uint32_t o = threadIdx.x; o < (uint32_t)kScale; o += kThreads) tt[o] = 0u, ts[o] = 0;
     }
