@@ -151,6 +151,19 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
   return v;
 }
 
+// Sum over the 64 lanes of a wavefront, the same in every lane: through the lanes' own registers (six adds),
+// where a shuffle would take an LDS round trip each.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  uint32_t s = v;
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x111, 0xf, 0xf, true);  // row_shr:1
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x112, 0xf, 0xf, true);  // row_shr:2
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x114, 0xf, 0xf, true);  // row_shr:4
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x118, 0xf, 0xf, true);  // row_shr:8
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x142, 0xa, 0xf, true);  // row_bcast:15 into rows 1 and 3
+  s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x143, 0xc, 0xf, true);  // row_bcast:31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
+}
+
 // Exclusive prefix sum of one value per thread over a 256-thread workgroup.
 // `smem` needs 5 words.  Returns the exclusive prefix; *total gets the block sum.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *smem, uint32_t *total) {

@@ -160,40 +160,62 @@ __global__ __launch_bounds__(kBlock) void build_freq_kernel(const uint32_t *__re
     }
     return;
   }
-  // f[s] = floor(C[s] * 4096 / T) - floor(C[s-1] * 4096 / T)
+  // f[s] = floor(C[s] * 4096 / T) - floor(C[s-1] * 4096 / T).  The quotient, at most 4096, from the reciprocal in
+  // fp64 (C * 4096 < 2^44 is exact there), off by one at most and put right by its remainder.
+  const double inv = 1.0 / (double)T;
+  auto scaled = [&](uint64_t c) {
+    const int64_t n = (int64_t)(c * PLC_RANS_SCALE);
+    int64_t q = (int64_t)(uint32_t)((double)n * inv);
+    const int64_t rest = n - q * (int64_t)T;
+    q += rest < 0 ? -1 : rest >= (int64_t)T ? 1 : 0;
+    return (uint32_t)q;
+  };
   uint32_t f[4];
-  uint64_t prev = (before * PLC_RANS_SCALE) / T;
+  uint32_t prev = scaled(before);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const uint64_t cur = ((before + run[r]) * PLC_RANS_SCALE) / T;
-    f[r] = (uint32_t)(cur - prev);
+    const uint32_t cur = scaled(before + run[r]);
+    f[r] = cur - prev;
     prev = cur;
   }
-  // symbols that occur but were scaled to zero, in ascending symbol order
-  uint64_t need[4];
+  // Symbols that occur but were scaled to zero take one unit each, one after the other, from the largest
+  // frequency of the moment, the lowest symbol on ties.  Whose unit goes to whom does not matter (the frequencies
+  // sum to 4096 over 256 symbols, so a donor holds 16 or more and a symbol raised to 1 is never one), and taking
+  // n units that way brings everything above a level down to it: with L the lowest level for which
+  // sum max(0, f - L) <= n, f becomes min(f, L) and the units still missing come from the lowest symbols at L.
+  // L by halving, twelve sums over the wavefront (a repair at a time was an arg-max over it each: 17 us in all).
+  uint32_t n_zero = 0;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) need[r] = __ballot(cnt[r] > 0 && f[r] == 0);
-  if (need[0] | need[1] | need[2] | need[3]) {
-    for (int s = 0; s < 256; ++s) {
-      const int r = s & 3, owner = s >> 2;
-      if (!((need[r] >> owner) & 1ull)) continue;  // uniform
-      // donor: largest current frequency, lowest symbol on ties
-      uint32_t best = 0;
+  for (int r = 0; r < 4; ++r) n_zero += (uint32_t)__builtin_popcountll(__ballot(cnt[r] > 0 && f[r] == 0));
+  if (n_zero) {  // uniform
+    auto excess = [&](uint32_t level) {
+      uint32_t e = 0;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t key = (f[t] << 8) | (255u - (uint32_t)(lane * 4 + t));
-        best = key > best ? key : best;
+      for (int r = 0; r < 4; ++r) e += f[r] > level ? f[r] - level : 0u;
+      return wave_sum(e);
+    };
+    uint32_t level = 0;  // excess(level - 1) > n_zero, or level is 0
+    for (uint32_t half = PLC_RANS_SCALE / 2; half; half >>= 1)
+      if (excess(level + half - 1) > n_zero) level += half;
+    uint32_t missing = n_zero - excess(level);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (cnt[r] > 0 && f[r] == 0) {
+        f[r] = 1;
+      } else {
+        f[r] = f[r] < level ? f[r] : level;
       }
+    }
+    // the lane's four symbols come one after the other, so those at the level in lower lanes come first
+    uint32_t mine = 0;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t o = __shfl_xor(best, off, 64);
-        best = o > best ? o : best;
-      }
-      const int donor = 255 - (int)(best & 255u);
+    for (int r = 0; r < 4; ++r) mine += f[r] == level ? 1u : 0u;
+    uint32_t ahead = wave_inclusive_scan(mine) - mine;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        if (lane * 4 + t == donor) f[t] -= 1;
-        if (lane * 4 + t == s) f[t] = 1;
+    for (int r = 0; r < 4; ++r) {
+      if (f[r] == level) {
+        if (ahead < missing) f[r] -= 1;
+        ++ahead;
       }
     }
   }

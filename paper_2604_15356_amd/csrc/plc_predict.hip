@@ -447,32 +447,76 @@ __global__ __launch_bounds__(kBlock) void scan_streams_kernel(const uint32_t *__
   if (threadIdx.x == 0 && carry > esc_cap) raise(status, PLC_ERR_CAPACITY);
 }
 
-// One wavefront gathers the escapes of one tile again from its symbols and the actual values, 64 chunks at
-// a time, and writes them from dst on; for a tile whose staging row overflowed, or that has none.
-__device__ __forceinline__ void regather_tile(const CodecArgs &a, uint16_t *__restrict__ esc_vals, uint64_t esc_cap,
-                                              uint32_t stream, uint32_t tile, uint64_t dst, int lane) {
-  for (int round = 0; round < kBlock / 64; ++round) {
-    const Coord q = locate_chunk(a, stream, tile, (uint32_t)(round * 64 + lane));
-    uint2 sv = make_uint2(0u, 0u);
-    uint32_t n_esc = 0;
-    if (q.valid) {
-      sv = *reinterpret_cast<const uint2 *>(a.symbols + q.sym);
+// One wavefront walks the escapes of one tile, found in its symbols.  Gathering, it writes the actual values from
+// list position `at` on (for a tile whose staging row overflowed, or that has none); patching, it puts the list's
+// values from there on over the escaped components of the output.  What bounds it is latency: the symbols of the
+// lane's four chunks are asked for at once, and so is one value of each chunk at a time (a chunk seldom holds
+// two escapes); a chunk's place is worked out only where it has any.
+template <bool PATCH>
+__device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__restrict__ esc_vals, uint64_t esc_cap,
+                                                uint32_t stream, uint32_t tile, uint64_t at, int lane) {
+  constexpr int kRounds = kBlock / 64;
+  uint2 sv[kRounds];
 #pragma unroll
-      for (int e = 0; e < kChunk; ++e) n_esc += (((e < 4 ? sv.x : sv.y) >> (8 * (e & 3))) & 255u) == PLC_ESCAPE;
+  for (int r = 0; r < kRounds; ++r) {
+    const uint32_t chunk = tile * kBlock + (uint32_t)(r * 64 + lane);
+    sv[r] = make_uint2(0u, 0u);
+    if (chunk < a.chunks_per_stream)
+      sv[r] = *reinterpret_cast<const uint2 *>(a.symbols + (int64_t)stream * a.syms_per_stream + (int64_t)chunk * kChunk);
+  }
+  uint32_t bits[kRounds];  // which components of the chunk are escapes
+  uint64_t pos[kRounds];   // their places in the list
+  uint16_t *comp[kRounds];
+  bool any = false;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    // a byte is 0xff iff its low seven bits carry into bit 7 when 1 is added and bit 7 is set; bit 7 of byte e to bit e
+    const uint32_t hx = ((sv[r].x & 0x7f7f7f7fu) + 0x01010101u) & sv[r].x & 0x80808080u;
+    const uint32_t hy = ((sv[r].y & 0x7f7f7f7fu) + 0x01010101u) & sv[r].y & 0x80808080u;
+    bits[r] = (((hx >> 7) * 0x00204081u) >> 21 & 0xfu) | ((((hy >> 7) * 0x00204081u) >> 21 & 0xfu) << 4);
+    comp[r] = nullptr;
+    pos[r] = at;
+    if (__ballot(bits[r] != 0u) == 0) continue;  // uniform
+    uint32_t total;
+    pos[r] = at + wave_escape_prefix((uint32_t)__builtin_popcount(bits[r]), &total);
+    at += total;
+    if (bits[r]) {
+      const Coord q = locate_chunk(a, stream, tile, (uint32_t)(r * 64 + lane));
+      if (PATCH) {
+        comp[r] = (q.c ? a.out_v : a.out_k) + q.act;
+      } else {
+        comp[r] = const_cast<uint16_t *>((q.c ? a.act_v : a.act_k) + q.act);
+      }
+      any = true;
     }
-    uint32_t wave_total;
-    uint64_t at = dst + wave_escape_prefix(n_esc, &wave_total);
-    if (n_esc) {
-      const uint16_t *act = (q.c ? a.act_v : a.act_k) + q.act;
+  }
+  while (any) {
+    uint16_t v[kRounds];
 #pragma unroll
-      for (int e = 0; e < kChunk; ++e) {
-        if ((((e < 4 ? sv.x : sv.y) >> (8 * (e & 3))) & 255u) == PLC_ESCAPE) {
-          if (at < esc_cap) esc_vals[at] = act[e];
-          ++at;
-        }
+    for (int r = 0; r < kRounds; ++r) {
+      v[r] = 0;
+      if (!bits[r]) continue;
+      if (!PATCH) {
+        v[r] = comp[r][__builtin_ctz(bits[r])];
+      } else if (pos[r] < a.esc_len) {
+        v[r] = a.esc_in[pos[r]];
+      } else {  // the list is too short: this component stays as it is
+        raise(a.status, PLC_ERR_CORRUPT);
       }
     }
-    dst += wave_total;
+    any = false;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if (!bits[r]) continue;
+      if (PATCH) {
+        if (pos[r] < a.esc_len) comp[r][__builtin_ctz(bits[r])] = v[r];
+      } else {
+        if (pos[r] < esc_cap) esc_vals[pos[r]] = v[r];
+      }
+      ++pos[r];
+      bits[r] &= bits[r] - 1u;
+      any = any || bits[r] != 0u;
+    }
   }
 }
 
@@ -488,48 +532,67 @@ __global__ __launch_bounds__(kBlock) void gather_escapes_kernel(const CodecArgs 
   if (a.tile_cnt[t] == 0) return;  // uniform per wavefront
   const uint32_t stream = (uint32_t)(t / a.tiles_per_stream);
   const uint32_t tile = (uint32_t)(t - (int64_t)stream * a.tiles_per_stream);
-  regather_tile(a, esc_vals, esc_cap, stream, tile, esc_off[stream] + a.tile_off[t], lane);
+  escapes_of_tile<false>(a, esc_vals, esc_cap, stream, tile, esc_off[stream] + a.tile_off[t], lane);
 }
 
 // Move every tile's escapes from its staging row to their place in the stream's list.  A wavefront takes
-// 64 tiles in a row, a lane looks up the count and the destination of one of them, and the wavefront then
-// copies the rows one after the other (a row holds at most two wavefronts' worth).  A tile that overflowed
-// its row is gathered again from the symbols.
+// `per_wave` tiles in a row, a lane looks up the count and the destination of one of them, and the wavefront then
+// copies the rows, eight tiles' loads on their way at a time (a row holds at most two wavefronts' worth).  A tile
+// that overflowed its row is gathered again from the symbols.
 __global__ __launch_bounds__(kBlock) void compact_escapes_kernel(const CodecArgs a, uint16_t *__restrict__ esc_vals,
                                                                  uint64_t esc_cap,
                                                                  const uint64_t *__restrict__ esc_off,
-                                                                 int64_t n_tiles) {
+                                                                 int64_t n_tiles, int32_t per_wave) {
+  static_assert(kEscStage == 128, "two passes of a wavefront over a staging row");
+  constexpr int kAtOnce = 8;
   const int lane = threadIdx.x & 63;
-  const int64_t t0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * 64;
+  const int64_t t0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * per_wave;
   if (t0 >= n_tiles) return;
   const int64_t t = t0 + lane;
   uint32_t cnt = 0, stream = 0;
   uint64_t dst = 0;
-  if (t < n_tiles) {
+  if (lane < per_wave && t < n_tiles) {
     cnt = a.tile_cnt[t];
     if (cnt) {
       stream = (uint32_t)(t / a.tiles_per_stream);
       dst = esc_off[stream] + a.tile_off[t];
     }
   }
-  uint64_t todo = __ballot(cnt != 0);
+  auto dst_of = [&](int j) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dst, j) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(dst >> 32), j) << 32;
+  };
+  uint64_t todo = __ballot(cnt != 0 && cnt <= (uint32_t)kEscStage);
+  uint64_t again = __ballot(cnt > (uint32_t)kEscStage);
   while (todo) {  // uniform
-    const int j = __builtin_ctzll(todo);
-    todo &= todo - 1;
-    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cnt, j);
-    const uint64_t d = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dst, j) |
-                       (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(dst >> 32), j) << 32;
-    if (c <= (uint32_t)kEscStage) {
-      const uint16_t *row = a.esc_stage + (t0 + j) * kEscStage;
+    uint16_t lo[kAtOnce], hi[kAtOnce];
+    uint32_t c[kAtOnce];
+    uint64_t d[kAtOnce];
 #pragma unroll
-      for (uint32_t i = (uint32_t)lane; i < (uint32_t)kEscStage; i += 64)
-        if (i < c && d + i < esc_cap) esc_vals[d + i] = row[i];
-    } else {
-      const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)stream, j);
-      regather_tile(a, esc_vals, esc_cap, s, (uint32_t)(t0 + j - (int64_t)s * a.tiles_per_stream), d, lane);
+    for (int u = 0; u < kAtOnce; ++u) {
+      c[u] = 0;
+      if (!todo) continue;  // uniform
+      const int j = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      c[u] = (uint32_t)__builtin_amdgcn_readlane((int)cnt, j);
+      d[u] = dst_of(j);
+      const uint16_t *row = a.esc_stage + (t0 + j) * kEscStage;
+      if ((uint32_t)lane < c[u]) lo[u] = row[lane];
+      if ((uint32_t)lane + 64u < c[u]) hi[u] = row[lane + 64];
+    }
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      if ((uint32_t)lane < c[u] && d[u] + (uint64_t)lane < esc_cap) esc_vals[d[u] + (uint64_t)lane] = lo[u];
+      if ((uint32_t)lane + 64u < c[u] && d[u] + (uint64_t)lane + 64u < esc_cap)
+        esc_vals[d[u] + (uint64_t)lane + 64u] = hi[u];
     }
   }
-  static_assert(kEscStage == 128, "two passes of a wavefront over a staging row");
+  while (again) {  // uniform
+    const int j = __builtin_ctzll(again);
+    again &= again - 1;
+    const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)stream, j);
+    escapes_of_tile<false>(a, esc_vals, esc_cap, s, (uint32_t)(t0 + j - (int64_t)s * a.tiles_per_stream), dst_of(j), lane);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -578,36 +641,16 @@ __global__ __launch_bounds__(kBlock) void reconstruct_kernel(const CodecArgs a) 
   }
 }
 
-// Overwrite the escaped components of a tile's output with their raw values from the stream's list
-// (for outputs written by a kernel that does not handle escapes itself); one workgroup per tile.
-__global__ __launch_bounds__(kBlock) void patch_escapes_kernel(const CodecArgs a) {
-  __shared__ uint32_t smem[8];
-  if (a.tile_cnt[blockIdx.x] == 0) return;  // uniform
-  const Coord q = locate(a);
-  uint2 sv = make_uint2(0u, 0u);
-  uint32_t n_esc = 0;
-  if (q.valid) {
-    sv = *reinterpret_cast<const uint2 *>(a.symbols + q.sym);
-#pragma unroll
-    for (int e = 0; e < kChunk; ++e) n_esc += (((e < 4 ? sv.x : sv.y) >> (8 * (e & 3))) & 255u) == PLC_ESCAPE;
-  }
-  uint32_t total;
-  const uint32_t rank = block_exclusive_scan(n_esc, smem, &total);
-  if (n_esc) {
-    uint64_t src = a.esc_off[q.stream] + a.tile_off[blockIdx.x] + rank;
-    uint16_t *dst = (q.c ? a.out_v : a.out_k) + q.act;
-#pragma unroll
-    for (int e = 0; e < kChunk; ++e) {
-      if ((((e < 4 ? sv.x : sv.y) >> (8 * (e & 3))) & 255u) == PLC_ESCAPE) {
-        if (src < a.esc_len) {
-          dst[e] = a.esc_in[src];
-        } else {
-          raise(a.status, PLC_ERR_CORRUPT);
-        }
-        ++src;
-      }
-    }
-  }
+// Overwrite the escaped components of every tile's output with their raw values from the stream's list (for
+// outputs written by a kernel that does not handle escapes itself); one wavefront per tile.
+__global__ __launch_bounds__(kBlock) void patch_escapes_kernel(const CodecArgs a, int64_t n_tiles) {
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (t >= n_tiles) return;
+  if (a.tile_cnt[t] == 0) return;  // uniform per wavefront
+  const uint32_t stream = (uint32_t)(t / a.tiles_per_stream);
+  const uint32_t tile = (uint32_t)(t - (int64_t)stream * a.tiles_per_stream);
+  escapes_of_tile<true>(a, nullptr, 0, stream, tile, a.esc_off[stream] + a.tile_off[t], lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -808,8 +851,11 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
                      (uint32_t)p.tiles_per_stream, esc_cnt);
   hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
                      status);
-  hipLaunchKernelGGL(compact_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock - 1) / kBlock)), dim3(kBlock), 0, st,
-                     a, esc_vals, esc_cap, esc_off, p.n_tiles);
+  // 64 tiles per wavefront start the fewest wavefronts; where that would leave compute units without one, eight
+  const int32_t per_wave = p.n_tiles >= 64 * 1024 ? 64 : 8;
+  const int64_t per_block = (int64_t)per_wave * (kBlock / 64);
+  hipLaunchKernelGGL(compact_escapes_kernel, dim3((unsigned)((p.n_tiles + per_block - 1) / per_block)), dim3(kBlock), 0,
+                     st, a, esc_vals, esc_cap, esc_off, p.n_tiles, per_wave);
   return launch_status();
 }
 
@@ -911,7 +957,8 @@ int plc::patch_escapes(const plc_dims *dims, const uint8_t *symbols, const uint1
                      a, (uint32_t)p.n_tiles);
   hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
                      (uint32_t)p.tiles_per_stream, (uint32_t *)nullptr);
-  hipLaunchKernelGGL(patch_escapes_kernel, dim3((unsigned)p.n_tiles), dim3(kBlock), 0, st, a);
+  hipLaunchKernelGGL(patch_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
+                     0, st, a, p.n_tiles);
   return launch_status();
 }
 

@@ -674,3 +674,29 @@ def test_statistics_inside_the_prediction_pass_equal_the_histogram_call(oracle, 
         ref = _oracle_encode(O, w, O.F32)
         assert np.array_equal(u8(a.symbols), ref["symbols"])
         assert np.array_equal(u32(first[1]), O.histogram(ref["symbols"]))
+
+
+@pytest.mark.parametrize("occur", [1, 2, 17, 100, 255, 256])
+@pytest.mark.parametrize("skew", [1, 6, 20])
+def test_frequency_tables_of_skewed_counts(oracle, dev, occur, skew):
+    """Counts from flat to one symbol holding nearly all of up to 2^32 - 1: most symbols are then scaled to zero and
+    take their unit from the largest, with and without ties among those."""
+    from paper_2604_15356_amd import plc
+    rng = np.random.default_rng(occur * 100 + skew)
+    rows = []
+    for total in (300, 70001, 2 ** 32 - 1):
+        for _ in range(3):
+            share = rng.exponential(size=occur) ** skew
+            c = np.maximum(1, np.floor(share / share.sum() * (total - occur))).astype(np.int64)
+            row = np.zeros(256, np.int64)
+            row[rng.choice(256, occur, replace=False)] = np.minimum(c, total - occur)
+            rows.append(row)
+    counts = np.stack(rows).astype(np.uint32)
+    assert (counts.astype(np.int64) == np.stack(rows)).all()
+    ref_freq, ref_cum = oracle.build_freq(counts)
+    freq = torch.empty((len(rows), 256), dtype=torch.int16, device=dev)
+    cum = torch.empty((len(rows), 257), dtype=torch.int16, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    plc.plc_build_freq(torch.from_numpy(counts.view(np.int32)).to(dev), len(rows), freq, cum, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u16(freq), ref_freq) and np.array_equal(u16(cum), ref_cum)
