@@ -6,7 +6,8 @@
 namespace plc {
 namespace {
 
-constexpr int kHistSegment = 64 * 1024;  // symbols per workgroup
+constexpr int kHistSegment = 64 * 1024;     // symbols per workgroup
+constexpr int kBucketSegment = 128 * 1024;  // the same where there is a table per bit depth
 
 __global__ __launch_bounds__(kBlock) void zero_u32_kernel(uint32_t *p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -14,23 +15,33 @@ __global__ __launch_bounds__(kBlock) void zero_u32_kernel(uint32_t *p, int64_t n
 }
 
 // Each workgroup counts one segment of one stream into LDS histograms, then adds the non-empty bins to
-// the stream's global counts.  Lanes that hit the same counter in one instruction are served one after
-// the other, and quantised residuals crowd into a few symbols (a dozen on the token-conditional path),
-// so every wavefront has kHistCopies histograms, a lane using copy lane mod kHistCopies; the copies
-// start 8 banks apart, so that equal symbols in different copies do not share a bank either.
-constexpr int kHistCopies = 8;
-constexpr int kHistStride = 256 + 8;
+// the stream's global counts.  Lanes that meet at one counter, or at one bank, in an instruction are served one
+// after the other, and quantised residuals crowd into a few symbols (a dozen on the token-conditional path).  So
+// the workgroup has kHistCopies histograms, a lane using copy lane mod kHistCopies, and a symbol's copies lie side
+// by side: lane and bank then go together whatever the symbols are, and only lanes 32 apart can meet.  256 streams
+// of 1,048,576 symbols: 62-64 us however the symbols are distributed (4.3 TB/s); with eight copies a wavefront, of
+// which equal symbols met in one of eight banks, 92 us for residuals 60 steps wide and 152 us for 0.6 steps.
+constexpr int kHistCopies = 32;
+
+// The sum of one counter's copies, each thread starting at another one (side by side they would share a bank).
+template <int COPIES>
+__device__ __forceinline__ uint32_t sum_copies(const uint32_t *row, int thread) {
+  uint32_t c = 0;
+#pragma unroll
+  for (int r = 0; r < COPIES; ++r) c += row[(r + thread) & (COPIES - 1)];
+  return c;
+}
 
 __global__ __launch_bounds__(kBlock) void histogram_kernel(const uint8_t *__restrict__ symbols,
                                                            int64_t syms_per_stream, uint32_t segs_per_stream,
                                                            uint32_t *__restrict__ counts) {
-  __shared__ uint32_t hist[kBlock / 64][kHistCopies][kHistStride];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[256 * kHistCopies];
   const uint32_t stream = blockIdx.x / segs_per_stream;
   const uint32_t seg = blockIdx.x - stream * segs_per_stream;
-  const int wave = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < (kBlock / 64) * kHistCopies * kHistStride; i += kBlock) (&hist[0][0][0])[i] = 0u;
+  for (int i = threadIdx.x; i < 256 * kHistCopies / 4; i += kBlock)
+    reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  uint32_t *mine = hist[wave][threadIdx.x & (kHistCopies - 1)];
+  uint32_t *mine = hist + (threadIdx.x & (kHistCopies - 1));
 
   const int64_t seg_begin = (int64_t)seg * kHistSegment;
   const int64_t seg_end = seg_begin + kHistSegment < syms_per_stream ? seg_begin + kHistSegment : syms_per_stream;
@@ -41,88 +52,85 @@ __global__ __launch_bounds__(kBlock) void histogram_kernel(const uint8_t *__rest
   const uintptr_t mis = reinterpret_cast<uintptr_t>(p) & 15u;
   int64_t head = mis ? 16 - (int64_t)mis : 0;
   if (head > end - p) head = end - p;
-  if ((int64_t)threadIdx.x < head) atomicAdd(&mine[p[threadIdx.x]], 1u);
+  if ((int64_t)threadIdx.x < head) atomicAdd(&mine[(uint32_t)p[threadIdx.x] * kHistCopies], 1u);
   p += head;
   const int64_t n_vec = (end - p) / 16;
   const uint4 *pv = reinterpret_cast<const uint4 *>(p);
+  uint4 next = make_uint4(0u, 0u, 0u, 0u);
+  if ((int64_t)threadIdx.x < n_vec) next = load16_stream(pv + threadIdx.x);
   for (int64_t i = threadIdx.x; i < n_vec; i += kBlock) {
-    const uint4 v = load16_stream(pv + i);
+    const uint4 v = next;
+    if (i + kBlock < n_vec) next = load16_stream(pv + i + kBlock);
     const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) atomicAdd(&mine[(wds[j] >> (8 * b)) & 255u], 1u);
+      for (int b = 0; b < 4; ++b) atomicAdd(&mine[((wds[j] >> (8 * b)) & 255u) * kHistCopies], 1u);
     }
   }
   p += n_vec * 16;
-  if ((int64_t)threadIdx.x < end - p) atomicAdd(&mine[p[threadIdx.x]], 1u);
+  if ((int64_t)threadIdx.x < end - p) atomicAdd(&mine[(uint32_t)p[threadIdx.x] * kHistCopies], 1u);
   __syncthreads();
 
-  uint32_t c = 0;
-#pragma unroll
-  for (int w = 0; w < kBlock / 64; ++w)
-#pragma unroll
-    for (int r = 0; r < kHistCopies; ++r) c += hist[w][r][threadIdx.x];
+  const uint32_t c = sum_copies<kHistCopies>(hist + threadIdx.x * kHistCopies, threadIdx.x);
   if (c) atomicAdd(&counts[(int64_t)stream * 256 + threadIdx.x], c);
 }
 
 // The same with one histogram per bit depth: the depth of a symbol is that of its position, and a
-// thread's 16 symbols always share a position (positions hold a multiple of 16 symbols).
-__global__ __launch_bounds__(kBlock) void histogram_bucketed_kernel(const uint8_t *__restrict__ symbols,
-                                                                    int64_t syms_per_stream, uint32_t segs_per_stream,
-                                                                    uint32_t syms_per_pos, uint32_t streams_per_session,
-                                                                    const uint8_t *__restrict__ bits, int n_tables,
-                                                                    uint32_t pos_lanes, uint32_t *__restrict__ counts,
-                                                                    uint32_t *status) {
-  __shared__ uint32_t hist[kBlock / 64][PLC_MAX_BITS][256];
+// thread's 16 symbols always share a position (positions hold a multiple of 16 symbols).  Sixteen copies of four
+// tables are 64 KB, so a workgroup has eight wavefronts to share them, two workgroups to a compute unit.  The same
+// sizes: 71-72 us, against 105-226 us with one copy a wavefront; counting a thread's zeros in a register besides,
+// as that needed, costs more than the atomics it saves (82-86 us).
+constexpr int kBucketCopies = 16;
+constexpr int kBucketThreads = 512;
+
+__global__ __launch_bounds__(kBucketThreads) void histogram_bucketed_kernel(
+    const uint8_t *__restrict__ symbols, int64_t syms_per_stream, uint32_t segs_per_stream, uint32_t syms_per_pos,
+    uint32_t streams_per_session, const uint8_t *__restrict__ bits, int n_tables, uint32_t *__restrict__ counts,
+    uint32_t *status) {
+  __shared__ __attribute__((aligned(16))) uint32_t hist[PLC_MAX_BITS * 256 * kBucketCopies];
   const uint32_t stream = blockIdx.x / segs_per_stream;
   const uint32_t seg = blockIdx.x - stream * segs_per_stream;
-  const int wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int w = 0; w < kBlock / 64; ++w)
-#pragma unroll
-    for (int t = 0; t < PLC_MAX_BITS; ++t) hist[w][t][threadIdx.x] = 0u;
+  for (int i = threadIdx.x; i < n_tables * 256 * kBucketCopies / 4; i += kBucketThreads)
+    reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  uint32_t *mine = hist + (threadIdx.x & (kBucketCopies - 1));
 
-  const int64_t seg_begin = (int64_t)seg * kHistSegment;
-  const int64_t seg_end = seg_begin + kHistSegment < syms_per_stream ? seg_begin + kHistSegment : syms_per_stream;
+  constexpr int64_t kStep = kBucketThreads * 16;
+  const int64_t seg_begin = (int64_t)seg * kBucketSegment;
+  const int64_t seg_end = seg_begin + kBucketSegment < syms_per_stream ? seg_begin + kBucketSegment : syms_per_stream;
   const uint8_t *base = symbols + (int64_t)stream * syms_per_stream;
   const uint8_t *brow = bits + (int64_t)(stream / streams_per_session) * (syms_per_stream / syms_per_pos);
-  for (int64_t t0 = seg_begin + (int64_t)threadIdx.x * 16; t0 < seg_end; t0 += kBlock * 16) {
-    int b = brow[t0 / syms_per_pos];
+  int64_t t0 = seg_begin + (int64_t)threadIdx.x * 16;
+  uint4 next = make_uint4(0u, 0u, 0u, 0u);
+  int next_b = 1;
+  if (t0 < seg_end) {
+    next = load16_stream(base + t0);
+    next_b = brow[(uint32_t)t0 / syms_per_pos];
+  }
+  for (; t0 < seg_end; t0 += kStep) {
+    const uint4 v = next;
+    int b = next_b;
+    if (t0 + kStep < seg_end) {
+      next = load16_stream(base + t0 + kStep);
+      next_b = brow[(uint32_t)(t0 + kStep) / syms_per_pos];
+    }
     if (b < 1 || b > n_tables) {
       raise(status, PLC_ERR_INVALID);
       b = 1;
     }
-    uint32_t *h = hist[wave][b - 1];
-    const uint4 v = load16_stream(base + t0);
+    uint32_t *h = mine + (b - 1) * 256 * kBucketCopies;
     const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
-    // At coarse steps most residuals quantise to zero, and every lane would queue at that one counter: the
-    // zeros are counted apart and summed over the `pos_lanes` neighbouring lanes that share the position
-    // (a power of two, at most 16) before one lane adds them.
-    uint32_t zeros = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t sym = (wds[j] >> (8 * q)) & 255u;
-        if (sym == kZeroSymbol)
-          ++zeros;
-        else
-          atomicAdd(&h[sym], 1u);
-      }
+      for (int q = 0; q < 4; ++q) atomicAdd(&h[((wds[j] >> (8 * q)) & 255u) * kBucketCopies], 1u);
     }
-#pragma unroll
-    for (uint32_t m = 1; m < 16; m <<= 1)
-      if (m < pos_lanes) zeros += __shfl_xor(zeros, (int)m);
-    if ((threadIdx.x & (pos_lanes - 1)) == 0 && zeros) atomicAdd(&h[kZeroSymbol], zeros);
   }
   __syncthreads();
-  for (int t = 0; t < n_tables; ++t) {
-    uint32_t c = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) c += hist[w][t][threadIdx.x];
-    if (c) atomicAdd(&counts[((int64_t)stream * n_tables + t) * 256 + threadIdx.x], c);
+  for (int i = threadIdx.x; i < n_tables * 256; i += kBucketThreads) {
+    const uint32_t c = sum_copies<kBucketCopies>(hist + i * kBucketCopies, threadIdx.x);
+    if (c) atomicAdd(&counts[(int64_t)stream * n_tables * 256 + i], c);
   }
 }
 
@@ -281,17 +289,14 @@ extern "C" int plc_histogram_bucketed(const uint8_t *symbols, int64_t n_streams,
   if (syms_per_pos < 32 || syms_per_pos % 32 || syms_per_stream % syms_per_pos || streams_per_session < 1)
     return PLC_ERR_INVALID;
   if (reinterpret_cast<uintptr_t>(counts) % 16 || reinterpret_cast<uintptr_t>(symbols) % 16) return PLC_ERR_INVALID;
-  const int64_t segs = (syms_per_stream + kHistSegment - 1) / kHistSegment;
+  const int64_t segs = (syms_per_stream + kBucketSegment - 1) / kBucketSegment;
   if (n_streams * segs >= (1ll << 31) || n_streams >= (1ll << 31) / (256 * PLC_MAX_BITS)) return PLC_ERR_INVALID;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t n = n_streams * n_tables * 256;
-  // neighbouring lanes (16 symbols each) that always share a position: a power of two dividing syms_per_pos / 16
-  uint32_t pos_lanes = 2;
-  while (pos_lanes < 16 && (syms_per_pos / 16) % (2 * pos_lanes) == 0) pos_lanes *= 2;
   hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, counts, n);
-  hipLaunchKernelGGL(histogram_bucketed_kernel, dim3((unsigned)(n_streams * segs)), dim3(kBlock), 0, st, symbols,
-                     syms_per_stream, (uint32_t)segs, (uint32_t)syms_per_pos, (uint32_t)streams_per_session, bits,
-                     n_tables, pos_lanes, counts, status);
+  hipLaunchKernelGGL(histogram_bucketed_kernel, dim3((unsigned)(n_streams * segs)), dim3(kBucketThreads), 0, st,
+                     symbols, syms_per_stream, (uint32_t)segs, (uint32_t)syms_per_pos, (uint32_t)streams_per_session,
+                     bits, n_tables, counts, status);
   return launch_status();
 }
 

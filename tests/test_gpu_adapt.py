@@ -245,3 +245,36 @@ def test_bucketed_more_whole_streams_than_the_chain_decoder_takes(oracle, dev):
     words[woff[300] + 3] ^= 0x1555
     plc.plc_rans_decode_bucketed(freq, states, words, woff, nw, n_streams, N, 0, spp, sps, bits, B, dec, status)
     assert int(status.item()) == plc.PLC_ERR_CORRUPT
+
+
+@pytest.mark.parametrize("N", [1, 15, 17, 4095, 65535, 65536, 65537, 131089])
+@pytest.mark.parametrize("spread", [0.4, 60.0])
+def test_histogram_at_the_edges_of_segments(oracle, dev, N, spread):
+    """Segments of 65,536 symbols begun, full and passed, streams that start at odd addresses, symbols that crowd
+    into one counter and symbols all over the range."""
+    from paper_2604_15356_amd import plc
+    rng = np.random.default_rng(N)
+    sym = np.clip(np.rint(rng.normal(127, spread, size=(3, N))), 0, 255).astype(np.uint8)
+    counts = torch.full((3, 256), 7, dtype=torch.int32, device=dev)
+    print(f"N {N} spread {spread}", flush=True)
+    plc.plc_histogram(torch.from_numpy(sym).to(dev), 3, N, counts)
+    assert np.array_equal(u32(counts), oracle.histogram(sym))
+
+
+@pytest.mark.parametrize("spp, positions", [(32, 1), (32, 4095), (32, 4096), (32, 4097), (96, 1365), (96, 1366), (160, 1700)])
+@pytest.mark.parametrize("n_tables", [1, 3, 4])
+def test_bucketed_histogram_at_the_edges_of_segments(oracle, dev, spp, positions, n_tables):
+    """Segments of 131,072 symbols begun, full and passed; positions that straddle two of them (96 does not divide
+    one); fewer tables than the kernel has room for."""
+    from paper_2604_15356_amd import plc
+    N = spp * positions
+    rng = np.random.default_rng(N + n_tables)
+    sym = np.clip(np.rint(rng.normal(127, 1.5, size=(4, N))), 0, 255).astype(np.uint8)
+    bits = rng.integers(1, n_tables + 1, size=(2, positions)).astype(np.uint8)
+    counts = torch.full((4, n_tables, 256), 7, dtype=torch.int32, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    print(f"spp {spp} positions {positions} tables {n_tables}", flush=True)
+    plc.plc_histogram_bucketed(torch.from_numpy(sym).to(dev), 4, N, spp, 2, torch.from_numpy(bits).to(dev), n_tables,
+                               counts, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(counts), oracle.histogram_bucketed(sym, spp, 2, bits, n_tables=n_tables))
