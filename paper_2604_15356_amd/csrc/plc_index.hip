@@ -7,6 +7,7 @@
 // one session it is a single chain of n / 32 steps, so the per-position tables are prepared off the
 // chain; words go straight to global memory at positions ranked from the emission mask.
 #include <cmath>
+#include <type_traits>
 
 #include "plc_device.h"
 
@@ -18,85 +19,79 @@ constexpr uint32_t kScale = PLC_RANS_SCALE;
 constexpr uint32_t kLow = 1u << 16;
 constexpr int kMaxK = 32;
 
-// Frequencies of the k + 1 index symbols of one probability row; returns false for an invalid row
-// (its negative / NaN entries are taken as 0, so the table is usable either way).
-__device__ bool index_table(const float *__restrict__ p, int k, uint32_t f[kMaxK + 1]) {
+// Probabilities of one row into registers, all k loads in flight (k <= MAXK; k is uniform).
+template <int MAXK>
+__device__ __forceinline__ void load_row(const float *__restrict__ p, int k, float (&v)[MAXK]) {
+#pragma unroll
+  for (int j = 0; j < MAXK; ++j)
+    if (j < k) v[j] = p[j];
+}
+
+// Frequencies of the k + 1 index symbols of one probability row (zero behind them); returns false for an invalid
+// row (its negative / NaN entries are taken as 0, so the table is usable either way).  In registers throughout:
+// with the row in LDS and the loads inside the loop a position cost a memory latency per candidate.
+template <int MAXK>
+__device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint32_t (&f)[MAXK + 1]) {
   bool ok = true;
   float c = 0.0f;
   uint32_t prev = 0;
-  for (int j = 0; j < k; ++j) {
-    float pj = p[j];
-    if (!(pj >= 0.0f)) {
-      ok = false;
-      pj = 0.0f;
+  uint64_t zero = 0;  // symbols without a frequency
+#pragma unroll
+  for (int j = 0; j <= MAXK; ++j) {
+    uint32_t b = kScale;
+    if (j < MAXK && j < k) {  // uniform
+      float pj = p[j < MAXK ? j : 0];
+      if (!(pj >= 0.0f)) {
+        ok = false;
+        pj = 0.0f;
+      }
+      c = c + pj;
+      float scaled = __builtin_floorf(c * 4096.0f);
+      if (!(scaled < 4096.0f)) scaled = 4096.0f;  // probability above one (or an overflow) is clipped
+      b = (uint32_t)scaled;
     }
-    c = c + pj;
-    float scaled = __builtin_floorf(c * 4096.0f);
-    if (!(scaled < 4096.0f)) scaled = 4096.0f;  // probability above one (or an overflow) is clipped
-    const uint32_t b = (uint32_t)scaled;
     f[j] = b - prev;
     prev = b;
+    if (j <= k && f[j] == 0) zero |= 1ull << j;
   }
-  f[k] = kScale - prev;
-  for (int j = 0; j <= k; ++j) {
-    if (f[j] == 0) {
-      int donor = 0;
-      for (int m = 1; m <= k; ++m)
-        if (f[m] > f[donor]) donor = m;
-      f[donor] -= 1;
-      f[j] = 1;
+  // each takes a unit from the largest frequency of the moment, the lowest symbol on ties
+  while (zero) {
+    const int j = __builtin_ctzll(zero);
+    zero &= zero - 1;
+    uint32_t best = 0;
+#pragma unroll
+    for (int m = 0; m <= MAXK; ++m) {
+      const uint32_t key = (f[m] << 6) | (uint32_t)(63 - m);
+      best = key > best ? key : best;
     }
+    const int donor = 63 - (int)(best & 63u);
+#pragma unroll
+    for (int m = 0; m <= MAXK; ++m) f[m] = m == j ? 1u : m == donor ? f[m] - 1u : f[m];
   }
   return ok;
 }
 
 // Both coders give a session one workgroup of four wavefronts.  The chain of rANS steps is sequential,
 // but what a step needs from its position -- the table made from that position's probabilities -- is not:
-// wavefronts 1-3 prepare the tables of the next six groups (192 positions, one per thread, the table living
-// in the thread's own LDS row) while wavefront 0 codes the current six from LDS; one barrier per tile.
+// wavefronts 1-3 prepare the tables of the next six groups (192 positions, one per thread, in registers, with the
+// probabilities of the tile after already on their way) while wavefront 0 codes the current six from LDS; one
+// barrier per tile.  Bound by latency on both sides.  MAXK, 8 or 32, is the row length the registers are laid out
+// for: up to 8 candidates, the ordinary case, the search of the decoder runs in registers too.
+// One session, encode / decode (before: rows in LDS, one load after the other, the decoder's results stored by
+// wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 34 / 51 us (43 / 91),
+// 32,768 of 4 196 / 328 us (246 / 635), 4096 of 20 83 / 93 us (93 / 206), 8192 of 32 235 / 244 us (661 / 655).
 constexpr int kTileGroups = 6;
 constexpr int kTilePos = kTileGroups * kLanes;  // 192 = the three helper wavefronts
-constexpr int kRow = kMaxK + 2;                 // k + 1 frequencies or k + 2 cumulative values, padded
+constexpr int kRowWords = (kMaxK + 2) / 2;      // k + 2 cumulative values, two to a word; odd: rows on different banks
 constexpr int kIdxStageWords = 8192;            // decoder: index streams up to this many words are read from LDS
 
-// Frequencies of one row into an LDS row (same arithmetic as index_table).
-__device__ __forceinline__ bool index_table_lds(const float *__restrict__ p, int k, uint16_t *f) {
-  bool ok = true;
-  float c = 0.0f;
-  uint32_t prev = 0;
-  for (int j = 0; j < k; ++j) {
-    float pj = p[j];
-    if (!(pj >= 0.0f)) {
-      ok = false;
-      pj = 0.0f;
-    }
-    c = c + pj;
-    float scaled = __builtin_floorf(c * 4096.0f);
-    if (!(scaled < 4096.0f)) scaled = 4096.0f;
-    const uint32_t b = (uint32_t)scaled;
-    f[j] = (uint16_t)(b - prev);
-    prev = b;
-  }
-  f[k] = (uint16_t)(kScale - prev);
-  for (int j = 0; j <= k; ++j) {
-    if (f[j] == 0) {
-      int donor = 0;
-      for (int m = 1; m <= k; ++m)
-        if (f[m] > f[donor]) donor = m;
-      f[donor] -= 1;
-      f[j] = 1;
-    }
-  }
-  return ok;
-}
-
+template <int MAXK>
 __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restrict__ probs,
                                                            const int32_t *__restrict__ chosen, int n, int k,
                                                            uint32_t *__restrict__ states, uint16_t *__restrict__ words,
                                                            const uint64_t *__restrict__ word_off, uint64_t word_cap,
                                                            uint32_t *__restrict__ n_words, uint32_t *status) {
-  __shared__ uint16_t rows[kTilePos][kRow];
-  __shared__ uint32_t pair[2][kTileGroups][kLanes];  // f | cum << 16 of the symbol to code
+  __shared__ uint2 pair[2][kTileGroups][kLanes];  // f | cum << 16 of the symbol to code, 1 / f
   const int s = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint16_t *out = words + word_off[s];
@@ -105,37 +100,62 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
   // tile t holds groups top(t) - 1 down to top(t) - 6, top(t) = groups - 6 t (the encoder walks downwards)
+  const int u = threadIdx.x - 64, gi_mine = u >> 5, l_mine = u & 31;  // of a helper thread
+  auto position = [&](int t) {  // of its symbol in tile t, or -1
+    const int g = groups - kTileGroups * t - 1 - gi_mine;
+    const int i = g * kLanes + l_mine;
+    return wave > 0 && g >= 0 && i < n ? i : -1;
+  };
+  float ahead[MAXK];
+  int32_t chosen_ahead = 0;
+  auto fetch = [&](int t) {
+    const int i = position(t);
+    if (i < 0) return;
+    const int64_t row = (int64_t)s * n + i;
+    load_row<MAXK>(probs + row * k, k, ahead);
+    chosen_ahead = chosen[row];
+  };
+  fetch(0);
   for (int it = 0; it <= tiles; ++it) {
     if (wave > 0) {
       if (it < tiles) {
-        const int u = threadIdx.x - 64, gi = u >> 5, l = u & 31;
-        const int g = groups - kTileGroups * it - 1 - gi;
-        const int i = g * kLanes + l;
+        const bool has = position(it) >= 0;
+        float p[MAXK];
+#pragma unroll
+        for (int j = 0; j < MAXK; ++j) p[j] = ahead[j];
+        int j = chosen_ahead;
+        fetch(it + 1);
         uint32_t v = 1u;  // f = 1, cum = 0 for lanes without a symbol (never used)
-        if (g >= 0 && i < n) {
-          const int64_t row = (int64_t)s * n + i;
-          if (!index_table_lds(probs + row * k, k, rows[u])) raise(status, PLC_ERR_INVALID);
-          int j = chosen[row];
+        if (has) {
+          uint32_t f[MAXK + 1];
+          if (!index_table<MAXK>(p, k, f)) raise(status, PLC_ERR_INVALID);
           if (j < -1 || j >= k) {
             raise(status, PLC_ERR_INVALID);
             j = -1;
           }
           const int sym = j < 0 ? k : j;
-          uint32_t cs = 0;
-          for (int m = 0; m < sym; ++m) cs += rows[u][m];
-          v = (uint32_t)rows[u][sym] | (cs << 16);
+          uint32_t cs = 0, fs = 0;
+#pragma unroll
+          for (int m = 0; m <= MAXK; ++m) {
+            cs += m < sym ? f[m] : 0u;
+            fs = m == sym ? f[m] : fs;
+          }
+          v = fs | (cs << 16);
         }
-        pair[it & 1][gi][l] = v;
+        pair[it & 1][gi_mine][l_mine] = make_uint2(v, __float_as_uint(1.0f / (float)(v & 0xffffu)));
       }
     } else if (it > 0) {
       const int t = it - 1;
+      uint2 pr[kTileGroups];  // the tile's reads in flight together
+#pragma unroll
+      for (int gi = 0; gi < kTileGroups; ++gi) pr[gi] = pair[t & 1][gi][lane & 31];
+#pragma unroll
       for (int gi = 0; gi < kTileGroups; ++gi) {
         const int g = groups - kTileGroups * t - 1 - gi;
-        if (g < 0) break;  // uniform
+        if (g < 0) continue;  // uniform
         const int i = g * kLanes + lane;
         const bool has = lane < kLanes && i < n;
-        const uint32_t v = pair[t & 1][gi][lane & 31];
-        const uint32_t fs = v & 0xffffu, cs = v >> 16;
+        const uint32_t fs = pr[gi].x & 0xffffu, cs = pr[gi].x >> 16;
         // The sequential definition visits lane 31 first: a lane's word comes after those of the
         // emitting lanes above it.
         const bool emit = has && (x >> 20) >= fs;
@@ -151,7 +171,20 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
           x >>= 16;
         }
         nw += (uint32_t)__builtin_popcount(mask);
-        if (has) x = (x / fs) * kScale + (x % fs) + cs;
+        if (has) {
+          // x < f * 2^20, so x / f from the reciprocal is less than 2^20 * 4 * 2^-24 off, its whole part one at
+          // most; the remainder puts it right
+          uint32_t q = (uint32_t)((float)x * __uint_as_float(pr[gi].y));
+          int32_t r = (int32_t)(x - q * fs);
+          if (r < 0) {
+            q -= 1;
+            r += (int32_t)fs;
+          } else if (r >= (int32_t)fs) {
+            q += 1;
+            r -= (int32_t)fs;
+          }
+          x = q * kScale + (uint32_t)r + cs;
+        }
       }
     }
     __syncthreads();
@@ -162,14 +195,16 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
   }
 }
 
+template <int MAXK>
 __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restrict__ probs,
                                                            const uint32_t *__restrict__ states,
                                                            const uint16_t *__restrict__ words, uint64_t words_len,
                                                            const uint64_t *__restrict__ word_off,
                                                            const uint32_t *__restrict__ n_words, int n, int k,
                                                            int32_t *__restrict__ chosen, uint32_t *status) {
-  // cumulative frequencies cum[0..k+1] of every position of a tile (rows of 68 bytes, read as words)
-  __shared__ __attribute__((aligned(4))) uint16_t cums[2][kTilePos][kRow];
+  // cumulative frequencies cum[0..k+1] of every position of a tile, two to a word, 4096 behind them
+  __shared__ uint32_t cums[2][kTilePos][kRowWords];
+  __shared__ int8_t picked[2][kTilePos];  // what a tile's positions decoded to, written out by the helpers
   __shared__ uint16_t wstage[kIdxStageWords];
   const int s = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -186,80 +221,121 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
   uint32_t x = rans_lane ? states[(int64_t)s * kLanes + lane] : kLow;
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
+  const int u = threadIdx.x - 64;  // of a helper thread: its place in a tile
+  float ahead[MAXK];
+  auto fetch = [&](int t) {
+    const int64_t i = (int64_t)kTilePos * t + u;
+    if (wave > 0 && i < n) load_row<MAXK>(probs + ((int64_t)s * n + i) * k, k, ahead);
+  };
+  fetch(0);
   __syncthreads();
-  for (int it = 0; it <= tiles; ++it) {
-    if (wave > 0) {
-      if (it < tiles) {
-        const int u = threadIdx.x - 64;
-        const int i = (kTileGroups * it + (u >> 5)) * kLanes + (u & 31);
-        if (i < n) {
-          uint16_t *row = cums[it & 1][u];
-          if (!index_table_lds(probs + ((int64_t)s * n + i) * k, k, row)) raise(status, PLC_ERR_INVALID);
-          uint32_t acc = 0;
-          for (int m = 0; m <= k; ++m) {  // frequencies -> exclusive prefix sums, in place
-            const uint32_t f = row[m];
-            row[m] = (uint16_t)acc;
-            acc += f;
-          }
-          row[k + 1] = (uint16_t)acc;  // 4096
-        }
-      }
-    } else if (it > 0) {
-      const int t = it - 1;
-      for (int gi = 0; gi < kTileGroups; ++gi) {
-        const int g = kTileGroups * t + gi;
-        if (g >= groups) break;  // uniform
-        const int i = g * kLanes + lane;
-        const bool has = rans_lane && i < n;
-        if (has) {
-          const uint16_t *row = cums[t & 1][gi * kLanes + lane];
-          const uint32_t slot = x & (kScale - 1);
-          int sym = 0;
-          uint32_t cs, fs;
-          if (k <= 8) {  // uniform
-            // the row's ten values in one LDS round trip, then the search in registers: the symbol is the
-            // number of interval starts cum[1..k] at or below the slot, its start the largest value at
-            // or below the slot and its end the smallest above (cum[k+1] = 4096 always is)
-            const uint32_t *r32 = reinterpret_cast<const uint32_t *>(row);
-            const uint32_t v[5] = {r32[0], r32[1], r32[2], r32[3], r32[4]};
-            cs = 0;
-            uint32_t next = kScale;
+  // One tile's steps.  Wavefront 0 touches global memory only where the words are not staged: a wait for a load would
+  // also be one for every store before it.
+  auto code_tile = [&](int t, auto from_lds) {
+    constexpr bool kStaged = decltype(from_lds)::value;
+    const uint32_t(*tile)[kRowWords] = cums[t & 1];
+    uint32_t v[5] = {};  // up to 8 candidates: a row whole, asked for a step ahead
+    if (MAXK == 8) {
 #pragma unroll
-            for (int m = 1; m <= 9; ++m) {
-              const uint32_t c = (m & 1) ? v[m >> 1] >> 16 : v[m >> 1] & 0xffffu;
-              const bool in = m <= k + 1;  // uniform
-              if (in && c <= slot) {
-                cs = c > cs ? c : cs;
-                sym += m <= k;
-              }
-              if (in && c > slot) next = c < next ? c : next;
-            }
-            fs = next - cs;
-          } else {
-            while (sym < k && row[sym + 1] <= slot) ++sym;  // the symbol whose interval holds the slot
-            cs = row[sym];
-            fs = (uint32_t)row[sym + 1] - cs;
-          }
-          chosen[(int64_t)s * n + i] = sym == k ? -1 : sym;
-          x = fs * (x >> 12) + slot - cs;
-        }
-        // Reading lanes are served from the end of the list, lane 0 first.
-        const bool need = has && x < kLow;
-        const uint32_t mask = (uint32_t)__ballot(need);
-        if (need) {
-          const uint32_t below = mask & ((1u << lane) - 1u);
-          const uint64_t rank = (uint32_t)__builtin_popcount(below);
-          uint32_t word = 0;
-          if (rank < ptr) {
-            word = staged ? wstage[ptr - 1 - rank] : words[base + ptr - 1 - rank];
-          } else {
-            corrupt = true;
-          }
-          x = (x << 16) | word;
-        }
-        const uint32_t used = (uint32_t)__builtin_popcount(mask);
-        ptr = used < ptr ? ptr - used : 0;
+      for (int m = 0; m < 5; ++m) v[m] = tile[lane & 31][m];
+    }
+    for (int gi = 0; gi < kTileGroups; ++gi) {
+      const int g = kTileGroups * t + gi;
+      if (g >= groups) break;  // uniform
+      const int i = g * kLanes + lane;
+      const bool has = rans_lane && i < n;
+      uint32_t next_v[5] = {};
+      if (MAXK == 8) {
+        const int ahead_gi = gi + 1 < kTileGroups ? gi + 1 : gi;
+#pragma unroll
+        for (int m = 0; m < 5; ++m) next_v[m] = tile[ahead_gi * kLanes + (lane & 31)][m];
       }
+      const uint32_t slot = x & (kScale - 1);
+      uint32_t sym = 0, cs = 0, next = kScale;
+      if (MAXK == 8) {
+        // the symbol is the number of interval starts cum[1..k] at or below the slot, its start the largest value
+        // at or below the slot and its end the smallest above (what lies behind cum[k+1] = 4096 is taken as that)
+#pragma unroll
+        for (int m = 1; m <= 8; ++m) {
+          uint32_t c = (m & 1) ? v[m >> 1] >> 16 : v[m >> 1] & 0xffffu;
+          c = m <= k ? c : kScale;  // uniform
+          const bool in = c <= slot;
+          cs = in ? c : cs;  // ascending
+          sym += in ? 1u : 0u;
+          const uint32_t above = in ? kScale : c;
+          next = above < next ? above : next;
+        }
+      } else {
+        // the last interval start at or below the slot, by halving; the last one found above it is its end
+        const uint32_t *row = tile[gi * kLanes + (lane & 31)];
+        for (uint32_t half = 32; half; half >>= 1) {
+          if (half > (uint32_t)k) continue;  // uniform
+          const uint32_t at = sym + half, within = at <= (uint32_t)k ? at : (uint32_t)k;
+          const uint32_t w = row[within >> 1];
+          const uint32_t c = at <= (uint32_t)k ? (at & 1 ? w >> 16 : w & 0xffffu) : kScale;
+          const bool in = c <= slot;
+          sym = in ? at : sym;
+          cs = in ? c : cs;
+          next = in ? next : c;
+        }
+      }
+      if (has) {
+        picked[t & 1][gi * kLanes + lane] = (int8_t)(sym == (uint32_t)k ? -1 : (int)sym);
+        x = (next - cs) * (x >> 12) + slot - cs;
+      }
+      if (MAXK == 8) {
+#pragma unroll
+        for (int m = 0; m < 5; ++m) v[m] = next_v[m];
+      }
+      // Reading lanes are served from the end of the list, lane 0 first.
+      const bool need = has && x < kLow;
+      const uint32_t mask = (uint32_t)__ballot(need);
+      if (need) {
+        const uint32_t below = mask & ((1u << lane) - 1u);
+        const uint64_t rank = (uint32_t)__builtin_popcount(below);
+        uint32_t word = 0;
+        if (rank < ptr) {
+          word = kStaged ? wstage[ptr - 1 - rank] : words[base + ptr - 1 - rank];
+        } else {
+          corrupt = true;
+        }
+        x = (x << 16) | word;
+      }
+      const uint32_t used = (uint32_t)__builtin_popcount(mask);
+      ptr = used < ptr ? ptr - used : 0;
+    }
+  };
+  // iteration it: tables of tile it, steps of tile it - 1, results of tile it - 2
+  for (int it = 0; it <= tiles + 1; ++it) {
+    if (wave > 0) {
+      if (it >= 2) {
+        const int64_t i = (int64_t)kTilePos * (it - 2) + u;
+        if (i < n) chosen[(int64_t)s * n + i] = picked[it & 1][u];
+      }
+      if (it < tiles) {
+        const bool has = (int64_t)kTilePos * it + u < n;
+        float p[MAXK];
+#pragma unroll
+        for (int j = 0; j < MAXK; ++j) p[j] = ahead[j];
+        fetch(it + 1);
+        if (has) {
+          uint32_t f[MAXK + 1];
+          if (!index_table<MAXK>(p, k, f)) raise(status, PLC_ERR_INVALID);
+          uint32_t *row = cums[it & 1][u];
+          uint32_t acc = 0;
+#pragma unroll
+          for (int m = 0; m <= MAXK; m += 2) {
+            const uint32_t odd = acc + f[m];
+            if (m <= k + 1) row[m / 2] = acc | (odd << 16);  // uniform
+            acc = odd + (m < MAXK ? f[m + 1 <= MAXK ? m + 1 : 0] : 0u);
+          }
+        }
+      }
+    } else if (it > 0 && it <= tiles) {
+      if (staged)
+        code_tile(it - 1, std::true_type{});
+      else
+        code_tile(it - 1, std::false_type{});
     }
     __syncthreads();
   }
@@ -274,20 +350,26 @@ struct Thresholds {
 };
 
 // Bit depth of every position from the frequency of its index symbol; one thread per position.
+template <int MAXK>
 __global__ __launch_bounds__(kBlock) void surprisal_bits_kernel(const float *__restrict__ probs,
                                                                 const int32_t *__restrict__ chosen, int64_t rows,
                                                                 int k, Thresholds t, int bmax,
                                                                 uint8_t *__restrict__ bits, uint32_t *status) {
   const int64_t row = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (row >= rows) return;
-  uint32_t f[kMaxK + 1];
-  if (!index_table(probs + row * k, k, f)) raise(status, PLC_ERR_INVALID);
+  float p[MAXK];
+  uint32_t f[MAXK + 1];
+  load_row<MAXK>(probs + row * k, k, p);
   int j = chosen[row];
+  if (!index_table<MAXK>(p, k, f)) raise(status, PLC_ERR_INVALID);
   if (j < -1 || j >= k) {
     raise(status, PLC_ERR_INVALID);
     j = -1;
   }
-  const uint32_t fs = f[j < 0 ? k : j];
+  const int sym = j < 0 ? k : j;
+  uint32_t fs = 0;
+#pragma unroll
+  for (int m = 0; m <= MAXK; ++m) fs = m == sym ? f[m] : fs;
   int b = 1;
   for (int m = 2; m <= bmax; ++m)
     if (fs <= t.thr[m]) b = m;
@@ -316,8 +398,9 @@ extern "C" int plc_index_encode(const float *probs, const int32_t *chosen, int32
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((word_cap > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  hipLaunchKernelGGL(index_encode_kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs,
-                     chosen, n, k, states, words, word_off, word_cap, n_words, status);
+  const auto kernel = k <= 8 ? index_encode_kernel<8> : index_encode_kernel<kMaxK>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
+                     k, states, words, word_off, word_cap, n_words, status);
   return launch_status();
 }
 
@@ -327,8 +410,9 @@ extern "C" int plc_index_decode(const float *probs, const uint32_t *states, cons
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((words_len > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  hipLaunchKernelGGL(index_decode_kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs,
-                     states, words, words_len, word_off, n_words, n, k, chosen, status);
+  const auto kernel = k <= 8 ? index_decode_kernel<8> : index_decode_kernel<kMaxK>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, states, words,
+                     words_len, word_off, n_words, n, k, chosen, status);
   return launch_status();
 }
 
@@ -358,7 +442,8 @@ extern "C" int plc_surprisal_bits(const float *probs, const int32_t *chosen, int
     t.thr[m] = thr[m];
   }
   const int64_t rows = (int64_t)S * n;
-  hipLaunchKernelGGL(surprisal_bits_kernel, dim3((unsigned)((rows + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+  const auto kernel = k <= 8 ? surprisal_bits_kernel<8> : surprisal_bits_kernel<kMaxK>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), probs, chosen, rows, k, t, bmax, bits, status);
   return launch_status();
 }

@@ -183,6 +183,44 @@ def test_oracle_written_index_stream_decodes_on_the_gpu(oracle, dev):
     assert int(status.item()) == plc.PLC_ERR_CORRUPT
 
 
+@pytest.mark.parametrize("k, n", [(1, 1), (1, 193), (2, 31), (7, 191), (8, 192), (8, 385), (9, 33), (15, 193), (16, 200),
+                                  (31, 70), (32, 193)])
+def test_index_coder_at_the_edges_of_rows_and_tiles(oracle, dev, k, n):
+    """Row lengths around the register form's limit of 8, tiles of 192 positions begun, full and passed, rows whose
+    symbols get no frequency of their own (zeros, tiny values) and rows that sum to more than one."""
+    O = oracle
+    from paper_2604_15356_amd import plc
+    S = 2
+    rng = np.random.default_rng(100 * k + n)
+    probs = rng.exponential(size=(S, n, k)).astype(np.float32) ** 3
+    probs /= probs.sum(-1, keepdims=True) * rng.uniform(0.6, 1.3, size=(S, n, 1)).astype(np.float32)
+    probs[:, ::3] *= rng.choice(np.array([0.0, 1e-5, 1.0], np.float32), size=probs[:, ::3].shape)
+    probs[:, ::7] = 0.0
+    ch = rng.integers(-1, k, size=(S, n)).astype(np.int32)
+    cap = 2 * n + 64
+    ref = O.index_encode(probs, ch, word_cap=cap)
+    thr = np.array([0, 0, 2048, 700, 90], np.uint16)
+    dp, dc = torch.from_numpy(probs).to(dev), torch.from_numpy(ch).to(dev)
+    z = lambda count, dt: torch.zeros(count, dtype=dt, device=dev)
+    states, words, n_words, status = z(S * 32, torch.int32), z(S * cap, torch.int16), z(S, torch.int32), z(1, torch.int32)
+    off = torch.arange(S, dtype=torch.int64, device=dev) * cap
+    print(f"k {k} n {n}", flush=True)
+    plc.plc_index_encode(dp, dc, S, n, k, states, words, off, cap, n_words, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), ref["n_words"])
+    assert np.array_equal(u32(states).ravel(), ref["states"].ravel())
+    for s in range(S):
+        nw = int(ref["n_words"][s])
+        at = int(ref["word_off"][s])
+        assert np.array_equal(u16(words)[s * cap:s * cap + nw], ref["words"][at:at + nw]), f"session {s}"
+    out = torch.full((S, n), -9, dtype=torch.int32, device=dev)
+    plc.plc_index_decode(dp, states, words, off, n_words, S, n, k, out, status)
+    assert int(status.item()) == 0 and np.array_equal(out.cpu().numpy(), ch)
+    bits = z(S * n, torch.uint8)
+    plc.plc_surprisal_bits(dp, dc, S, n, k, thr, bits, status)
+    assert int(status.item()) == 0 and np.array_equal(u8(bits).ravel(), O.surprisal_bits(probs, ch, thr).ravel())
+
+
 def test_error_statuses_of_the_conditional_calls(oracle, dev):
     from paper_2604_15356_amd import plc
     w = make_workload("tiny", device=dev, overrides=dict(L=1, H=1, n=64, seed=33))
