@@ -1149,6 +1149,8 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
           if (v >= pad && v - pad < cap) wp[v - pad] = tail;
         }
       }
+      wave_sync();  // the next pair's reads come behind the tail's way to its front, from other lanes (no barrier
+                    // stands between them where pairs leave one behind the other at the unit's end)
     };
     for (int32_t it = 0; it < n_iters; ++it) {
       const int32_t phase = it & 3;

@@ -288,6 +288,49 @@ def test_few_unit_coders_at_the_edges_of_their_batches(oracle, dev, N):
     assert torch.equal(dec, sym_t)
 
 
+@pytest.mark.parametrize("batches", [1, 2, 3, 4, 5, 6, 7, 9, 13, 17])
+@pytest.mark.parametrize("tables", [1, 4])
+def test_few_unit_encoders_whose_last_words_leave_together(oracle, dev, batches, tables):
+    """What is left of a unit's words at its end leaves pair of batches behind pair of batches, each handing the
+    words of its incomplete 16-byte piece on to the next: every number of pairs left over, units at every
+    16-byte misalignment (so with every number of words handed on), with one table and with one per bit depth."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    spp, n_streams = 64, 16
+    for N in (512 * batches, 512 * batches - 7 * 32):
+        N -= N % spp
+        rng = np.random.default_rng(N + tables)
+        bits = rng.integers(1, tables + 1, size=(2, N // spp)).astype(np.uint8)
+        width = 2.0 * 2.0 ** np.repeat(np.repeat(bits, spp, axis=1), n_streams // 2, axis=0) if tables > 1 else 40.0
+        sym = np.clip(np.rint(rng.standard_normal((n_streams, N)) * width + 127), 0, 254).astype(np.uint8)
+        sym_t, bits_t = torch.from_numpy(sym).to(dev), torch.from_numpy(bits).to(dev)
+        cap, lead = (N + 7) // 8 * 8 + 5, 3
+        i32, i16 = torch.int32, torch.int16
+        states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+        words = torch.zeros(lead + n_streams * cap, dtype=i16, device=dev)
+        word_off = lead + torch.arange(n_streams, dtype=torch.int64, device=dev) * cap
+        status = torch.zeros(1, dtype=i32, device=dev)
+        print(f"  {N} symbols, {tables} tables", flush=True)
+        if tables > 1:
+            freq = O.build_freq_sparse(O.histogram_bucketed(sym, spp, n_streams // 2, bits, n_tables=tables))
+            enc = O.rans_encode_bucketed(sym, freq, spp, n_streams // 2, bits, word_cap_per_unit=cap)
+            freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+            plc.plc_rans_encode_bucketed(sym_t, n_streams, N, 0, spp, n_streams // 2, bits_t, tables, freq_t, states,
+                                         words, word_off, cap, n_words, status)
+        else:
+            freq, _ = O.build_freq(O.histogram(sym))
+            enc = O.rans_encode(sym, freq, word_cap_per_unit=cap)
+            freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+            plc.plc_rans_encode(sym_t, n_streams, N, 0, freq_t, states, words, word_off, cap, n_words, status)
+        assert int(status.item()) == 0
+        assert np.array_equal(u32(n_words), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+        expect = np.zeros(lead + n_streams * cap, dtype=np.uint16)
+        for unit in range(n_streams):
+            nw = int(enc["n_words"][unit])
+            expect[lead + unit * cap:lead + unit * cap + nw] = enc["words"][unit * cap:unit * cap + nw]
+        assert np.array_equal(u16(words), expect)
+
+
 def test_more_whole_stream_units_than_the_chain_kernels_take(oracle, dev):
     """Whole-stream units beyond the bound of the three-wavefront encoder and the chain decoder
     (plc_rans_encode / plc_rans_decode then run the many-unit kernels with one wavefront per workgroup):
