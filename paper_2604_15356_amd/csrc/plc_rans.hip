@@ -809,18 +809,21 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 //           steps and packs the 16-bit words into an LDS region per batch.
 // They meet at one workgroup barrier per batch of 16 steps.  The coder writes its last four states of a batch in
 // the batch after (and waits for nothing at a barrier), so the packer works two batches behind it.
-// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer batch it - 4.  The mover takes in a round
+// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer batch it - 4, whose thresholds it has read
+// two iterations earlier: the ring then needs three slots and three units share a compute unit's LDS.  The mover takes in a round
 // of symbols every fourth iteration and sends the words of two batches out in each of the two after it: waiting
 // for symbols is waiting for every store before them as well (one counter), and these are then two iterations
 // old (stores in every iteration held the barrier up every round).
-constexpr int kEntrySlots = 5;  // feeder writes b + 2, coder reads b and b + 1, packer reads b - 2
+constexpr int kEntrySlots = 3;  // feeder writes b + 2, coder reads b and b + 1, packer the thresholds of b
 constexpr int kStateSlots = 3;  // coder writes b and the end of b - 1, packer reads b - 2
 constexpr int kListRegion = 2 * kBatchSyms + 8;  // the words of a pair of batches behind up to seven carried ones
 constexpr int kListRegions = 3;  // the packer's, and the up to two in front of it that have not left
 constexpr int kPipeThreads = 256;
-// These kernels hold two units per compute unit (LDS), 512 at a time, and a unit's time is that of its chain:
-// up to two rounds they beat the many-unit kernels (768 units: encode 1.7 against 2.8 ms, decode 3.3 against
-// 4.9 ms), at three they tie with them.
+// Up to two rounds of 512 units the kernels with one chain per workgroup beat the many-unit kernels.  The encoder's
+// LDS lets three units share a compute unit (768 at a time), the decoder's two, and the more of them do the less
+// each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at 1025:
+// encode 100 / 143 / 190 / 266 and 398 us, with a table per depth 131 / 165 / 201 / 298 and 407 us (with five entry
+// slots, two units to a compute unit, 768 took 229 and 277 us), decode 190 / 199 / 390 / 394 and 621 us.
 constexpr int64_t kPipeMaxUnits = 1024;
 constexpr int64_t kChainMaxUnits = 1024;  // the same bound for the decoder of whole-stream units
 // The decoder with one table per depth holds one unit per compute unit (its tables take 128 KB of LDS): two
@@ -886,16 +889,41 @@ __device__ __forceinline__ void pipe_batch(uint32_t &x, u32x4 (&e)[2][4], u32x4 
   }
 }
 
+// Table entry of 8 bytes, for the form with a table per bit depth.  .x = m; .y = (4096 - f) | .w << 12 | s << 25, and bit
+// 31 for a symbol with f = 0; the threshold follows from f: f * 2^20 - 1 = -(4096 - f) * 2^20 - 1 mod 2^32.
+__device__ __forceinline__ uint2 pack_enc_entry(const uint4 e) {
+  if (e.w & 0x80000000u) return make_uint2(0u, 0x80000000u);
+  return make_uint2(e.x, (e.z & 0xfffu) | (e.w << 12) | ((e.z >> 24) << 25));
+}
+__device__ __forceinline__ u32x4 unpack_enc_entry(const uint2 c) {
+  u32x4 e;
+  e.x = c.x;
+  e.z = ((c.y >> 1) & 0x0f000000u) | (c.y & 0xfffu);
+  uint32_t thr;
+  asm("v_mad_i32_i24 %0, %1, %2, -1" : "=v"(thr) : "v"(e.z), "s"(-(1 << 20)));  // (of the low 24 bits)
+  e.y = thr;
+  e.w = (c.y >> 12) & 0x1fffu;
+  return e;
+}
+
 template <bool ADAPT>  // ADAPT: one table per bit depth (the *_bucketed call)
 __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const RansArgs a) {
   constexpr int kIdentity = (ADAPT ? PLC_MAX_BITS : 1) * 256;  // index of the entry that leaves a state unchanged
-  __shared__ uint4 table[kIdentity + 1];
-  __shared__ uint16_t table_of_group[2][kSuperGroups];  // ADAPT: table offset of each group of a staging round
+  using Entry = std::conditional_t<ADAPT, uint2, uint4>;
+  __shared__ Entry table[kIdentity + 1];
+  // ADAPT: table of each group of a staging round, in the order in which the feeder's halves want them: a full
+  // batch's eight odd groups from the top, then its eight even ones
+  __shared__ __attribute__((aligned(8))) uint8_t table_of_group[2][kSuperGroups];
+  auto group_at = [](int g) { return (g & ~15) + ((g & 1) ? 0 : 8) + 7 - ((g & 15) >> 1); };
   __shared__ uint4 entry_ring[kEntrySlots][kBatch][kLanes];
   __shared__ uint4 state_ring[kStateSlots][kBatch / 4][kLanes];
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
-  __shared__ __attribute__((aligned(16))) uint16_t word_list[kListRegions + 1][kListRegion];  // + 1: spare, see below
+  __shared__ __attribute__((aligned(16))) uint16_t word_list[kListRegions][kListRegion];
+  __shared__ uint16_t spare_word[64];
   __shared__ uint32_t list_fill[kListRegions];  // positions in use of each region of the list
+  static_assert(workgroups_per_cu(sizeof(table) + sizeof(table_of_group) + sizeof(entry_ring) + sizeof(state_ring) +
+                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill)) >= 3,
+                "three units to a compute unit: without the third 513 to 768 units take a second round");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t unit = blockIdx.x;  // one unit per stream, one workgroup per unit
@@ -912,13 +940,25 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     for (int t = 0; t < n_tables; ++t) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if (r == wave)
-          table[t * 256 + lane * 4 + r] =
-              long_form ? make_enc_entry<true>(f[t][r], cum[t]) : make_enc_entry<false>(f[t][r], cum[t]);
+        if (r == wave) {
+          const uint4 e = long_form ? make_enc_entry<true>(f[t][r], cum[t]) : make_enc_entry<false>(f[t][r], cum[t]);
+          if constexpr (ADAPT) {
+            table[t * 256 + lane * 4 + r] = pack_enc_entry(e);
+          } else {
+            table[t * 256 + lane * 4 + r] = e;
+          }
+        }
         cum[t] += f[t][r];
       }
     }
-    if (threadIdx.x == 0) table[kIdentity] = make_uint4(0u, 0xffffffffu, 0u, 0u);  // never emits, x' = x
+    if (threadIdx.x == 0) {  // never emits, x' = x
+      const uint4 e = make_uint4(0u, 0xffffffffu, 0u, 0u);
+      if constexpr (ADAPT) {
+        table[kIdentity] = pack_enc_entry(e);
+      } else {
+        table[kIdentity] = e;
+      }
+    }
   }
 
   const uint32_t len = (uint32_t)a.syms_per_stream;
@@ -1000,19 +1040,26 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
           u32x4 e[kBatch / 2];  // native vectors: each entry moves as one 16-byte LDS access
 #pragma unroll
           for (int p = 0; p < kBatch / 2; ++p) sy[p] = s0[2 * kLanes * (kBatch / 2 - 1 - p)];
-          if (ADAPT) {  // the group of step 2p + half sits at top - bottom - 1 - half - 2p of the round
-            const uint16_t *tg = &table_of_group[r & 1][top - bottom - 2 * (kBatch / 2 - 1) - 1 - half];
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p) sy[p] += tg[2 * (kBatch / 2 - 1 - p)];
-          }
-#pragma unroll
-          for (int p = 0; p < kBatch / 2; ++p) e[p] = *reinterpret_cast<const u32x4 *>(&table[sy[p]]);
           uint32_t any = 0;
+          if constexpr (ADAPT) {  // the group of step 2p + half sits at top - bottom - 1 - half - 2p of the round
+            const uint2 tg = *reinterpret_cast<const uint2 *>(&table_of_group[r & 1][top - bottom - kBatch + 8 * half]);
+            uint2 c[kBatch / 2];
 #pragma unroll
-          for (int p = 0; p < kBatch / 2; ++p) {
-            any |= e[p].w;
-            *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = e[p];
+            for (int p = 0; p < kBatch / 2; ++p)  // symbol | table << 8
+              c[p] = table[__builtin_amdgcn_perm(p < 4 ? tg.x : tg.y, sy[p], 0x0c0c0400u + ((uint32_t)(p & 3) << 8))];
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) {
+              any |= c[p].y;
+              e[p] = unpack_enc_entry(c[p]);
+            }
+          } else {
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) e[p] = *reinterpret_cast<const u32x4 *>(&table[sy[p]]);
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) any |= e[p].w;
           }
+#pragma unroll
+          for (int p = 0; p < kBatch / 2; ++p) *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = e[p];
           bad_symbol = bad_symbol || (any & 0x80000000u) != 0;
         } else {
           // the top batch: `head` groups, the first of them possibly ragged, then identity steps
@@ -1023,10 +1070,15 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
             const bool has = j < head && t < (int64_t)len;
             const int64_t idx = has ? t - (int64_t)bottom * kLanes + mis : 0;
             uint32_t byte = sb[idx];
-            if (ADAPT && has) byte += table_of_group[r & 1][top - 1 - j - bottom];
-            const uint4 e = table[has ? byte : (uint32_t)kIdentity];
-            bad_symbol = bad_symbol || (e.w & 0x80000000u) != 0;
-            eo[2 * p * kLanes] = e;
+            if (ADAPT && has) byte += (uint32_t)table_of_group[r & 1][group_at(top - 1 - j - bottom)] << 8;
+            const Entry c = table[has ? byte : (uint32_t)kIdentity];
+            if constexpr (ADAPT) {
+              bad_symbol = bad_symbol || (c.y & 0x80000000u) != 0;
+              *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = unpack_enc_entry(c);
+            } else {
+              bad_symbol = bad_symbol || (c.w & 0x80000000u) != 0;
+              eo[2 * p * kLanes] = c;
+            }
           }
         }
         slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
@@ -1039,49 +1091,59 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     __syncthreads();  // tables
     __syncthreads();  // first symbols
     uint32_t fill = pad;  // uniform: positions of the region in use, the first of them not this pair's words
-    int slot = 0, sslot = 0, region = 0;
-    for (int32_t it = 0; it < n_iters; ++it) {
+    int region = 0;
+    // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
+    // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
+    const int half = lane >> 5, rl = 31 - (lane & 31);
+    uint16_t *const spare = &spare_word[lane];
+    // The thresholds are read two batches ahead of the states, while the coder is at their entries, and wait in
+    // registers: three sets, so three iterations a turn.
+    uint32_t thrs[3][kBatch / 2];
+    auto pack = [&](auto turn, int32_t it) {
+      constexpr int kTurn = decltype(turn)::value;  // it mod 3
+      {
+        const uint32_t *ts = &entry_ring[(kTurn + 1) % 3][half][rl].y;  // batch it - 2
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) thrs[kTurn][p] = ts[2 * p * kLanes * 4];
+      }
       const int32_t b = it - 4;
       if (b >= 0 && b < n_batches) {
-        // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
-        // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
-        const int half = lane >> 5, rl = 31 - (lane & 31);
-        const uint32_t *xs = reinterpret_cast<const uint32_t *>(&state_ring[sslot][0][rl]) + half;
-        const uint32_t *ts = &entry_ring[slot][half][rl].y;
+        const uint32_t(&thr)[kBatch / 2] = thrs[(kTurn + 1) % 3];
+        const uint32_t *xs = reinterpret_cast<const uint32_t *>(&state_ring[(kTurn + 2) % 3][0][rl]) + half;
         uint16_t *list = word_list[region];
-        uint16_t *spare = &word_list[kListRegions][lane];
         // In phases, each over all eight step pairs: reads, emit masks, list positions, stores.  A lane without
         // a word stores into a slot of its own instead of sitting out the store.
-        uint32_t xps[kBatch / 2], thrs[kBatch / 2], at[kBatch / 2];
+        uint32_t xps[kBatch / 2], at[kBatch / 2];
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
 #pragma unroll
         for (int p = 0; p < kBatch / 2; ++p) {
-          xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
-          thrs[p] = ts[2 * p * kLanes * 4];
-        }
-#pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) {
-          const uint64_t mask = __ballot(xps[p] > thrs[p]);
+          const uint64_t mask = __ballot(xps[p] > thr[p]);
           at[p] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, fill));
           fill += (uint32_t)__builtin_popcountll(mask);
         }
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) *(xps[p] > thrs[p] ? list + at[p] : spare) = (uint16_t)xps[p];
+        for (int p = 0; p < kBatch / 2; ++p) *(xps[p] > thr[p] ? list + at[p] : spare) = (uint16_t)xps[p];
         if ((b & 1) || b == n_batches - 1) {  // on to the next pair's region
           if (lane == 0) list_fill[region] = fill;
           region = region == kListRegions - 1 ? 0 : region + 1;
           fill &= 7u;
         }
-        slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
-        sslot = sslot == kStateSlots - 1 ? 0 : sslot + 1;
       }
       lds_barrier();
+    };
+    static_assert(kEntrySlots == 3 && kStateSlots == 3, "three iterations a turn");
+    for (int32_t it = 0; it < n_iters; it += 3) {
+      pack(std::integral_constant<int, 0>{}, it);
+      if (it + 1 < n_iters) pack(std::integral_constant<int, 1>{}, it + 1);
+      if (it + 2 < n_iters) pack(std::integral_constant<int, 2>{}, it + 2);
     }
   } else {
     // ---- mover: symbols of the coming round, words of batch it - 5
     bool bad_depth = false;
     uint4 nv[kStagePieces];         // next round's symbols in flight
     bool ntake[kStagePieces];
-    uint32_t ntog = 0;              // ADAPT: table offset of group bottom + lane of the next round
+    uint32_t ntog = 0;              // ADAPT: table of group bottom + lane of the next round
     auto round_load = [&](int32_t r) {
       const int64_t lo = (int64_t)round_bottom(r) * kLanes;
       int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
@@ -1094,14 +1156,14 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       }
       if (ADAPT) {
         const int32_t g = round_bottom(r) + lane;
-        ntog = (r < n_rounds && g < batch_top(4 * r)) ? group_table(a, unit, 0, g, 256u, &bad_depth) : 0u;
+        ntog = (r < n_rounds && g < batch_top(4 * r)) ? group_table(a, unit, 0, g, 1u, &bad_depth) : 0u;
       }
     };
     auto round_store = [&](int buf) {
 #pragma unroll
       for (int i = 0; i < kStagePieces; ++i)
         if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
-      if (ADAPT) table_of_group[buf][lane] = (uint16_t)ntog;
+      if (ADAPT) table_of_group[buf][group_at(lane)] = (uint8_t)ntog;
     };
     round_load(0);
     __syncthreads();  // tables

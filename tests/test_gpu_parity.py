@@ -331,6 +331,46 @@ def test_few_unit_encoders_whose_last_words_leave_together(oracle, dev, batches,
         assert np.array_equal(u16(words), expect)
 
 
+@pytest.mark.parametrize("n_streams", [257, 513, 768, 769, 1024])
+@pytest.mark.parametrize("tables", [1, 4])
+def test_few_unit_encoders_side_by_side_on_a_compute_unit(oracle, dev, n_streams, tables):
+    """Two, three and more whole-stream units to a compute unit, one table and one per bit depth, a ragged first batch
+    and more batches than the rings have slots; every unit against the oracle."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    spp, N = 96, 16 * 32 * 9 + 96 * 3
+    rng = np.random.default_rng(n_streams + tables)
+    bits = rng.integers(1, tables + 1, size=(1, N // spp)).astype(np.uint8)
+    width = 2.0 * 3.0 ** np.repeat(bits, spp, axis=1)
+    sym = np.clip(np.rint(rng.standard_normal((n_streams, N)) * width + 127), 0, 254).astype(np.uint8)
+    cap = (N + 7) // 8 * 8 + 3
+    i32, i16 = torch.int32, torch.int16
+    sym_t, bits_t = torch.from_numpy(sym).to(dev), torch.from_numpy(bits).to(dev)
+    states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+    words = torch.zeros(n_streams * cap, dtype=i16, device=dev)
+    word_off = torch.arange(n_streams, dtype=torch.int64, device=dev) * cap
+    status = torch.zeros(1, dtype=i32, device=dev)
+    print(f"  {n_streams} units, {tables} tables", flush=True)
+    if tables > 1:
+        freq = O.build_freq_sparse(O.histogram_bucketed(sym, spp, n_streams, bits, n_tables=tables))
+        enc = O.rans_encode_bucketed(sym, freq, spp, n_streams, bits, word_cap_per_unit=cap)
+        freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+        plc.plc_rans_encode_bucketed(sym_t, n_streams, N, 0, spp, n_streams, bits_t, tables, freq_t, states, words,
+                                     word_off, cap, n_words, status)
+    else:
+        freq, _ = O.build_freq(O.histogram(sym))
+        enc = O.rans_encode(sym, freq, word_cap_per_unit=cap)
+        freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+        plc.plc_rans_encode(sym_t, n_streams, N, 0, freq_t, states, words, word_off, cap, n_words, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+    w = u16(words).reshape(n_streams, cap)
+    for unit in range(n_streams):
+        nw = int(enc["n_words"][unit])
+        assert np.array_equal(w[unit, :nw], enc["words"][unit * cap:unit * cap + nw])
+        assert not w[unit, nw:].any()
+
+
 def test_more_whole_stream_units_than_the_chain_kernels_take(oracle, dev):
     """Whole-stream units beyond the bound of the three-wavefront encoder and the chain decoder
     (plc_rans_encode / plc_rans_decode then run the many-unit kernels with one wavefront per workgroup):
