@@ -81,22 +81,23 @@ __global__ __launch_bounds__(kBlock) void histogram_kernel(const uint8_t *__rest
 // tables are 64 KB, so a workgroup has eight wavefronts to share them, two workgroups to a compute unit.  The same
 // sizes: 71-72 us, against 105-226 us with one copy a wavefront; counting a thread's zeros in a register besides,
 // as that needed, costs more than the atomics it saves (82-86 us).
-constexpr int kBucketCopies = 16;
-constexpr int kBucketThreads = 512;
-
-__global__ __launch_bounds__(kBucketThreads) void histogram_bucketed_kernel(
+// Clearing and adding up the copies is a fixed cost of a segment -- for sixteen copies of four tables 40 LDS
+// instructions a thread, where 4096 symbols are 16 for half the threads -- so short streams get fewer copies
+// (bucket_copies below).
+template <int COPIES, int THREADS>
+__global__ __launch_bounds__(THREADS) void histogram_bucketed_kernel(
     const uint8_t *__restrict__ symbols, int64_t syms_per_stream, uint32_t segs_per_stream, uint32_t syms_per_pos,
     uint32_t streams_per_session, const uint8_t *__restrict__ bits, int n_tables, uint32_t *__restrict__ counts,
     uint32_t *status) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[PLC_MAX_BITS * 256 * kBucketCopies];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[PLC_MAX_BITS * 256 * COPIES];
   const uint32_t stream = blockIdx.x / segs_per_stream;
   const uint32_t seg = blockIdx.x - stream * segs_per_stream;
-  for (int i = threadIdx.x; i < n_tables * 256 * kBucketCopies / 4; i += kBucketThreads)
+  for (int i = threadIdx.x; i < n_tables * 256 * COPIES / 4; i += THREADS)
     reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  uint32_t *mine = hist + (threadIdx.x & (kBucketCopies - 1));
+  uint32_t *mine = hist + (threadIdx.x & (COPIES - 1));
 
-  constexpr int64_t kStep = kBucketThreads * 16;
+  constexpr int64_t kStep = THREADS * 16;
   const int64_t seg_begin = (int64_t)seg * kBucketSegment;
   const int64_t seg_end = seg_begin + kBucketSegment < syms_per_stream ? seg_begin + kBucketSegment : syms_per_stream;
   const uint8_t *base = symbols + (int64_t)stream * syms_per_stream;
@@ -119,17 +120,17 @@ __global__ __launch_bounds__(kBucketThreads) void histogram_bucketed_kernel(
       raise(status, PLC_ERR_INVALID);
       b = 1;
     }
-    uint32_t *h = mine + (b - 1) * 256 * kBucketCopies;
+    uint32_t *h = mine + (b - 1) * 256 * COPIES;
     const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) atomicAdd(&h[((wds[j] >> (8 * q)) & 255u) * kBucketCopies], 1u);
+      for (int q = 0; q < 4; ++q) atomicAdd(&h[((wds[j] >> (8 * q)) & 255u) * COPIES], 1u);
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < n_tables * 256; i += kBucketThreads) {
-    const uint32_t c = sum_copies<kBucketCopies>(hist + i * kBucketCopies, threadIdx.x);
+  for (int i = threadIdx.x; i < n_tables * 256; i += THREADS) {
+    const uint32_t c = sum_copies<COPIES>(hist + i * COPIES, threadIdx.x);
     if (c) atomicAdd(&counts[(int64_t)stream * n_tables * 256 + i], c);
   }
 }
@@ -281,6 +282,15 @@ extern "C" int plc_build_freq(const uint32_t *counts, int64_t n_streams, uint16_
   return launch_status();
 }
 
+// Copies of each table in histogram_bucketed_kernel.  Lanes of one copy meet where symbols crowd, which costs by the
+// symbol; clearing and summing cost by the copy and table.  5120 streams, four tables, 4 / 8 / 16 copies, residuals
+// 0.6 and 30 steps wide: 4096 symbols 27 and 22 / 30 and 29 / 40 and 41 us, 8192: 38 and 26 / 37 and 32 / 44 and 44,
+// 16,384: 58 and 34 / 49 and 40 / 53 and 51, 32,768: 100 and 49 / 73 and 55 / 66 and 65.  One table: 4096 symbols
+// 22 and 13 / 20 and 15 / 24 and 24 us, 16,384: 62 and 27 / 41 and 28 / 38 and 35.
+inline int bucket_copies(int64_t syms_per_stream, int n_tables) {
+  return syms_per_stream <= 2048 * n_tables ? 4 : syms_per_stream < 4096 * (n_tables + 2) ? 8 : 16;
+}
+
 extern "C" int plc_histogram_bucketed(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
                                       int32_t syms_per_pos, int32_t streams_per_session, const uint8_t *bits,
                                       int32_t n_tables, uint32_t *counts, uint32_t *status, void *stream) {
@@ -294,9 +304,13 @@ extern "C" int plc_histogram_bucketed(const uint8_t *symbols, int64_t n_streams,
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t n = n_streams * n_tables * 256;
   hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, counts, n);
-  hipLaunchKernelGGL(histogram_bucketed_kernel, dim3((unsigned)(n_streams * segs)), dim3(kBucketThreads), 0, st,
-                     symbols, syms_per_stream, (uint32_t)segs, (uint32_t)syms_per_pos, (uint32_t)streams_per_session,
-                     bits, n_tables, counts, status);
+  const int copies = bucket_copies(syms_per_stream, n_tables);
+  const auto kernel = copies == 4   ? histogram_bucketed_kernel<4, 256>
+                      : copies == 8 ? histogram_bucketed_kernel<8, 256>
+                                    : histogram_bucketed_kernel<16, 512>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(n_streams * segs)), dim3(copies == 16 ? 512 : 256), 0, st, symbols,
+                     syms_per_stream, (uint32_t)segs, (uint32_t)syms_per_pos, (uint32_t)streams_per_session, bits,
+                     n_tables, counts, status);
   return launch_status();
 }
 

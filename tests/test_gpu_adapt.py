@@ -278,3 +278,23 @@ def test_bucketed_histogram_at_the_edges_of_segments(oracle, dev, spp, positions
                                counts, status)
     assert int(status.item()) == 0
     assert np.array_equal(u32(counts), oracle.histogram_bucketed(sym, spp, 2, bits, n_tables=n_tables))
+
+
+@pytest.mark.parametrize("n_tables", [1, 2, 3, 4])
+@pytest.mark.parametrize("spread", [0.0, 40.0])
+def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
+    """Streams on both sides of the lengths from which a table gets eight copies and sixteen, and the shortest; all
+    symbols alike and symbols all over the range."""
+    from paper_2604_15356_amd import plc
+    spp = 32
+    for N in (32, 64, 2048 * n_tables, 2048 * n_tables + 32, 4096 * (n_tables + 2) - 32, 4096 * (n_tables + 2)):
+        rng = np.random.default_rng(N + n_tables)
+        sym = np.clip(np.rint(rng.normal(127, spread, size=(6, N))), 0, 255).astype(np.uint8)
+        bits = rng.integers(1, n_tables + 1, size=(3, N // spp)).astype(np.uint8)
+        counts = torch.full((6, n_tables, 256), 7, dtype=torch.int32, device=dev)
+        status = torch.zeros(1, dtype=torch.int32, device=dev)
+        print(f"N {N} tables {n_tables} spread {spread}", flush=True)
+        plc.plc_histogram_bucketed(torch.from_numpy(sym).to(dev), 6, N, spp, 2, torch.from_numpy(bits).to(dev),
+                                   n_tables, counts, status)
+        assert int(status.item()) == 0
+        assert np.array_equal(u32(counts), oracle.histogram_bucketed(sym, spp, 2, bits, n_tables=n_tables))
