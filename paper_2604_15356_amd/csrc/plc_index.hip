@@ -75,8 +75,11 @@ __device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint3
 // but what a step needs from its position -- the table made from that position's probabilities -- is not:
 // wavefronts 1-3 prepare the tables of the next six groups (192 positions, one per thread, in registers, with the
 // probabilities of the tile after already on their way) while wavefront 0 codes the current six from LDS; one
-// barrier per tile.  Bound by latency on both sides.  MAXK, 8 or 32, is the row length the registers are laid out
-// for: up to 8 candidates, the ordinary case, the search of the decoder runs in registers too.
+// barrier per tile.  Bound by latency on both sides.  MAXK, 8, 16 or 32, is the row length the registers are laid out
+// for, and what a position costs whatever its own length: up to 8 candidates, the ordinary case, the search of the
+// decoder runs in registers too; rows of 9 to 16 laid out for 32 took longer than the rows in LDS had with thousands
+// of sessions (4096 of 512 positions and 9 candidates: encode 65 us with rows in LDS, 78 in registers for 32, 44 in
+// registers for 16; one session of 4096: 131, 100, 53 us).
 // One session, encode / decode (before: rows in LDS, one load after the other, the decoder's results stored by
 // wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 34 / 51 us (43 / 91),
 // 32,768 of 4 196 / 328 us (246 / 635), 4096 of 20 83 / 93 us (93 / 206), 8192 of 32 235 / 244 us (661 / 655).
@@ -398,7 +401,7 @@ extern "C" int plc_index_encode(const float *probs, const int32_t *chosen, int32
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((word_cap > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const auto kernel = k <= 8 ? index_encode_kernel<8> : index_encode_kernel<kMaxK>;
+  const auto kernel = k <= 8 ? index_encode_kernel<8> : k <= 16 ? index_encode_kernel<16> : index_encode_kernel<kMaxK>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
                      k, states, words, word_off, word_cap, n_words, status);
   return launch_status();
@@ -410,7 +413,7 @@ extern "C" int plc_index_decode(const float *probs, const uint32_t *states, cons
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((words_len > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const auto kernel = k <= 8 ? index_decode_kernel<8> : index_decode_kernel<kMaxK>;
+  const auto kernel = k <= 8 ? index_decode_kernel<8> : k <= 16 ? index_decode_kernel<16> : index_decode_kernel<kMaxK>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, states, words,
                      words_len, word_off, n_words, n, k, chosen, status);
   return launch_status();
@@ -442,7 +445,7 @@ extern "C" int plc_surprisal_bits(const float *probs, const int32_t *chosen, int
     t.thr[m] = thr[m];
   }
   const int64_t rows = (int64_t)S * n;
-  const auto kernel = k <= 8 ? surprisal_bits_kernel<8> : surprisal_bits_kernel<kMaxK>;
+  const auto kernel = k <= 8 ? surprisal_bits_kernel<8> : k <= 16 ? surprisal_bits_kernel<16> : surprisal_bits_kernel<kMaxK>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), probs, chosen, rows, k, t, bmax, bits, status);
   return launch_status();

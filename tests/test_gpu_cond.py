@@ -184,7 +184,7 @@ def test_oracle_written_index_stream_decodes_on_the_gpu(oracle, dev):
 
 
 @pytest.mark.parametrize("k, n", [(1, 1), (1, 193), (2, 31), (7, 191), (8, 192), (8, 385), (9, 33), (15, 193), (16, 200),
-                                  (31, 70), (32, 193)])
+                                  (17, 193), (31, 70), (32, 193)])
 def test_index_coder_at_the_edges_of_rows_and_tiles(oracle, dev, k, n):
     """Row lengths around the register form's limit of 8, tiles of 192 positions begun, full and passed, rows whose
     symbols get no frequency of their own (zeros, tiny values) and rows that sum to more than one."""
@@ -219,6 +219,46 @@ def test_index_coder_at_the_edges_of_rows_and_tiles(oracle, dev, k, n):
     bits = z(S * n, torch.uint8)
     plc.plc_surprisal_bits(dp, dc, S, n, k, thr, bits, status)
     assert int(status.item()) == 0 and np.array_equal(u8(bits).ravel(), O.surprisal_bits(probs, ch, thr).ravel())
+
+
+@pytest.mark.parametrize("k", [8, 16, 32])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_index_streams_around_the_words_that_are_staged(oracle, dev, k, beyond):
+    """The decoder reads index streams of up to 8192 words from LDS and longer ones from memory: lengths just below
+    and just above, of rows that are nearly uniform, beside a session of few words."""
+    O = oracle
+    from paper_2604_15356_amd import plc
+
+    def draw(n):
+        rng = np.random.default_rng(k)
+        probs = rng.uniform(0.8, 1.2, size=(2, n, k)).astype(np.float32)
+        probs /= probs.sum(-1, keepdims=True) * np.float32((k + 1) / k)     # a miss as likely as a candidate
+        ch = rng.integers(-1, k, size=(2, n)).astype(np.int32)
+        probs[0], ch[0] = np.float32(0.01), 0
+        probs[0, :, 0] = 0.6
+        return probs, ch, O.index_encode(probs, ch, word_cap=2 * n + 64)
+
+    n = 24000
+    per_word = n / int(draw(n)[2]["n_words"][1])
+    n = int((8192 + (24 if beyond else -24)) * per_word)
+    probs, ch, ref = draw(n)
+    words_coded = int(ref["n_words"][1])
+    print(f"k {k} n {n} words {words_coded}", flush=True)
+    assert 8192 < words_coded < 8320 if beyond else 8064 < words_coded <= 8192
+    cap = 2 * n + 64
+    dp, dc = torch.from_numpy(probs).to(dev), torch.from_numpy(ch).to(dev)
+    z = lambda count, dt: torch.zeros(count, dtype=dt, device=dev)
+    states, words, n_words, status = z(64, torch.int32), z(2 * cap, torch.int16), z(2, torch.int32), z(1, torch.int32)
+    off = torch.arange(2, dtype=torch.int64, device=dev) * cap
+    plc.plc_index_encode(dp, dc, 2, n, k, states, words, off, cap, n_words, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), ref["n_words"]) and np.array_equal(u32(states).ravel(), ref["states"].ravel())
+    for s in range(2):
+        nw, at = int(ref["n_words"][s]), int(ref["word_off"][s])
+        assert np.array_equal(u16(words)[s * cap:s * cap + nw], ref["words"][at:at + nw]), f"session {s}"
+    out = torch.full((2, n), -9, dtype=torch.int32, device=dev)
+    plc.plc_index_decode(dp, states, words, off, n_words, 2, n, k, out, status)
+    assert int(status.item()) == 0 and np.array_equal(out.cpu().numpy(), ch)
 
 
 def test_error_statuses_of_the_conditional_calls(oracle, dev):
