@@ -450,8 +450,8 @@ __global__ __launch_bounds__(kBlock) void scan_streams_kernel(const uint32_t *__
 // One wavefront walks the escapes of one tile, found in its symbols.  Gathering, it writes the actual values from
 // list position `at` on (for a tile whose staging row overflowed, or that has none); patching, it puts the list's
 // values from there on over the escaped components of the output.  What bounds it is latency: the symbols of the
-// lane's four chunks are asked for at once, and so is one value of each chunk at a time (a chunk seldom holds
-// two escapes); a chunk's place is worked out only where it has any.
+// lane's four chunks are asked for at once, and so are all values -- a chunk of the actual vectors as one 16-byte
+// piece, the list's one by one as far as the fullest chunk goes; a chunk's place is worked out only where it has any.
 template <bool PATCH>
 __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__restrict__ esc_vals, uint64_t esc_cap,
                                                 uint32_t stream, uint32_t tile, uint64_t at, int lane) {
@@ -467,7 +467,8 @@ __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__
   uint32_t bits[kRounds];  // which components of the chunk are escapes
   uint64_t pos[kRounds];   // their places in the list
   uint16_t *comp[kRounds];
-  bool any = false;
+  uint4 act[kRounds];      // gathering: the chunk's values
+  uint32_t most = 0;       // escapes of the lane's fullest chunk
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     // a byte is 0xff iff its low seven bits carry into bit 7 when 1 is added and bit 7 is set; bit 7 of byte e to bit e
@@ -475,47 +476,53 @@ __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__
     const uint32_t hy = ((sv[r].y & 0x7f7f7f7fu) + 0x01010101u) & sv[r].y & 0x80808080u;
     bits[r] = (((hx >> 7) * 0x00204081u) >> 21 & 0xfu) | ((((hy >> 7) * 0x00204081u) >> 21 & 0xfu) << 4);
     comp[r] = nullptr;
+    act[r] = make_uint4(0u, 0u, 0u, 0u);
     pos[r] = at;
     if (__ballot(bits[r] != 0u) == 0) continue;  // uniform
+    const uint32_t cnt = (uint32_t)__builtin_popcount(bits[r]);
     uint32_t total;
-    pos[r] = at + wave_escape_prefix((uint32_t)__builtin_popcount(bits[r]), &total);
+    pos[r] = at + wave_escape_prefix(cnt, &total);
     at += total;
     if (bits[r]) {
       const Coord q = locate_chunk(a, stream, tile, (uint32_t)(r * 64 + lane));
       if (PATCH) {
         comp[r] = (q.c ? a.out_v : a.out_k) + q.act;
       } else {
-        comp[r] = const_cast<uint16_t *>((q.c ? a.act_v : a.act_k) + q.act);
+        act[r] = *reinterpret_cast<const uint4 *>((q.c ? a.act_v : a.act_k) + q.act);
       }
-      any = true;
+      most = cnt > most ? cnt : most;
     }
   }
-  while (any) {
-    uint16_t v[kRounds];
+  uint16_t v[kRounds][kChunk];  // patching: the chunks' values from the list
+  if (PATCH) {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      v[r] = 0;
-      if (!bits[r]) continue;
-      if (!PATCH) {
-        v[r] = comp[r][__builtin_ctz(bits[r])];
-      } else if (pos[r] < a.esc_len) {
-        v[r] = a.esc_in[pos[r]];
-      } else {  // the list is too short: this component stays as it is
-        raise(a.status, PLC_ERR_CORRUPT);
+    for (int j = 0; j < kChunk; ++j) {
+      if (__ballot(most > (uint32_t)j) == 0) break;  // uniform
+#pragma unroll
+      for (int r = 0; r < kRounds; ++r) {
+        if (j >= __builtin_popcount(bits[r])) continue;
+        if (pos[r] + j < a.esc_len) {
+          v[r][j] = a.esc_in[pos[r] + j];
+        } else {  // the list is too short: this component stays as it is
+          raise(a.status, PLC_ERR_CORRUPT);
+        }
       }
     }
-    any = false;
+  }
+#pragma unroll
+  for (int j = 0; j < kChunk; ++j) {
+    if (__ballot(most > (uint32_t)j) == 0) break;  // uniform
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
       if (!bits[r]) continue;
-      if (PATCH) {
-        if (pos[r] < a.esc_len) comp[r][__builtin_ctz(bits[r])] = v[r];
-      } else {
-        if (pos[r] < esc_cap) esc_vals[pos[r]] = v[r];
-      }
-      ++pos[r];
+      const uint32_t e = (uint32_t)__builtin_ctz(bits[r]);
       bits[r] &= bits[r] - 1u;
-      any = any || bits[r] != 0u;
+      if (PATCH) {
+        if (pos[r] + j < a.esc_len) comp[r][e] = v[r][j];
+      } else if (pos[r] + j < esc_cap) {
+        const uint64_t four = e < 4 ? (uint64_t)act[r].y << 32 | act[r].x : (uint64_t)act[r].w << 32 | act[r].z;
+        esc_vals[pos[r] + j] = (uint16_t)(four >> (16 * (e & 3)));
+      }
     }
   }
 }

@@ -53,3 +53,10 @@ def near_tie_report(sym_gpu, sym_f64, u_f64, tau):
     one_step = (np.abs(a - b) == 1) | ((a == 255) & (b >= 253)) | ((b == 255) & (a >= 253)) \
         | ((a == 255) & (b <= 1)) | ((b == 255) & (a <= 1))
     return n_diff, int(((frac < tau) & one_step).sum())
+
+
+def escape_lists(symbols, act_k, act_v):
+    """The escape lists that symbols [streams, n * 2 * d] of act [S, L, H, n, d] ask for, one behind the other: the
+    actual values (as 16-bit words) wherever a symbol is 255, in the symbols' order."""
+    both = torch.stack([act_k, act_v], dim=4).contiguous().view(torch.int16)   # [S, L, H, n, 2, d]
+    return u16(both.reshape(symbols.shape)[symbols == 255])

@@ -16,7 +16,7 @@ import torch
 
 from oracle import plc_oracle_linear as OL
 from paper_2604_15356_amd.workloads import make_linear_workload
-from tests.gpu_util import u8, u16, u32, u64
+from tests.gpu_util import escape_lists, u8, u16, u32, u64
 
 pytestmark = pytest.mark.gpu
 
@@ -156,3 +156,43 @@ def test_expected_embedding_large_tiles(dev, V):
         + (V + 2) * 2.0 ** -24 * (np.abs(P.numpy().astype(np.float64)) @ np.abs(E.numpy().astype(np.float64)).T)
     assert (np.abs(got.astype(np.float64) - want64) <= tol).all()
     assert (got.view(np.uint16) != want64.astype(np.float16).view(np.uint16)).mean() < 0.02
+
+
+@pytest.mark.parametrize("sigma", [0.9, 1.4, 4.0, 1000.0])
+def test_escapes_of_finished_symbols(dev, sigma):
+    """Escapes gathered from and patched into what the contraction wrote, from a few per hundred chunks to every
+    component: the list, the output, and both where the list is too short."""
+    from paper_2604_15356_amd import plc
+    w = make_linear_workload("tiny", device=dev, overrides=dict(L=2, H=1, d=64, n=128, m=128, V=96, sigma=sigma, seed=62))
+    codec = _codec(w, dev)
+    codec.encode_linear(w.probs_full, w.embed_t, w.A, w.bias_k, w.bias_v, w.act_k, w.act_v)
+    codec.check_status("encode_linear")
+    ref = escape_lists(codec.symbols, w.act_k, w.act_v)
+    assert ref.size > 64 and int(codec.esc_cnt.sum()) == ref.size
+    assert np.array_equal(u16(codec.esc_vals)[:ref.size], ref)
+    out_k, out_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
+    codec.decode_linear(w.probs_full, w.embed_t, w.A, w.bias_k, w.bias_v, out_k, out_v)
+    codec.check_status("decode_linear")
+    assert np.array_equal(escape_lists(codec.symbols, out_k, out_v), ref)
+    full_k, full_v, full = out_k.clone(), out_v.clone(), codec.esc_vals
+    escaped = (codec.symbols == 255).reshape(*w.act_k.shape[:4], 2, -1)
+    for cap in (1, 17, ref.size // 2, ref.size - 1):
+        print(f"  sigma {sigma}: {cap} of {ref.size} escapes", flush=True)
+        guarded = torch.full((ref.size + 40,), 0x5a5a, dtype=torch.int16, device=dev)
+        codec.esc_vals = guarded[3:3 + cap]
+        plc.plc_predict_residual_linear(codec.dims, codec.ebar, w.A, w.bias_k, w.bias_v, w.act_k, w.act_v, codec.symbols,
+                                        codec.esc_vals, codec.esc_cnt, codec.esc_off, codec.ws, codec.status)
+        assert int(codec.status.item()) == plc.PLC_ERR_CAPACITY
+        expect = np.full(ref.size + 40, 0x5a5a, dtype=np.uint16)
+        expect[3:3 + cap] = ref[:cap]
+        assert np.array_equal(u16(guarded), expect)
+        codec.status.zero_()
+        codec.decode_linear(w.probs_full, w.embed_t, w.A, w.bias_k, w.bias_v, out_k, out_v)
+        assert int(codec.status.item()) == plc.PLC_ERR_CORRUPT
+        codec.status.zero_()
+        # what the list holds is in place, and what is no escape is as it was
+        assert np.array_equal(escape_lists(codec.symbols, out_k, out_v)[:cap], ref[:cap])
+        for i, (out, whole) in enumerate(((out_k, full_k), (out_v, full_v))):
+            keep = ~escaped[..., i, :]
+            assert torch.equal(out[keep].view(torch.int16), whole[keep].view(torch.int16))
+    codec.esc_vals = full

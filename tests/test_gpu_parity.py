@@ -12,7 +12,7 @@ import pytest
 import torch
 
 from paper_2604_15356_amd.workloads import make_workload, random_bytes
-from tests.gpu_util import (codec_for, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64)
+from tests.gpu_util import (codec_for, escape_lists, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64)
 
 pytestmark = pytest.mark.gpu
 
@@ -480,6 +480,34 @@ def test_encoder_writes_word_lists_at_odd_addresses(oracle, dev, chunk):
         o = 1 + 3 + unit * cap
         expect[o:o + nw] = enc["words"][unit * cap:unit * cap + nw]
     assert np.array_equal(got, expect)
+
+
+@pytest.mark.parametrize("sigma", [0.9, 1.4, 4.0, 1000.0])
+@pytest.mark.parametrize("layout", ["lhnkd", "lnkhd"])
+def test_escape_lists_whole_and_cut_short(dev, sigma, layout):
+    """Tiles whose escapes fit their staging rows (the smallest sigma), that overflow them now and then, and of which
+    most or all components are escapes; lists that have room, and lists that end in the middle, of which the first
+    part is there and nothing behind it is touched."""
+    from paper_2604_15356_amd import plc
+    w = make_workload("tiny", device=dev, layout=layout, overrides=dict(L=1, H=3, n=75, k=5, d=40, sigma=sigma, seed=61))
+    codec = codec_for(w, esc_frac=1.0)
+    codec.predict_residual(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
+    codec.check_status()
+    ref = escape_lists(codec.symbols, w.act_k, w.act_v)
+    assert ref.size > 64 and int(codec.esc_cnt.sum()) == ref.size
+    assert np.array_equal(u16(codec.esc_vals)[:ref.size], ref)
+    for cap in (1, 17, ref.size // 2, ref.size - 1):
+        print(f"  sigma {sigma}: {cap} of {ref.size} escapes", flush=True)
+        guarded = torch.full((ref.size + 40,), 0x5a5a, dtype=torch.int16, device=dev)
+        codec.esc_vals = guarded[3:3 + cap]
+        codec.predict_residual(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
+        with pytest.raises(plc.PlcError) as e:
+            codec.check_status()
+        assert e.value.code == plc.PLC_ERR_CAPACITY
+        expect = np.full(ref.size + 40, 0x5a5a, dtype=np.uint16)
+        expect[3:3 + cap] = ref[:cap]
+        assert np.array_equal(u16(guarded), expect)
+        codec.status.zero_()
 
 
 def test_data_dependent_errors_are_reported_not_fatal(oracle, dev):
