@@ -467,7 +467,6 @@ __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__
   uint32_t bits[kRounds];  // which components of the chunk are escapes
   uint64_t pos[kRounds];   // their places in the list
   uint16_t *comp[kRounds];
-  uint4 act[kRounds];      // gathering: the chunk's values
   uint32_t most = 0;       // escapes of the lane's fullest chunk
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
@@ -476,7 +475,6 @@ __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__
     const uint32_t hy = ((sv[r].y & 0x7f7f7f7fu) + 0x01010101u) & sv[r].y & 0x80808080u;
     bits[r] = (((hx >> 7) * 0x00204081u) >> 21 & 0xfu) | ((((hy >> 7) * 0x00204081u) >> 21 & 0xfu) << 4);
     comp[r] = nullptr;
-    act[r] = make_uint4(0u, 0u, 0u, 0u);
     pos[r] = at;
     if (__ballot(bits[r] != 0u) == 0) continue;  // uniform
     const uint32_t cnt = (uint32_t)__builtin_popcount(bits[r]);
@@ -488,13 +486,19 @@ __device__ __forceinline__ void escapes_of_tile(const CodecArgs &a, uint16_t *__
       if (PATCH) {
         comp[r] = (q.c ? a.out_v : a.out_k) + q.act;
       } else {
-        act[r] = *reinterpret_cast<const uint4 *>((q.c ? a.act_v : a.act_k) + q.act);
+        comp[r] = const_cast<uint16_t *>((q.c ? a.act_v : a.act_k) + q.act);
       }
       most = cnt > most ? cnt : most;
     }
   }
-  uint16_t v[kRounds][kChunk];  // patching: the chunks' values from the list
-  if (PATCH) {
+  uint4 act[kRounds];           // gathering: the chunks' values
+  uint16_t v[kRounds][kChunk];  // patching: the same from the list
+  if (!PATCH) {
+    // (here and not above: between the rounds the symbols that are still to come would be waited for behind them)
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+      if (bits[r]) act[r] = *reinterpret_cast<const uint4 *>(comp[r]);
+  } else {
 #pragma unroll
     for (int j = 0; j < kChunk; ++j) {
       if (__ballot(most > (uint32_t)j) == 0) break;  // uniform
