@@ -1865,7 +1865,7 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
 // taken off behind the read.
 // The ring holds RB blocks of 512 words.  Four let the helper leave its newest block on its way for a batch
 // (below); three are what the decoder strictly needs -- the block of the pointer, the one below it, and the
-// one being staged for the batch after -- and bring the workgroup's LDS from 56.6 to 52.5 KB, so that a
+// one being staged for the batch after -- and bring the workgroup's LDS from 57.6 to 53.5 KB, so that a
 // compute unit holds three workgroups instead of two where the registers allow it (k <= 6).  That is the
 // variant for thousands of streams, where units in flight count for more than the helper's wait: 9.1 -> 7.9 ms
 // on 5120 streams with k = 4.  (With k = 8 and 16,384 streams the kernel is bound by HBM at 5.4 TB/s whatever
@@ -1929,6 +1929,9 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][2 * kBatchSyms];  // second half: lanes 32..63
   __shared__ uint32_t cum_of[256], most[256];  // per symbol: first slot; floor((2^16 - 1) / f) | remainder << 16
   __shared__ int32_t ptr_pub[2];  // the word pointer after batch b, in slot b mod 2
+  static_assert(workgroups_per_cu(sizeof(tab) + sizeof(sym_stage) + sizeof(cum_of) + sizeof(most) + sizeof(ptr_pub)) >=
+                    (RB == 3 ? 3 : 2),
+                "what the ring of three blocks is for, and the other holds");
   constexpr int kThreads = RK ? 192 : 128;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

@@ -372,7 +372,7 @@ def test_few_unit_encoders_side_by_side_on_a_compute_unit(oracle, dev, n_streams
 
 
 def test_more_whole_stream_units_than_the_chain_kernels_take(oracle, dev):
-    """Whole-stream units beyond the bound of the three-wavefront encoder and the chain decoder
+    """Whole-stream units beyond the bound of the few-unit encoder and the chain decoder
     (plc_rans_encode / plc_rans_decode then run the many-unit kernels with one wavefront per workgroup):
     ragged streams, bit-exact both ways against the oracle, one damaged unit reported."""
     from paper_2604_15356_amd import plc
@@ -510,6 +510,48 @@ def test_escape_lists_whole_and_cut_short(dev, sigma, layout):
         codec.status.zero_()
 
 
+@pytest.mark.parametrize("tables", [1, 4])
+@pytest.mark.parametrize("n_streams", [3, 1100])
+def test_word_lists_that_are_too_short(oracle, dev, n_streams, tables):
+    """Whole streams (few, and more than the few-unit encoder takes) with room for fewer words than they have, around
+    multiples of 8 in the first pair of batches, in the middle and at the last word, at odd addresses: the first
+    words are in place, what lies between the lists is not touched, and the shortage is reported."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    spp, N = 32, 32 * 16 * (11 if n_streams == 3 else 3) + 96
+    rng = np.random.default_rng(tables)
+    bits = rng.integers(1, tables + 1, size=(1, N // spp)).astype(np.uint8)
+    sym = np.clip(np.rint(rng.standard_normal((n_streams, N)) * 40.0 + 127), 0, 254).astype(np.uint8)
+    i32, i16 = torch.int32, torch.int16
+    sym_t, bits_t = torch.from_numpy(sym).to(dev), torch.from_numpy(bits).to(dev)
+    if tables > 1:
+        freq = O.build_freq_sparse(O.histogram_bucketed(sym, spp, n_streams, bits, n_tables=tables))
+        enc = O.rans_encode_bucketed(sym, freq, spp, n_streams, bits, word_cap_per_unit=N)
+    else:
+        freq, _ = O.build_freq(O.histogram(sym))
+        enc = O.rans_encode(sym, freq, word_cap_per_unit=N)
+    freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+    least = int(enc["n_words"].min())
+    for cap in (0, 1, 7, 8, 9, 500, 512, least // 2 // 8 * 8, least // 2 // 8 * 8 + 5, least - 1):
+        pitch, lead, guard = cap + 13, 5, 0x5a5a
+        words = torch.full((lead + n_streams * pitch,), guard, dtype=i16, device=dev)
+        off = lead + torch.arange(n_streams, dtype=torch.int64, device=dev) * pitch
+        states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+        status = torch.zeros(1, dtype=i32, device=dev)
+        print(f"  {n_streams} streams of {N}, {tables} tables, room for {cap} words", flush=True)
+        if tables > 1:
+            plc.plc_rans_encode_bucketed(sym_t, n_streams, N, 0, spp, n_streams, bits_t, tables, freq_t, states, words,
+                                         off, cap, n_words, status)
+        else:
+            plc.plc_rans_encode(sym_t, n_streams, N, 0, freq_t, states, words, off, cap, n_words, status)
+        assert int(status.item()) == plc.PLC_ERR_CAPACITY
+        assert np.array_equal(u32(n_words), enc["n_words"])
+        expect = np.full(lead + n_streams * pitch, guard, dtype=np.uint16)
+        lists = expect[lead:].reshape(n_streams, pitch)
+        lists[:, :cap] = enc["words"].reshape(n_streams, N)[:, :cap]
+        assert np.array_equal(u16(words), expect)
+
+
 def test_data_dependent_errors_are_reported_not_fatal(oracle, dev):
     from paper_2604_15356_amd import plc
     O = oracle
@@ -522,16 +564,14 @@ def test_data_dependent_errors_are_reported_not_fatal(oracle, dev):
     with pytest.raises(plc.PlcError) as e:
         codec.check_status()
     assert e.value.code == plc.PLC_ERR_INVALID
-    # escape list too small -> CAPACITY, nothing written past the end
+    # escape list too small -> CAPACITY
     codec = codec_for(w, esc_frac=0.0)          # 64 entries
-    guard = codec.esc_vals.clone()
-    coded = codec.encode(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
-    n_esc = int(coded.esc_cnt.sum())
-    if n_esc > codec.esc_vals.numel():
-        with pytest.raises(plc.PlcError) as e:
-            codec.check_status()
-        assert e.value.code == plc.PLC_ERR_CAPACITY
-    del guard
+    act_k = w.act_k.clone()
+    act_k.view(-1)[:200] = 1000.0
+    codec.encode(w.cand_k, w.cand_v, w.probs, act_k, w.act_v)
+    with pytest.raises(plc.PlcError) as e:
+        codec.check_status()
+    assert e.value.code == plc.PLC_ERR_CAPACITY
     # word list too small -> CAPACITY
     codec = codec_for(w, word_frac=0.25)
     codec.encode(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
