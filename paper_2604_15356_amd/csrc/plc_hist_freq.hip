@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void build_freq_kernel(const uint32_t *__re
     return;
   }
   // f[s] = floor(C[s] * 4096 / T) - floor(C[s-1] * 4096 / T).  The quotient, at most 4096, from the reciprocal in
-  // fp64 (C * 4096 < 2^44 is exact there), off by one at most and put right by its remainder.
+  // fp64 (counts of 32 bits: C * 4096 <= 2^52 is exact there), off by one at most and put right by its remainder.
   const double inv = 1.0 / (double)T;
   auto scaled = [&](uint64_t c) {
     const int64_t n = (int64_t)(c * PLC_RANS_SCALE);
@@ -283,12 +283,13 @@ extern "C" int plc_build_freq(const uint32_t *counts, int64_t n_streams, uint16_
 }
 
 // Copies of each table in histogram_bucketed_kernel.  Lanes of one copy meet where symbols crowd, which costs by the
-// symbol; clearing and summing cost by the copy and table.  5120 streams, four tables, 4 / 8 / 16 copies, residuals
-// 0.6 and 30 steps wide: 4096 symbols 27 and 22 / 30 and 29 / 40 and 41 us, 8192: 38 and 26 / 37 and 32 / 44 and 44,
-// 16,384: 58 and 34 / 49 and 40 / 53 and 51, 32,768: 100 and 49 / 73 and 55 / 66 and 65.  One table: 4096 symbols
-// 22 and 13 / 20 and 15 / 24 and 24 us, 16,384: 62 and 27 / 41 and 28 / 38 and 35.
+// symbol; clearing and summing cost by the copy and table.  5120 streams, four tables, 4 / 8 / 16 copies, all symbols
+// alike, residuals 0.6 and 30 steps wide: 4096 symbols 30, 27 and 22 / 31, 30 and 29 / 40 us, 8192: 42, 38 and 26 / 40,
+// 37 and 32 / 45, 16,384: 67, 58 and 34 / 52, 49 and 40 / 53, 53 and 51, 24,576: 92, 80 and 41 / 67, 61 and 48 / 61,
+// 60 and 58.  The lines lie where symbols that are all alike take no longer with fewer copies.  One table: 4096
+// symbols 26, 22 and 13 / 21, 20 and 15 / 24 us, 16,384: 77, 62 and 27 / 44, 41 and 28 / 38, 38 and 35.
 inline int bucket_copies(int64_t syms_per_stream, int n_tables) {
-  return syms_per_stream <= 2048 * n_tables ? 4 : syms_per_stream < 4096 * (n_tables + 2) ? 8 : 16;
+  return syms_per_stream <= 1024 * (n_tables + 1) ? 4 : syms_per_stream <= 4096 * n_tables ? 8 : 16;
 }
 
 extern "C" int plc_histogram_bucketed(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,

@@ -287,7 +287,7 @@ def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
     symbols alike and symbols all over the range."""
     from paper_2604_15356_amd import plc
     spp = 32
-    for N in (32, 64, 2048 * n_tables, 2048 * n_tables + 32, 4096 * (n_tables + 2) - 32, 4096 * (n_tables + 2)):
+    for N in (32, 64, 1024 * (n_tables + 1), 1024 * (n_tables + 1) + 32, 4096 * n_tables, 4096 * n_tables + 32):
         rng = np.random.default_rng(N + n_tables)
         sym = np.clip(np.rint(rng.normal(127, spread, size=(6, N))), 0, 255).astype(np.uint8)
         bits = rng.integers(1, n_tables + 1, size=(3, N // spp)).astype(np.uint8)
