@@ -371,6 +371,57 @@ def test_few_unit_encoders_side_by_side_on_a_compute_unit(oracle, dev, n_streams
         assert not w[unit, nw:].any()
 
 
+@pytest.mark.parametrize("tables", [1, 4])
+def test_few_unit_encoders_with_extreme_frequencies(oracle, dev, tables):
+    """Tables of one symbol (f = 4096), of f = 4095 and 1, of two halves (2048 each) and of 256 symbols, each by itself
+    and as the tables of one stream's bit depths; a symbol without a frequency is reported in either form."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    spp, N, n_streams = 32, 32 * 16 * 40 + 64, 4
+    rng = np.random.default_rng(9)
+    kinds = [np.full(N, 127), np.where(np.arange(N) == 7, 3, 255), rng.integers(0, 2, N) * 200,
+             np.clip(np.rint(rng.standard_normal(N) * 60 + 127), 0, 255)]
+    sym = np.stack(kinds).astype(np.uint8)
+    bits = np.ones((1, N // spp), np.uint8)
+    if tables > 1:  # every stream goes through the four kinds, another one first
+        bits = (1 + np.arange(N // spp) % 4)[None].astype(np.uint8)
+        depth = np.repeat(bits[0], spp) - 1
+        sym = np.stack([np.choose((depth + s) % 4, kinds) for s in range(4)]).astype(np.uint8)
+    i32, i16 = torch.int32, torch.int16
+    sym_t, bits_t = torch.from_numpy(sym).to(dev), torch.from_numpy(bits).to(dev)
+    states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+    words = torch.zeros(n_streams * N, dtype=i16, device=dev)
+    off = torch.arange(n_streams, dtype=torch.int64, device=dev) * N
+    status = torch.zeros(1, dtype=i32, device=dev)
+    if tables > 1:
+        freq = O.build_freq_sparse(O.histogram_bucketed(sym, spp, n_streams, bits, n_tables=tables))
+        enc = O.rans_encode_bucketed(sym, freq, spp, n_streams, bits, word_cap_per_unit=N)
+    else:
+        freq, _ = O.build_freq(O.histogram(sym))
+        enc = O.rans_encode(sym, freq, word_cap_per_unit=N)
+    assert {1, 4095, 4096} <= set(freq.ravel().tolist())
+    freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+
+    def encode(symbols):
+        if tables > 1:
+            plc.plc_rans_encode_bucketed(symbols, n_streams, N, 0, spp, n_streams, bits_t, tables, freq_t, states, words,
+                                         off, N, n_words, status)
+        else:
+            plc.plc_rans_encode(symbols, n_streams, N, 0, freq_t, states, words, off, N, n_words, status)
+
+    encode(sym_t)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+    w = u16(words).reshape(n_streams, N)
+    for unit in range(n_streams):
+        nw = int(enc["n_words"][unit])
+        assert np.array_equal(w[unit, :nw], enc["words"].reshape(n_streams, N)[unit, :nw])
+    bad = sym_t.clone()
+    bad[0, 5 * spp * tables] = 9            # stream 0, depth 1 (or its only table): 127 is the only symbol
+    encode(bad)
+    assert int(status.item()) == plc.PLC_ERR_INVALID
+
+
 def test_more_whole_stream_units_than_the_chain_kernels_take(oracle, dev):
     """Whole-stream units beyond the bound of the few-unit encoder and the chain decoder
     (plc_rans_encode / plc_rans_decode then run the many-unit kernels with one wavefront per workgroup):
@@ -850,4 +901,23 @@ def test_frequency_tables_of_skewed_counts(oracle, dev, occur, skew):
     status = torch.zeros(1, dtype=torch.int32, device=dev)
     plc.plc_build_freq(torch.from_numpy(counts.view(np.int32)).to(dev), len(rows), freq, cum, status)
     assert int(status.item()) == 0
+    assert np.array_equal(u16(freq), ref_freq) and np.array_equal(u16(cum), ref_cum)
+
+
+def test_frequency_tables_of_the_largest_counts(oracle, dev):
+    """Counts up to 2^32 - 1 and rows that sum to as much as 2^40: the scaled sums need 52 bits."""
+    from paper_2604_15356_amd import plc
+    rng = np.random.default_rng(40)
+    top = 2 ** 32 - 1
+    rows = [np.full(256, top), np.where(np.arange(256) % 2, top, 1), np.where(np.arange(256) == 9, top, 0),
+            np.where(np.arange(256) < 3, top, 1), rng.integers(0, top, 256, endpoint=True),
+            rng.integers(0, top, 256, endpoint=True) >> rng.integers(0, 32, 256), np.arange(256) * (top // 255)]
+    counts = np.stack(rows).astype(np.uint64).astype(np.uint32)
+    assert counts.astype(np.uint64).sum(1).max() > 2 ** 39
+    freq = torch.empty((len(rows), 256), dtype=torch.int16, device=dev)
+    cum = torch.empty((len(rows), 257), dtype=torch.int16, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    plc.plc_build_freq(torch.from_numpy(counts.view(np.int32)).to(dev), len(rows), freq, cum, status)
+    assert int(status.item()) == 0
+    ref_freq, ref_cum = oracle.build_freq(counts)
     assert np.array_equal(u16(freq), ref_freq) and np.array_equal(u16(cum), ref_cum)
