@@ -186,11 +186,10 @@ __device__ __forceinline__ void enc_step(uint32_t &x, const uint4 e, uint16_t *&
   }
 }
 
-// The same step for the unrolled batches, with its instruction order pinned.  A wavefront issues in
-// order and a dependent VALU result takes about two issue slots to arrive (measured on gfx950: 8.5
-// cycles dependent, 4.3 independent).  The step has two dependent chains that both start at the
-// compare -- the state update and the address of the word to store -- so they are interleaved one for
-// one; left to itself the compiler emits them one after the other and the wavefront idles.
+// The same step for the unrolled batches, with its instruction order pinned.  A wavefront issues in order, an
+// instruction every 4.6 cycles whether or not it needs the result before it, but reading the lane mask of a compare
+// costs two wait states (8.6 cycles) unless other instructions stand there.  The step has two chains that both start
+// at the compare -- the state update and the address of the word to store -- so they are interleaved one for one.
 #define PLC_PIN() __builtin_amdgcn_sched_barrier(0)
 
 template <bool LONG>
@@ -2167,9 +2166,9 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
 //                 symbols through a 4 KB table per depth, while the next batch is decoded, and moves them out
 //   step          multiply | add (each takes its half of the entry), compare, rank, select, shift | read:
 //                 six dependent instructions and one round trip
-// What a step costs is its dependent chain -- the round trip and six vector instructions at about eight cycles
-// each, three more than the kernel above, whose entry needs no taking apart: 134 against 104 cycles a step with
-// the barrier's share -- so the decoder's uniform operands are formed once per batch, and whatever else can
+// A step takes 62 to 69 ns (150-165 cycles, the barrier's share in it) against 42 in the kernel above, 256 units of
+// 1,048,576 symbols: three more instructions, which explain 14 cycles of the difference; what the rest is has not
+// been taken apart.  The decoder's uniform operands are formed once per batch, and whatever else can
 // be is left to the helper (handing on the slot itself, read by the decoder from the raw ring behind its
 // entry, was tried: 2.4 against 2.1 ms on the Llama shape).  The helper stages the
 // words, tells the decoder each batch's tables (16 tables in a word, two batches before they are needed; the
