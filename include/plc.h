@@ -224,6 +224,50 @@ int plc_rans_decode(const uint16_t *freq, const uint32_t *states, const uint16_t
                     uint8_t *symbols, uint32_t *status, void *stream);
 
 /*
+ * Restart points: an aid to the decoder of streams that are one unit each (chunk_syms = 0).  Such a
+ * unit is one chain of syms_per_stream / 32 dependent steps, and with few streams the chain is the
+ * time.  The encoder passes on its way, last symbol first, through every state the decoder will hold,
+ * and the *_restart form of its calls writes some of them down; the *_restart form of a decoding call
+ * then decodes the pieces between them side by side.
+ *   points      u32 [n_streams, per_stream, PLC_RESTART_WORDS], written by the encoding call, read by
+ *               the decoding one.  Record r of a stream stands at a group of 32 symbols (the groups
+ *               counted from the stream's end, in steps of equal length): the 32 lane states, the words
+ *               emitted and the escape symbols passed so far; record 0 the same at the stream's start.
+ *               Records that the stream is too short for are left unwritten.
+ *   per_stream  plc_restart_points() of the shape, or another number of at least 2, the same in both calls.
+ *   scratch     u32 [n_streams, per_stream, 2], decoding calls only: overwritten.
+ * The bitstream is the same with and without, and so is what a decoding call returns: the records are
+ * hints.  Every piece is checked against the record behind it, and a stream whose pieces do not fit
+ * together (records of other words, damaged words) is decoded again from its start as if there were
+ * no records; status then tells what it would have told.  They need not be stored with the words
+ * (136 bytes each): a cache decoded without them takes the time of one chain.
+ * A null `restart` makes a call the one of the same name without the suffix.  With restart points
+ * n_streams is at most 1024 and chunk_syms 0, else PLC_ERR_INVALID.
+ */
+#define PLC_RESTART_WORDS 34
+typedef struct plc_restart {
+  uint32_t *points;
+  uint32_t *scratch;
+  int32_t per_stream;
+} plc_restart;
+
+/* Records per stream that pay for this shape; 0 where they do not (many streams, short ones, units shorter
+ * than a stream).  Host call. */
+int32_t plc_restart_points(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms);
+
+int plc_rans_encode_restart(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
+                            int32_t chunk_syms, const uint16_t *freq, uint32_t *states,
+                            uint16_t *words, const uint64_t *word_off, uint64_t word_cap_per_unit,
+                            uint32_t *n_words, const plc_restart *restart, uint32_t *status,
+                            void *stream);
+
+int plc_rans_decode_restart(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
+                            uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words,
+                            int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
+                            const plc_restart *restart, uint8_t *symbols, uint32_t *status,
+                            void *stream);
+
+/*
  * Decode side, floating-point part (Sec. 7.2, point 2: the stored residual is
  * dequantised and added to a prediction that the reader forms exactly as the
  * writer did; Prop. "Three-layer composition", correctness: the error of the
@@ -262,6 +306,13 @@ int plc_rans_decode_reconstruct(const plc_dims *dims, const uint16_t *freq, cons
                                 uint64_t esc_len, const uint64_t *esc_off, uint8_t *symbols,
                                 void *out_k, void *out_v, void *ws, size_t ws_bytes,
                                 uint32_t *status, void *stream);
+
+int plc_rans_decode_reconstruct_restart(const plc_dims *dims, const uint16_t *freq, const uint32_t
+    *states, const uint16_t *words, uint64_t words_len, const uint64_t *word_off, const uint32_t
+    *n_words, int32_t chunk_syms, const void *cand_k, const void *cand_v, const float *probs, const
+    uint16_t *esc_vals, uint64_t esc_len, const uint64_t *esc_off, uint8_t *symbols, void *out_k,
+    void *out_v, void *ws, size_t ws_bytes, const plc_restart *restart, uint32_t *status, void
+    *stream);
 
 /*
  * ---- Token-conditional coding -------------------------------------------------
@@ -313,6 +364,13 @@ int plc_rans_decode_reconstruct_cond(const plc_dims *dims, const uint16_t *freq,
                                      uint64_t esc_len, const uint64_t *esc_off, uint8_t *symbols,
                                      void *out_k, void *out_v, void *ws, size_t ws_bytes,
                                      uint32_t *status, void *stream);
+
+int plc_rans_decode_reconstruct_cond_restart(const plc_dims *dims, const uint16_t *freq, const
+    uint32_t *states, const uint16_t *words, uint64_t words_len, const uint64_t *word_off, const
+    uint32_t *n_words, int32_t chunk_syms, const void *cand_k, const void *cand_v, const float
+    *probs, const int32_t *chosen, const uint16_t *esc_vals, uint64_t esc_len, const uint64_t
+    *esc_off, uint8_t *symbols, void *out_k, void *out_v, void *ws, size_t ws_bytes, const
+    plc_restart *restart, uint32_t *status, void *stream);
 
 /*
  * `chosen` from the vectors alone, for an encoder that is not told the token:
@@ -432,11 +490,23 @@ int plc_rans_encode_bucketed(const uint8_t *symbols, int64_t n_streams, int64_t 
                              uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status,
                              void *stream);
 
+int plc_rans_encode_bucketed_restart(const uint8_t *symbols, int64_t n_streams, int64_t
+    syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos, int32_t streams_per_session, const
+    uint8_t *bits, int32_t n_tables, const uint16_t *freq, uint32_t *states, uint16_t *words, const
+    uint64_t *word_off, uint64_t word_cap_per_unit, uint32_t *n_words, const plc_restart *restart,
+    uint32_t *status, void *stream);
+
 int plc_rans_decode_bucketed(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
                              uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words,
                              int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
                              int32_t syms_per_pos, int32_t streams_per_session, const uint8_t *bits,
                              int32_t n_tables, uint8_t *symbols, uint32_t *status, void *stream);
+
+int plc_rans_decode_bucketed_restart(const uint16_t *freq, const uint32_t *states, const uint16_t
+    *words, uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words, int64_t
+    n_streams, int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos, int32_t
+    streams_per_session, const uint8_t *bits, int32_t n_tables, const plc_restart *restart, uint8_t
+    *symbols, uint32_t *status, void *stream);
 
 /* plc_rans_decode_bucketed (syms_per_pos = 2d, streams_per_session = L*H) followed by
  * plc_reconstruct_adapt as one call, the way plc_rans_decode_reconstruct stands for
@@ -453,6 +523,14 @@ int plc_rans_decode_reconstruct_adapt(const plc_dims *dims, const uint16_t *freq
                                       const uint64_t *esc_off, uint8_t *symbols, void *out_k,
                                       void *out_v, void *ws, size_t ws_bytes, uint32_t *status,
                                       void *stream);
+
+int plc_rans_decode_reconstruct_adapt_restart(const plc_dims *dims, const uint16_t *freq, const
+    uint32_t *states, const uint16_t *words, uint64_t words_len, const uint64_t *word_off, const
+    uint32_t *n_words, int32_t chunk_syms, int32_t n_tables, const void *cand_k, const void
+    *cand_v, const float *probs, const int32_t *chosen, const uint8_t *bits, float range, const
+    uint16_t *esc_vals, uint64_t esc_len, const uint64_t *esc_off, uint8_t *symbols, void *out_k,
+    void *out_v, void *ws, size_t ws_bytes, const plc_restart *restart, uint32_t *status, void
+    *stream);
 
 /*
  * ---- Linear-embedding predictor ------------------------------------------------

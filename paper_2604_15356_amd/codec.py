@@ -42,6 +42,8 @@ class Coded:
     bits: torch.Tensor = None           # u8 [S, n] bit depth per position
     counts_d: torch.Tensor = None       # i32 [streams, MAX_BITS, 256]
     freq_d: torch.Tensor = None         # i16 [streams, MAX_BITS, 256]
+    # where the decoder may begin inside a stream (None: nowhere): hints, see plc_restart in include/plc.h
+    restart: torch.Tensor = None        # i32 [streams, points, RESTART_WORDS]
 
 
 class KVDeltaCodec:
@@ -78,6 +80,12 @@ class KVDeltaCodec:
         self.words = torch.empty(self.n_units * self.word_cap, dtype=torch.int16, device=dev)
         self.word_off = torch.arange(self.n_units, dtype=torch.int64, device=dev) * self.word_cap
         self.n_words = torch.empty(self.n_units, dtype=torch.int32, device=dev)
+        # restart points, where streams are so few that the decoder gains from them
+        points = plc.plc_restart_points(self.n_streams, self.N, self.chunk_syms)
+        self.restart = (torch.zeros((self.n_streams, points, plc.RESTART_WORDS), dtype=torch.int32, device=dev)
+                        if points else None)
+        self._restart_scratch = (torch.empty((self.n_streams, points, 2), dtype=torch.int32, device=dev)
+                                 if points else None)
         self.pred = (torch.empty((self.n_streams, self.N), dtype=torch.float32, device=dev)
                      if want_pred else None)
         self.dec_symbols = torch.empty_like(self.symbols)
@@ -89,6 +97,9 @@ class KVDeltaCodec:
         self.idx_words = torch.empty(S * self.idx_word_cap, dtype=torch.int16, device=dev)
         self.idx_word_off = torch.arange(S, dtype=torch.int64, device=dev) * self.idx_word_cap
         self.idx_n_words = torch.empty(S, dtype=torch.int32, device=dev)
+
+    def _points(self):
+        return None if self.restart is None else (self.restart, self._restart_scratch)
 
     # -- single steps -------------------------------------------------------------------
     def predict_residual(self, cand_k, cand_v, probs, act_k, act_v, with_counts=False):
@@ -111,12 +122,12 @@ class KVDeltaCodec:
     def rans_encode(self, symbols=None):
         plc.plc_rans_encode(self.symbols if symbols is None else symbols, self.n_streams, self.N,
                             self.chunk_syms, self.freq, self.states, self.words, self.word_off,
-                            self.word_cap, self.n_words, self.status)
+                            self.word_cap, self.n_words, self.status, restart=self._points())
 
     def rans_decode(self, out=None):
         out = self.dec_symbols if out is None else out
         plc.plc_rans_decode(self.freq, self.states, self.words, self.word_off, self.n_words,
-                            self.n_streams, self.N, self.chunk_syms, out, self.status)
+                            self.n_streams, self.N, self.chunk_syms, out, self.status, restart=self._points())
         return out
 
     def reconstruct(self, cand_k, cand_v, probs, out_k, out_v, symbols=None):
@@ -141,7 +152,8 @@ class KVDeltaCodec:
         if fused:
             plc.plc_rans_decode_reconstruct(self.dims, self.freq, self.states, self.words, self.word_off,
                                             self.n_words, self.chunk_syms, cand_k, cand_v, probs, self.esc_vals,
-                                            self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status)
+                                            self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status,
+                                            restart=self._points())
         else:
             self.rans_decode()
             self.reconstruct(cand_k, cand_v, probs, out_k, out_v)
@@ -194,7 +206,7 @@ class KVDeltaCodec:
         plc.plc_build_freq_bucketed(self.counts_d, self.n_streams, B, self.freq_d, self.status)
         plc.plc_rans_encode_bucketed(self.symbols, self.n_streams, self.N, self.chunk_syms, spp, sps, self.bits, B,
                                      self.freq_d, self.states, self.words, self.word_off, self.word_cap,
-                                     self.n_words, self.status)
+                                     self.n_words, self.status, restart=self._points())
         plc.plc_index_encode(probs, self.chosen, self.S, self.n, self.k, self.idx_states, self.idx_words,
                              self.idx_word_off, self.idx_word_cap, self.idx_n_words, self.status)
         c = self.coded(cond=True)
@@ -211,11 +223,12 @@ class KVDeltaCodec:
             plc.plc_rans_decode_reconstruct_adapt(self.dims, self.freq_d, self.states, self.words, self.word_off,
                                                   self.n_words, self.chunk_syms, B, cand_k, cand_v, probs,
                                                   self.dec_chosen, self.dec_bits, step_range, self.esc_vals,
-                                                  self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status)
+                                                  self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status,
+                                                  restart=self._points())
             return
         plc.plc_rans_decode_bucketed(self.freq_d, self.states, self.words, self.word_off, self.n_words,
                                      self.n_streams, self.N, self.chunk_syms, spp, sps, self.dec_bits, B,
-                                     self.dec_symbols, self.status)
+                                     self.dec_symbols, self.status, restart=self._points())
         plc.plc_reconstruct_adapt(self.dims, cand_k, cand_v, probs, self.dec_chosen, self.dec_bits, step_range,
                                   self.dec_symbols, self.esc_vals, self.esc_off, out_k, out_v, self.ws, self.status)
 
@@ -250,7 +263,7 @@ class KVDeltaCodec:
             plc.plc_rans_decode_reconstruct_cond(self.dims, self.freq, self.states, self.words, self.word_off,
                                                  self.n_words, self.chunk_syms, cand_k, cand_v, probs,
                                                  self.dec_chosen, self.esc_vals, self.esc_off, self.dec_symbols,
-                                                 out_k, out_v, self.ws, self.status)
+                                                 out_k, out_v, self.ws, self.status, restart=self._points())
         else:
             self.rans_decode()
             plc.plc_reconstruct_cond(self.dims, cand_k, cand_v, probs, self.dec_chosen, self.dec_symbols,
@@ -260,9 +273,9 @@ class KVDeltaCodec:
         if cond:
             return Coded(self.symbols, self.esc_vals, self.esc_cnt, self.esc_off, self.counts, self.freq,
                          self.cum, self.states, self.words, self.word_off, self.n_words, self.chosen,
-                         self.idx_states, self.idx_words, self.idx_word_off, self.idx_n_words)
+                         self.idx_states, self.idx_words, self.idx_word_off, self.idx_n_words, restart=self.restart)
         return Coded(self.symbols, self.esc_vals, self.esc_cnt, self.esc_off, self.counts, self.freq,
-                     self.cum, self.states, self.words, self.word_off, self.n_words)
+                     self.cum, self.states, self.words, self.word_off, self.n_words, restart=self.restart)
 
     def check_status(self, where="plc"):
         """Synchronises and raises if a kernel reported a data-dependent error."""

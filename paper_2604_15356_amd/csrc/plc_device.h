@@ -114,8 +114,9 @@ struct ReconView {
   const uint64_t *esc_off;
 };
 // Whether plc_rans.hip has a decoder that reconstructs as it goes for this many streams and candidates
-// (cond: token-conditional prediction; per_depth: with one table per bit depth besides).
-bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth);
+// (cond: token-conditional prediction; per_depth: with one table per bit depth besides; restart: in pieces between
+// restart points).
+bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart);
 // That decoder: plc_rans_decode with one unit per stream, plus out = prediction + symbol * delta for every
 // component, escapes from their lists.  With recon.bits: plc_rans_decode_bucketed with n_tables tables per
 // stream instead.  The weights must be in place on `st`.  With launch = false the arguments are checked and
@@ -123,7 +124,7 @@ bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, b
 int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                       const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
-                      uint32_t *status, hipStream_t st, bool launch);
+                      const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch);
 
 // Escape bookkeeping for callers that produce or consume symbols outside the tile-structured kernels
 // (plc_predict.hip): collect the escaped components' raw fp16 values of `act` into the per-stream lists /

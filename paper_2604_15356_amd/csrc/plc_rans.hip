@@ -59,7 +59,70 @@ struct RansArgs {
   int32_t syms_per_pos, streams_per_session, n_tables;
   // reconstruction inside the decoder (rans_decode_chain_kernel with candidates)
   ReconView recon;
+  // restart points of streams coded as one unit (plc_restart; see "Pieces" below)
+  uint32_t *points_out;        // encode
+  const uint32_t *points_in;   // decode
+  uint32_t *piece_state;       // decode, scratch: two words per piece
+  int32_t point_stride;        // records per stream in points_*
+  int32_t pieces;              // decode: pieces per stream a workgroup's unit is one of (0: units as coded)
+  int32_t piece_batches;       // batches per piece
+  int32_t verified_pieces;     // decode: a stream all of whose so many pieces were verified is left alone
 };
+
+// Pieces.  The decoder of a stream that is one unit can begin in the middle of it if it knows what the sequential
+// decoder would hold there: the 32 states, how many words are left and how many escapes lie ahead.  The encoder,
+// which passes the same point on its way from the stream's end, leaves that in a record, and the decoder gives
+// the pieces between records to workgroups of their own.  A record is a hint and nothing more: the workgroup that
+// decodes up to it compares what it has arrived at with what the record says, and where all of a stream's pieces
+// agree, each began exactly where the one before it ended, so that together they are the sequential decode.  A
+// stream with a piece that does not (a record that belongs to other words, damage to the words) is decoded again
+// from its start by a second launch, which otherwise returns at once; it alone reports errors.
+//
+// Piece i counts from the end of the stream, as the encoder goes: its groups of 32 symbols are
+// [piece_top(i + 1), piece_top(i)).  Pieces end where one of the encoder's batches begins, so all but piece 0 are
+// whole batches.  Record i stands at piece_top(i), i >= 1; record 0 holds the stream's totals.
+__host__ __device__ __forceinline__ int32_t piece_top(int32_t G, int32_t pieces, int32_t piece_batches, int32_t i) {
+  if (i == 0) return G;
+  if (i >= pieces) return 0;
+  const int32_t head = G % kBatch ? G % kBatch : kBatch;
+  return G - head - (i * piece_batches - 1) * kBatch;
+}
+// A piece as its workgroup decodes it.
+struct Piece {
+  uint32_t begin, len;         // symbols, from the stream's start
+  uint32_t words, words_left;  // words of the list that are left at its start and at its end
+  uint32_t esc, esc_end;       // escapes of the stream in front of its start and in front of its end
+  const uint32_t *states;      // at its start
+  const uint32_t *end_states;  // at its end; null: the end of the stream
+};
+// Piece i (0 is the last) of a stream whose list has n_words words; false where the records cannot be true.
+__device__ __forceinline__ bool load_piece(const RansArgs &a, int64_t stream, int32_t i, uint32_t n_words, Piece *p) {
+  const int32_t G = (int32_t)((a.syms_per_stream + kLanes - 1) / kLanes);
+  const uint32_t *rec = a.points_in + stream * a.point_stride * PLC_RESTART_WORDS;
+  const uint32_t *end = rec + (int64_t)i * PLC_RESTART_WORDS, *at = end + PLC_RESTART_WORDS;
+  const bool first = i + 1 == a.pieces;
+  p->begin = (uint32_t)piece_top(G, a.pieces, a.piece_batches, i + 1) * kLanes;
+  p->len = (i == 0 ? (uint32_t)a.syms_per_stream : (uint32_t)piece_top(G, a.pieces, a.piece_batches, i) * kLanes) - p->begin;
+  p->words = first ? n_words : at[kLanes];
+  p->words_left = i == 0 ? 0u : end[kLanes];
+  p->esc = first ? 0u : rec[kLanes + 1] - at[kLanes + 1];
+  p->esc_end = i == 0 ? rec[kLanes + 1] : rec[kLanes + 1] - end[kLanes + 1];
+  p->states = first ? a.states_in + stream * kLanes : at;
+  p->end_states = i == 0 ? nullptr : end;
+  return p->words <= n_words && p->words_left <= p->words;
+}
+// What a piece's workgroup found: the decoding wavefront's word and the reconstructing one's (two alike where none is).
+constexpr uint32_t kPieceGood = 0x600du;
+__device__ __forceinline__ void report_piece(const RansArgs &a, int64_t stream, int32_t i, int which, bool good) {
+  a.piece_state[(stream * a.pieces + i) * 2 + which] = good ? kPieceGood : 0u;
+}
+// For the launch behind the pieces': whether this stream needs no second decode (uniform).
+__device__ __forceinline__ bool stream_verified(const RansArgs &a, int64_t stream) {
+  const uint32_t *w = a.piece_state + stream * a.verified_pieces * 2;
+  bool good = true;
+  for (int32_t i = (int32_t)(threadIdx.x & 63); i < 2 * a.verified_pieces; i += 64) good = good && w[i] == kPieceGood;
+  return __ballot(!good) == 0;
+}
 
 // Offset (in table entries of `stride` each) of the table that the 32 symbols from unit-relative group g on use.
 __device__ __forceinline__ uint32_t group_table(const RansArgs &a, int64_t stream, int64_t begin, int32_t g,
@@ -828,6 +891,15 @@ constexpr int64_t kChainMaxUnits = 1024;  // the same bound for the decoder of w
 // The decoder with one table per depth holds one unit per compute unit (its tables take 128 KB of LDS): two
 // rounds of 256 are what it may take before the many-unit decoder is as fast.
 constexpr int64_t kDepthsMaxUnits = 512;
+// Restart points: so many pieces altogether -- 16 per compute unit, four wavefronts per SIMD of the many-unit decoder
+// (256 streams of 1,048,576 symbols in 4, 8, 16, 32 pieces each, decode and reconstruction given the tokens:
+// 1.51, 0.93, 0.68, 0.66 ms; in one piece 1.50) -- and none shorter than two of the encoder's rounds (4096 symbols:
+// 8 streams of 65,536 symbols in 4, 8, 16, 32 pieces 53, 45, 38, 32 us, in one 120, where a record's 136 bytes come
+// to 4 % of the words of the shortest).
+constexpr int64_t kPiecesWanted = 4096;
+constexpr int32_t kPieceMinRounds = 2;
+// Up to here a piece gets a workgroup of the decoder with the shortest step: two to a compute unit, one round.
+constexpr int64_t kChainMaxPieces = 512;
 // From this many streams on (more than two workgroups per compute unit) the decoder that reconstructs takes
 // its three-block ring where k <= 4 lets three workgroups share a compute unit.
 constexpr int64_t kComputeUnits = 256;  // MI355X
@@ -979,6 +1051,8 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
   const int32_t n_iters = n_batches + 4;
   uint16_t *wp = a.words_out + a.word_off[unit];
   const uint32_t pad = __builtin_amdgcn_readfirstlane((uint32_t)((reinterpret_cast<uintptr_t>(wp) >> 1) & 7u));
+  // Restart points: the packer has a record's states and words at hand, the mover its escapes.
+  uint32_t *const points = a.points_out ? a.points_out + unit * a.point_stride * PLC_RESTART_WORDS : nullptr;
 
   if (wave == 0) {
     // ---- coder: batch it - 2
@@ -1016,7 +1090,10 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     }
     *held = before;  // the last four states, in place before the barrier behind them
     for (int32_t it = n_batches + 2; it < n_iters; ++it) lds_barrier();
-    if (lane < kLanes) a.states_out[unit * kLanes + lane] = x;
+    if (lane < kLanes) {
+      a.states_out[unit * kLanes + lane] = x;
+      if (points) points[lane] = x;
+    }
   } else if (wave == 1) {
     // ---- feeder: entries of batch it
     __syncthreads();  // tables
@@ -1091,6 +1168,9 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     __syncthreads();  // first symbols
     uint32_t fill = pad;  // uniform: positions of the region in use, the first of them not this pair's words
     int region = 0;
+    uint32_t gone = 0u - pad;  // words of the regions before (the padding in front of the first taken off)
+    int32_t point_at = points ? a.piece_batches : INT32_MAX;  // the batch that the next record stands in front of
+    uint32_t *record = points;
     // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
     // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
     const int half = lane >> 5, rl = 31 - (lane & 31);
@@ -1115,6 +1195,12 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
         uint32_t xps[kBatch / 2], at[kBatch / 2];
 #pragma unroll
         for (int p = 0; p < kBatch / 2; ++p) xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
+        if (b == point_at) {  // uniform; the states in front of the batch's first step
+          point_at += a.piece_batches;
+          record += PLC_RESTART_WORDS;
+          if (half == 0) record[rl] = xps[0];
+          if (lane == 0) record[kLanes] = gone + fill;
+        }
 #pragma unroll
         for (int p = 0; p < kBatch / 2; ++p) {
           const uint64_t mask = __ballot(xps[p] > thr[p]);
@@ -1126,6 +1212,7 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
         if ((b & 1) || b == n_batches - 1) {  // on to the next pair's region
           if (lane == 0) list_fill[region] = fill;
           region = region == kListRegions - 1 ? 0 : region + 1;
+          gone += fill & ~7u;
           fill &= 7u;
         }
       }
@@ -1213,8 +1300,37 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       wave_sync();  // the next pair's reads come behind the tail's way to its front, from other lanes (no barrier
                     // stands between them where pairs leave one behind the other at the unit's end)
     };
+    // Escapes, for the restart points: a round's symbols are counted in the stage in the last iteration before others
+    // take their place, in which the mover has nothing else to do.
+    uint32_t esc_mine = 0;  // this lane's, of the rounds so far
+    int32_t point_at = points ? a.piece_batches / 4 : INT32_MAX;  // the round that the next record stands in front of
+    uint32_t *record = points;
+    auto count_round = [&](int32_t r) {
+      if (r == point_at) {
+        point_at += a.piece_batches / 4;
+        record += PLC_RESTART_WORDS;
+        const uint32_t total = wave_sum(esc_mine);
+        if (lane == 0) record[kLanes + 1] = total;
+      }
+      const uint8_t *sb = sym_stage[r & 1];
+      const uint32_t lo = (uint32_t)round_bottom(r) * kLanes, top = (uint32_t)batch_top(4 * r) * kLanes;
+      const uint32_t n = (top < len ? top : len) - lo;
+      if (mis == 0 && n == (uint32_t)kSuperSyms) {  // uniform
+#pragma unroll
+        for (int h = 0; h < kSuperSyms / 1024; ++h) {
+          const uint4 v = *reinterpret_cast<const uint4 *>(&sb[(lane + 64 * h) * 16]);
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)  // a byte is 0xff iff its low seven bits carry into bit 7 and bit 7 is set
+            esc_mine += (uint32_t)__builtin_popcount(((w[i] & 0x7f7f7f7fu) + 0x01010101u) & w[i] & 0x80808080u);
+        }
+      } else {
+        for (uint32_t t = lane; t < n; t += 64) esc_mine += sb[t + mis] == PLC_ESCAPE;
+      }
+    };
     for (int32_t it = 0; it < n_iters; ++it) {
       const int32_t phase = it & 3;
+      if (phase == 3 && points && (it >> 2) < n_rounds) count_round(it >> 2);
       if (phase == 0 && it < n_batches) {  // the feeder has begun a round: the next one's symbols land
         const int32_t r = it >> 2;
         round_store((r + 1) & 1);
@@ -1226,9 +1342,11 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     }
     while (out_pair < n_pairs) words_out();
     const uint32_t n_words = vbase + rest - pad;
+    const uint32_t esc_total = wave_sum(esc_mine);
     if (lane == 0) {
       a.n_words_out[unit] = n_words;
       if ((uint64_t)n_words > a.word_cap) raise(a.status, PLC_ERR_CAPACITY);
+      if (points) points[kLanes] = n_words, points[kLanes + 1] = esc_total;
     }
     if (bad_depth) raise(a.status, PLC_ERR_INVALID);
   }
@@ -1290,7 +1408,8 @@ __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const
   }
 }
 
-template <int W, bool ADAPT, bool COMPACT = false>
+// PIECES: a unit is a piece of a stream, and errors are left to the second launch.
+template <int W, bool ADAPT, bool COMPACT = false, bool PIECES = false>
 __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   __shared__ uint32_t lut_one[ADAPT ? 1 : (COMPACT ? kCompactTable : kScale)];
   extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
@@ -1302,7 +1421,8 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t stream = blockIdx.x / a.wgs_per_stream;
   const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
-  const bool live = chunk < a.units_per_stream;
+  if (!PIECES && a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
+  const bool live = chunk < (PIECES ? (int64_t)a.pieces : a.units_per_stream);
   bool bad = false;
 
   if (!ADAPT) {  // slot table, built by all wavefronts: symbol s is filled in by wavefront s mod W
@@ -1353,31 +1473,47 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   }
   __syncthreads();
   if (!table_ok) {  // not a table: nothing can be decoded
-    if (live && lane == 0) raise(a.status, PLC_ERR_CORRUPT);
+    if (live && lane == 0) {
+      if (PIECES) {
+        report_piece(a, stream, (int32_t)chunk, 0, false);
+      } else {
+        raise(a.status, PLC_ERR_CORRUPT);
+      }
+    }
     return;
   }
   if (!live) return;  // no workgroup barrier below
 
-  const int64_t unit = stream * a.units_per_stream + chunk;
-  const int64_t begin = chunk * a.unit_syms;
+  const int64_t unit = PIECES ? stream : stream * a.units_per_stream + chunk;
+  const uint64_t off = a.word_off[unit];
+  const uint32_t n = a.n_words_in[unit];
+  Piece piece;
+  const bool list_ok = !(off > a.words_len || (uint64_t)n > a.words_len - off) &&
+                       (!PIECES || load_piece(a, stream, (int32_t)chunk, n, &piece));
+  if (!list_ok) {
+    if (lane == 0) {
+      if (PIECES) {
+        report_piece(a, stream, (int32_t)chunk, 0, false);
+      } else {
+        raise(a.status, PLC_ERR_CORRUPT);
+      }
+    }
+    return;
+  }
+  const int64_t begin = PIECES ? (int64_t)piece.begin : chunk * a.unit_syms;
   const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  const uint32_t len = PIECES ? piece.len : (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
   uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
   const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 15u) == 0;
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;
 
   // ---- word list geometry, relative to a 1 KiB-aligned address at or below the unit's first word
-  const uint64_t off = a.word_off[unit];
-  const uint32_t n = a.n_words_in[unit];
-  if (off > a.words_len || (uint64_t)n > a.words_len - off) {
-    if (lane == 0) raise(a.status, PLC_ERR_CORRUPT);
-    return;
-  }
   const uint16_t *first_word = a.words_in + off;
   const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kBlockWords * 2 - 1)) >> 1);
   const uint16_t *aligned_base = first_word - lo;  // pointer arithmetic keeps the loads global, not flat
-  const int32_t hi = lo + (int32_t)n;
+  const int32_t hi = lo + (int32_t)(PIECES ? piece.words : n);
+  const int32_t stop = lo + (int32_t)(PIECES ? piece.words_left : 0u);  // where the pointer has to arrive
   uint16_t *myring = ring[wave];
 
   // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
@@ -1413,7 +1549,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   const int rl = lane & (kLanes - 1);
   const uint32_t below = (1u << rl) - 1u;
   const bool top_active = (uint32_t)rl < top_syms;
-  uint32_t x = a.states_in[unit * kLanes + rl];
+  uint32_t x = (PIECES ? piece.states : a.states_in + unit * kLanes)[rl];
 
   // Full batches of 16 groups are fully unrolled; the groups that do not fill a batch (and the last
   // group if it is ragged) form a tail that runs in a rolled loop.
@@ -1496,9 +1632,15 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
     }
     wave_sync();
   }
-  // integrity: every word consumed, every lane back at the initial state
-  if (ptr != lo || (coder && x != kLow)) bad = true;
-  if (bad) raise(a.status, PLC_ERR_CORRUPT);
+  // integrity: every word consumed, every lane back at the initial state (a piece: at what the record behind it says)
+  const uint32_t x_end = PIECES && piece.end_states ? piece.end_states[rl] : kLow;
+  if (ptr != stop || (coder && x != x_end)) bad = true;
+  if (PIECES) {
+    const bool good = __ballot(bad) == 0;
+    if (lane < 2) report_piece(a, stream, (int32_t)chunk, lane, good);
+  } else if (bad) {
+    raise(a.status, PLC_ERR_CORRUPT);
+  }
   if (bad_depth) raise(a.status, PLC_ERR_INVALID);
 }
 
@@ -1547,13 +1689,13 @@ __device__ __forceinline__ void for_each_slot(const uint32_t *cum_of, Put put) {
 // same on every path and the wait before a use leaves the later requests in flight (the few loads and
 // stores that escapes add are issued only where there are escapes and cost at most their own number in
 // that count).
-//   stream, len, G   the unit's stream, its symbols and groups of 32
+//   stream, piece, G the unit's stream, the part of it that the unit is (all of it, but for pieces), its groups of 32
 //   sym_stage        the two symbol stages: batch b is in stage b mod 2 from its barrier to the next (kLate = 1:
 //                    from the barrier after its own, where the symbols pass through another wavefront first)
 constexpr int kRecDepthBase = 3;  // batches a request runs ahead of its symbols
 
 template <int RK, bool COND, bool ADAPT, int kRecDepth, int kLate = 0, int kStageSyms = 2 * kBatchSyms>
-__device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t stream, uint32_t len, int32_t G,
+__device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t stream, const Piece &piece, int32_t G,
                                                     const uint8_t (&sym_stage)[2][kStageSyms], int lane) {
   static_assert(COND || !ADAPT, "the adaptive quantiser lives on the token-conditional path");
   const ReconView &r = a.recon;
@@ -1563,13 +1705,14 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
   const int64_t cand0 = s * r.cs[0] + l * r.cs[1] + h * r.cs[2];
   const int64_t out0 = s * r.as[0] + l * r.as[1] + h * r.as[2];
   const float *w0 = r.weights + (int64_t)s * r.n * r.k;
-  const uint32_t n_chunks = len / kChunk;
+  const bool pieces = a.pieces > 0;  // uniform
+  const uint32_t chunk0 = piece.begin / kChunk, n_chunks = piece.len / kChunk;
   const uint32_t d8 = (uint32_t)r.d8, adv_row = 64u / d8, adv_e8 = 64u - adv_row * d8;
   // The chunk this lane requests next: row = position * 2 + (0 = K, 1 = V), e8 = chunk inside the row,
   // and where its candidates, weights and output are.  From batch to batch a lane moves on by 64
   // chunks; where that is a whole, even number of rows (d = 8, 16, ... 256) it is the same position
   // step in the same half every time, and the three pointers advance by constants.
-  uint32_t at_chunk = (uint32_t)lane, row = (uint32_t)lane / d8, e8 = (uint32_t)lane - row * d8;
+  uint32_t at_chunk = (uint32_t)lane, row = (chunk0 + (uint32_t)lane) / d8, e8 = chunk0 + (uint32_t)lane - row * d8;
   const bool steady = adv_e8 == 0u && (adv_row & 1u) == 0u;
   const int64_t cand_step = (int64_t)(adv_row / 2u) * r.cs[3], out_step = (int64_t)(adv_row / 2u) * r.as[3];
   const uint32_t w_step = (adv_row / 2u) * (uint32_t)RK;
@@ -1585,14 +1728,15 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
   if (at_chunk < n_chunks) {
     point(row, e8);
   } else {
-    point(0u, 0u);
+    row = chunk0 / d8, e8 = chunk0 - row * d8;
+    point(row, e8);
   }
   // COND: the position names its true candidate (plc_reconstruct_cond), whose vector then is the
   // prediction; which candidate to request is itself a load, so it runs one round further ahead: a
   // second cursor walks the chunks 2 * kRecDepth batches in front and fetches their chosen index.
   // ADAPT: the position's bit depth, which sets its step, is fetched with the chosen index.
   uint32_t far_chunk = at_chunk, far_row = row, far_e8 = e8;
-  int64_t far_pos = (int64_t)s * r.n + (at_chunk < n_chunks ? row >> 1 : 0u);  // entry in chosen and bits
+  int64_t far_pos = (int64_t)s * r.n + (row >> 1);  // entry in chosen and bits
   int32_t pick_next[kRecDepth];  // chosen index of the chunk the stage requests next
   int32_t pick_used[kRecDepth];  // and of the chunk whose candidates it holds (-1: the weighted mean)
   bool mean_path[kRecDepth];     // uniform: some lane of the stage's request needed all candidates
@@ -1615,7 +1759,8 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
   u32x4 esc_held[kRecDepth];
   global_u32x4 esc_dst[kRecDepth];
   const uint64_t esc_base = r.esc_off[stream];
-  uint32_t esc_seen = 0;  // escapes of the stream so far
+  uint32_t esc_seen = piece.esc;  // escapes of the stream so far
+  bool esc_bad = false;           // an escape past the end of the lists
 #pragma unroll
   for (int j = 0; j < kRecDepth; ++j) esc_bits[j] = 0u, esc_dst[j] = nullptr, esc_held[j] = u32x4{0u, 0u, 0u, 0u};
   // Loads of the lane's next chunk (of its last one again once the stream is at its end, so that every
@@ -1793,7 +1938,7 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
             if (src + i < r.esc_len) {
               value = r.esc_in[src + i];
             } else {
-              raise(a.status, PLC_ERR_CORRUPT);
+              esc_bad = true;
             }
             put_raw(now, bits, value);
           }
@@ -1809,7 +1954,7 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
             if (src + i < r.esc_len) {
               raw[i] = r.esc_in[src + i];
             } else {
-              raise(a.status, PLC_ERR_CORRUPT);
+              esc_bad = true;
               raw[i] = 0u;
             }
           }
@@ -1835,6 +1980,12 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
            mean_path[j], depth_next[j], depth_used[j], b0 + j, false);
 #pragma unroll
   for (int j = 0; j < kRecDepth; ++j) patch(esc_dst[j], esc_bits[j], esc_raw[j], esc_held[j]);
+  if (pieces) {
+    const bool good = __ballot(esc_bad) == 0 && esc_seen == piece.esc_end;
+    if (lane == 0) report_piece(a, stream, (int32_t)(blockIdx.x - (uint32_t)stream * a.wgs_per_stream), 1, good);
+  } else if (esc_bad) {
+    raise(a.status, PLC_ERR_CORRUPT);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1937,13 +2088,24 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   const bool helper = wave == 1;
   const int64_t stream = blockIdx.x / a.wgs_per_stream;
   const int64_t chunk = blockIdx.x - stream * a.wgs_per_stream;
+  const bool pieces = a.pieces > 0;  // uniform: the unit is a piece of the stream
   bool bad = false;
+  if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
+  // (uniform: every wavefront leaves, before any barrier that another might wait at)
+  auto give_up = [&]() {
+    if (threadIdx.x != 0) return;
+    if (pieces) {
+      report_piece(a, stream, (int32_t)chunk, 0, false);
+    } else {
+      raise(a.status, PLC_ERR_CORRUPT);
+    }
+  };
 
   {  // slot table
     uint32_t f[4], cum;
     const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
-    if (total != kScale) {  // not a table: nothing can be decoded (both wavefronts leave, before any barrier)
-      if (threadIdx.x == 0) raise(a.status, PLC_ERR_CORRUPT);
+    if (total != kScale) {  // not a table: nothing can be decoded
+      give_up();
       return;
     }
     if (wave == 0) {
@@ -1964,26 +2126,26 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   }
   uint2 *ring = tab + kScale;
 
-  const int64_t unit = stream * a.units_per_stream + chunk;
-  const int64_t begin = chunk * a.unit_syms;
-  const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  // ---- the unit: the stream, or a piece of it
+  const uint64_t off = a.word_off[stream];
+  const uint32_t n = a.n_words_in[stream];
+  Piece piece = {0u, (uint32_t)a.syms_per_stream, n, 0u, 0u, 0u, a.states_in + stream * kLanes, nullptr};
+  if (off > a.words_len || (uint64_t)n > a.words_len - off ||
+      (pieces && !load_piece(a, stream, (int32_t)chunk, n, &piece))) {
+    give_up();
+    return;
+  }
+  const uint32_t begin = piece.begin, len = piece.len;
   uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
   const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 15u) == 0;
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;
 
   // ---- word list geometry, relative to a 1 KiB-aligned address at or below the unit's first word
-  const uint64_t off = a.word_off[unit];
-  const uint32_t n = a.n_words_in[unit];
-  if (off > a.words_len || (uint64_t)n > a.words_len - off) {  // uniform: both wavefronts leave
-    if (threadIdx.x == 0) raise(a.status, PLC_ERR_CORRUPT);
-    return;
-  }
   const uint16_t *first_word = a.words_in + off;
   const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kBlockWords * 2 - 1)) >> 1);
   const uint16_t *aligned_base = first_word - lo;  // pointer arithmetic keeps the loads global, not flat
-  const int32_t hi = lo + (int32_t)n;
+  const int32_t hi = lo + (int32_t)piece.words;
 
   int32_t tail_groups = G % kBatch;
   if (tail_groups == 0 && top_syms < kLanes) tail_groups = kBatch;
@@ -1991,7 +2153,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
 
   if constexpr (RK > 0) {
     if (wave == 2) {
-      reconstruct_batches<RK, COND, false, kRecDepthBase>(a, stream, len, G, sym_stage, lane);
+      reconstruct_batches<RK, COND, false, kRecDepthBase>(a, stream, piece, G, sym_stage, lane);
       return;
     }
   }
@@ -2098,7 +2260,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   const bool coder = lane < kLanes;
   const int rl = lane & (kLanes - 1);
   const bool top_active = (uint32_t)rl < top_syms;
-  const uint32_t x0 = a.states_in[unit * kLanes + rl];
+  const uint32_t x0 = piece.states[rl];
   uint32_t xc = x0 >> kScaleBits;
   uint2 e = tab[x0 & (kScale - 1)];
   int32_t ptr = hi;
@@ -2137,13 +2299,18 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
       dec_chain_step<true>(xc, e, tab, ring_at, sbb + kLanes * j, j != tail_groups - 1 || top_active);
     batch_done(parity);
   }
-  // integrity: every word consumed, every lane back at the initial state: x >> 12 as carried, and the entry
-  // in hand that of the initial state's slot with w4 = 0 (entries of different slots differ in .y, and
-  // f * w4 > 0 otherwise)
-  const uint2 e0 = tab[kLow & (kScale - 1)];
-  const bool home = xc == (kLow >> kScaleBits) && e.x == e0.x && e.y == e0.y;
-  if (ptr != lo || (coder && !home)) bad = true;
-  if (bad) raise(a.status, PLC_ERR_CORRUPT);
+  // integrity: every word consumed, every lane back at the initial state (a piece: at what the record behind it
+  // says).  The state from x >> 12 as carried and the entry in hand, whose .y has f * w4 + slot - cum in its lower half.
+  const uint32_t fs = e.x & 0xffffffu, y = e.y & 0xffffu, w4 = y / fs;
+  const uint32_t x_now = ((xc + w4) << kScaleBits) + cum_of[e.x >> 24] + (y - w4 * fs);
+  const uint32_t x_end = piece.end_states ? piece.end_states[rl] : kLow;
+  if (ptr != lo + (int32_t)piece.words_left || (coder && x_now != x_end)) bad = true;
+  if (pieces) {
+    const bool good = __ballot(bad) == 0;
+    if (lane < (RK ? 1 : 2)) report_piece(a, stream, (int32_t)chunk, lane, good);
+  } else if (bad) {
+    raise(a.status, PLC_ERR_CORRUPT);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2276,7 +2443,18 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   const uint32_t ring_off = (uint32_t)n_tables * kDepthTableBytes;
   const uint32_t raw_off = ring_off + (uint32_t)n_tables * kDepthRingBytes;
   const uint32_t symtab_off = raw_off + kDepthRawBytes;
+  const bool pieces = a.pieces > 0;  // uniform: the unit is a piece of the stream
   bool bad = false;
+  if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
+  // (uniform: every wavefront leaves, before any barrier that another might wait at)
+  auto give_up = [&]() {
+    if (threadIdx.x != 0) return;
+    if (pieces) {
+      report_piece(a, stream, (int32_t)chunk, 0, false);
+    } else {
+      raise(a.status, PLC_ERR_CORRUPT);
+    }
+  };
 
   // slot and symbol tables, one depth after the other; an all-zero table (a depth the stream does not use)
   // stays zero
@@ -2308,28 +2486,29 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
     }
     __syncthreads();
   }
-  if (!tables_ok) {  // not a table: nothing can be decoded (uniform: every wavefront leaves)
-    if (threadIdx.x == 0) raise(a.status, PLC_ERR_CORRUPT);
+  if (!tables_ok) {  // not a table: nothing can be decoded
+    give_up();
     return;
   }
 
-  const int64_t unit = stream * a.units_per_stream + chunk;
-  const int64_t begin = chunk * a.unit_syms;
-  const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  // the unit: the stream, or a piece of it
+  const uint64_t off = a.word_off[stream];
+  const uint32_t n = a.n_words_in[stream];
+  Piece piece = {0u, (uint32_t)a.syms_per_stream, n, 0u, 0u, 0u, a.states_in + stream * kLanes, nullptr};
+  if (off > a.words_len || (uint64_t)n > a.words_len - off ||
+      (pieces && !load_piece(a, stream, (int32_t)chunk, n, &piece))) {
+    give_up();
+    return;
+  }
+  const int64_t begin = piece.begin;
+  const uint32_t len = piece.len;
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;
 
-  const uint64_t off = a.word_off[unit];
-  const uint32_t n = a.n_words_in[unit];
-  if (off > a.words_len || (uint64_t)n > a.words_len - off) {  // uniform: every wavefront leaves
-    if (threadIdx.x == 0) raise(a.status, PLC_ERR_CORRUPT);
-    return;
-  }
   const uint16_t *first_word = a.words_in + off;
   const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kBlockWords * 2 - 1)) >> 1);
   const uint16_t *aligned_base = first_word - lo;
-  const int32_t hi = lo + (int32_t)n;
+  const int32_t hi = lo + (int32_t)piece.words;
 
   int32_t tail_groups = G % kBatch;
   if (tail_groups == 0 && top_syms < kLanes) tail_groups = kBatch;
@@ -2337,7 +2516,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
 
   if constexpr (RK > 0) {  // the wavefront that reconstructs, one barrier behind the decoder's batch
     if (wave == 2) {
-      reconstruct_batches<RK, MODE != 1, MODE == 0, kRecDepthBase, 1, kBatchSyms>(a, stream, len, G, sym_stage, lane);
+      reconstruct_batches<RK, MODE != 1, MODE == 0, kRecDepthBase, 1, kBatchSyms>(a, stream, piece, G, sym_stage, lane);
       return;
     }
   }
@@ -2515,7 +2694,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   const bool coder = lane < kLanes;
   const int rl = lane & (kLanes - 1);
   const bool top_active = (uint32_t)rl < top_syms;
-  const uint32_t x0 = a.states_in[unit * kLanes + rl];
+  const uint32_t x0 = piece.states[rl];
   int32_t ptr = hi;
   __syncthreads();  // barrier "start": the first words are staged, the first tables known
   const uint32_t *lds_words = reinterpret_cast<const uint32_t *>(depth_lds);
@@ -2569,18 +2748,25 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
     tables = MODE ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane(tables_coming);
   }
   if constexpr (RK > 0) __syncthreads();  // the helper's last batch of symbols, for the reconstruction
-  // integrity: every word consumed, every lane back at the initial state: x >> 12 as carried, and slot 0, which
-  // the place of the entry in hand tells (the helper stages nothing after the last batch's barrier)
-  uint32_t slot;
+  // integrity: every word consumed, every lane back at the initial state (a piece: at what the record behind it
+  // says): x >> 12 as carried, and what the place of the entry in hand tells (the helper stages nothing after the
+  // last batch's barrier), the word shifted in or the slot
+  uint32_t w;
   if (at >= ring0) {
     const uint32_t p = (at - ring0) % kDepthRingSlots;
-    slot = reinterpret_cast<const uint16_t *>(depth_lds + raw_off)[p] & (kScale - 1);
+    w = reinterpret_cast<const uint16_t *>(depth_lds + raw_off)[p];
   } else {
-    slot = at & (kScale - 1);
+    w = at & (kScale - 1);
   }
-  const bool home = xh == (kLow >> kScaleBits) && slot == 0u;
-  if (ptr != lo || (coder && !home)) bad = true;
-  if (bad) raise(a.status, PLC_ERR_CORRUPT);
+  const uint32_t x_now = (xh << kScaleBits) + w;
+  const uint32_t x_end = piece.end_states ? piece.end_states[rl] : kLow;
+  if (ptr != lo + (int32_t)piece.words_left || (coder && x_now != x_end)) bad = true;
+  if (pieces) {
+    const bool good = __ballot(bad) == 0;
+    if (lane < (RK ? 1 : 2)) report_piece(a, stream, (int32_t)chunk, lane, good);
+  } else if (bad) {
+    raise(a.status, PLC_ERR_CORRUPT);
+  }
 }
 
 int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, RansArgs *a, int *waves) {
@@ -2598,6 +2784,41 @@ int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
   if (wgs >= (1ll << 31) || n_streams * wgs >= (1ll << 31)) return PLC_ERR_INVALID;
   a->wgs_per_stream = (uint32_t)wgs;
   return PLC_OK;
+}
+
+// Rounds of the encoder's staging, four batches each, of a stream coded as one unit: pieces are whole rounds.
+int32_t restart_rounds(int64_t syms_per_stream) {
+  const int32_t G = (int32_t)((syms_per_stream + kLanes - 1) / kLanes);
+  const int32_t head = G % kBatch ? G % kBatch : kBatch;
+  return ((G - head) / kBatch + 1 + 3) / 4;
+}
+// Restart points, for a call with one unit per stream (check_common before).
+int check_restart(const plc_restart *r, bool decode, RansArgs *a) {
+  if (!r) return PLC_OK;
+  if (a->units_per_stream != 1 || a->unit_syms != a->syms_per_stream || a->n_units > kPipeMaxUnits) return PLC_ERR_INVALID;
+  if (r->per_stream < 2 || r->per_stream > (1 << 20) || !r->points || reinterpret_cast<uintptr_t>(r->points) % 4)
+    return PLC_ERR_INVALID;
+  if (decode && (!r->scratch || reinterpret_cast<uintptr_t>(r->scratch) % 4)) return PLC_ERR_INVALID;
+  const int32_t rounds = restart_rounds(a->syms_per_stream);
+  const int32_t per = (rounds + r->per_stream - 1) / r->per_stream;
+  a->point_stride = r->per_stream;
+  a->piece_batches = 4 * per;
+  if (decode) {
+    a->points_in = r->points;
+    a->piece_state = r->scratch;
+    a->pieces = (rounds + per - 1) / per;
+    if (a->pieces < 2) a->pieces = 0;
+  } else {
+    a->points_out = r->points;
+  }
+  return PLC_OK;
+}
+// The arguments of the launch behind the pieces', which decodes the streams whose pieces do not agree.
+RansArgs again_args(RansArgs a) {
+  a.verified_pieces = a.pieces;
+  a.pieces = 0;
+  a.wgs_per_stream = 1;
+  return a;
 }
 
 template <template <int> class Launcher>
@@ -2626,7 +2847,16 @@ struct LaunchDecode {
     // One unit per stream and few enough units (kChainMaxUnits): time is the length of one unit's chain,
     // so take the variant with the shortest step.  With more units its 60 KB of LDS per workgroup would
     // cost more in occupancy than the shorter step gains.
-    if (a.bits && W == 1 && a.n_units <= kDepthsMaxUnits) {
+    if (a.pieces) {  // (see decode_impl)
+      if (a.bits) {
+        const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, true, true>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL((rans_decode_kernel<W, true, true, true>), dim3(grid), dim3(W * 64), lds, st, a);
+      } else {
+        hipLaunchKernelGGL((rans_decode_kernel<W, false, true, true>), dim3(grid), dim3(W * 64), 0, st, a);
+      }
+    } else if (a.bits && W == 1 && a.n_units <= kDepthsMaxUnits) {
       const size_t lds = depths_lds_bytes(a.n_tables);
       (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<0>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2675,9 +2905,11 @@ int check_depths(int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_p
 
 int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
                 const uint16_t *freq, uint32_t *states, uint16_t *words, const uint64_t *word_off,
-                uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status, void *stream, RansArgs a) {
+                uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status, void *stream, RansArgs a,
+                const plc_restart *restart = nullptr) {
   int waves = 1;
   int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a, &waves);
+  if (!rc) rc = check_restart(restart, false, &a);
   if (rc) return rc;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (word_cap_per_unit > 0 && !words) return PLC_ERR_INVALID;
@@ -2731,9 +2963,11 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
 
 int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                 const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams, int64_t syms_per_stream,
-                int32_t chunk_syms, uint8_t *symbols, uint32_t *status, void *stream, RansArgs a) {
+                int32_t chunk_syms, uint8_t *symbols, uint32_t *status, void *stream, RansArgs a,
+                const plc_restart *restart = nullptr) {
   int waves = 1;
   int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a, &waves);
+  if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (words_len > 0 && !words) return PLC_ERR_INVALID;
@@ -2749,6 +2983,18 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
   hipStream_t st = static_cast<hipStream_t>(stream);
   {
     TraceScope trace(PLC_TRACE_RANS_DECODE, st);
+    if (a.pieces) {
+      if (!a.bits && n_streams * a.pieces <= kChainMaxPieces) {
+        a.wgs_per_stream = (uint32_t)a.pieces;
+        hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3((unsigned)(n_streams * a.pieces)), dim3(128), 0, st, a);
+      } else {
+        while (waves < kMaxWaves && 2 * waves <= a.pieces) waves *= 2;
+        a.wgs_per_stream = (uint32_t)((a.pieces + waves - 1) / waves);
+        dispatch_waves<LaunchDecode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+      }
+      a = again_args(a);
+      waves = 1;
+    }
     dispatch_waves<LaunchDecode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);
   }
   return launch_status();
@@ -2756,7 +3002,12 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
 
 }  // namespace
 
-bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth) {
+bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart) {
+  // In pieces the many-unit decoder fills the chip, and the one kernel pays only where the reconstruction keeps the
+  // memory busy for longer than it takes, or four workgroups share a compute unit (256 streams of 1,048,576 symbols, k =
+  // 8, 16 pieces: given the tokens the two calls take 0.68 ms, with a table per depth 0.75; the one kernel on whole
+  // streams 1.50 and 2.07).
+  if (restart && (per_depth || (cond && k > 4))) return false;
   // Candidates that fit the registers of one wavefront kRecDepth batches deep, and whole chunks.  As to
   // the number of streams: two or three workgroups per compute unit run at a time, and a round takes its
   // chain's time or the HBM time of its reconstruction, whichever is longer.  With the weighted mean the two
@@ -2775,12 +3026,14 @@ bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, b
 int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                       const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
-                      uint32_t *status, hipStream_t st, bool launch) {
+                      const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch) {
   RansArgs a = {};
   int waves = 1;
   int rc = check_common(n_streams, syms_per_stream, 0, &a, &waves);
+  if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
-  if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr))
+  if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr,
+                              restart != nullptr))
     return PLC_ERR_INVALID;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (words_len > 0 && !words) return PLC_ERR_INVALID;
@@ -2804,8 +3057,13 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
   a.recon = recon;
   {
     TraceScope trace(PLC_TRACE_RANS_DECODE, st);
-    const dim3 grid((unsigned)n_streams), block(192);
+    const dim3 block(192);
     const size_t lds = depths_lds_bytes(a.n_tables);
+    // With pieces: those, then a launch over the streams, in which one whose pieces agree is left alone.
+    for (int round = a.pieces ? 0 : 1; round < 2; ++round) {
+    const int64_t n_units = a.pieces ? n_streams * a.pieces : n_streams;
+    const dim3 grid((unsigned)n_units);
+    if (a.pieces) a.wgs_per_stream = (uint32_t)a.pieces;
     switch (recon.k) {
 #define PLC_CASE(K)                                                                              \
   case K:                                                                                        \
@@ -2813,7 +3071,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
       (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<K>),   \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);           \
       hipLaunchKernelGGL(rans_decode_depths_kernel<K>, grid, dim3(depths_threads(K)), lds, st, a); \
-    } else if (K <= kCompactMaxK && n_streams > kDenseStreams) {                                 \
+    } else if (K <= kCompactMaxK && n_units > kDenseStreams) {                                   \
       const size_t lds1 = depths_lds_bytes(1);                                                \
       if (recon.chosen) {                                                                        \
         hipLaunchKernelGGL((rans_decode_depths_kernel<(K <= kCompactMaxK ? K : 1), 2>), grid, block, lds1, st, a); \
@@ -2822,7 +3080,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
       }                                                                                          \
     } else if (recon.chosen) {                                                                   \
       hipLaunchKernelGGL((rans_decode_chain_kernel<K, true>), grid, block, 0, st, a);            \
-    } else if (K <= kDenseMaxK && n_streams > kDenseStreams) {                                   \
+    } else if (K <= kDenseMaxK && n_units > kDenseStreams) {                                     \
       hipLaunchKernelGGL((rans_decode_chain_kernel<(K <= kDenseMaxK ? K : 1), false, 3>), grid, block, 0, st, a); \
     } else {                                                                                     \
       hipLaunchKernelGGL((rans_decode_chain_kernel<K, false>), grid, block, 0, st, a);           \
@@ -2832,26 +3090,68 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
 #undef PLC_CASE
       default: return PLC_ERR_INVALID;
     }
+    if (a.pieces) a = again_args(a);
+    }
   }
   return launch_status();
 }
 
 }  // namespace plc
 
+extern "C" int32_t plc_restart_points(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms) {
+  if (n_streams < 1 || n_streams > kPipeMaxUnits || syms_per_stream < 1 || syms_per_stream >= (1ll << 31) - 1024 ||
+      chunk_syms != 0)
+    return 0;
+  const int32_t rounds = restart_rounds(syms_per_stream);
+  const int32_t most = rounds / kPieceMinRounds;
+  int32_t points = (int32_t)(kPiecesWanted / n_streams);
+  if (points > most) points = most;
+  return points < 2 ? 0 : points;
+}
+
+extern "C" int plc_rans_encode_restart(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
+                                       int32_t chunk_syms, const uint16_t *freq, uint32_t *states, uint16_t *words,
+                                       const uint64_t *word_off, uint64_t word_cap_per_unit, uint32_t *n_words,
+                                       const plc_restart *restart, uint32_t *status, void *stream) {
+  return encode_impl(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
+                     word_cap_per_unit, n_words, status, stream, RansArgs{}, restart);
+}
+
 extern "C" int plc_rans_encode(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
                                int32_t chunk_syms, const uint16_t *freq, uint32_t *states, uint16_t *words,
                                const uint64_t *word_off, uint64_t word_cap_per_unit, uint32_t *n_words,
                                uint32_t *status, void *stream) {
-  return encode_impl(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
-                     word_cap_per_unit, n_words, status, stream, RansArgs{});
+  return plc_rans_encode_restart(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
+                                 word_cap_per_unit, n_words, nullptr, status, stream);
+}
+
+extern "C" int plc_rans_decode_restart(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
+                                       uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words,
+                                       int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
+                                       const plc_restart *restart, uint8_t *symbols, uint32_t *status, void *stream) {
+  return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
+                     symbols, status, stream, RansArgs{}, restart);
 }
 
 extern "C" int plc_rans_decode(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
                                uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words,
                                int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, uint8_t *symbols,
                                uint32_t *status, void *stream) {
-  return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
-                     symbols, status, stream, RansArgs{});
+  return plc_rans_decode_restart(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream,
+                                 chunk_syms, nullptr, symbols, status, stream);
+}
+
+extern "C" int plc_rans_encode_bucketed_restart(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
+                                                int32_t chunk_syms, int32_t syms_per_pos, int32_t streams_per_session,
+                                                const uint8_t *bits, int32_t n_tables, const uint16_t *freq,
+                                                uint32_t *states, uint16_t *words, const uint64_t *word_off,
+                                                uint64_t word_cap_per_unit, uint32_t *n_words,
+                                                const plc_restart *restart, uint32_t *status, void *stream) {
+  RansArgs a = {};
+  const int rc = check_depths(syms_per_stream, chunk_syms, syms_per_pos, streams_per_session, bits, n_tables, &a);
+  if (rc) return rc;
+  return encode_impl(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
+                     word_cap_per_unit, n_words, status, stream, a, restart);
 }
 
 extern "C" int plc_rans_encode_bucketed(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
@@ -2860,11 +3160,22 @@ extern "C" int plc_rans_encode_bucketed(const uint8_t *symbols, int64_t n_stream
                                         uint32_t *states, uint16_t *words, const uint64_t *word_off,
                                         uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status,
                                         void *stream) {
+  return plc_rans_encode_bucketed_restart(symbols, n_streams, syms_per_stream, chunk_syms, syms_per_pos,
+                                          streams_per_session, bits, n_tables, freq, states, words, word_off,
+                                          word_cap_per_unit, n_words, nullptr, status, stream);
+}
+
+extern "C" int plc_rans_decode_bucketed_restart(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
+                                                uint64_t words_len, const uint64_t *word_off, const uint32_t *n_words,
+                                                int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
+                                                int32_t syms_per_pos, int32_t streams_per_session, const uint8_t *bits,
+                                                int32_t n_tables, const plc_restart *restart, uint8_t *symbols,
+                                                uint32_t *status, void *stream) {
   RansArgs a = {};
   const int rc = check_depths(syms_per_stream, chunk_syms, syms_per_pos, streams_per_session, bits, n_tables, &a);
   if (rc) return rc;
-  return encode_impl(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
-                     word_cap_per_unit, n_words, status, stream, a);
+  return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
+                     symbols, status, stream, a, restart);
 }
 
 extern "C" int plc_rans_decode_bucketed(const uint16_t *freq, const uint32_t *states, const uint16_t *words,
@@ -2872,9 +3183,7 @@ extern "C" int plc_rans_decode_bucketed(const uint16_t *freq, const uint32_t *st
                                         int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
                                         int32_t syms_per_pos, int32_t streams_per_session, const uint8_t *bits,
                                         int32_t n_tables, uint8_t *symbols, uint32_t *status, void *stream) {
-  RansArgs a = {};
-  const int rc = check_depths(syms_per_stream, chunk_syms, syms_per_pos, streams_per_session, bits, n_tables, &a);
-  if (rc) return rc;
-  return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
-                     symbols, status, stream, a);
+  return plc_rans_decode_bucketed_restart(freq, states, words, words_len, word_off, n_words, n_streams,
+                                          syms_per_stream, chunk_syms, syms_per_pos, streams_per_session, bits,
+                                          n_tables, nullptr, symbols, status, stream);
 }

@@ -30,11 +30,16 @@ EXPORTS = ("plc_version", "plc_strerror", "plc_workspace_bytes", "plc_units_per_
            "plc_surprisal_thresholds", "plc_surprisal_bits", "plc_predict_residual_adapt", "plc_reconstruct_adapt",
            "plc_histogram_bucketed", "plc_build_freq_bucketed", "plc_rans_encode_bucketed",
            "plc_rans_decode_bucketed",
+           "plc_restart_points", "plc_rans_encode_restart", "plc_rans_decode_restart",
+           "plc_rans_encode_bucketed_restart", "plc_rans_decode_bucketed_restart",
+           "plc_rans_decode_reconstruct_restart", "plc_rans_decode_reconstruct_cond_restart",
+           "plc_rans_decode_reconstruct_adapt_restart",
            "plc_expected_embedding", "plc_predict_residual_linear", "plc_reconstruct_linear",
            "plc_trie_create", "plc_trie_destroy", "plc_trie_size", "plc_trie_nodes", "plc_trie_insert",
            "plc_trie_best_match", "plc_trie_evict")
 
 MAX_BITS = 4
+RESTART_WORDS = 34
 
 (TRACE_PREDICT, TRACE_RECONSTRUCT, TRACE_HISTOGRAM, TRACE_RANS_ENCODE, TRACE_RANS_DECODE,
  TRACE_PREDICT_COND, TRACE_RECONSTRUCT_COND, TRACE_EXPECTED_EMBEDDING, TRACE_PREDICT_LINEAR,
@@ -52,6 +57,10 @@ class plc_dims(C.Structure):
                 ("k", C.c_int32), ("d", C.c_int32),
                 ("cand_stride", C.c_int64 * 5), ("act_stride", C.c_int64 * 4),
                 ("delta", C.c_float), ("qmax", C.c_int32)]
+
+
+class plc_restart(C.Structure):
+    _fields_ = [("points", C.c_void_p), ("scratch", C.c_void_p), ("per_stream", C.c_int32)]
 
 
 _lib = None
@@ -101,6 +110,21 @@ def lib() -> C.CDLL:
         L.plc_build_freq_bucketed.argtypes = [p, i64, i32, p, p, p]
         L.plc_rans_encode_bucketed.argtypes = [p, i64, i64, i32, i32, i32, p, i32, p, p, p, p, u64, p, p, p]
         L.plc_rans_decode_bucketed.argtypes = [p, p, p, u64, p, p, i64, i64, i32, i32, i32, p, i32, p, p, p]
+        rp = C.POINTER(plc_restart)
+        L.plc_restart_points.restype = i32
+        L.plc_restart_points.argtypes = [i64, i64, i32]
+        L.plc_rans_encode_restart.argtypes = [p, i64, i64, i32, p, p, p, p, u64, p, rp, p, p]
+        L.plc_rans_decode_restart.argtypes = [p, p, p, u64, p, p, i64, i64, i32, rp, p, p, p]
+        L.plc_rans_encode_bucketed_restart.argtypes = [p, i64, i64, i32, i32, i32, p, i32, p, p, p, p, u64, p, rp, p,
+                                                       p]
+        L.plc_rans_decode_bucketed_restart.argtypes = [p, p, p, u64, p, p, i64, i64, i32, i32, i32, p, i32, rp, p, p,
+                                                       p]
+        L.plc_rans_decode_reconstruct_restart.argtypes = [dp, p, p, p, u64, p, p, i32, p, p, p, p, u64, p, p, p, p, p,
+                                                          sz, rp, p, p]
+        L.plc_rans_decode_reconstruct_cond_restart.argtypes = [dp, p, p, p, u64, p, p, i32, p, p, p, p, p, u64, p, p,
+                                                               p, p, p, sz, rp, p, p]
+        L.plc_rans_decode_reconstruct_adapt_restart.argtypes = [dp, p, p, p, u64, p, p, i32, i32, p, p, p, p, p,
+                                                                C.c_float, p, u64, p, p, p, p, p, sz, rp, p, p]
         L.plc_trie_create.restype = p
         L.plc_trie_create.argtypes = [C.c_double]
         L.plc_trie_destroy.restype = None
@@ -149,6 +173,10 @@ def plc_units_per_stream(syms_per_stream: int, chunk_syms: int) -> int:
     return int(lib().plc_units_per_stream(int(syms_per_stream), int(chunk_syms)))
 
 
+def plc_restart_points(n_streams: int, syms_per_stream: int, chunk_syms: int) -> int:
+    return int(lib().plc_restart_points(int(n_streams), int(syms_per_stream), int(chunk_syms)))
+
+
 def _ptr(t, dtype=None):
     if t is None:
         return None
@@ -165,6 +193,18 @@ def _contig(t, dtype):
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     return _ptr(t, dtype)
+
+
+def _restart(points_and_scratch):
+    """(points int32 [streams, per_stream, RESTART_WORDS], scratch int32 [streams, per_stream, 2] or None) as a
+    plc_restart, or None."""
+    if points_and_scratch is None:
+        return None
+    points, scratch = points_and_scratch
+    r = plc_restart()
+    r.points, r.scratch = _contig(points, torch.int32), _contig(scratch, torch.int32)
+    r.per_stream = points.shape[1]
+    return C.byref(r)
 
 
 def _stream():
@@ -226,21 +266,22 @@ def plc_build_freq(counts, n_streams, freq, cum, status):
 
 
 def plc_rans_encode(symbols, n_streams, syms_per_stream, chunk_syms, freq, states, words, word_off,
-                    word_cap_per_unit, n_words, status):
-    rc = lib().plc_rans_encode(_contig(symbols, torch.uint8), n_streams, syms_per_stream, chunk_syms,
+                    word_cap_per_unit, n_words, status, restart=None):
+    rc = lib().plc_rans_encode_restart(_contig(symbols, torch.uint8), n_streams, syms_per_stream, chunk_syms,
                                _contig(freq, torch.int16), _contig(states, torch.int32),
                                _contig(words, torch.int16), _contig(word_off, torch.int64),
                                int(word_cap_per_unit), _contig(n_words, torch.int32),
-                               _contig(status, torch.int32), _stream())
+                               _restart(restart), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_encode")
 
 
 def plc_rans_decode(freq, states, words, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
-                    symbols, status):
-    rc = lib().plc_rans_decode(_contig(freq, torch.int16), _contig(states, torch.int32),
+                    symbols, status, restart=None):
+    rc = lib().plc_rans_decode_restart(_contig(freq, torch.int16), _contig(states, torch.int32),
                                _contig(words, torch.int16), words.numel(),
                                _contig(word_off, torch.int64), _contig(n_words, torch.int32),
-                               n_streams, syms_per_stream, chunk_syms, _contig(symbols, torch.uint8),
+                               n_streams, syms_per_stream, chunk_syms, _restart(restart),
+                               _contig(symbols, torch.uint8),
                                _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_decode")
 
@@ -256,26 +297,26 @@ def plc_reconstruct(dims, cand_k, cand_v, probs, symbols, esc_vals, esc_off, out
 
 
 def plc_rans_decode_reconstruct(dims, freq, states, words, word_off, n_words, chunk_syms, cand_k, cand_v, probs,
-                                esc_vals, esc_off, symbols, out_k, out_v, ws, status):
-    rc = lib().plc_rans_decode_reconstruct(
+                                esc_vals, esc_off, symbols, out_k, out_v, ws, status, restart=None):
+    rc = lib().plc_rans_decode_reconstruct_restart(
         C.byref(dims), _contig(freq, torch.int16), _contig(states, torch.int32), _contig(words, torch.int16),
         words.numel(), _contig(word_off, torch.int64), _contig(n_words, torch.int32), chunk_syms,
         _ptr(cand_k, torch.float16), _ptr(cand_v, torch.float16), _contig(probs, torch.float32),
         _contig(esc_vals, None), esc_vals.numel(), _contig(esc_off, torch.int64), _contig(symbols, torch.uint8),
         _ptr(out_k, torch.float16), _ptr(out_v, torch.float16), _contig(ws, torch.uint8), ws.numel(),
-        _contig(status, torch.int32), _stream())
+        _restart(restart), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_decode_reconstruct")
 
 
 def plc_rans_decode_reconstruct_cond(dims, freq, states, words, word_off, n_words, chunk_syms, cand_k, cand_v,
-                                     probs, chosen, esc_vals, esc_off, symbols, out_k, out_v, ws, status):
-    rc = lib().plc_rans_decode_reconstruct_cond(
+                                     probs, chosen, esc_vals, esc_off, symbols, out_k, out_v, ws, status, restart=None):
+    rc = lib().plc_rans_decode_reconstruct_cond_restart(
         C.byref(dims), _contig(freq, torch.int16), _contig(states, torch.int32), _contig(words, torch.int16),
         words.numel(), _contig(word_off, torch.int64), _contig(n_words, torch.int32), chunk_syms,
         _ptr(cand_k, torch.float16), _ptr(cand_v, torch.float16), _contig(probs, torch.float32),
         _contig(chosen, torch.int32), _contig(esc_vals, None), esc_vals.numel(), _contig(esc_off, torch.int64),
         _contig(symbols, torch.uint8), _ptr(out_k, torch.float16), _ptr(out_v, torch.float16),
-        _contig(ws, torch.uint8), ws.numel(), _contig(status, torch.int32), _stream())
+        _contig(ws, torch.uint8), ws.numel(), _restart(restart), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_decode_reconstruct_cond")
 
 
@@ -382,38 +423,38 @@ def plc_build_freq_bucketed(counts, n_streams, n_tables, freq, status):
 
 def plc_rans_encode_bucketed(symbols, n_streams, syms_per_stream, chunk_syms, syms_per_pos,
                              streams_per_session, bits, n_tables, freq, states, words, word_off,
-                             word_cap_per_unit, n_words, status):
-    rc = lib().plc_rans_encode_bucketed(_contig(symbols, torch.uint8), n_streams, syms_per_stream, chunk_syms,
+                             word_cap_per_unit, n_words, status, restart=None):
+    rc = lib().plc_rans_encode_bucketed_restart(_contig(symbols, torch.uint8), n_streams, syms_per_stream, chunk_syms,
                                         syms_per_pos, streams_per_session, _contig(bits, torch.uint8), n_tables,
                                         _contig(freq, torch.int16), _contig(states, torch.int32),
                                         _contig(words, torch.int16), _contig(word_off, torch.int64),
                                         int(word_cap_per_unit), _contig(n_words, torch.int32),
-                                        _contig(status, torch.int32), _stream())
+                                        _restart(restart), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_encode_bucketed")
 
 
 def plc_rans_decode_bucketed(freq, states, words, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
-                             syms_per_pos, streams_per_session, bits, n_tables, symbols, status):
-    rc = lib().plc_rans_decode_bucketed(_contig(freq, torch.int16), _contig(states, torch.int32),
+                             syms_per_pos, streams_per_session, bits, n_tables, symbols, status, restart=None):
+    rc = lib().plc_rans_decode_bucketed_restart(_contig(freq, torch.int16), _contig(states, torch.int32),
                                         _contig(words, torch.int16), words.numel(),
                                         _contig(word_off, torch.int64), _contig(n_words, torch.int32),
                                         n_streams, syms_per_stream, chunk_syms, syms_per_pos,
                                         streams_per_session, _contig(bits, torch.uint8), n_tables,
-                                        _contig(symbols, torch.uint8), _contig(status, torch.int32), _stream())
+                                        _restart(restart), _contig(symbols, torch.uint8), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_decode_bucketed")
 
 
 def plc_rans_decode_reconstruct_adapt(dims, freq, states, words, word_off, n_words, chunk_syms, n_tables, cand_k,
                                       cand_v, probs, chosen, bits, step_range, esc_vals, esc_off, symbols, out_k,
-                                      out_v, ws, status):
-    rc = lib().plc_rans_decode_reconstruct_adapt(
+                                      out_v, ws, status, restart=None):
+    rc = lib().plc_rans_decode_reconstruct_adapt_restart(
         C.byref(dims), _contig(freq, torch.int16), _contig(states, torch.int32), _contig(words, torch.int16),
         words.numel(), _contig(word_off, torch.int64), _contig(n_words, torch.int32), chunk_syms, n_tables,
         _ptr(cand_k, torch.float16), _ptr(cand_v, torch.float16), _contig(probs, torch.float32),
         _contig(chosen, torch.int32), _contig(bits, torch.uint8), float(step_range), _contig(esc_vals, None),
         esc_vals.numel(), _contig(esc_off, torch.int64), _contig(symbols, torch.uint8),
         _ptr(out_k, torch.float16), _ptr(out_v, torch.float16), _contig(ws, torch.uint8), ws.numel(),
-        _contig(status, torch.int32), _stream())
+        _restart(restart), _contig(status, torch.int32), _stream())
     _check(rc, "plc_rans_decode_reconstruct_adapt")
 
 
