@@ -145,20 +145,9 @@ __device__ __forceinline__ void raise(uint32_t *status, uint32_t code) {
   if (status) atomicMax(status, code);
 }
 
-// Inclusive prefix sum over the 64 lanes of a wavefront.
+// Inclusive prefix sum over the 64 lanes of a wavefront, all of them active: through the lanes' own registers (six
+// adds), where a shuffle would take an LDS round trip each.
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    uint32_t up = __shfl_up(v, off, 64);
-    if (lane >= off) v += up;
-  }
-  return v;
-}
-
-// Sum over the 64 lanes of a wavefront, the same in every lane: through the lanes' own registers (six adds),
-// where a shuffle would take an LDS round trip each.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   uint32_t s = v;
   s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x111, 0xf, 0xf, true);  // row_shr:1
   s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x112, 0xf, 0xf, true);  // row_shr:2
@@ -166,7 +155,12 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x118, 0xf, 0xf, true);  // row_shr:8
   s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x142, 0xa, 0xf, true);  // row_bcast:15 into rows 1 and 3
   s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x143, 0xc, 0xf, true);  // row_bcast:31 into rows 2 and 3
-  return (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
+  return s;
+}
+
+// Sum over the 64 lanes of a wavefront, the same in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v), 63);
 }
 
 // Exclusive prefix sum of one value per thread over a 256-thread workgroup.

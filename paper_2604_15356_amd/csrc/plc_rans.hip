@@ -150,7 +150,7 @@ __device__ __forceinline__ uint32_t load_freq4(const uint16_t *freq, int lane, u
   const uint32_t sum = f[0] + f[1] + f[2] + f[3];
   const uint32_t inc = wave_inclusive_scan(sum);
   *cum0 = inc - sum;
-  return __shfl(inc, 63, 64);
+  return (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -1355,7 +1355,54 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
 // ---------------------------------------------------------------------------
 // Decoder
 // ---------------------------------------------------------------------------
-// Slot table: for each of the 4096 slots, sym | (f - 1) << 8 | (slot - cum) << 20.
+// Slot tables are filled through an index of the symbols that occur: a bit for each slot at which one begins, and
+// the symbols' frequencies and first slots in a row.  A slot's symbol is the one whose number is the count of set bits
+// up to it: a read that 32 lanes share, a count, and a read of the row, then whatever the table's entry takes.  A table
+// for a workgroup of 128 threads takes 1.6 us so; searching each slot's symbol in eight halvings took 7.5, and
+// filling in each symbol's slots in a loop 14.
+struct SlotIndex {
+  uint2 words[kScale / 32];  // .x the bits, .y the occurring symbols in front of them
+  uint32_t row[256];         // f - 1 | first slot << 12 | symbol << 24
+};
+// By one wavefront, from what load_freq4 gave it of a table that sums to 4096.
+__device__ __forceinline__ void build_slot_index(SlotIndex *ix, const uint32_t f[4], uint32_t cum, int lane) {
+  ix->words[lane] = ix->words[lane + 64] = make_uint2(0u, 0u);
+  wave_sync();
+  const uint32_t occur = (f[0] ? 1u : 0u) + (f[1] ? 1u : 0u) + (f[2] ? 1u : 0u) + (f[3] ? 1u : 0u);
+  uint32_t at = wave_inclusive_scan(occur) - occur;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (f[r]) {
+      atomicOr(&ix->words[cum >> 5].x, 1u << (cum & 31u));
+      ix->row[at] = (f[r] - 1u) | (cum << 12) | ((uint32_t)(lane * 4 + r) << 24);
+      ++at;
+      cum += f[r];
+    }
+  }
+  wave_sync();
+  const uint32_t n0 = __builtin_popcount(ix->words[2 * lane].x), n1 = __builtin_popcount(ix->words[2 * lane + 1].x);
+  const uint32_t before = wave_inclusive_scan(n0 + n1) - (n0 + n1);
+  ix->words[2 * lane].y = before;
+  ix->words[2 * lane + 1].y = before + n0;
+}
+// put(slot, entry of the row) for every slot, by THREADS threads; the index in place behind a barrier.
+template <int THREADS, typename Put>
+__device__ __forceinline__ void for_each_slot(const SlotIndex *ix, Put put) {
+  static_assert(THREADS % 32 == 0, "a thread stays at one bit");
+  constexpr int kAtOnce = kScale / THREADS < 8 ? kScale / THREADS : 8;  // so that their LDS round trips overlap
+  const uint32_t upto = 0xffffffffu >> (31u - (threadIdx.x & 31u));
+  for (uint32_t o0 = threadIdx.x; o0 < kScale; o0 += THREADS * kAtOnce) {
+    uint2 w[kAtOnce];
+    uint32_t row[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) w[i] = ix->words[(o0 + (uint32_t)(THREADS * i)) >> 5];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) row[i] = ix->row[__builtin_popcount(w[i].x & upto) + w[i].y - 1u];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) put(o0 + (uint32_t)(THREADS * i), row[i]);
+  }
+}
+
 // Words are consumed from the end of the unit's list.  They are staged through
 // a per-wavefront LDS ring of four 512-word blocks (blocks aligned in absolute
 // address), refilled at most one block per batch of 16 groups, which consumes
@@ -1366,22 +1413,17 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
 // mirrored at 2048..2591 so that q + r never needs a wrap inside a batch.
 constexpr int kRingWords = 2048, kBlockWords = 512, kRingMirror = kBlockWords + 32;
 
-// COMPACT: the slot table is split in two, slot -> symbol (one byte per slot) and symbol -> f - 1 | cum << 16,
-// 5 KB instead of 16 KB per table at the price of a second dependent lookup.
+// The slot table is split in two, slot -> symbol (one byte per slot) and symbol -> f - 1 | cum << 16: 5 KB instead of
+// the 16 KB of a word per slot, at the price of a second dependent lookup.
 constexpr uint32_t kCompactTable = 256 + kScale / 4;  // in 32-bit words
-template <bool MASKED, bool COMPACT = false>
+template <bool MASKED>
 __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const uint16_t *&top, uint8_t *sym_slot,
                                          uint32_t below, bool on, uint32_t table_off = 0) {
-  uint32_t e;
-  if (COMPACT) {
-    const uint32_t slot = x & (kScale - 1);
-    const uint32_t *mine = lut + table_off;
-    const uint32_t s = reinterpret_cast<const uint8_t *>(mine + 256)[slot];
-    const uint32_t fc = mine[s];
-    e = s | ((fc & 0xfffu) << 8) | ((slot - (fc >> 16)) << 20);
-  } else {
-    e = lut[(x & (kScale - 1)) + table_off];
-  }
+  const uint32_t slot = x & (kScale - 1);
+  const uint32_t *mine = lut + table_off;
+  const uint32_t s = reinterpret_cast<const uint8_t *>(mine + 256)[slot];
+  const uint32_t fc = mine[s];
+  const uint32_t e = s | ((fc & 0xfffu) << 8) | ((slot - (fc >> 16)) << 20);
   const uint32_t xh = x >> kScaleBits;
   uint32_t xn = __umul24((e >> 8) & 0xfffu, xh) + (xh + (e >> 20));  // f * (x >> 12) + slot - cum
   uint32_t m32 = (uint32_t)__builtin_amdgcn_uicmp(xn, kLow, 36 /* unsigned < */);
@@ -1409,9 +1451,9 @@ __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const
 }
 
 // PIECES: a unit is a piece of a stream, and errors are left to the second launch.
-template <int W, bool ADAPT, bool COMPACT = false, bool PIECES = false>
+template <int W, bool ADAPT, bool PIECES = false>
 __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
-  __shared__ uint32_t lut_one[ADAPT ? 1 : (COMPACT ? kCompactTable : kScale)];
+  __shared__ uint32_t lut_one[ADAPT ? 1 : kCompactTable];
   extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
   uint32_t *lut = ADAPT ? lut_per_depth : lut_one;
   __shared__ uint16_t table_of_group[ADAPT ? W : 1][2][kBatch];  // ADAPT: table offset of each group of a batch
@@ -1425,52 +1467,36 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   const bool live = chunk < (PIECES ? (int64_t)a.pieces : a.units_per_stream);
   bool bad = false;
 
-  if (!ADAPT) {  // slot table, built by all wavefronts: symbol s is filled in by wavefront s mod W
+  // One slot table, or one per bit depth: that of a depth the stream does not use is all zero.  The index in the
+  // place of a ring.
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0][0]);
+  static_assert(sizeof(ring[0]) >= sizeof(SlotIndex), "room for the index");
+  const int n_tables = ADAPT ? a.n_tables : 1;
+  bool ok = true;
+  for (int t = 0; t < n_tables; ++t) {
     uint32_t f[4], cum;
-    const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
-    if (threadIdx.x == 0) table_ok = total == kScale;
-    if (total == kScale) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int s = lane * 4 + r;
-        if ((s & (W - 1)) == wave) {
-          if (COMPACT) {
-            lut[s] = ((f[r] - 1u) & 0xfffu) | (cum << 16);  // a symbol that does not occur is never looked up
-            for (uint32_t o = 0; o < f[r]; ++o) reinterpret_cast<uint8_t *>(lut + 256)[cum + o] = (uint8_t)s;
-          } else {
-            for (uint32_t o = 0; o < f[r]; ++o) lut[cum + o] = (uint32_t)s | ((f[r] - 1u) << 8) | (o << 20);
-          }
-        }
-        cum += f[r];
-      }
-    }
-  } else {  // one slot table per bit depth; the table of a depth the stream does not use is all zero
-    bool ok = true;
-    for (int t = 0; t < a.n_tables; ++t) {
-      uint32_t f[4], cum;
-      const uint32_t total = load_freq4(a.freq + (stream * a.n_tables + t) * 256, lane, f, &cum);
-      ok = ok && (total == kScale || total == 0);
-      uint32_t *lt = lut + t * (COMPACT ? kCompactTable : (uint32_t)kScale);
-      if (total == kScale) {
+    const uint32_t total = load_freq4(a.freq + (stream * n_tables + t) * 256, lane, f, &cum);
+    ok = ok && (total == kScale || (ADAPT && total == 0));
+    uint32_t *lt = lut + t * kCompactTable;
+    if (total == kScale) {  // uniform
+      if (wave == 0) {
+        build_slot_index(index, f, cum, lane);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int s = lane * 4 + r;
-          if ((s & (W - 1)) == wave) {
-            if (COMPACT) {
-              lt[s] = ((f[r] - 1u) & 0xfffu) | (cum << 16);
-              for (uint32_t o = 0; o < f[r]; ++o) reinterpret_cast<uint8_t *>(lt + 256)[cum + o] = (uint8_t)s;
-            } else {
-              for (uint32_t o = 0; o < f[r]; ++o) lt[cum + o] = (uint32_t)s | ((f[r] - 1u) << 8) | (o << 20);
-            }
-          }
+          lt[lane * 4 + r] = ((f[r] - 1u) & 0xfffu) | (cum << 16);  // a symbol that does not occur is never looked up
           cum += f[r];
         }
-      } else {
-        for (uint32_t o = threadIdx.x; o < (COMPACT ? kCompactTable : (uint32_t)kScale); o += W * 64) lt[o] = 0u;
       }
+      __syncthreads();
+      for_each_slot<W * 64>(index, [&](uint32_t o, uint32_t row) {
+        reinterpret_cast<uint8_t *>(lt + 256)[o] = (uint8_t)(row >> 24);
+      });
+    } else {
+      for (uint32_t o = threadIdx.x; o < kCompactTable; o += W * 64) lt[o] = 0u;
     }
-    if (threadIdx.x == 0) table_ok = ok;
+    if (ADAPT) __syncthreads();  // before the index serves the next table
   }
+  if (threadIdx.x == 0) table_ok = ok;
   __syncthreads();
   if (!table_ok) {  // not a table: nothing can be decoded
     if (live && lane == 0) {
@@ -1563,7 +1589,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   auto group_load = [&](int32_t g0) -> uint32_t {
     const int32_t g = g0 + lane;
     if (!ADAPT || lane >= kBatch || g >= G) return 0u;
-    return group_table(a, stream, begin, g, COMPACT ? kCompactTable : (uint32_t)kScale, &bad_depth);
+    return group_table(a, stream, begin, g, kCompactTable, &bad_depth);
   };
   if (ADAPT) {
     const uint32_t gt0 = group_load(0);
@@ -1589,7 +1615,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
     const uint16_t *wtop = wtop0;
     if (tail) {
       for (int32_t j = 0; j < cnt_groups; ++j)
-        dec_step<true, COMPACT>(x, lut, wtop, sb + kLanes * j, below, j != cnt_groups - 1 || top_active,
+        dec_step<true>(x, lut, wtop, sb + kLanes * j, below, j != cnt_groups - 1 || top_active,
                                 ADAPT ? gt[j] : 0u);
     } else {
       // the batch's table offsets are read before its first symbol is stored (the compiler cannot tell
@@ -1598,7 +1624,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) off[j] = ADAPT ? (uint32_t)__builtin_amdgcn_readfirstlane(gt[j]) : 0u;
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) dec_step<false, COMPACT>(x, lut, wtop, sb + kLanes * j, below, true, off[j]);
+      for (int j = 0; j < kBatch; ++j) dec_step<false>(x, lut, wtop, sb + kLanes * j, below, true, off[j]);
     }
     if (ADAPT) {
       if (lane < kBatch) table_of_group[wave][gbuf ^ 1][lane] = (uint16_t)ngt;
@@ -1644,36 +1670,6 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   if (bad_depth) raise(a.status, PLC_ERR_INVALID);
 }
 
-// Slot tables.  Every thread of the workgroup takes every THREADS-th slot and finds its symbol -- the last one
-// whose first slot is not above it, which passes over symbols that do not occur -- in eight halvings, eight slots
-// at a time so that their LDS round trips overlap: some 4000 cycles for a table.  (Walking the symbols one after
-// the other and filling in each one's slots was a round trip and a loop per symbol, 33,000 cycles.)
-// cum_of: first slot of each symbol (of a table that sums to 4096).  put(slot, symbol, first slot, frequency).
-template <int THREADS, typename Put>
-__device__ __forceinline__ void for_each_slot(const uint32_t *cum_of, Put put) {
-  constexpr int kAtOnce = 8;
-  for (uint32_t o0 = threadIdx.x; o0 < kScale; o0 += THREADS * kAtOnce) {
-    uint32_t s[kAtOnce], lo[kAtOnce], hi[kAtOnce];
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) s[i] = 0u;
-#pragma unroll
-    for (uint32_t half = 128u; half; half >>= 1) {
-#pragma unroll
-      for (int i = 0; i < kAtOnce; ++i) s[i] += cum_of[s[i] + half] <= o0 + (uint32_t)(THREADS * i) ? half : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) {
-      lo[i] = cum_of[s[i]];
-      hi[i] = s[i] < 255u ? cum_of[s[i] < 255u ? s[i] + 1u : 255u] : kScale;
-    }
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) {
-      const uint32_t o = o0 + (uint32_t)(THREADS * i);
-      if (o < kScale) put(o, s[i], lo[i], hi[i] - lo[i]);
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Reconstruction inside the decoder for units coded as whole streams
 // ---------------------------------------------------------------------------
@@ -1692,11 +1688,13 @@ __device__ __forceinline__ void for_each_slot(const uint32_t *cum_of, Put put) {
 //   stream, piece, G the unit's stream, the part of it that the unit is (all of it, but for pieces), its groups of 32
 //   sym_stage        the two symbol stages: batch b is in stage b mod 2 from its barrier to the next (kLate = 1:
 //                    from the barrier after its own, where the symbols pass through another wavefront first)
+//   table_barriers   barriers of the wavefronts that build the tables meanwhile, in front of "start"
 constexpr int kRecDepthBase = 3;  // batches a request runs ahead of its symbols
 
 template <int RK, bool COND, bool ADAPT, int kRecDepth, int kLate = 0, int kStageSyms = 2 * kBatchSyms>
 __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t stream, const Piece &piece, int32_t G,
-                                                    const uint8_t (&sym_stage)[2][kStageSyms], int lane) {
+                                                    const uint8_t (&sym_stage)[2][kStageSyms], int lane,
+                                                    int table_barriers) {
   static_assert(COND || !ADAPT, "the adaptive quantiser lives on the token-conditional path");
   const ReconView &r = a.recon;
   const uint32_t lh = (uint32_t)(r.L * r.H);
@@ -1705,7 +1703,7 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
   const int64_t cand0 = s * r.cs[0] + l * r.cs[1] + h * r.cs[2];
   const int64_t out0 = s * r.as[0] + l * r.as[1] + h * r.as[2];
   const float *w0 = r.weights + (int64_t)s * r.n * r.k;
-  const bool pieces = a.pieces > 0;  // uniform
+  const bool pieces = !ADAPT && a.pieces > 0;  // uniform
   const uint32_t chunk0 = piece.begin / kChunk, n_chunks = piece.len / kChunk;
   const uint32_t d8 = (uint32_t)r.d8, adv_row = 64u / d8, adv_e8 = 64u - adv_row * d8;
   // The chunk this lane requests next: row = position * 2 + (0 = K, 1 = V), e8 = chunk inside the row,
@@ -1868,6 +1866,7 @@ __device__ __forceinline__ void reconstruct_batches(const RansArgs &a, int64_t s
   for (int j = 0; j < kRecDepth; ++j)
     request(cv[j], wv[j], dst[j], live[j], pick_next[j], pick_used[j], mean_path[j], depth_next[j], depth_used[j]);
   asm volatile("" ::: "memory");
+  for (int i = 0; i < table_barriers; ++i) __builtin_amdgcn_s_barrier();  // (uniform)
   __builtin_amdgcn_s_barrier();  // barrier "start"
   asm volatile("" ::: "memory");
   if constexpr (kLate > 0) {  // the first batch's own barrier: its symbols come one barrier later
@@ -2077,12 +2076,10 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   constexpr uint32_t kRing = RB * kBlockWords;  // words the ring holds: word i sits at kRing - 1 - i mod kRing
   __shared__ __attribute__((aligned(16))) uint2 tab[kScale + kRing + kRingMirror];  // slot table, then the ring
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][2 * kBatchSyms];  // second half: lanes 32..63
-  __shared__ uint32_t cum_of[256], most[256];  // per symbol: first slot; floor((2^16 - 1) / f) | remainder << 16
   __shared__ int32_t ptr_pub[2];  // the word pointer after batch b, in slot b mod 2
-  static_assert(workgroups_per_cu(sizeof(tab) + sizeof(sym_stage) + sizeof(cum_of) + sizeof(most) + sizeof(ptr_pub)) >=
+  static_assert(workgroups_per_cu(sizeof(tab) + sizeof(sym_stage) + sizeof(ptr_pub)) >=
                     (RB == 3 ? 3 : 2),
                 "what the ring of three blocks is for, and the other holds");
-  constexpr int kThreads = RK ? 192 : 128;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const bool helper = wave == 1;
@@ -2101,37 +2098,20 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
     }
   };
 
-  {  // slot table
-    uint32_t f[4], cum;
-    const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
-    if (total != kScale) {  // not a table: nothing can be decoded
-      give_up();
-      return;
-    }
-    if (wave == 0) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t fs = f[r] ? f[r] : 1u, t = 0xffffu / fs;
-        cum_of[lane * 4 + r] = cum;
-        most[lane * 4 + r] = t | ((0xffffu - t * fs) << 16);
-        cum += f[r];
-      }
-    }
-    __syncthreads();
-    for_each_slot<kThreads>(cum_of, [&](uint32_t o, uint32_t s, uint32_t cs, uint32_t fs) {
-      const uint32_t r = o - cs, m = most[s];
-      tab[o] = make_uint2(fs | (s << 24), r | (((m & 0xffffu) - (r > (m >> 16) ? 1u : 0u)) << 16));
-    });
-    __syncthreads();
-  }
   uint2 *ring = tab + kScale;
 
+  // Everything that the start needs from global memory is asked for before the table is built, which takes as long as
+  // the answers: the first words by the helper, the candidates of the first batches by the wavefront that
+  // reconstructs, which has no part in the table.
+
   // ---- the unit: the stream, or a piece of it
+  uint32_t f[4], cum;
+  const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
   const uint64_t off = a.word_off[stream];
   const uint32_t n = a.n_words_in[stream];
   Piece piece = {0u, (uint32_t)a.syms_per_stream, n, 0u, 0u, 0u, a.states_in + stream * kLanes, nullptr};
-  if (off > a.words_len || (uint64_t)n > a.words_len - off ||
-      (pieces && !load_piece(a, stream, (int32_t)chunk, n, &piece))) {
+  if (total != kScale || off > a.words_len || (uint64_t)n > a.words_len - off ||
+      (pieces && !load_piece(a, stream, (int32_t)chunk, n, &piece))) {  // (not a table: nothing can be decoded)
     give_up();
     return;
   }
@@ -2153,19 +2133,51 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
 
   if constexpr (RK > 0) {
     if (wave == 2) {
-      reconstruct_batches<RK, COND, false, kRecDepthBase>(a, stream, piece, G, sym_stage, lane);
+      reconstruct_batches<RK, COND, false, kRecDepthBase>(a, stream, piece, G, sym_stage, lane, 2);
       return;
     }
   }
 
+  // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
+  auto block_load = [&](int32_t blk, uint4 &v) -> bool {
+    const int32_t first = blk * kBlockWords + lane * 8;
+    const bool take = blk >= 0 && hi > lo && first + 8 > lo && first < hi;
+    if (take) v = *reinterpret_cast<const uint4 *>(aligned_base + first);
+    return take;
+  };
+  // A batch consumes at most one block of words.  While batch b runs, the pointer p_b it started from is
+  // known to the helper: the words down to p_b - 3 blocks are requested and those down to p_(b-1) - 3 blocks, at
+  // or below p_b - 2 blocks, are in the ring -- batch b + 1 reads no further down than that.
+  // With three blocks the words are staged two blocks below the pointer and none is left on its way: the
+  // block written while batch b runs then takes the slot of the block three above it, which lies wholly
+  // above the pointer batch b started from.
+  constexpr int kBelow = (RB == 4 ? 3 : 2) * kBlockWords;
+  const int32_t top_block = (hi - 1) >> 9;
+  const int32_t first_down = hi - kBelow > 0 ? (hi - kBelow) >> 9 : 0;  // the blocks down to here come first
+  uint4 first_v[RB];
+  bool first_take[RB];
   if (helper) {
-    // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
-    auto block_load = [&](int32_t blk, uint4 &v) -> bool {
-      const int32_t first = blk * kBlockWords + lane * 8;
-      const bool take = blk >= 0 && hi > lo && first + 8 > lo && first < hi;
-      if (take) v = *reinterpret_cast<const uint4 *>(aligned_base + first);
-      return take;
-    };
+#pragma unroll
+    for (int i = 0; i < RB; ++i) first_take[i] = top_block - i >= first_down && block_load(top_block - i, first_v[i]);
+  }
+  const uint32_t x0 = piece.states[lane & (kLanes - 1)];
+
+  // ---- slot table, its index in the ring's place
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(ring);
+  static_assert(sizeof(SlotIndex) <= kRing * sizeof(uint2) && kScale % 2 == 0, "room for the index");
+  if (wave == 0) build_slot_index(index, f, cum, lane);
+  lds_barrier();
+  for_each_slot<128>(index, [&](uint32_t o, uint32_t row) {
+    const uint32_t fs = (row & 0xfffu) + 1u, r = o - ((row >> 12) & 0xfffu);
+    // floor((2^16 - 1 - r) / f): the quotient in fp32 is off by less than one, and put right by what is left
+    uint32_t t = (uint32_t)((float)(0xffffu - r) * __builtin_amdgcn_rcpf((float)fs));
+    const int32_t left = (int32_t)(0xffffu - r - t * fs);
+    t = left < 0 ? t - 1u : (uint32_t)left >= fs ? t + 1u : t;
+    tab[o] = make_uint2(fs | (row & 0xff000000u), r | (t << 16));
+  });
+  lds_barrier();
+
+  if (helper) {
     // Word i goes to ring position (~i) mod 2048: the slot-table entry of its low 12 bits, its top four
     // bits multiplied in.
     auto block_store = [&](int32_t blk, bool take, const uint4 &v) {
@@ -2196,7 +2208,9 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
     // Stages every block that holds a word at or above `down_to` and is not staged yet.  The last of them
     // may be left on its way (`ahead`): its words go to the ring at the next call, a batch later, so that
     // the wavefront does not sit out the load's latency in front of the barrier.
-    int32_t lowest = ((hi - 1) >> 9) + 1;  // lowest block already requested (none yet)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) block_store(top_block - i, first_take[i], first_v[i]);
+    int32_t lowest = top_block + 1 < first_down ? top_block + 1 : first_down;  // lowest block already requested
     uint4 ahead_v;
     int32_t ahead_blk = 0;
     bool ahead = false, ahead_take = false;
@@ -2220,15 +2234,7 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
         }
       }
     };
-    // A batch consumes at most one block of words.  While batch b runs, the pointer p_b it started from is
-    // known here: the words down to p_b - 3 blocks are requested and those down to p_(b-1) - 3 blocks, at
-    // or below p_b - 2 blocks, are in the ring -- batch b + 1 reads no further down than that.
-    // With three blocks the words are staged two blocks below the pointer and none is left on its way: the
-    // block written while batch b runs then takes the slot of the block three above it, which lies wholly
-    // above the pointer batch b started from.
-    constexpr int kBelow = (RB == 4 ? 3 : 2) * kBlockWords;
-    stage_down_to(hi - kBelow, false);
-    __syncthreads();  // barrier "start"
+    lds_barrier();  // barrier "start"
     int32_t ptr_before = hi;  // the pointer as it stood before the batch now running
     for (int32_t g0 = 0; g0 < G; g0 += kBatch) {
       stage_down_to(ptr_before - kBelow, RB == 4);
@@ -2260,11 +2266,10 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
   const bool coder = lane < kLanes;
   const int rl = lane & (kLanes - 1);
   const bool top_active = (uint32_t)rl < top_syms;
-  const uint32_t x0 = piece.states[rl];
   uint32_t xc = x0 >> kScaleBits;
   uint2 e = tab[x0 & (kScale - 1)];
   int32_t ptr = hi;
-  __syncthreads();  // barrier "start": the first words are staged
+  lds_barrier();  // barrier "start": the first words are staged
   // The top word's entry in tab (uniform): in a vector register where the ranks are added to it, and a scalar copy
   // as of the batch's first step.  Everything a batch needs besides its steps is done behind the last step's read.
   uint32_t ring_start = (uint32_t)kScale + kRing - 1u - (uint32_t)(ptr - 1) % kRing;
@@ -2300,11 +2305,13 @@ __global__ __launch_bounds__(RK ? 192 : 128) void rans_decode_chain_kernel(const
     batch_done(parity);
   }
   // integrity: every word consumed, every lane back at the initial state (a piece: at what the record behind it
-  // says).  The state from x >> 12 as carried and the entry in hand, whose .y has f * w4 + slot - cum in its lower half.
-  const uint32_t fs = e.x & 0xffffffu, y = e.y & 0xffffu, w4 = y / fs;
-  const uint32_t x_now = ((xc + w4) << kScaleBits) + cum_of[e.x >> 24] + (y - w4 * fs);
+  // says).  The entry in hand has f * w4 + slot - cum in the lower half of .y, which with x >> 12 as carried makes the
+  // state: it is the expected one if it has the symbol, the slot - cum and the x >> 12 of that.
   const uint32_t x_end = piece.end_states ? piece.end_states[rl] : kLow;
-  if (ptr != lo + (int32_t)piece.words_left || (coder && x_now != x_end)) bad = true;
+  const uint2 e_end = tab[x_end & (kScale - 1)];
+  const uint32_t fs = e.x & 0xffffffu, y = e.y & 0xffffu, w4 = y / fs;
+  const bool there = e.x == e_end.x && y - w4 * fs == (e_end.y & 0xffffu) && xc + w4 == x_end >> kScaleBits;
+  if (ptr != lo + (int32_t)piece.words_left || (coder && !there)) bad = true;
   if (pieces) {
     const bool good = __ballot(bad) == 0;
     if (lane < (RK ? 1 : 2)) report_piece(a, stream, (int32_t)chunk, lane, good);
@@ -2428,13 +2435,11 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   __shared__ __attribute__((aligned(16))) uint16_t code_stage[2][kBatchSyms];  // where the entries were read from
   __shared__ uint16_t code_spare[kBatchSyms];                                  // the same from lanes 32..63, never read
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kBatchSyms];    // symbols, for the reconstruction
-  uint32_t *const fc = reinterpret_cast<uint32_t *>(&code_stage[0][0]);        // first slots while the tables are built
-  static_assert(sizeof(code_stage) >= 256 * sizeof(uint32_t), "room for the first slots");
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&code_stage[0][0]);   // while the tables are built
+  static_assert(sizeof(code_stage) >= sizeof(SlotIndex), "room for the index");
   __shared__ uint32_t tables_of_batch[4];  // batch b mod 4: the tables of groups 16 b + 1 .. 16 b + 16, two bits each
   __shared__ uint32_t first_table;
   __shared__ int32_t ptr_pub[2];  // the word pointer after batch b, in slot b mod 2
-  __shared__ uint32_t tables_ok;
-  constexpr int kThreads = depths_threads(RK);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const bool helper = wave == 1;
@@ -2443,9 +2448,10 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   const uint32_t ring_off = (uint32_t)n_tables * kDepthTableBytes;
   const uint32_t raw_off = ring_off + (uint32_t)n_tables * kDepthRingBytes;
   const uint32_t symtab_off = raw_off + kDepthRawBytes;
-  const bool pieces = a.pieces > 0;  // uniform: the unit is a piece of the stream
+  // (pieces with a table per depth go to the many-unit decoder, what they leave to the form without reconstruction)
+  const bool pieces = MODE && a.pieces > 0;  // uniform: the unit is a piece of the stream
   bool bad = false;
-  if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
+  if ((MODE || RK == 0) && a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
   // (uniform: every wavefront leaves, before any barrier that another might wait at)
   auto give_up = [&]() {
     if (threadIdx.x != 0) return;
@@ -2456,46 +2462,28 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
     }
   };
 
-  // slot and symbol tables, one depth after the other; an all-zero table (a depth the stream does not use)
-  // stays zero
-  if (threadIdx.x == 0) tables_ok = 1u;
-  __syncthreads();
-  uint32_t used = 0;  // uniform: bit t set when table t is one
-  for (int t = 0; t < n_tables; ++t) {
-    uint32_t f[4], cum;
-    const uint32_t total = load_freq4(a.freq + (stream * n_tables + t) * 256, lane, f, &cum);
-    if (total != kScale && (MODE || total != 0) && threadIdx.x == 0) tables_ok = 0u;
-    if (wave == 0) {
+  // As in the kernel above, everything that the start needs from global memory is asked for before the tables are
+  // built, in which the wavefront that reconstructs has no part.
+  constexpr int kMaxTables = MODE ? 1 : PLC_MAX_BITS;
+  uint32_t f[kMaxTables][4], cum[kMaxTables];
+  uint32_t used = 0;  // uniform: bit t set when table t is one; an all-zero table (a depth the stream does not use) is none
+  bool tables_ok = true;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        fc[lane * 4 + r] = cum;
-        cum += f[r];
-      }
-    }
-    __syncthreads();
-    uint32_t *tt = reinterpret_cast<uint32_t *>(depth_lds + (size_t)t * kDepthTableBytes);
-    uint8_t *ts = reinterpret_cast<uint8_t *>(depth_lds + symtab_off + (size_t)t * kDepthSymBytes);
+  for (int t = 0; t < kMaxTables; ++t) {
+    if (t >= n_tables) break;
+    const uint32_t total = load_freq4(a.freq + (stream * n_tables + t) * 256, lane, f[t], &cum[t]);
     if (total == kScale) {
       used |= 1u << t;
-      for_each_slot<kThreads>(fc, [&](uint32_t o, uint32_t sy, uint32_t cs, uint32_t fs) {
-        tt[o] = fs | ((o - cs) << 16);
-        ts[o] = (uint8_t)sy;
-      });
-    } else {
-      for (uint32_t o = threadIdx.x; o < (uint32_t)kScale; o += kThreads) tt[o] = 0u, ts[o] = 0;
+    } else if (MODE || total != 0) {
+      tables_ok = false;
     }
-    __syncthreads();
-  }
-  if (!tables_ok) {  // not a table: nothing can be decoded
-    give_up();
-    return;
   }
 
   // the unit: the stream, or a piece of it
   const uint64_t off = a.word_off[stream];
   const uint32_t n = a.n_words_in[stream];
   Piece piece = {0u, (uint32_t)a.syms_per_stream, n, 0u, 0u, 0u, a.states_in + stream * kLanes, nullptr};
-  if (off > a.words_len || (uint64_t)n > a.words_len - off ||
+  if (!tables_ok || off > a.words_len || (uint64_t)n > a.words_len - off ||
       (pieces && !load_piece(a, stream, (int32_t)chunk, n, &piece))) {
     give_up();
     return;
@@ -2516,21 +2504,51 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
 
   if constexpr (RK > 0) {  // the wavefront that reconstructs, one barrier behind the decoder's batch
     if (wave == 2) {
-      reconstruct_batches<RK, MODE != 1, MODE == 0, kRecDepthBase, 1, kBatchSyms>(a, stream, piece, G, sym_stage, lane);
+      reconstruct_batches<RK, MODE != 1, MODE == 0, kRecDepthBase, 1, kBatchSyms>(a, stream, piece, G, sym_stage, lane,
+                                                                                  2 * n_tables);
       return;
     }
+  }
+
+  auto block_load = [&](int32_t blk, uint4 &v) -> bool {
+    const int32_t first = blk * kBlockWords + lane * 8;
+    const bool take = blk >= 0 && hi > lo && first + 8 > lo && first < hi;
+    if (take) v = *reinterpret_cast<const uint4 *>(aligned_base + first);
+    return take;
+  };
+  const int32_t top_block = (hi - 1) >> 9;
+  const int32_t first_down = hi - kBelow > 0 ? (hi - kBelow) >> 9 : 0;  // the blocks down to here come first
+  uint4 first_v[RB];
+  bool first_take[RB];
+  if (helper) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i) first_take[i] = top_block - i >= first_down && block_load(top_block - i, first_v[i]);
+  }
+  const uint32_t x0 = piece.states[lane & (kLanes - 1)];
+
+  // slot and symbol tables, one depth after the other
+#pragma unroll
+  for (int t = 0; t < kMaxTables; ++t) {
+    if (t >= n_tables) break;
+    if (wave == 0 && ((used >> t) & 1u)) build_slot_index(index, f[t], cum[t], lane);
+    lds_barrier();
+    uint32_t *tt = reinterpret_cast<uint32_t *>(depth_lds + (size_t)t * kDepthTableBytes);
+    uint8_t *ts = reinterpret_cast<uint8_t *>(depth_lds + symtab_off + (size_t)t * kDepthSymBytes);
+    if ((used >> t) & 1u) {
+      for_each_slot<128>(index, [&](uint32_t o, uint32_t row) {
+        tt[o] = ((row & 0xfffu) + 1u) | ((o - ((row >> 12) & 0xfffu)) << 16);
+        ts[o] = (uint8_t)(row >> 24);
+      });
+    } else {
+      for (uint32_t o = threadIdx.x; o < (uint32_t)kScale; o += 128) tt[o] = 0u, ts[o] = 0;
+    }
+    lds_barrier();
   }
 
   if (helper) {
     bool bad_depth = false;
     uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
     const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 7u) == 0;
-    auto block_load = [&](int32_t blk, uint4 &v) -> bool {
-      const int32_t first = blk * kBlockWords + lane * 8;
-      const bool take = blk >= 0 && hi > lo && first + 8 > lo && first < hi;
-      if (take) v = *reinterpret_cast<const uint4 *>(aligned_base + first);
-      return take;
-    };
     // word i goes to ring position (~i) mod 2048: the lane's eight words, last one first
     auto block_store = [&](int32_t blk, bool take, const uint4 &v) {
       if (take) {
@@ -2563,7 +2581,9 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
       }
     };
     // as in the kernel above: the newest block stays on its way for a batch
-    int32_t lowest = ((hi - 1) >> 9) + 1;  // lowest block already requested (none yet)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) block_store(top_block - i, first_take[i], first_v[i]);
+    int32_t lowest = top_block + 1 < first_down ? top_block + 1 : first_down;  // lowest block already requested
     uint4 ahead_v;
     int32_t ahead_blk = 0;
     bool ahead = false, ahead_take = false;
@@ -2609,7 +2629,6 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
       for (int off = 1; off < kBatch; off <<= 1) v |= __shfl_xor(v, off, 64);
       return (uint32_t)__builtin_amdgcn_readfirstlane(v);
     };
-    stage_down_to(hi - kBelow, false);
     uint32_t t_first = 0, tables_cur = 0, tables_next = 0, depth_ahead = 1;
     if constexpr (MODE == 0) {
       t_first = group_table(a, stream, begin, 0, 1u, &bad_depth);  // table of the coming batch's first group
@@ -2621,7 +2640,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
       }
       depth_ahead = fetch_depths(2 * kBatch);
     }
-    __syncthreads();  // barrier "start"
+    lds_barrier();  // barrier "start"
     int32_t ptr_before = hi;
     for (int32_t g0 = 0; g0 < G; g0 += kBatch) {
       stage_down_to(ptr_before - kBelow, true);
@@ -2694,9 +2713,8 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   const bool coder = lane < kLanes;
   const int rl = lane & (kLanes - 1);
   const bool top_active = (uint32_t)rl < top_syms;
-  const uint32_t x0 = piece.states[rl];
   int32_t ptr = hi;
-  __syncthreads();  // barrier "start": the first words are staged, the first tables known
+  lds_barrier();  // barrier "start": the first words are staged, the first tables known
   const uint32_t *lds_words = reinterpret_cast<const uint32_t *>(depth_lds);
   uint32_t slot_mask = kScale - 1;
   asm volatile("" : "+v"(slot_mask));
@@ -2850,11 +2868,11 @@ struct LaunchDecode {
     if (a.pieces) {  // (see decode_impl)
       if (a.bits) {
         const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, true, true>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, true>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((rans_decode_kernel<W, true, true, true>), dim3(grid), dim3(W * 64), lds, st, a);
+        hipLaunchKernelGGL((rans_decode_kernel<W, true, true>), dim3(grid), dim3(W * 64), lds, st, a);
       } else {
-        hipLaunchKernelGGL((rans_decode_kernel<W, false, true, true>), dim3(grid), dim3(W * 64), 0, st, a);
+        hipLaunchKernelGGL((rans_decode_kernel<W, false, true>), dim3(grid), dim3(W * 64), 0, st, a);
       }
     } else if (a.bits && W == 1 && a.n_units <= kDepthsMaxUnits) {
       const size_t lds = depths_lds_bytes(a.n_tables);
@@ -2864,15 +2882,15 @@ struct LaunchDecode {
     } else if (a.bits) {
       // (the split tables here too: 5 KB per depth instead of 16 lets three times the wavefronts in)
       const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, true>),
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL((rans_decode_kernel<W, true, true>), dim3(grid), dim3(W * 64), lds, st, a);
+      hipLaunchKernelGGL((rans_decode_kernel<W, true>), dim3(grid), dim3(W * 64), lds, st, a);
     } else if (W == 1 && a.n_units <= kChainMaxUnits) {
       hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3(grid), dim3(128), 0, st, a);
     } else {
       // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in
       // (twice as many where every one-wavefront workgroup has a table of its own).
-      hipLaunchKernelGGL((rans_decode_kernel<W, false, true>), dim3(grid), dim3(W * 64), 0, st, a);
+      hipLaunchKernelGGL((rans_decode_kernel<W, false>), dim3(grid), dim3(W * 64), 0, st, a);
     }
   }
 };
