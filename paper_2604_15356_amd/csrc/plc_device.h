@@ -126,6 +126,30 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
                       const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch);
 
+// plc_rans_decode_restart (bits = null) and plc_rans_decode_bucketed_restart, which besides may count the escapes of
+// each tile of 2048 symbols into tile_cnt.  counts->counted tells whether it did; then, with counts->piece_state, only
+// for the streams whose pieces are all good -- the others were decoded once more, by a kernel that does not count.
+struct TileCounts {
+  bool counted;
+  const uint32_t *piece_state;
+  int32_t pieces;
+};
+int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
+                         const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
+                         int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos,
+                         int32_t streams_per_session, const uint8_t *bits, int32_t n_tables,
+                         const plc_restart *restart, uint8_t *symbols, uint32_t *tile_cnt, TileCounts *counts,
+                         uint32_t *status, void *stream);
+
+// A stream's two words per piece, as the decoder leaves them: whether all are good (uniform over the wavefront).
+constexpr uint32_t kPieceGood = 0x600du;
+__device__ __forceinline__ bool pieces_good(const uint32_t *piece_state, int32_t pieces, int64_t stream) {
+  const uint32_t *w = piece_state + stream * pieces * 2;
+  bool good = true;
+  for (int32_t i = (int32_t)(threadIdx.x & 63); i < 2 * pieces; i += 64) good = good && w[i] == kPieceGood;
+  return __ballot(!good) == 0;
+}
+
 // Escape bookkeeping for callers that produce or consume symbols outside the tile-structured kernels
 // (plc_predict.hip): collect the escaped components' raw fp16 values of `act` into the per-stream lists /
 // overwrite the escaped components of `out` from the lists.  dims->k and the candidate strides are not used.

@@ -387,18 +387,17 @@ __global__ __launch_bounds__(kBlock) void predict_residual_cond_kernel(const Cod
 
 // Count the escape symbols of each tile (decode side).  One wavefront per tile, 32 bytes per lane: a tile per
 // workgroup would spend its time starting workgroups, this way the pass runs at memory speed.
-__global__ __launch_bounds__(kBlock) void count_escapes_kernel(const CodecArgs a, uint32_t n_tiles) {
-  const uint32_t t = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);  // tile, uniform per wavefront
-  if (t >= n_tiles) return;
+__device__ __forceinline__ void count_tile(const uint8_t *__restrict__ symbols, int64_t syms_per_stream,
+                                           uint32_t tiles_per_stream, uint32_t t, uint32_t *tile_cnt) {
   const int lane = threadIdx.x & 63;
-  const uint32_t stream = t / a.tiles_per_stream;
-  const uint32_t tile = t - stream * a.tiles_per_stream;
+  const uint32_t stream = t / tiles_per_stream;
+  const uint32_t tile = t - stream * tiles_per_stream;
   const uint32_t chunk0 = tile * kBlock + lane * 4;  // this lane's four chunks of 8 symbols
-  const uint8_t *p = a.symbols + (int64_t)stream * a.syms_per_stream + (int64_t)chunk0 * kChunk;
+  const uint8_t *p = symbols + (int64_t)stream * syms_per_stream + (int64_t)chunk0 * kChunk;
   uint32_t n_esc = 0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {  // 8-byte loads: that is the alignment the symbols are promised to have
-    if (chunk0 + c < a.chunks_per_stream) {
+    if ((int64_t)(chunk0 + c) * kChunk < syms_per_stream) {
       const uint2 v = *reinterpret_cast<const uint2 *>(p + kChunk * c);
       // a byte is 0xff iff its low seven bits carry into bit 7 when 1 is added and bit 7 is set
       n_esc += (uint32_t)__builtin_popcount(((v.x & 0x7f7f7f7fu) + 0x01010101u) & v.x & 0x80808080u);
@@ -406,18 +405,29 @@ __global__ __launch_bounds__(kBlock) void count_escapes_kernel(const CodecArgs a
     }
   }
   static_assert(PLC_ESCAPE == 255, "the byte test above");
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) n_esc += __shfl_xor(n_esc, off, 64);
-  if (lane == 0) a.tile_cnt[t] = n_esc;
+  n_esc = wave_sum(n_esc);
+  if (lane == 0) tile_cnt[t] = n_esc;
+}
+__global__ __launch_bounds__(kBlock) void count_escapes_kernel(const CodecArgs a, uint32_t n_tiles) {
+  const uint32_t t = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);  // tile, uniform per wavefront
+  if (t < n_tiles) count_tile(a.symbols, a.syms_per_stream, a.tiles_per_stream, t, a.tile_cnt);
 }
 
 // Exclusive prefix sum of the tile counts inside each stream; one workgroup per stream.
-__global__ __launch_bounds__(kBlock) void scan_tiles_kernel(const uint32_t *__restrict__ tile_cnt,
-                                                            uint32_t *__restrict__ tile_off,
+// With piece_state: the counts are the decoder's, and those of a stream whose pieces are not all good are taken here first.
+__global__ __launch_bounds__(kBlock) void scan_tiles_kernel(uint32_t *tile_cnt, uint32_t *__restrict__ tile_off,
                                                             uint32_t tiles_per_stream,
-                                                            uint32_t *__restrict__ esc_cnt) {
+                                                            uint32_t *__restrict__ esc_cnt,
+                                                            const uint32_t *__restrict__ piece_state, int32_t pieces,
+                                                            const uint8_t *__restrict__ symbols,
+                                                            int64_t syms_per_stream) {
   __shared__ uint32_t smem[8];
   const int64_t base = (int64_t)blockIdx.x * tiles_per_stream;
+  if (piece_state && !pieces_good(piece_state, pieces, blockIdx.x)) {  // uniform; never but for damaged records or words
+    for (uint32_t t = threadIdx.x >> 6; t < tiles_per_stream; t += kBlock / 64)
+      count_tile(symbols, syms_per_stream, tiles_per_stream, (uint32_t)base + t, tile_cnt);
+    __syncthreads();
+  }
   uint32_t carry = 0;
   for (uint32_t t0 = 0; t0 < tiles_per_stream; t0 += kBlock) {
     const uint32_t t = t0 + threadIdx.x;
@@ -818,6 +828,15 @@ extern "C" size_t plc_workspace_bytes(const plc_dims *dims) {
 namespace plc {
 namespace {
 
+// counts: of the decoder, where it took them.
+void launch_scan_tiles(const Plan &p, const CodecArgs &a, uint32_t *tile_off, uint32_t *esc_cnt, const TileCounts &counts,
+                       hipStream_t st) {
+  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
+                     (uint32_t)p.tiles_per_stream, esc_cnt, counts.piece_state, counts.pieces, a.symbols,
+                     p.syms_per_stream);
+}
+
+
 int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, const float *probs,
                   const int32_t *chosen, const uint8_t *bits, float range, int trace_id, const void *act_k, const void *act_v, uint8_t *symbols,
                   uint16_t *esc_vals, uint64_t esc_cap, uint32_t *esc_cnt, uint64_t *esc_off, float *pred_out,
@@ -858,8 +877,7 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
     TraceScope trace(trace_id, st);
     dispatch_k<LaunchPredict>(dims->k, a, (unsigned)p.n_tiles, st);
   }
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
-                     (uint32_t)p.tiles_per_stream, esc_cnt);
+  launch_scan_tiles(p, a, tile_off, esc_cnt, TileCounts{}, st);
   hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
                      status);
   // 64 tiles per wavefront start the fewest wavefronts; where that would leave compute units without one, eight
@@ -873,7 +891,7 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
 int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, const float *probs,
                   const int32_t *chosen, const uint8_t *bits, float range, int trace_id, const uint8_t *symbols, const uint16_t *esc_vals,
                   uint64_t esc_len, const uint64_t *esc_off, void *out_k, void *out_v, void *ws, size_t ws_bytes,
-                  uint32_t *status, void *stream) {
+                  uint32_t *status, void *stream, const TileCounts &counts = TileCounts{}) {
   Plan p;
   if (!make_plan(dims, &p)) return PLC_ERR_INVALID;
   if (!aligned(cand_k, 16) || !aligned(cand_v, 16) || !aligned(out_k, 16) || !aligned(out_v, 16))
@@ -902,10 +920,10 @@ int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
 
   hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
                      weights, p.rows, dims->k, status);
-  hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, st,
-                     a, (uint32_t)p.n_tiles);
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
-                     (uint32_t)p.tiles_per_stream, (uint32_t *)nullptr);
+  if (!counts.counted)
+    hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
+                       0, st, a, (uint32_t)p.n_tiles);
+  launch_scan_tiles(p, a, tile_off, nullptr, counts, st);
   {
     TraceScope trace(trace_id, st);
     dispatch_k<LaunchReconstruct>(dims->k, a, (unsigned)p.n_tiles, st);
@@ -935,8 +953,7 @@ int plc::gather_escapes(const plc_dims *dims, const void *act_k, const void *act
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
   hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, st,
                      a, (uint32_t)p.n_tiles);
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
-                     (uint32_t)p.tiles_per_stream, esc_cnt);
+  launch_scan_tiles(p, a, tile_off, esc_cnt, TileCounts{}, st);
   hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
                      status);
   hipLaunchKernelGGL(gather_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))),
@@ -966,8 +983,7 @@ int plc::patch_escapes(const plc_dims *dims, const uint8_t *symbols, const uint1
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
   hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, st,
                      a, (uint32_t)p.n_tiles);
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
-                     (uint32_t)p.tiles_per_stream, (uint32_t *)nullptr);
+  launch_scan_tiles(p, a, tile_off, nullptr, TileCounts{}, st);
   hipLaunchKernelGGL(patch_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
                      0, st, a, p.n_tiles);
   return launch_status();
@@ -1079,16 +1095,16 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
   if (chunk_syms != 0 ||
       !decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, chosen != nullptr, bits != nullptr,
                               restart != nullptr)) {
-    const int rc = bits ? plc_rans_decode_bucketed_restart(freq, states, words, words_len, word_off, n_words,
-                                                           p.n_streams, p.syms_per_stream, chunk_syms, 2 * dims->d,
-                                                           dims->L * dims->H, bits, n_tables, restart, symbols, status,
-                                                           stream)
-                        : plc_rans_decode_restart(freq, states, words, words_len, word_off, n_words, p.n_streams,
-                                                  p.syms_per_stream, chunk_syms, restart, symbols, status, stream);
+    CodecArgs a = {};
+    fill_args(dims, p, ws, &a);
+    TileCounts counts;
+    const int rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams,
+                                        p.syms_per_stream, chunk_syms, 2 * dims->d, dims->L * dims->H, bits, n_tables,
+                                        restart, symbols, a.tile_cnt, &counts, status, stream);
     if (rc) return rc;
     return decode_floats(dims, cand_k, cand_v, probs, chosen, bits, range,
                          chosen ? PLC_TRACE_RECONSTRUCT_COND : PLC_TRACE_RECONSTRUCT, symbols, esc_vals, esc_len,
-                         esc_off, out_k, out_v, ws, ws_bytes, status, stream);
+                         esc_off, out_k, out_v, ws, ws_bytes, status, stream, counts);
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
 

@@ -66,7 +66,10 @@ struct RansArgs {
   int32_t point_stride;        // records per stream in points_*
   int32_t pieces;              // decode: pieces per stream a workgroup's unit is one of (0: units as coded)
   int32_t piece_batches;       // batches per piece
+  int32_t point_step;          // decode: records per piece
   int32_t verified_pieces;     // decode: a stream all of whose so many pieces were verified is left alone
+  // decode, nullable: escapes of each tile of a stream, where its units are whole tiles (see count_tiles)
+  uint32_t *tile_cnt;
 };
 
 // Pieces.  The decoder of a stream that is one unit can begin in the middle of it if it knows what the sequential
@@ -99,7 +102,8 @@ struct Piece {
 __device__ __forceinline__ bool load_piece(const RansArgs &a, int64_t stream, int32_t i, uint32_t n_words, Piece *p) {
   const int32_t G = (int32_t)((a.syms_per_stream + kLanes - 1) / kLanes);
   const uint32_t *rec = a.points_in + stream * a.point_stride * PLC_RESTART_WORDS;
-  const uint32_t *end = rec + (int64_t)i * PLC_RESTART_WORDS, *at = end + PLC_RESTART_WORDS;
+  const uint32_t *end = rec + (int64_t)i * a.point_step * PLC_RESTART_WORDS;
+  const uint32_t *at = end + (int64_t)a.point_step * PLC_RESTART_WORDS;
   const bool first = i + 1 == a.pieces;
   p->begin = (uint32_t)piece_top(G, a.pieces, a.piece_batches, i + 1) * kLanes;
   p->len = (i == 0 ? (uint32_t)a.syms_per_stream : (uint32_t)piece_top(G, a.pieces, a.piece_batches, i) * kLanes) - p->begin;
@@ -112,16 +116,12 @@ __device__ __forceinline__ bool load_piece(const RansArgs &a, int64_t stream, in
   return p->words <= n_words && p->words_left <= p->words;
 }
 // What a piece's workgroup found: the decoding wavefront's word and the reconstructing one's (two alike where none is).
-constexpr uint32_t kPieceGood = 0x600du;
 __device__ __forceinline__ void report_piece(const RansArgs &a, int64_t stream, int32_t i, int which, bool good) {
   a.piece_state[(stream * a.pieces + i) * 2 + which] = good ? kPieceGood : 0u;
 }
 // For the launch behind the pieces': whether this stream needs no second decode (uniform).
 __device__ __forceinline__ bool stream_verified(const RansArgs &a, int64_t stream) {
-  const uint32_t *w = a.piece_state + stream * a.verified_pieces * 2;
-  bool good = true;
-  for (int32_t i = (int32_t)(threadIdx.x & 63); i < 2 * a.verified_pieces; i += 64) good = good && w[i] == kPieceGood;
-  return __ballot(!good) == 0;
+  return pieces_good(a.piece_state, a.verified_pieces, stream);
 }
 
 // Offset (in table entries of `stride` each) of the table that the 32 symbols from unit-relative group g on use.
@@ -891,15 +891,24 @@ constexpr int64_t kChainMaxUnits = 1024;  // the same bound for the decoder of w
 // The decoder with one table per depth holds one unit per compute unit (its tables take 128 KB of LDS): two
 // rounds of 256 are what it may take before the many-unit decoder is as fast.
 constexpr int64_t kDepthsMaxUnits = 512;
-// Restart points: so many pieces altogether -- 16 per compute unit, four wavefronts per SIMD of the many-unit decoder
-// (256 streams of 1,048,576 symbols in 4, 8, 16, 32 pieces each, decode and reconstruction given the tokens:
-// 1.51, 0.93, 0.68, 0.66 ms; in one piece 1.50) -- and none shorter than two of the encoder's rounds (4096 symbols:
-// 8 streams of 65,536 symbols in 4, 8, 16, 32 pieces 53, 45, 38, 32 us, in one 120, where a record's 136 bytes come
-// to 4 % of the words of the shortest).
-constexpr int64_t kPiecesWanted = 4096;
+// Restart points: so many pieces altogether -- 32 per compute unit, four wavefronts per SIMD of the decoder with two
+// units per wavefront (256 streams of 1,048,576 symbols in 8, 16, 32, 64 pieces each: 521, 306, 196, 191 us; as whole
+// streams 1.39 ms) -- and none shorter than two of the encoder's rounds (4096 symbols: 8 streams of 65,536 symbols in
+// 8, 16, 32 pieces 29, 24, 22 us, where a record's 136 bytes come to 4 % of the words of the shortest).
+constexpr int64_t kPiecesWanted = 8192;
 constexpr int32_t kPieceMinRounds = 2;
-// Up to here a piece gets a workgroup of the decoder with the shortest step: two to a compute unit, one round.
-constexpr int64_t kChainMaxPieces = 512;
+// Up to here a piece gets a workgroup of the decoder with the shortest step, two rounds of two to a compute unit (128
+// streams of 262,144 symbols, 8 pieces each: 117 us, the decoder with two units per wavefront 141; 256 streams: 217 and
+// 143).
+constexpr int64_t kChainMaxPieces = 1024;
+// Symbols altogether from which pieces are decoded in one call and reconstructed in another.  Fewer go to the kernel
+// that does both, in pieces of several records: a round of workgroups (two or, up to kCompactMaxK candidates, four to a
+// compute unit) is best there, whose start is then paid once.  k = 8, 12, 32, 64, 128, 256 million symbols, one kernel
+// and two calls: 100 and 112, 157 and 158, 290 and 280, 577 and 530, 1140 and 1065 us; k = 4: 74 and 87, 112 and 112,
+// 190 and 186, 365 and 347, 716 and 697 us.  Given the tokens (k = 8), 4, 12, 32 million: 53 and 59, 96 and 86, 167 and
+// 126 us.
+constexpr int64_t kTwoCallSymbols = 1ll << 25, kTwoCallSymbolsCond = 1ll << 23;
+constexpr int64_t kPiecesPerRound = 512, kPiecesPerRoundCompact = 1024;
 // From this many streams on (more than two workgroups per compute unit) the decoder that reconstructs takes
 // its three-block ring where k <= 4 lets three workgroups share a compute unit.
 constexpr int64_t kComputeUnits = 256;  // MI355X
@@ -1450,27 +1459,24 @@ __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const
   }
 }
 
-// PIECES: a unit is a piece of a stream, and errors are left to the second launch.
-template <int W, bool ADAPT, bool PIECES = false>
-__global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
+// Many streams of one unit each: a wavefront, with tables of its own, per workgroup.
+template <bool ADAPT>
+__global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
   __shared__ uint32_t lut_one[ADAPT ? 1 : kCompactTable];
   extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
   uint32_t *lut = ADAPT ? lut_per_depth : lut_one;
-  __shared__ uint16_t table_of_group[ADAPT ? W : 1][2][kBatch];  // ADAPT: table offset of each group of a batch
-  __shared__ __attribute__((aligned(16))) uint16_t ring[W][kRingWords + kRingMirror];
-  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[W][kBatchSyms];
-  __shared__ uint32_t table_ok;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t stream = blockIdx.x / a.wgs_per_stream;
-  const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
-  if (!PIECES && a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
-  const bool live = chunk < (PIECES ? (int64_t)a.pieces : a.units_per_stream);
+  __shared__ uint16_t table_of_group[2][kBatch];  // ADAPT: table offset of each group of a batch
+  __shared__ __attribute__((aligned(16))) uint16_t ring[kRingWords + kRingMirror];
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[kBatchSyms];
+  const int lane = threadIdx.x;
+  const int64_t stream = blockIdx.x;
+  if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
   bool bad = false;
 
   // One slot table, or one per bit depth: that of a depth the stream does not use is all zero.  The index in the
   // place of a ring.
-  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0][0]);
-  static_assert(sizeof(ring[0]) >= sizeof(SlotIndex), "room for the index");
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0]);
+  static_assert(sizeof(ring) >= sizeof(SlotIndex), "room for the index");
   const int n_tables = ADAPT ? a.n_tables : 1;
   bool ok = true;
   for (int t = 0; t < n_tables; ++t) {
@@ -1479,57 +1485,29 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
     ok = ok && (total == kScale || (ADAPT && total == 0));
     uint32_t *lt = lut + t * kCompactTable;
     if (total == kScale) {  // uniform
-      if (wave == 0) {
-        build_slot_index(index, f, cum, lane);
+      build_slot_index(index, f, cum, lane);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          lt[lane * 4 + r] = ((f[r] - 1u) & 0xfffu) | (cum << 16);  // a symbol that does not occur is never looked up
-          cum += f[r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        lt[lane * 4 + r] = ((f[r] - 1u) & 0xfffu) | (cum << 16);  // a symbol that does not occur is never looked up
+        cum += f[r];
       }
-      __syncthreads();
-      for_each_slot<W * 64>(index, [&](uint32_t o, uint32_t row) {
+      wave_sync();
+      for_each_slot<64>(index, [&](uint32_t o, uint32_t row) {
         reinterpret_cast<uint8_t *>(lt + 256)[o] = (uint8_t)(row >> 24);
       });
     } else {
-      for (uint32_t o = threadIdx.x; o < kCompactTable; o += W * 64) lt[o] = 0u;
+      for (uint32_t o = threadIdx.x; o < kCompactTable; o += 64) lt[o] = 0u;
     }
-    if (ADAPT) __syncthreads();  // before the index serves the next table
+    wave_sync();  // before the index serves the next table, or the ring takes its place
   }
-  if (threadIdx.x == 0) table_ok = ok;
-  __syncthreads();
-  if (!table_ok) {  // not a table: nothing can be decoded
-    if (live && lane == 0) {
-      if (PIECES) {
-        report_piece(a, stream, (int32_t)chunk, 0, false);
-      } else {
-        raise(a.status, PLC_ERR_CORRUPT);
-      }
-    }
+  const uint64_t off = a.word_off[stream];
+  const uint32_t n = a.n_words_in[stream];
+  if (!ok || off > a.words_len || (uint64_t)n > a.words_len - off) {  // (not a table: nothing can be decoded)
+    if (lane == 0) raise(a.status, PLC_ERR_CORRUPT);
     return;
   }
-  if (!live) return;  // no workgroup barrier below
-
-  const int64_t unit = PIECES ? stream : stream * a.units_per_stream + chunk;
-  const uint64_t off = a.word_off[unit];
-  const uint32_t n = a.n_words_in[unit];
-  Piece piece;
-  const bool list_ok = !(off > a.words_len || (uint64_t)n > a.words_len - off) &&
-                       (!PIECES || load_piece(a, stream, (int32_t)chunk, n, &piece));
-  if (!list_ok) {
-    if (lane == 0) {
-      if (PIECES) {
-        report_piece(a, stream, (int32_t)chunk, 0, false);
-      } else {
-        raise(a.status, PLC_ERR_CORRUPT);
-      }
-    }
-    return;
-  }
-  const int64_t begin = PIECES ? (int64_t)piece.begin : chunk * a.unit_syms;
-  const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = PIECES ? piece.len : (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
-  uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
+  const uint32_t len = (uint32_t)a.syms_per_stream;
+  uint8_t *ubase = a.sym_out + stream * a.syms_per_stream;
   const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 15u) == 0;
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;
@@ -1538,9 +1516,8 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   const uint16_t *first_word = a.words_in + off;
   const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kBlockWords * 2 - 1)) >> 1);
   const uint16_t *aligned_base = first_word - lo;  // pointer arithmetic keeps the loads global, not flat
-  const int32_t hi = lo + (int32_t)(PIECES ? piece.words : n);
-  const int32_t stop = lo + (int32_t)(PIECES ? piece.words_left : 0u);  // where the pointer has to arrive
-  uint16_t *myring = ring[wave];
+  const int32_t hi = lo + (int32_t)n;
+  uint16_t *myring = ring;
 
   // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
   auto block_load = [&](int32_t blk, uint4 &v) -> bool {
@@ -1575,25 +1552,25 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   const int rl = lane & (kLanes - 1);
   const uint32_t below = (1u << rl) - 1u;
   const bool top_active = (uint32_t)rl < top_syms;
-  uint32_t x = (PIECES ? piece.states : a.states_in + unit * kLanes)[rl];
+  uint32_t x = a.states_in[stream * kLanes + rl];
 
   // Full batches of 16 groups are fully unrolled; the groups that do not fill a batch (and the last
   // group if it is ragged) form a tail that runs in a rolled loop.
   int32_t tail_groups = G % kBatch;
   if (tail_groups == 0 && top_syms < kLanes) tail_groups = kBatch;
   const int32_t g_tail = G - tail_groups;
-  uint8_t *sb = &sym_stage[wave][rl];
+  uint8_t *sb = &sym_stage[rl];
 
   // ADAPT: table offsets of the batch's 16 groups, fetched one batch ahead by lanes 0..15
   bool bad_depth = false;
   auto group_load = [&](int32_t g0) -> uint32_t {
     const int32_t g = g0 + lane;
     if (!ADAPT || lane >= kBatch || g >= G) return 0u;
-    return group_table(a, stream, begin, g, kCompactTable, &bad_depth);
+    return group_table(a, stream, 0, g, kCompactTable, &bad_depth);
   };
   if (ADAPT) {
     const uint32_t gt0 = group_load(0);
-    if (lane < kBatch) table_of_group[wave][0][lane] = (uint16_t)gt0;
+    if (lane < kBatch) table_of_group[0][lane] = (uint16_t)gt0;
     wave_sync();
   }
   int gbuf = 0;
@@ -1609,7 +1586,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
     bool ptake = false;
     if (fetch) ptake = block_load(blk, pre);
     const uint32_t ngt = group_load(g0 + kBatch);
-    const uint16_t *gt = table_of_group[ADAPT ? wave : 0][gbuf];
+    const uint16_t *gt = table_of_group[gbuf];
 
     const uint16_t *wtop0 = myring + ((uint32_t)(-ptr) & (kRingWords - 1));
     const uint16_t *wtop = wtop0;
@@ -1627,7 +1604,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
       for (int j = 0; j < kBatch; ++j) dec_step<false>(x, lut, wtop, sb + kLanes * j, below, true, off[j]);
     }
     if (ADAPT) {
-      if (lane < kBatch) table_of_group[wave][gbuf ^ 1][lane] = (uint16_t)ngt;
+      if (lane < kBatch) table_of_group[gbuf ^ 1][lane] = (uint16_t)ngt;
       gbuf ^= 1;
     }
     ptr -= (int32_t)(wtop - wtop0);
@@ -1650,22 +1627,330 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
       const uint32_t full = nsym / 16;
       if ((uint32_t)lane < full)
         *reinterpret_cast<uint4 *>(ubase + done + lane * 16) =
-            *reinterpret_cast<const uint4 *>(&sym_stage[wave][lane * 16]);
+            *reinterpret_cast<const uint4 *>(&sym_stage[lane * 16]);
       const uint32_t tail = full * 16 + (uint32_t)lane;
-      if (tail < nsym) ubase[done + tail] = sym_stage[wave][tail];
+      if (tail < nsym) ubase[done + tail] = sym_stage[tail];
     } else {
-      for (uint32_t i = lane; i < nsym; i += 64) ubase[done + i] = sym_stage[wave][i];
+      for (uint32_t i = lane; i < nsym; i += 64) ubase[done + i] = sym_stage[i];
+    }
+    wave_sync();
+  }
+  // integrity: every word consumed, every lane back at the initial state
+  if (ptr != lo || (coder && x != kLow)) bad = true;
+  if (bad) raise(a.status, PLC_ERR_CORRUPT);
+  if (bad_depth) raise(a.status, PLC_ERR_INVALID);
+}
+
+// ---------------------------------------------------------------------------
+// Decoder, many units of one stream: two units per wavefront
+// ---------------------------------------------------------------------------
+// With the chip full of units the decoder is bound by instruction issue, and half of every instruction's lanes above only
+// mirror the other half.  Here lanes 32-63 decode a unit of their own with the same instructions, the next of the
+// same stream, so that a workgroup's units share one slot table of whole entries (16 KB, one lookup a step) -- or,
+// with a table per bit depth, one split table per depth.  What is per half: the list of words and the place in it, a
+// lane's rank among its own half's renormalising lanes, and the ends of the units.  The words are staged as
+// above, in blocks of 256 for batches of eight steps, so that a unit needs 1.8 KB of LDS instead of 5.7 and a compute
+// unit holds 48 of them: what the wider wavefronts gain in issue they would lose again in latency with fewer.
+// The ring keeps the words in their order, word i at place i mod 512 behind a guard of one block that repeats the
+// upper; a lane's word is the rank-th below the pointer, counted through the lanes that do NOT take one.
+constexpr int kPairSteps = 8;
+constexpr int kPairBlock = kPairSteps * kLanes;  // words: the most a batch takes
+constexpr int kPairRing = 2 * kPairBlock;
+constexpr int kPairDrain = 2 * kPairBlock;       // symbols: two batches leave together, 16 bytes a lane
+static_assert(kTileSyms % kPairDrain == 0, "a tile's symbols leave in whole drains");
+
+// One step of both halves, all 64 lanes on.  `at`: a lane's word is `later` steps' worth of lanes above place at + the
+// number of lanes below it in its half that take none; at moves on by the half's number of them.  MASKED: lanes that
+// are not in `on` do nothing, and a frequency of 4096 (0 in its twelve bits; elsewhere such tables do not come here)
+// is minded.  ADAPT: `table` is the offset of the half's table.
+// The two halves take turns at ranking and moving on, each with its own 32 bits of the mask and the other's lanes
+// switched off; then the lanes that take a word shift it in, the others switched off.  (Between the compare and the
+// first reader of its mask there have to be two instructions.)
+template <bool ADAPT, bool MASKED>
+__device__ __forceinline__ void dec_pair_step(uint32_t &x, const uint32_t *lut, uint32_t table, uint32_t &at,
+                                              const uint16_t *ring, int later, uint8_t *sym_slot, uint64_t on) {
+  const uint32_t slot = x & (kScale - 1);
+  uint32_t s, f, r;  // symbol, frequency, slot - cum
+  if constexpr (ADAPT) {
+    const uint32_t *mine = lut + table;
+    s = reinterpret_cast<const uint8_t *>(mine + 256)[slot];
+    const uint32_t fc = mine[s];
+    f = fc & 0xfffu;
+    r = slot - (fc >> 16);
+  } else {
+    const uint32_t e = lut[slot];
+    s = e;
+    f = (e >> 8) & 0xfffu;
+    r = e >> 20;
+  }
+  if (MASKED) f = f ? f : kScale;
+  uint32_t xn = __umul24(f, x >> kScaleBits) + r;
+  uint64_t keep = __builtin_amdgcn_uicmp(xn, kLow, 35 /* unsigned >= */);
+  if (MASKED) keep |= ~on;
+  uint32_t place;
+  uint64_t all;
+  asm volatile(
+      "s_mov_b64 %2, exec\n\t"
+      "s_mov_b32 exec_hi, 0\n\t"
+      "v_mbcnt_lo_u32_b32 %0, %3, %1\n\t"
+      "v_bcnt_u32_b32 %1, %3, %1\n\t"
+      "s_mov_b64 exec, %2\n\t"
+      "s_mov_b32 exec_lo, 0\n\t"
+      "v_mbcnt_hi_u32_b32 %0, %4, %1\n\t"
+      "v_bcnt_u32_b32 %1, %4, %1\n\t"
+      "s_mov_b64 exec, %2"
+      : "=&v"(place), "+v"(at), "=&s"(all)
+      : "s"((uint32_t)keep), "s"((uint32_t)(keep >> 32)));
+  const uint32_t word = ring[place + (uint32_t)(kLanes * later)];  // (read by every lane: no branch around it)
+  const bool live = !MASKED || __builtin_amdgcn_inverse_ballot_w64(on);
+  if (live) *sym_slot = (uint8_t)s;
+  if (MASKED) {
+    x = !live ? x : __builtin_amdgcn_inverse_ballot_w64(keep) ? xn : (xn << 16) | word;
+  } else {
+    asm volatile(
+        "s_not_b64 exec, %2\n\t"
+        "v_lshl_or_b32 %0, %0, 16, %1\n\t"
+        "s_mov_b64 exec, -1"
+        : "+v"(xn)
+        : "v"(word), "s"(keep)
+        : "scc");
+    x = xn;
+  }
+}
+
+// PIECES: a unit is a piece of a stream, and errors are left to the second launch.
+template <int W, bool ADAPT, bool PIECES>
+__global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs a) {
+  __shared__ uint32_t lut_one[ADAPT ? 1 : kScale];
+  extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
+  uint32_t *lut = ADAPT ? lut_per_depth : lut_one;
+  __shared__ __attribute__((aligned(16))) uint16_t table_of_group[ADAPT ? W : 1][2][2][2 * kPairSteps];  // ADAPT: table offsets
+  __shared__ __attribute__((aligned(16))) uint16_t ring[W][2][kPairBlock + kPairRing];
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[W][2][kPairDrain];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, hl = lane & (kLanes - 1);
+  const int64_t stream = blockIdx.x / a.wgs_per_stream;
+  const int64_t chunk = ((int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave) * 2 + half;
+  const int64_t n_units = PIECES ? (int64_t)a.pieces : a.units_per_stream;
+  const bool live = chunk < n_units;
+  auto fail = [&]() {  // every lane of a half alike
+    if (!live || hl != 0) return;
+    if (PIECES) {
+      report_piece(a, stream, (int32_t)chunk, 0, false);
+    } else {
+      raise(a.status, PLC_ERR_CORRUPT);
+    }
+  };
+
+  // One slot table, or one per bit depth: that of a depth the stream does not use is all zero.  The index in the
+  // place of the rings.
+  constexpr int kThreads = W * 64;
+  static_assert(sizeof(ring[0]) >= sizeof(SlotIndex), "room for the index");
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0][0][0]);
+  const int n_tables = ADAPT ? a.n_tables : 1;
+  bool ok = true, wide = false;  // uniform; wide: a table of one symbol
+  for (int t = 0; t < n_tables; ++t) {
+    uint32_t f[4], cum;
+    const uint32_t total = load_freq4(a.freq + (stream * n_tables + t) * 256, lane, f, &cum);
+    ok = ok && (total == kScale || (ADAPT && total == 0));
+    wide = wide || __ballot((f[0] | f[1] | f[2] | f[3]) & kScale) != 0;
+    if (total == kScale && wave == 0) {
+      build_slot_index(index, f, cum, lane);
+      if constexpr (ADAPT) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // (a symbol that does not occur is never looked up)
+          lut[t * kCompactTable + lane * 4 + r] = (f[r] & 0xfffu) | (cum << 16);
+          cum += f[r];
+        }
+      }
+    }
+    __syncthreads();
+    if (total == kScale) {
+      for_each_slot<kThreads>(index, [&](uint32_t o, uint32_t row) {
+        if constexpr (ADAPT) {
+          reinterpret_cast<uint8_t *>(lut + t * kCompactTable + 256)[o] = (uint8_t)(row >> 24);
+        } else {
+          lut[o] = (row >> 24) | (((row + 1u) & 0xfffu) << 8) | ((o - ((row >> 12) & 0xfffu)) << 20);
+        }
+      });
+    } else {
+      constexpr uint32_t kWords = ADAPT ? kCompactTable : kScale;
+      for (uint32_t o = threadIdx.x; o < kWords; o += kThreads) lut[t * kWords + o] = 0u;
+    }
+    __syncthreads();  // before the index serves the next table, or the rings take its place
+  }
+  if (!ok) {  // not a table: nothing can be decoded
+    fail();
+    return;
+  }
+
+  // ---- the half's unit; one that does not exist, or whose list is none, is empty
+  const int64_t my_chunk = live ? chunk : 0;
+  const int64_t unit = PIECES ? stream : stream * a.units_per_stream + my_chunk;
+  const uint64_t off = a.word_off[unit];
+  const uint32_t n = a.n_words_in[unit];
+  Piece piece;
+  bool list_ok = !(off > a.words_len || (uint64_t)n > a.words_len - off);
+  if (PIECES) list_ok = load_piece(a, stream, (int32_t)my_chunk, n, &piece) && list_ok;
+  if (!list_ok) fail();
+  const bool runs = live && list_ok;
+  const int64_t begin = PIECES ? (int64_t)piece.begin : my_chunk * a.unit_syms;
+  const int64_t rest = a.syms_per_stream - begin;
+  const uint32_t len = !runs ? 0u : PIECES ? piece.len : (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
+  const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 15u) == 0;
+
+  // ---- word list geometry, relative to a 512-byte-aligned address at or below the unit's first word
+  const uint16_t *first_word = a.words_in + (list_ok ? off : 0);
+  const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kPairBlock * 2 - 1)) >> 1);
+  const uint16_t *aligned_base = first_word - lo;  // pointer arithmetic keeps the loads global, not flat
+  const int32_t hi = lo + (runs ? (int32_t)(PIECES ? piece.words : n) : 0);
+  const int32_t stop = lo + (PIECES && runs ? (int32_t)piece.words_left : 0);  // where the pointer has to arrive
+  uint16_t *const myring = ring[wave][half];
+
+  // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
+  auto block_load = [&](int32_t blk, uint4 &v) -> bool {
+    const int32_t first = blk * kPairBlock + hl * 8;
+    const bool take = blk >= 0 && hi > lo && first + 8 > lo && first < hi;
+    if (take) v = *reinterpret_cast<const uint4 *>(aligned_base + first);
+    return take;
+  };
+  auto block_store = [&](int32_t blk, bool take, const uint4 &v) {
+    if (take) {
+      *reinterpret_cast<uint4 *>(myring + kPairBlock + (blk & 1) * kPairBlock + hl * 8) = v;
+      if (blk & 1) *reinterpret_cast<uint4 *>(myring + hl * 8) = v;
+    }
+  };
+
+  int32_t ptr = hi;
+  // A batch takes its words from the pointer's block, `top`, and the one below.  The one below that is on its way, in
+  // registers until the pointer has left the block whose place it takes.
+  static_assert(kPairBlock == 256, "blocks by shifts");
+  int32_t top = (hi - 1) >> 8;
+  uint4 coming;
+  bool coming_take;
+  {
+    uint4 v0, v1;
+    const bool t0 = block_load(top, v0), t1 = block_load(top - 1, v1);
+    coming_take = block_load(top - 2, coming);
+    block_store(top, t0, v0);
+    block_store(top - 1, t1, v1);
+  }
+  uint32_t x = runs ? (PIECES ? piece.states : a.states_in + unit * kLanes)[hl] : kLow;
+  bool bad = false;
+
+  // Batches whose eight groups are whole in both halves run without a mask.
+  const int32_t G = (int32_t)((len + kLanes - 1) / kLanes), whole = wide ? 0 : (int32_t)(len / kLanes);
+  const int32_t G0 = __builtin_amdgcn_readlane(G, 0), G1 = __builtin_amdgcn_readlane(G, 32);
+  const int32_t whole0 = __builtin_amdgcn_readlane(whole, 0), whole1 = __builtin_amdgcn_readlane(whole, 32);
+  const int32_t n_groups = G0 > G1 ? G0 : G1, n_whole = whole0 < whole1 ? whole0 : whole1;
+  uint8_t *const my_stage = sym_stage[wave][half];
+  const uint16_t *const rings = &ring[0][0][0];
+  const uint32_t my_place = (uint32_t)((wave * 2 + half) * (kPairBlock + kPairRing) + kPairBlock - hl - kLanes * (kPairSteps - 1));
+
+  // ADAPT: table offsets of the next two batches' groups, fetched two batches ahead by the first lanes of a half
+  constexpr int kAhead = 2 * kPairSteps;
+  bool bad_depth = false;
+  auto group_load = [&](int32_t g0) -> uint32_t {
+    const int32_t g = g0 + hl;
+    if (!ADAPT || hl >= kAhead || g >= G) return 0u;
+    return group_table(a, stream, begin, g, kCompactTable, &bad_depth);
+  };
+  if (ADAPT) {
+    const uint32_t gt0 = group_load(0);
+    if (hl < kAhead) table_of_group[wave][0][half][hl] = (uint16_t)gt0;
+  }
+  wave_sync();
+  int gbuf = 0;
+
+  // Escapes of each tile: a unit's symbols leave 512 at a time, each 512 of one tile.
+  uint32_t *const tile_cnt =
+      a.tile_cnt + stream * ((a.syms_per_stream + kTileSyms - 1) / kTileSyms) + begin / kTileSyms;  // (if a.tile_cnt)
+  uint32_t esc_mine = 0;  // this lane's, of the tile so far
+
+  for (int32_t g0 = 0; g0 < n_groups; g0 += 2 * kPairSteps) {
+    const uint32_t ngt = group_load(g0 + 2 * kPairSteps);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int32_t gb = g0 + b * kPairSteps;
+      uint32_t tables[kPairSteps];
+      if constexpr (ADAPT) {
+        const uint4 tv = *reinterpret_cast<const uint4 *>(&table_of_group[wave][gbuf][half][b * kPairSteps]);
+        const uint32_t t4[4] = {tv.x, tv.y, tv.z, tv.w};
+#pragma unroll
+        for (int j = 0; j < kPairSteps; ++j) tables[j] = (t4[j / 2] >> (16 * (j & 1))) & 0xffffu;
+      }
+      const uint32_t at0 = my_place + ((uint32_t)(ptr - 1) & (kPairRing - 1));
+      uint32_t at = at0;
+      uint8_t *const sb = my_stage + b * kPairBlock + hl;
+      if (gb + kPairSteps <= n_whole) {  // uniform
+#pragma unroll
+        for (int j = 0; j < kPairSteps; ++j)
+          dec_pair_step<ADAPT, false>(x, lut, ADAPT ? tables[j] : 0u, at, rings, kPairSteps - 1 - j, sb + kLanes * j, 0);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kPairSteps; ++j) {
+          const uint64_t on = __ballot((uint32_t)(gb + j) * kLanes + (uint32_t)hl < len);
+          dec_pair_step<ADAPT, true>(x, lut, ADAPT ? tables[j] : 0u, at, rings, kPairSteps - 1 - j, sb + kLanes * j, on);
+        }
+      }
+      ptr -= kPairBlock - (int32_t)(at - at0);
+      if (ptr < lo) {  // ran out of words: the stream is damaged
+        bad = true;
+        ptr = lo;
+      }
+      if ((ptr - 1) >> 8 != top) {  // (a batch takes a block's words at the most)
+        --top;
+        block_store(top - 1, coming_take, coming);
+        coming_take = block_load(top - 2, coming);
+      }
+      wave_sync();
+    }
+    if (ADAPT) {
+      if (hl < kAhead) table_of_group[wave][gbuf ^ 1][half][hl] = (uint16_t)ngt;
+      gbuf ^= 1;
+    }
+    // the symbols of both batches
+    const uint32_t done = (uint32_t)g0 * kLanes, mine = (uint32_t)hl * 16;
+    const uint32_t left = len > done ? len - done : 0u;
+    if (out_aligned && mine + 16 <= left) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(&my_stage[mine]);
+      *reinterpret_cast<uint4 *>(ubase + done + mine) = v;
+      if (a.tile_cnt) {  // uniform
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)  // a byte is 0xff iff its low seven bits carry into bit 7 and bit 7 is set
+          esc_mine += (uint32_t)__builtin_popcount(((w[i] & 0x7f7f7f7fu) + 0x01010101u) & w[i] & 0x80808080u);
+      }
+    } else {
+      for (uint32_t i = mine; i < mine + 16 && i < left; ++i) {
+        ubase[done + i] = my_stage[i];
+        esc_mine += my_stage[i] == PLC_ESCAPE;
+      }
+    }
+    // the tile is through, or the units are (uniform)
+    if (a.tile_cnt && ((done + kPairDrain) % kTileSyms == 0 || g0 + 2 * kPairSteps >= n_groups)) {
+      uint32_t sum = esc_mine;
+      esc_mine = 0;
+#pragma unroll
+      for (int d = 1; d < kLanes; d <<= 1) sum += __shfl_xor(sum, d, 64);
+      if (hl == 0 && done / kTileSyms * kTileSyms < len) tile_cnt[done / kTileSyms] = sum;
     }
     wave_sync();
   }
   // integrity: every word consumed, every lane back at the initial state (a piece: at what the record behind it says)
-  const uint32_t x_end = PIECES && piece.end_states ? piece.end_states[rl] : kLow;
-  if (ptr != stop || (coder && x != x_end)) bad = true;
-  if (PIECES) {
-    const bool good = __ballot(bad) == 0;
-    if (lane < 2) report_piece(a, stream, (int32_t)chunk, lane, good);
-  } else if (bad) {
-    raise(a.status, PLC_ERR_CORRUPT);
+  if (runs) {
+    const uint32_t x_end = PIECES && piece.end_states ? piece.end_states[hl] : kLow;
+    if (ptr != stop || x != x_end) bad = true;
+  }
+  const uint64_t bads = __ballot(bad);
+  if (runs) {
+    const bool good = (uint32_t)(half ? bads >> 32 : bads) == 0;
+    if (PIECES) {
+      if (hl < 2) report_piece(a, stream, (int32_t)chunk, hl, good);
+    } else if (!good && hl == 0) {
+      raise(a.status, PLC_ERR_CORRUPT);
+    }
   }
   if (bad_depth) raise(a.status, PLC_ERR_INVALID);
 }
@@ -2787,7 +3072,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   }
 }
 
-int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, RansArgs *a, int *waves) {
+int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, RansArgs *a, int *waves = nullptr) {
   if (n_streams < 1 || syms_per_stream < 1) return PLC_ERR_INVALID;
   if (syms_per_stream >= (1ll << 31) - 1024) return PLC_ERR_INVALID;
   if (chunk_syms < 0 || chunk_syms % kLanes) return PLC_ERR_INVALID;
@@ -2797,7 +3082,7 @@ int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
   a->syms_per_stream = syms_per_stream;
   int w = 1;
   while (w < kMaxWaves && 2 * w <= a->units_per_stream) w *= 2;
-  *waves = w;
+  if (waves) *waves = w;
   const int64_t wgs = (a->units_per_stream + w - 1) / w;
   if (wgs >= (1ll << 31) || n_streams * wgs >= (1ll << 31)) return PLC_ERR_INVALID;
   a->wgs_per_stream = (uint32_t)wgs;
@@ -2821,6 +3106,7 @@ int check_restart(const plc_restart *r, bool decode, RansArgs *a) {
   const int32_t per = (rounds + r->per_stream - 1) / r->per_stream;
   a->point_stride = r->per_stream;
   a->piece_batches = 4 * per;
+  a->point_step = 1;
   if (decode) {
     a->points_in = r->points;
     a->piece_state = r->scratch;
@@ -2830,6 +3116,15 @@ int check_restart(const plc_restart *r, bool decode, RansArgs *a) {
     a->points_out = r->points;
   }
   return PLC_OK;
+}
+// Pieces of several records each, so that there are about `most` of them.
+void merge_pieces(RansArgs *a, int64_t n_streams, int64_t most) {
+  const int64_t per_stream = most / n_streams < 1 ? 1 : most / n_streams;
+  if (a->pieces <= per_stream) return;
+  a->point_step = (int32_t)((a->pieces + per_stream - 1) / per_stream);
+  a->piece_batches *= a->point_step;
+  a->pieces = (a->pieces + a->point_step - 1) / a->point_step;
+  if (a->pieces < 2) a->pieces = 0;
 }
 // The arguments of the launch behind the pieces', which decodes the streams whose pieces do not agree.
 RansArgs again_args(RansArgs a) {
@@ -2860,40 +3155,51 @@ struct LaunchEncode {
   }
 };
 template <int W>
-struct LaunchDecode {
+struct LaunchDecodePairs {  // workgroups of 2 W units of one stream
   static void run(const RansArgs &a, unsigned grid, hipStream_t st) {
-    // One unit per stream and few enough units (kChainMaxUnits): time is the length of one unit's chain,
-    // so take the variant with the shortest step.  With more units its 60 KB of LDS per workgroup would
-    // cost more in occupancy than the shorter step gains.
-    if (a.pieces) {  // (see decode_impl)
-      if (a.bits) {
-        const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, true>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((rans_decode_kernel<W, true, true>), dim3(grid), dim3(W * 64), lds, st, a);
-      } else {
-        hipLaunchKernelGGL((rans_decode_kernel<W, false, true>), dim3(grid), dim3(W * 64), 0, st, a);
-      }
-    } else if (a.bits && W == 1 && a.n_units <= kDepthsMaxUnits) {
-      const size_t lds = depths_lds_bytes(a.n_tables);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<0>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL(rans_decode_depths_kernel<0>, dim3(grid), dim3(depths_threads(0)), lds, st, a);
-    } else if (a.bits) {
-      // (the split tables here too: 5 KB per depth instead of 16 lets three times the wavefronts in)
+    if (a.bits) {
       const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL((rans_decode_kernel<W, true>), dim3(grid), dim3(W * 64), lds, st, a);
-    } else if (W == 1 && a.n_units <= kChainMaxUnits) {
-      hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3(grid), dim3(128), 0, st, a);
+      const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, true, true> : &rans_decode_pair_kernel<W, true, false>;
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), lds, st, a);
     } else {
-      // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in
-      // (twice as many where every one-wavefront workgroup has a table of its own).
-      hipLaunchKernelGGL((rans_decode_kernel<W, false>), dim3(grid), dim3(W * 64), 0, st, a);
+      const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, false, true> : &rans_decode_pair_kernel<W, false, false>;
+      hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), 0, st, a);
     }
   }
 };
+// Two or more units per stream, or pieces.
+void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
+  const int64_t units = a.pieces ? a.pieces : a.units_per_stream;
+  int w = 1;
+  while (w < kMaxWaves && 4 * w <= units) w *= 2;
+  a.wgs_per_stream = (uint32_t)((units + 2 * w - 1) / (2 * w));
+  dispatch_waves<LaunchDecodePairs>(w, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+}
+// One unit per stream.
+void launch_decode_streams(const RansArgs &a, hipStream_t st) {
+  const dim3 grid((unsigned)a.n_units);
+  // Few enough units (kChainMaxUnits): time is the length of one unit's chain, so take the variant with the shortest
+  // step.  With more units its 60 KB of LDS per workgroup would cost more in occupancy than the shorter step gains.
+  if (a.bits && a.n_units <= kDepthsMaxUnits) {
+    const size_t lds = depths_lds_bytes(a.n_tables);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<0>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(rans_decode_depths_kernel<0>, grid, dim3(depths_threads(0)), lds, st, a);
+  } else if (a.bits) {
+    // (the split tables here too: 5 KB per depth instead of 16 lets three times the wavefronts in)
+    const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(rans_decode_kernel<true>, grid, dim3(64), lds, st, a);
+  } else if (a.n_units <= kChainMaxUnits) {
+    hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), grid, dim3(128), 0, st, a);
+  } else {
+    // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in (twice as many
+    // where every one-wavefront workgroup has a table of its own).
+    hipLaunchKernelGGL(rans_decode_kernel<false>, grid, dim3(64), 0, st, a);
+  }
+}
 
 }  // namespace
 }  // namespace plc
@@ -2982,9 +3288,8 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
 int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                 const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams, int64_t syms_per_stream,
                 int32_t chunk_syms, uint8_t *symbols, uint32_t *status, void *stream, RansArgs a,
-                const plc_restart *restart = nullptr) {
-  int waves = 1;
-  int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a, &waves);
+                const plc_restart *restart = nullptr, uint32_t *tile_cnt = nullptr, TileCounts *counts = nullptr) {
+  int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a);
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
@@ -3001,31 +3306,43 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
   hipStream_t st = static_cast<hipStream_t>(stream);
   {
     TraceScope trace(PLC_TRACE_RANS_DECODE, st);
-    if (a.pieces) {
-      if (!a.bits && n_streams * a.pieces <= kChainMaxPieces) {
-        a.wgs_per_stream = (uint32_t)a.pieces;
-        hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3((unsigned)(n_streams * a.pieces)), dim3(128), 0, st, a);
-      } else {
-        while (waves < kMaxWaves && 2 * waves <= a.pieces) waves *= 2;
-        a.wgs_per_stream = (uint32_t)((a.pieces + waves - 1) / waves);
-        dispatch_waves<LaunchDecode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+    if (a.pieces && !a.bits && n_streams * a.pieces <= kChainMaxPieces) {
+      a.wgs_per_stream = (uint32_t)a.pieces;
+      hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3((unsigned)(n_streams * a.pieces)), dim3(128), 0, st, a);
+    } else if (a.pieces || a.units_per_stream > 1) {
+      // (pieces begin at whole tiles if the stream is whole tiles: the encoder's rounds are as long as a tile)
+      if (tile_cnt && (a.pieces ? syms_per_stream : a.unit_syms) % kTileSyms == 0) {
+        a.tile_cnt = tile_cnt;
+        *counts = TileCounts{true, a.pieces ? a.piece_state : nullptr, a.pieces};
       }
-      a = again_args(a);
-      waves = 1;
+      launch_decode_pairs(a, n_streams, st);
     }
-    dispatch_waves<LaunchDecode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+    if (a.pieces) a = again_args(a);
+    if (a.units_per_stream == 1) launch_decode_streams(a, st);
   }
   return launch_status();
 }
 
 }  // namespace
 
+int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
+                         const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
+                         int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos,
+                         int32_t streams_per_session, const uint8_t *bits, int32_t n_tables,
+                         const plc_restart *restart, uint8_t *symbols, uint32_t *tile_cnt, TileCounts *counts,
+                         uint32_t *status, void *stream) {
+  *counts = TileCounts{};
+  RansArgs a = {};
+  if (bits) {
+    const int rc = check_depths(syms_per_stream, chunk_syms, syms_per_pos, streams_per_session, bits, n_tables, &a);
+    if (rc) return rc;
+  }
+  return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
+                     symbols, status, stream, a, restart, tile_cnt, counts);
+}
+
 bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart) {
-  // In pieces the many-unit decoder fills the chip, and the one kernel pays only where the reconstruction keeps the
-  // memory busy for longer than it takes, or four workgroups share a compute unit (256 streams of 1,048,576 symbols, k =
-  // 8, 16 pieces: given the tokens the two calls take 0.68 ms, with a table per depth 0.75; the one kernel on whole
-  // streams 1.50 and 2.07).
-  if (restart && (per_depth || (cond && k > 4))) return false;
+  if (restart && (per_depth || n_streams * syms_per_stream >= (cond ? kTwoCallSymbolsCond : kTwoCallSymbols))) return false;
   // Candidates that fit the registers of one wavefront kRecDepth batches deep, and whole chunks.  As to
   // the number of streams: two or three workgroups per compute unit run at a time, and a round takes its
   // chain's time or the HBM time of its reconstruction, whichever is longer.  With the weighted mean the two
@@ -3036,6 +3353,7 @@ bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, b
   // 7.9 ms); with more candidates (two workgroups) the many-unit decoder's shorter total wins from some eight
   // rounds on (16,384 streams, k = 8: 28.4 against 22.5 ms): 2048 streams at most.  With one table per depth a
   // round is 256 workgroups, and the bound of that decoder applies.
+  // (Streams in pieces have a line of their own: kTwoCallSymbols.)
   const int64_t most = per_depth ? kDepthsMaxUnits : (cond && k > 4) ? 2048 : INT64_MAX;
   return n_streams >= 1 && n_streams <= most && k >= 1 && k <= 8 && syms_per_stream >= kChunk &&
          syms_per_stream % kChunk == 0;
@@ -3046,8 +3364,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
                       const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch) {
   RansArgs a = {};
-  int waves = 1;
-  int rc = check_common(n_streams, syms_per_stream, 0, &a, &waves);
+  int rc = check_common(n_streams, syms_per_stream, 0, &a);
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr,
@@ -3077,38 +3394,39 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
     TraceScope trace(PLC_TRACE_RANS_DECODE, st);
     const dim3 block(192);
     const size_t lds = depths_lds_bytes(a.n_tables);
+    merge_pieces(&a, n_streams, recon.k <= kCompactMaxK ? kPiecesPerRoundCompact : kPiecesPerRound);
     // With pieces: those, then a launch over the streams, in which one whose pieces agree is left alone.
     for (int round = a.pieces ? 0 : 1; round < 2; ++round) {
-    const int64_t n_units = a.pieces ? n_streams * a.pieces : n_streams;
-    const dim3 grid((unsigned)n_units);
-    if (a.pieces) a.wgs_per_stream = (uint32_t)a.pieces;
-    switch (recon.k) {
+      const int64_t n_units = a.pieces ? n_streams * a.pieces : n_streams;
+      const dim3 grid((unsigned)n_units);
+      if (a.pieces) a.wgs_per_stream = (uint32_t)a.pieces;
+      switch (recon.k) {
 #define PLC_CASE(K)                                                                              \
-  case K:                                                                                        \
-    if (recon.bits) {                                                                            \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<K>),   \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);           \
-      hipLaunchKernelGGL(rans_decode_depths_kernel<K>, grid, dim3(depths_threads(K)), lds, st, a); \
-    } else if (K <= kCompactMaxK && n_units > kDenseStreams) {                                   \
-      const size_t lds1 = depths_lds_bytes(1);                                                \
-      if (recon.chosen) {                                                                        \
-        hipLaunchKernelGGL((rans_decode_depths_kernel<(K <= kCompactMaxK ? K : 1), 2>), grid, block, lds1, st, a); \
-      } else {                                                                                   \
-        hipLaunchKernelGGL((rans_decode_depths_kernel<(K <= kCompactMaxK ? K : 1), 1>), grid, block, lds1, st, a); \
-      }                                                                                          \
-    } else if (recon.chosen) {                                                                   \
-      hipLaunchKernelGGL((rans_decode_chain_kernel<K, true>), grid, block, 0, st, a);            \
-    } else if (K <= kDenseMaxK && n_units > kDenseStreams) {                                     \
-      hipLaunchKernelGGL((rans_decode_chain_kernel<(K <= kDenseMaxK ? K : 1), false, 3>), grid, block, 0, st, a); \
-    } else {                                                                                     \
-      hipLaunchKernelGGL((rans_decode_chain_kernel<K, false>), grid, block, 0, st, a);           \
-    }                                                                                            \
-    break;
-      PLC_CASE(1) PLC_CASE(2) PLC_CASE(3) PLC_CASE(4) PLC_CASE(5) PLC_CASE(6) PLC_CASE(7) PLC_CASE(8)
+    case K:                                                                                        \
+      if (recon.bits) {                                                                            \
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<K>),   \
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);           \
+        hipLaunchKernelGGL(rans_decode_depths_kernel<K>, grid, dim3(depths_threads(K)), lds, st, a); \
+      } else if (K <= kCompactMaxK && n_units > kDenseStreams) {                                   \
+        const size_t lds1 = depths_lds_bytes(1);                                                \
+        if (recon.chosen) {                                                                        \
+          hipLaunchKernelGGL((rans_decode_depths_kernel<(K <= kCompactMaxK ? K : 1), 2>), grid, block, lds1, st, a); \
+        } else {                                                                                   \
+          hipLaunchKernelGGL((rans_decode_depths_kernel<(K <= kCompactMaxK ? K : 1), 1>), grid, block, lds1, st, a); \
+        }                                                                                          \
+      } else if (recon.chosen) {                                                                   \
+        hipLaunchKernelGGL((rans_decode_chain_kernel<K, true>), grid, block, 0, st, a);            \
+      } else if (K <= kDenseMaxK && n_units > kDenseStreams) {                                     \
+        hipLaunchKernelGGL((rans_decode_chain_kernel<(K <= kDenseMaxK ? K : 1), false, 3>), grid, block, 0, st, a); \
+      } else {                                                                                     \
+        hipLaunchKernelGGL((rans_decode_chain_kernel<K, false>), grid, block, 0, st, a);           \
+      }                                                                                            \
+      break;
+        PLC_CASE(1) PLC_CASE(2) PLC_CASE(3) PLC_CASE(4) PLC_CASE(5) PLC_CASE(6) PLC_CASE(7) PLC_CASE(8)
 #undef PLC_CASE
-      default: return PLC_ERR_INVALID;
-    }
-    if (a.pieces) a = again_args(a);
+        default: return PLC_ERR_INVALID;
+      }
+      if (a.pieces) a = again_args(a);
     }
   }
   return launch_status();

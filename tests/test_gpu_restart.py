@@ -33,7 +33,13 @@ CASES = {
     "k6_dense": ("mean", dict(L=8, H=16, n=200, k=6, d=128, sigma=0.5), "lhnkd", 12),
     # two calls: more candidates than the one-kernel decode takes
     "k20": ("mean", dict(L=2, H=2, n=257, k=20, d=64, sigma=0.8), "lhnkd", 6),
-    "k20_many": ("mean", dict(L=8, H=16, n=130, k=20, d=64), "lhnkd", 8),
+    # more than 1024 pieces: the decoder with two units per wavefront, which counts the tiles' escapes where pieces are
+    # whole tiles, and where they are not leaves that to a pass of its own
+    "k20_tiles": ("mean", dict(L=8, H=16, n=256, k=20, d=64, sigma=0.8), "lhnkd", 16),
+    "k20_no_tiles": ("mean", dict(L=8, H=16, n=257, k=20, d=64, sigma=0.8), "lhnkd", 16),
+    # so many symbols that two calls are made
+    "k2_two_calls": ("mean", dict(L=8, H=16, n=1024, k=2, d=128, sigma=0.5), "lhnkd", 11),
+    "cond_k5_two_calls": ("cond", dict(L=8, H=16, n=256, k=5, d=128, sigma=0.4), "lhnkd", 32),
     "cond_k4": ("cond", dict(L=2, H=2, n=300, k=4, d=128, sigma=0.4), "lhnkd", 4),
     "cond_k8": ("cond", dict(L=2, H=2, n=300, k=8, d=80, sigma=0.4), "lnkhd", 7),
     "adapt": ("adapt", dict(L=2, H=2, n=400, k=8, d=64), "lhnkd", 5),
@@ -103,9 +109,19 @@ def _geometry(codec):
     return G, [G - head - (4 * per * r - 1) * 16 for r in range(1, -(-rounds // per))]
 
 
-def _pieces_good(codec):
+def _step(codec, case):
+    """Records per piece: the one-kernel decode takes a round of workgroups' worth of pieces."""
+    path, overrides, _, _ = CASES[case]
+    symbols = codec.n_streams * codec.N
+    if path == "adapt" or overrides["k"] > 8 or symbols >= (1 << 25 if path == "mean" else 1 << 23):
+        return 1
+    most = (1024 if overrides["k"] <= 4 else 512) // codec.n_streams
+    return -(-(len(_geometry(codec)[1]) + 1) // most)
+
+
+def _pieces_good(codec, case):
     """Streams all of whose pieces were found to fit together, from the decoder's scratch."""
-    pieces = len(_geometry(codec)[1]) + 1
+    pieces = -(-(len(_geometry(codec)[1]) + 1) // _step(codec, case))
     assert pieces >= 2
     s = codec._restart_scratch.reshape(-1)
     assert bool((s[codec.n_streams * pieces * 2:] == -1).all())
@@ -120,7 +136,7 @@ def test_pieces_equal_the_whole_stream(dev, case):
     whole = decode(False)
     assert whole[3] == 0 and torch.equal(whole[0], codec.symbols)
     assert _same(decode(True), whole)
-    assert bool(_pieces_good(codec).all())
+    assert bool(_pieces_good(codec, case).all())
     # the encoder writes the same bitstream without records
     keep, codec.restart = codec.restart, None
     encode()
@@ -142,21 +158,22 @@ def test_records_that_are_not_true_change_nothing(dev, case):
         codec.restart.copy_(true)
         codec.restart[last, record, word] = change(codec.restart[last, record, word])
 
-    for record in (1, len(_geometry(codec)[1])):
+    step = _step(codec, case)
+    for record in (step, len(_geometry(codec)[1]) // step * step):
         for word, change in ((0, lambda v: v ^ 1), (31, lambda v: v ^ (1 << 17)), (32, lambda v: v + 1),
                              (32, lambda v: v - 300), (32, lambda v: v * 0 - 1), (33, lambda v: v + 1)):
-            if word == 33 and CASES[case][0] != "mean" or word == 33 and CASES[case][1]["k"] > 8:
+            if word == 33 and ("two_calls" in case or CASES[case][0] != "mean" or CASES[case][1]["k"] > 8):
                 continue  # (two calls: the escapes are counted again, the record's are not looked at)
             wrong(record, word, change)
             assert _same(decode(True), whole), (record, word)
-            good = _pieces_good(codec)
+            good = _pieces_good(codec, case)
             assert not bool(good[last]) and bool(good[:last].all())
     for points in (torch.zeros_like(true), torch.full_like(true, -1), true.roll(1, 0), true.roll(1, 1)):
         codec.restart.copy_(points)
         assert _same(decode(True), whole)
 
 
-@pytest.mark.parametrize("case", ["k8", "k5_d24", "k4_dense", "k20", "cond_k8", "adapt"])
+@pytest.mark.parametrize("case", ["k8", "k5_d24", "k4_dense", "k20", "k20_tiles", "k20_no_tiles", "cond_k8", "adapt"])
 def test_damaged_words_are_reported(dev, case):
     """What the decoder reports of damage does not depend on the records, nor do the streams that have none."""
     codec, encode, decode = _setup(dev, case)
@@ -167,7 +184,7 @@ def test_damaged_words_are_reported(dev, case):
     assert whole[3] == pieces[3] == 3
     for a, b in zip(whole[:1], pieces[:1]):
         assert torch.equal(a, b)
-    good = _pieces_good(codec)
+    good = _pieces_good(codec, case)
     assert not bool(good[0]) and bool(good[1:].all())
 
 
