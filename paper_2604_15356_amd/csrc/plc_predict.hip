@@ -144,10 +144,16 @@ __device__ __forceinline__ void predict_chunk(const CodecArgs &a, const Coord &q
 // ---------------------------------------------------------------------------
 // w[s,i,j] = p[s,i,j] / sum_m p[s,i,m]   (one thread per probability row)
 // ---------------------------------------------------------------------------
+// The workgroups behind those of the rows clear n_zero counters, where statistics follow.
 __global__ __launch_bounds__(kBlock) void weights_kernel(const float *__restrict__ probs, float *__restrict__ w,
-                                                         int64_t rows, int k, uint32_t *status) {
+                                                         int64_t rows, int k, uint32_t *status,
+                                                         uint32_t *__restrict__ zero, int64_t n_zero) {
   const int64_t row = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (row >= rows) return;
+  if (row >= rows) {
+    const int64_t i = row - (rows + kBlock - 1) / kBlock * kBlock;
+    if (i >= 0 && i < n_zero) zero[i] = 0u;
+    return;
+  }
   const float *p = probs + row * k;
   float Z = 0.0f;
   bool bad = false;
@@ -299,11 +305,6 @@ __global__ __launch_bounds__(kBlock) void predict_residual_hist_kernel(const Cod
   const uint32_t v = hist[0][threadIdx.x] + hist[1][threadIdx.x] + hist[2][threadIdx.x] + hist[3][threadIdx.x];
   if (v) atomicAdd(&counts[(int64_t)stream * 256 + threadIdx.x], v);
   static_assert(kBlock == 256, "one thread per bin");
-}
-
-__global__ __launch_bounds__(kBlock) void zero_counts_kernel(uint32_t *__restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) p[i] = 0u;
 }
 
 // Token-conditional encode.  A position whose token is a candidate reads 2 bytes per component of that
@@ -560,9 +561,13 @@ __global__ __launch_bounds__(kBlock) void gather_escapes_kernel(const CodecArgs 
 // `per_wave` tiles in a row, a lane looks up the count and the destination of one of them, and the wavefront then
 // copies the rows, eight tiles' loads on their way at a time (a row holds at most two wavefronts' worth).  A tile
 // that overflowed its row is gathered again from the symbols.
+// esc_cnt: with few streams (kScanStreamsHere) the wavefronts also add the streams' counts up themselves and write esc_off;
+// null: it is in place.
+constexpr int64_t kScanStreamsHere = 1024;
+
 __global__ __launch_bounds__(kBlock) void compact_escapes_kernel(const CodecArgs a, uint16_t *__restrict__ esc_vals,
-                                                                 uint64_t esc_cap,
-                                                                 const uint64_t *__restrict__ esc_off,
+                                                                 uint64_t esc_cap, uint64_t *__restrict__ esc_off,
+                                                                 const uint32_t *__restrict__ esc_cnt,
                                                                  int64_t n_tiles, int32_t per_wave) {
   static_assert(kEscStage == 128, "two passes of a wavefront over a staging row");
   constexpr int kAtOnce = 8;
@@ -572,7 +577,21 @@ __global__ __launch_bounds__(kBlock) void compact_escapes_kernel(const CodecArgs
   const int64_t t = t0 + lane;
   uint32_t cnt = 0, stream = 0;
   uint64_t dst = 0;
-  if (lane < per_wave && t < n_tiles) {
+  if (esc_cnt) {  // uniform
+    const uint32_t first = (uint32_t)(t0 / a.tiles_per_stream);  // the streams in front of the wavefront's first
+    uint64_t before = 0;
+    for (uint32_t s = (uint32_t)lane; s < first; s += 64) before += esc_cnt[s];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    if (lane < per_wave && t < n_tiles) {
+      cnt = a.tile_cnt[t];
+      stream = (uint32_t)(t / a.tiles_per_stream);
+      for (uint32_t s = first; s < stream; ++s) before += esc_cnt[s];  // one or two, at most the wavefront's tiles
+      dst = before + a.tile_off[t];
+      if (t == (int64_t)stream * a.tiles_per_stream) esc_off[stream] = before;
+      if (t == n_tiles - 1 && before + esc_cnt[stream] > esc_cap) raise(a.status, PLC_ERR_CAPACITY);
+    }
+  } else if (lane < per_wave && t < n_tiles) {
     cnt = a.tile_cnt[t];
     if (cnt) {
       stream = (uint32_t)(t / a.tiles_per_stream);
@@ -868,23 +887,24 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   float *weights = const_cast<float *>(a.weights);
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
 
-  hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
-                     weights, p.rows, dims->k, status);
-  if (counts)
-    hipLaunchKernelGGL(zero_counts_kernel, dim3((unsigned)((p.n_streams * 256 + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                       st, counts, p.n_streams * 256);
+  const int64_t n_zero = counts ? p.n_streams * 256 : 0;
+  hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock + n_zero / kBlock)), dim3(kBlock), 0,
+                     st, probs, weights, p.rows, dims->k, status, counts, n_zero);
   {
     TraceScope trace(trace_id, st);
     dispatch_k<LaunchPredict>(dims->k, a, (unsigned)p.n_tiles, st);
   }
   launch_scan_tiles(p, a, tile_off, esc_cnt, TileCounts{}, st);
-  hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
-                     status);
+  // (a launch less where a wavefront's sum over the streams is short: 8 streams of 65,536 symbols 89 -> 87 us)
+  const bool scan_here = p.n_streams <= kScanStreamsHere;
+  if (!scan_here)
+    hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
+                       status);
   // 64 tiles per wavefront start the fewest wavefronts; where that would leave compute units without one, eight
   const int32_t per_wave = p.n_tiles >= 64 * 1024 ? 64 : 8;
   const int64_t per_block = (int64_t)per_wave * (kBlock / 64);
   hipLaunchKernelGGL(compact_escapes_kernel, dim3((unsigned)((p.n_tiles + per_block - 1) / per_block)), dim3(kBlock), 0,
-                     st, a, esc_vals, esc_cap, esc_off, p.n_tiles, per_wave);
+                     st, a, esc_vals, esc_cap, esc_off, scan_here ? esc_cnt : nullptr, p.n_tiles, per_wave);
   return launch_status();
 }
 
@@ -919,7 +939,7 @@ int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
 
   hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
-                     weights, p.rows, dims->k, status);
+                     weights, p.rows, dims->k, status, (uint32_t *)nullptr, (int64_t)0);
   if (!counts.counted)
     hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
                        0, st, a, (uint32_t)p.n_tiles);
@@ -1138,7 +1158,7 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
                                    p.syms_per_stream, n_tables, symbols, r, restart, status, st, false);
   if (rc) return rc;  // nothing enqueued
   hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
-                     const_cast<float *>(a.weights), p.rows, dims->k, status);
+                     const_cast<float *>(a.weights), p.rows, dims->k, status, (uint32_t *)nullptr, (int64_t)0);
   return rans_decode_fused(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
                            n_tables, symbols, r, restart, status, st, true);
 }
