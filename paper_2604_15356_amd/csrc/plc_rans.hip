@@ -1054,10 +1054,14 @@ __device__ __forceinline__ u32x4 unpack_enc_entry(const uint2 c) {
   return e;
 }
 
-template <bool ADAPT>  // ADAPT: one table per bit depth (the *_bucketed call)
+// ADAPT: one table per bit depth (the *_bucketed call).  Its entries take 8 bytes where three units are to share a
+// compute unit, and unpacking them costs the feeder what the coder saves; WIDE: whole entries, two units to a compute unit
+// (256 units of 1,048,576 symbols 867 -> 832 us, 512 of 262,144 320 -> 298; 768 need the third).
+template <bool ADAPT, bool WIDE = !ADAPT>
 __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const RansArgs a) {
   constexpr int kIdentity = (ADAPT ? PLC_MAX_BITS : 1) * 256;  // index of the entry that leaves a state unchanged
-  using Entry = std::conditional_t<ADAPT, uint2, uint4>;
+  constexpr bool kPacked = ADAPT && !WIDE;
+  using Entry = std::conditional_t<kPacked, uint2, uint4>;
   __shared__ Entry table[kIdentity + 1];
   // ADAPT: table of each group of a staging round, in the order in which the feeder's halves want them: a full
   // batch's eight odd groups from the top, then its eight even ones
@@ -1070,7 +1074,8 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
   __shared__ uint16_t spare_word[64];
   __shared__ uint32_t list_fill[kListRegions];  // positions in use of each region of the list
   static_assert(workgroups_per_cu(sizeof(table) + sizeof(table_of_group) + sizeof(entry_ring) + sizeof(state_ring) +
-                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill)) >= 3,
+                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill)) >=
+                    (ADAPT && WIDE ? 2 : 3),
                 "three units to a compute unit: without the third 513 to 768 units take a second round");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1090,7 +1095,7 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       for (int r = 0; r < 4; ++r) {
         if (r == wave) {
           const uint4 e = make_enc_entry(form, f[t][r], cum[t]);
-          if constexpr (ADAPT) {
+          if constexpr (kPacked) {
             table[t * 256 + lane * 4 + r] = pack_enc_entry(e);
           } else {
             table[t * 256 + lane * 4 + r] = e;
@@ -1101,7 +1106,7 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     }
     if (threadIdx.x == 0) {  // never emits, x' = x
       const uint4 e = make_uint4(0u, 0xffffffffu, 0u, 0u);
-      if constexpr (ADAPT) {
+      if constexpr (kPacked) {
         table[kIdentity] = pack_enc_entry(e);
       } else {
         table[kIdentity] = e;
@@ -1202,10 +1207,14 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
           uint32_t any = 0;
           if constexpr (ADAPT) {  // the group of step 2p + half sits at top - bottom - 1 - half - 2p of the round
             const uint2 tg = *reinterpret_cast<const uint2 *>(&table_of_group[r & 1][top - bottom - kBatch + 8 * half]);
-            uint2 c[kBatch / 2];
 #pragma unroll
             for (int p = 0; p < kBatch / 2; ++p)  // symbol | table << 8
-              c[p] = table[__builtin_amdgcn_perm(p < 4 ? tg.x : tg.y, sy[p], 0x0c0c0400u + ((uint32_t)(p & 3) << 8))];
+              sy[p] = __builtin_amdgcn_perm(p < 4 ? tg.x : tg.y, sy[p], 0x0c0c0400u + ((uint32_t)(p & 3) << 8));
+          }
+          if constexpr (kPacked) {
+            uint2 c[kBatch / 2];
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) c[p] = table[sy[p]];
 #pragma unroll
             for (int p = 0; p < kBatch / 2; ++p) {
               any |= c[p].y;
@@ -1231,7 +1240,7 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
             uint32_t byte = sb[idx];
             if (ADAPT && has) byte += (uint32_t)table_of_group[r & 1][group_at(top - 1 - j - bottom)] << 8;
             const Entry c = table[has ? byte : (uint32_t)kIdentity];
-            if constexpr (ADAPT) {
+            if constexpr (kPacked) {
               bad_symbol = bad_symbol || (c.y & 0x80000000u) != 0;
               *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = unpack_enc_entry(c);
             } else {
@@ -1312,7 +1321,13 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
     bool bad_depth = false;
     uint4 nv[kStagePieces];         // next round's symbols in flight
     bool ntake[kStagePieces];
-    uint32_t ntog = 0;              // ADAPT: table of group bottom + lane of the next round
+    // ADAPT: depth of group bottom + lane of the next round.  It is looked at when the round's symbols land: where it
+    // is asked for, its range check would have the wavefront, and at the barrier the others, wait for the answer in
+    // every round (964 -> 829 us for 256 units of 1,048,576 symbols).
+    uint32_t next_depth = 1;
+    const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
+    const uint8_t *const depth_row =
+        ADAPT ? a.bits + (int64_t)((uint32_t)unit / (uint32_t)a.streams_per_session) * (len / spp) : nullptr;
     auto round_load = [&](int32_t r) {
       const int64_t lo = (int64_t)round_bottom(r) * kLanes;
       int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
@@ -1325,14 +1340,18 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       }
       if (ADAPT) {
         const int32_t g = round_bottom(r) + lane;
-        ntog = (r < n_rounds && g < batch_top(4 * r)) ? group_table(a, unit, 0, g, 1u, &bad_depth) : 0u;
+        next_depth = (r < n_rounds && g < batch_top(4 * r)) ? depth_row[(uint32_t)g * kLanes / spp] : 1u;
       }
     };
     auto round_store = [&](int buf) {
 #pragma unroll
       for (int i = 0; i < kStagePieces; ++i)
         if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
-      if (ADAPT) table_of_group[buf][group_at(lane)] = (uint8_t)ntog;
+      if (ADAPT) {
+        const bool known = next_depth >= 1u && next_depth <= (uint32_t)a.n_tables;
+        bad_depth = bad_depth || !known;
+        table_of_group[buf][group_at(lane)] = (uint8_t)(known ? next_depth - 1u : 0u);
+      }
     };
     round_load(0);
     __syncthreads();  // tables
@@ -1922,18 +1941,25 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
   const uint16_t *const rings = &ring[0][0][0];
   const uint32_t my_place = (uint32_t)((wave * 2 + half) * (kPairBlock + kPairRing) + kPairBlock - hl - kLanes * (kPairSteps - 1));
 
-  // ADAPT: table offsets of the next two batches' groups, fetched two batches ahead by the first lanes of a half
+  // ADAPT: table offsets of the next two batches' groups, from the depths that the first lanes of a half ask for two
+  // batches ahead (and look at only then)
   constexpr int kAhead = 2 * kPairSteps;
   bool bad_depth = false;
-  auto group_load = [&](int32_t g0) -> uint32_t {
+  const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
+  const uint8_t *const depth_row =
+      ADAPT ? a.bits + (int64_t)((uint32_t)stream / (uint32_t)a.streams_per_session) * ((uint32_t)a.syms_per_stream / spp)
+            : nullptr;
+  auto fetch_depth = [&](int32_t g0) -> uint32_t {
     const int32_t g = g0 + hl;
-    if (!ADAPT || hl >= kAhead || g >= G) return 0u;
-    return group_table(a, stream, begin, g, kCompactTable, &bad_depth);
+    if (!ADAPT || hl >= kAhead || g >= G) return 1u;
+    return depth_row[((uint32_t)begin + (uint32_t)g * kLanes) / spp];
   };
-  if (ADAPT) {
-    const uint32_t gt0 = group_load(0);
-    if (hl < kAhead) table_of_group[wave][0][half][hl] = (uint16_t)gt0;
-  }
+  auto put_tables = [&](int buf, uint32_t depth) {
+    const bool known = depth >= 1u && depth <= (uint32_t)a.n_tables;
+    bad_depth = bad_depth || !known;
+    if (hl < kAhead) table_of_group[wave][buf][half][hl] = (uint16_t)(known ? (depth - 1u) * kCompactTable : 0u);
+  };
+  if (ADAPT) put_tables(0, fetch_depth(0));
   wave_sync();
   int gbuf = 0;
 
@@ -1943,7 +1969,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
   uint32_t esc_mine = 0;  // this lane's, of the tile so far
 
   for (int32_t g0 = 0; g0 < n_groups; g0 += 2 * kPairSteps) {
-    const uint32_t ngt = group_load(g0 + 2 * kPairSteps);
+    const uint32_t depth_ahead = fetch_depth(g0 + 2 * kPairSteps);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int32_t gb = g0 + b * kPairSteps;
@@ -1981,7 +2007,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
       wave_sync();
     }
     if (ADAPT) {
-      if (hl < kAhead) table_of_group[wave][gbuf ^ 1][half][hl] = (uint16_t)ngt;
+      put_tables(gbuf ^ 1, depth_ahead);
       gbuf ^= 1;
     }
     // the symbols of both batches
@@ -3326,7 +3352,9 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
     if (a.units_per_stream == 1 && a.n_units <= kPipeMaxUnits) {
       // few units (kPipeMaxUnits): the chain of one unit is the time, so give each unit four wavefronts
       // (with more units, four wavefronts per unit cost more in occupancy than the shorter chain gains)
-      if (a.bits) {
+      if (a.bits && a.n_units <= 2 * kComputeUnits) {
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, true>), dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
+      } else if (a.bits) {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<true>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       } else {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
