@@ -340,60 +340,41 @@ __device__ __forceinline__ void enc_step_pinned(uint32_t &x, const uint4 e, uint
   flags |= e.w;
 }
 
-template <int W, bool ADAPT>
-__global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
-  __shared__ uint4 table[ADAPT ? PLC_MAX_BITS * 256 : 256];
-  __shared__ uint16_t table_of_group[ADAPT ? W : 1][2][kSuperGroups];  // ADAPT: table offset of each staged group
-  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[W][2][kSymStage];
-  __shared__ __attribute__((aligned(16))) uint16_t word_stage[W][kBatchSyms + 8 + 64];  // list + carry + scratch slots
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t stream = blockIdx.x / a.wgs_per_stream;
-  const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
-  const bool live = chunk < a.units_per_stream;
+// Many whole streams with one table per bit depth, a unit per wavefront.  (Two units of different streams would need
+// eight tables, 32 KB, in LDS.)
+__global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
+  __shared__ uint4 table[PLC_MAX_BITS * 256];
+  __shared__ uint16_t table_of_group[2][kSuperGroups];  // table offset of each staged group
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
+  __shared__ __attribute__((aligned(16))) uint16_t word_stage[kBatchSyms + 8 + 64];  // list + carry + scratch slots
+  const int lane = threadIdx.x;
+  const int64_t unit = blockIdx.x;  // one unit per stream
 
   bool long_form = false;
-  if (!ADAPT) {  // every wavefront scans the frequencies; entry 4*lane + r is built by wavefront (4*lane + r) mod W
-    uint32_t f[4], cum;
-    const uint32_t total = load_freq4(a.freq + stream * 256, lane, f, &cum);
-    if (total != kScale && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
-    long_form = __ballot(f[0] > 2048u || f[1] > 2048u || f[2] > 2048u || f[3] > 2048u) != 0;  // uniform
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int s = lane * 4 + r;
-      if ((s & (W - 1)) == wave)
-        table[s] = make_enc_entry(long_form ? kEncLong : kEncShort, f[r], cum);
-      cum += f[r];
-    }
-  } else {  // one table per bit depth; an all-zero table (a depth the stream does not use) holds only invalid entries
+  {  // one table per bit depth; an all-zero table (a depth the stream does not use) holds only invalid entries
     uint32_t f[PLC_MAX_BITS][4], cum[PLC_MAX_BITS];
     for (int t = 0; t < a.n_tables; ++t) {
-      const uint32_t total = load_freq4(a.freq + (stream * a.n_tables + t) * 256, lane, f[t], &cum[t]);
+      const uint32_t total = load_freq4(a.freq + (unit * a.n_tables + t) * 256, lane, f[t], &cum[t]);
       if (total != kScale && total != 0 && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
       long_form = long_form || __ballot(f[t][0] > 2048u || f[t][1] > 2048u || f[t][2] > 2048u || f[t][3] > 2048u) != 0;
     }
     for (int t = 0; t < a.n_tables; ++t) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int s = lane * 4 + r;
-        if ((s & (W - 1)) == wave)
-          table[t * 256 + s] = make_enc_entry(long_form ? kEncLong : kEncShort, f[t][r], cum[t]);
+        table[t * 256 + lane * 4 + r] = make_enc_entry(long_form ? kEncLong : kEncShort, f[t][r], cum[t]);
         cum[t] += f[t][r];
       }
     }
   }
-  __syncthreads();
-  if (!live) return;  // no workgroup barrier below
+  wave_sync();
 
-  const int64_t unit = stream * a.units_per_stream + chunk;
-  const int64_t begin = chunk * a.unit_syms;
-  const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
-  const uint8_t *ubase = a.sym_in + stream * a.syms_per_stream + begin;
+  const uint32_t len = (uint32_t)a.syms_per_stream;
+  const uint8_t *ubase = a.sym_in + unit * a.syms_per_stream;
   const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(ubase) & 15u);
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;  // symbols in the last group, 1..32
   uint16_t *wp = a.words_out + a.word_off[unit];
-  uint16_t *wstage = word_stage[wave];
+  uint16_t *wstage = word_stage;
   uint16_t *scratch = wstage + kBatchSyms + 8 + lane;
 
   const int rl = 31 - (lane & 31);  // rANS lane carried by this hardware lane
@@ -406,11 +387,11 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
   // left over).  A round's symbols [32*glo, 32*ghi) are fetched as 16-byte pieces aligned in absolute
   // address and placed so that symbol (group ghi-1-j, lane l) always sits at  mis + l + 32 * (63 - j).
   bool bad_depth = false;
-  // ADAPT: the table of the group that stage position `lane` will hold (group ghi - 64 + lane), fetched with the symbols
+  // the table of the group that stage position `lane` will hold (group ghi - 64 + lane), fetched with the symbols
   auto group_load = [&](int32_t glo, int32_t ghi) -> uint32_t {
     const int32_t g = ghi - kSuperGroups + lane;
-    if (!ADAPT || ghi <= 0 || g < (glo > 0 ? glo : 0) || g >= ghi) return 0u;
-    return group_table(a, stream, begin, g, 256u, &bad_depth);
+    if (ghi <= 0 || g < (glo > 0 ? glo : 0) || g >= ghi) return 0u;
+    return group_table(a, unit, 0, g, 256u, &bad_depth);
   };
   auto stage_load = [&](int32_t glo, int32_t ghi, uint4 v[kStagePieces], bool take[kStagePieces]) {
     // byte offsets relative to the unit's first symbol; pointers are formed by plain pointer arithmetic
@@ -429,7 +410,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
 #pragma unroll
     for (int i = 0; i < kStagePieces; ++i)
       if (take[i])
-        *reinterpret_cast<uint4 *>(&sym_stage[wave][buf][(lane + 64 * i) * 16 + kLanes * (kSuperGroups - cnt)]) = v[i];
+        *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16 + kLanes * (kSuperGroups - cnt)]) = v[i];
   };
   // Words leave through an LDS list whose position p stands for the word at 16-byte-aligned address
   // (wp - pad) + vbase + p: the first `pad` positions of the unit are padding in front of its first word.
@@ -482,7 +463,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
     bool take[kStagePieces];
     stage_load(ghi - cnt_groups, ghi, v, take);
     stage_store(0, cnt_groups, v, take);
-    if (ADAPT) table_of_group[wave][0][lane] = (uint16_t)group_load(ghi - cnt_groups, ghi);
+    table_of_group[0][lane] = (uint16_t)group_load(ghi - cnt_groups, ghi);
   }
   wave_sync();
   int buf = 0;
@@ -492,8 +473,8 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
     bool ntake[kStagePieces];
     stage_load(glo - kSuperGroups, glo, nv, ntake);  // next round, in flight while this one is coded
     const uint32_t ngt = group_load(glo - kSuperGroups, glo);
-    const uint16_t *gt = table_of_group[ADAPT ? wave : 0][buf];  // group j from the round's top sits at 63 - j
-    const uint8_t *sb = &sym_stage[wave][buf][mis + rl];
+    const uint16_t *gt = table_of_group[buf];  // group j from the round's top sits at 63 - j
+    const uint8_t *sb = &sym_stage[buf][mis + rl];
     int32_t j0 = 0;
     // The prefetched round is written to LDS after the first batch of this round and BEFORE that batch's
     // words are stored: waiting for the loads then does not also wait for freshly issued stores (loads
@@ -502,7 +483,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
     if (head_groups) {
       uint16_t *wtop = wstage + fill;
       for (int32_t j = 0; j < head_groups; ++j) {
-        const uint4 e = table[sb[kLanes * (kSuperGroups - 1 - j)] + (ADAPT ? gt[kSuperGroups - 1 - j] : 0u)];
+        const uint4 e = table[sb[kLanes * (kSuperGroups - 1 - j)] + gt[kSuperGroups - 1 - j]];
         if (long_form) {
           enc_step<true, true>(x, e, wtop, scratch, flags, below, j != 0 || top_active);
         } else {
@@ -510,7 +491,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
         }
       }
       stage_store(buf ^ 1, kSuperGroups, nv, ntake);
-      if (ADAPT) table_of_group[wave][buf ^ 1][lane] = (uint16_t)ngt;
+      table_of_group[buf ^ 1][lane] = (uint16_t)ngt;
       landed = true;
       drain((uint32_t)(wtop - wstage));
       j0 = head_groups;
@@ -521,11 +502,9 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
       uint16_t *wtop = wstage + fill;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) sy[j] = sbb[kLanes * (kBatch - 1 - j)];
-      if (ADAPT) {
-        const uint16_t *gtb = gt + (kSuperGroups - kBatch - j0);
+      const uint16_t *gtb = gt + (kSuperGroups - kBatch - j0);
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) sy[j] += gtb[kBatch - 1 - j];
-      }
+      for (int j = 0; j < kBatch; ++j) sy[j] += gtb[kBatch - 1 - j];
       // table entries are fetched four groups ahead of the chain, so that their LDS time hides behind it
       uint4 e[2][4];
 #pragma unroll
@@ -546,7 +525,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
       }
       if (!landed) {
         stage_store(buf ^ 1, kSuperGroups, nv, ntake);
-        if (ADAPT) table_of_group[wave][buf ^ 1][lane] = (uint16_t)ngt;
+        table_of_group[buf ^ 1][lane] = (uint16_t)ngt;
         landed = true;
       }
       drain((uint32_t)(wtop - wstage));
@@ -580,6 +559,10 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
 // table), or two consecutive whole streams (TWO_TABLES); a unit without such a partner (an odd count, a
 // shorter last chunk) is coded by the lower half while the upper half shadows it and stores nothing.
 // Symbols and words are staged per half exactly as above.
+// ADAPT, one table per bit depth, chunks only: the stream's four tables serve all of a workgroup's units, and a group's
+// table is looked up per half.  Two batches a round there: beside 16 KB of tables that lets three workgroups share a
+// compute unit.  256 streams of 1,048,576 symbols in units of 4096: 566 us with a unit per wavefront, 342 with two and
+// rounds of four batches, 283 with two, 307 with one; units of 1024 1116 -> 420 us, of 16384 432 -> 259.
 template <bool LONG, bool MASKED>
 __device__ __forceinline__ void enc2_step(uint32_t &x, const uint4 e, uint16_t *&wtop, uint16_t *scratch,
                                           uint32_t &flags, uint32_t below, bool upper, bool on) {
@@ -651,13 +634,15 @@ constexpr int kPairMaxWaves = 4;
 // taken only where it lets every pair of streams be resident at once instead of leaving a second, mostly empty
 // round (5120 streams: 3.3 -> 2.5 ms); where there are several full rounds anyway the shorter rounds cost more
 // than the extra wavefronts gain (16,384 streams: 7.4 against 7.7 ms).
-template <int W, bool TWO_TABLES, int SUPER = 4>
+template <int W, bool TWO_TABLES, int SUPER = 4, bool ADAPT = false>
 __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs a) {
   constexpr int kPairGroups = SUPER * kBatch;                  // groups per staging round
   constexpr int kPairSymStage = kPairGroups * kLanes + 32;     // its symbols at any 16-byte misalignment
   constexpr int kPairPieces = (kPairSymStage + 1023) / 1024;   // 16-byte pieces per lane and round
   static_assert(!TWO_TABLES || W == 1, "whole streams: one pair of streams per workgroup");
-  __shared__ uint4 table[TWO_TABLES ? 2 : 1][256];
+  static_assert(!(TWO_TABLES && ADAPT));
+  __shared__ uint4 table[ADAPT ? PLC_MAX_BITS : TWO_TABLES ? 2 : 1][256];
+  __shared__ uint16_t table_of_group[ADAPT ? W : 1][2][2][kPairGroups];  // ADAPT: table offset of each staged group
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[W][2][2][kPairSymStage];                // [half][buffer]
   __shared__ __attribute__((aligned(16))) uint16_t word_stage[W][2][kBatchSyms + 8 + 64];       // list + carry + scratch slots
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -698,15 +683,20 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 
   bool long_form = false;
   {  // table entries: every wavefront scans the frequencies; entry 4*lane + r is built by wavefront (4*lane + r) mod W
-    uint32_t f[TWO_TABLES ? 2 : 1][4], cum[TWO_TABLES ? 2 : 1];
+    constexpr int kTables = ADAPT ? PLC_MAX_BITS : TWO_TABLES ? 2 : 1;
+    uint32_t f[kTables][4], cum[kTables];
 #pragma unroll
-    for (int t = 0; t < (TWO_TABLES ? 2 : 1); ++t) {
-      const uint32_t total = load_freq4(a.freq + stream[t] * 256, lane, f[t], &cum[t]);
-      if (total != kScale && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
+    for (int t = 0; t < kTables; ++t) {
+      if (ADAPT && t >= a.n_tables) break;
+      const uint16_t *freq = a.freq + (ADAPT ? stream[0] * a.n_tables + t : stream[TWO_TABLES ? t : 0]) * 256;
+      const uint32_t total = load_freq4(freq, lane, f[t], &cum[t]);
+      // (an all-zero table, of a depth the stream does not use, holds only invalid entries)
+      if (total != kScale && !(ADAPT && total == 0) && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
       long_form = long_form || __ballot(f[t][0] > 2048u || f[t][1] > 2048u || f[t][2] > 2048u || f[t][3] > 2048u) != 0;
     }
 #pragma unroll
-    for (int t = 0; t < (TWO_TABLES ? 2 : 1); ++t) {
+    for (int t = 0; t < kTables; ++t) {
+      if (ADAPT && t >= a.n_tables) break;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int s = lane * 4 + r;
@@ -738,6 +728,24 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
   const uint4 *mytable = table[TWO_TABLES ? half : 0];
   uint32_t x = kLow, flags = 0;
 
+  // ADAPT: depth of the group that stage position `lane` will hold (group ghi - kPairGroups + lane), asked for with the
+  // symbols; its range is checked when they land, so that nothing waits for it in between.
+  bool bad_depth = false;
+  const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
+  const uint8_t *const depth_row =
+      ADAPT ? a.bits + (int64_t)((uint32_t)stream[0] / (uint32_t)a.streams_per_session) * ((uint32_t)a.syms_per_stream / spp)
+            : nullptr;
+  auto depth_load = [&](int h, int32_t glo, int32_t ghi) -> uint32_t {
+    const int32_t g = ghi - kPairGroups + lane;
+    if (!ADAPT || lane >= kPairGroups || g < (glo > 0 ? glo : 0) || g >= ghi) return 1u;
+    return depth_row[((uint32_t)begin[h] + (uint32_t)g * kLanes) / spp];
+  };
+  auto depth_store = [&](int h, int buf, uint32_t depth) {
+    if (!ADAPT) return;
+    const bool known = depth >= 1u && depth <= (uint32_t)a.n_tables;
+    bad_depth = bad_depth || !known;
+    if (lane < kPairGroups) table_of_group[wave][h][buf][lane] = (uint16_t)(known ? (depth - 1u) * 256u : 0u);
+  };
   // Symbol staging per half, as in the kernel above: a round's symbols are fetched as 16-byte pieces aligned
   // in absolute address by all 64 lanes and placed so that symbol (group ghi-1-j, lane l) sits at
   // mis + l + 32 * (kPairGroups - 1 - j).
@@ -819,23 +827,30 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
     uint4 v[kPairPieces];
     bool take[kPairPieces];
     stage_load(h, ghi - cnt_groups, ghi, v, take);
+    const uint32_t depth = depth_load(h, ghi - cnt_groups, ghi);
     stage_store(h, 0, cnt_groups, v, take);
+    depth_store(h, 0, depth);
   }
   wave_sync();
   int buf = 0;
   while (ghi > 0) {
     const int32_t glo = ghi - cnt_groups;
     uint4 nv[2][kPairPieces];
+    uint32_t ndepth[2];
     bool ntake[2][kPairPieces];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) stage_load(h, glo - kPairGroups, glo, nv[h], ntake[h]);  // next round, in flight
+    for (int h = 0; h < 2; ++h) {  // next round, in flight
+      stage_load(h, glo - kPairGroups, glo, nv[h], ntake[h]);
+      ndepth[h] = depth_load(h, glo - kPairGroups, glo);
+    }
+    const uint16_t *gt = table_of_group[ADAPT ? wave : 0][half][buf];  // group j from the round's top sits at kPairGroups - 1 - j
     const uint8_t *sb = &sym_stage[wave][half][buf][(upper ? mis[1] : mis[0]) + rl];
     int32_t j0 = 0;
     bool landed = false;
     if (head_groups) {
       uint16_t *wtop = wstage + (upper ? fill[1] : fill[0]);
       for (int32_t j = 0; j < head_groups; ++j) {
-        const uint4 e = mytable[sb[kLanes * (kPairGroups - 1 - j)]];
+        const uint4 e = mytable[sb[kLanes * (kPairGroups - 1 - j)] + (ADAPT ? gt[kPairGroups - 1 - j] : 0u)];
         if (long_form) {
           enc2_step<true, true>(x, e, wtop, scratch, flags, below, upper, j != 0 || top_active);
         } else {
@@ -843,7 +858,10 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
         }
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) stage_store(h, buf ^ 1, kPairGroups, nv[h], ntake[h]);
+      for (int h = 0; h < 2; ++h) {
+        stage_store(h, buf ^ 1, kPairGroups, nv[h], ntake[h]);
+        depth_store(h, buf ^ 1, ndepth[h]);
+      }
       landed = true;
       drain_both(wtop);
       j0 = head_groups;
@@ -854,6 +872,11 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
       uint16_t *wtop = wstage + (upper ? fill[1] : fill[0]);
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) sy[j] = sbb[kLanes * (kBatch - 1 - j)];
+      if (ADAPT) {
+        const uint16_t *gtb = gt + (kPairGroups - kBatch - j0);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) sy[j] += gtb[kBatch - 1 - j];
+      }
       // table entries are fetched four groups ahead of the chain, so that their LDS time hides behind it
       uint4 e[2][4];
 #pragma unroll
@@ -874,7 +897,10 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
       }
       if (!landed) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) stage_store(h, buf ^ 1, kPairGroups, nv[h], ntake[h]);
+        for (int h = 0; h < 2; ++h) {
+          stage_store(h, buf ^ 1, kPairGroups, nv[h], ntake[h]);
+          depth_store(h, buf ^ 1, ndepth[h]);
+        }
         landed = true;
       }
       drain_both(wtop);
@@ -896,6 +922,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
     }
   }
   if ((!upper || second) && (flags & 0x80000000u)) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0 occurred
+  if (bad_depth) raise(a.status, PLC_ERR_INVALID);
 }
 
 // ---------------------------------------------------------------------------
@@ -3172,7 +3199,7 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   }
 }
 
-int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, RansArgs *a, int *waves = nullptr) {
+int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, RansArgs *a) {
   if (n_streams < 1 || syms_per_stream < 1) return PLC_ERR_INVALID;
   if (syms_per_stream >= (1ll << 31) - 1024) return PLC_ERR_INVALID;
   if (chunk_syms < 0 || chunk_syms % kLanes) return PLC_ERR_INVALID;
@@ -3182,7 +3209,6 @@ int check_common(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
   a->syms_per_stream = syms_per_stream;
   int w = 1;
   while (w < kMaxWaves && 2 * w <= a->units_per_stream) w *= 2;
-  if (waves) *waves = w;
   const int64_t wgs = (a->units_per_stream + w - 1) / w;
   if (wgs >= (1ll << 31) || n_streams * wgs >= (1ll << 31)) return PLC_ERR_INVALID;
   a->wgs_per_stream = (uint32_t)wgs;
@@ -3234,47 +3260,31 @@ RansArgs again_args(RansArgs a) {
   return a;
 }
 
-template <template <int> class Launcher>
-void dispatch_waves(int waves, const RansArgs &a, unsigned grid, hipStream_t st) {
-  switch (waves) {
-    case 1: Launcher<1>::run(a, grid, st); break;
-    case 2: Launcher<2>::run(a, grid, st); break;
-    case 4: Launcher<4>::run(a, grid, st); break;
-    default: Launcher<8>::run(a, grid, st); break;
+template <int W>  // workgroups of 2 W units of one stream
+void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+  if (a.bits) {
+    const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
+    const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, true, true> : &rans_decode_pair_kernel<W, true, false>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), lds, st, a);
+  } else {
+    const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, false, true> : &rans_decode_pair_kernel<W, false, false>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), 0, st, a);
   }
 }
-
-template <int W>
-struct LaunchEncode {
-  static void run(const RansArgs &a, unsigned grid, hipStream_t st) {
-    if (a.bits) {
-      hipLaunchKernelGGL((rans_encode_kernel<W, true>), dim3(grid), dim3(W * 64), 0, st, a);
-    } else {
-      hipLaunchKernelGGL((rans_encode_kernel<W, false>), dim3(grid), dim3(W * 64), 0, st, a);
-    }
-  }
-};
-template <int W>
-struct LaunchDecodePairs {  // workgroups of 2 W units of one stream
-  static void run(const RansArgs &a, unsigned grid, hipStream_t st) {
-    if (a.bits) {
-      const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-      const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, true, true> : &rans_decode_pair_kernel<W, true, false>;
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), lds, st, a);
-    } else {
-      const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, false, true> : &rans_decode_pair_kernel<W, false, false>;
-      hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), 0, st, a);
-    }
-  }
-};
 // Two or more units per stream, or pieces.
 void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
   const int64_t units = a.pieces ? a.pieces : a.units_per_stream;
   int w = 1;
   while (w < kMaxWaves && 4 * w <= units) w *= 2;
   a.wgs_per_stream = (uint32_t)((units + 2 * w - 1) / (2 * w));
-  dispatch_waves<LaunchDecodePairs>(w, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+  const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
+  switch (w) {
+    case 1: launch_decode_pairs_of<1>(a, grid, st); break;
+    case 2: launch_decode_pairs_of<2>(a, grid, st); break;
+    case 4: launch_decode_pairs_of<4>(a, grid, st); break;
+    default: launch_decode_pairs_of<8>(a, grid, st); break;
+  }
 }
 // One unit per stream.
 void launch_decode_streams(const RansArgs &a, hipStream_t st) {
@@ -3331,8 +3341,7 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
                 const uint16_t *freq, uint32_t *states, uint16_t *words, const uint64_t *word_off,
                 uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status, void *stream, RansArgs a,
                 const plc_restart *restart = nullptr) {
-  int waves = 1;
-  int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a, &waves);
+  int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a);
   if (!rc) rc = check_restart(restart, false, &a);
   if (rc) return rc;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
@@ -3359,8 +3368,8 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
       } else {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       }
-    } else if (a.bits) {
-      dispatch_waves<LaunchEncode>(waves, a, (unsigned)(n_streams * a.wgs_per_stream), st);
+    } else if (a.bits && a.units_per_stream == 1) {
+      hipLaunchKernelGGL(rans_encode_kernel, dim3((unsigned)a.n_units), dim3(64), 0, st, a);
     } else if (a.units_per_stream == 1) {
       // many whole streams: two streams per wavefront, one wavefront per workgroup
       const int64_t pairs = (a.n_units + 1) / 2;
@@ -3377,10 +3386,18 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
       while (w < kPairMaxWaves && 2 * w <= slots) w *= 2;
       a.pair_wgs_per_stream = (uint32_t)((slots + w - 1) / w);
       const unsigned grid = (unsigned)(n_streams * a.pair_wgs_per_stream);  // at most the grid checked above
-      switch (w) {
-        case 1: hipLaunchKernelGGL((rans_encode_pair_kernel<1, false>), dim3(grid), dim3(64), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((rans_encode_pair_kernel<2, false>), dim3(grid), dim3(128), 0, st, a); break;
-        default: hipLaunchKernelGGL((rans_encode_pair_kernel<4, false>), dim3(grid), dim3(256), 0, st, a); break;
+      if (a.bits) {
+        switch (w) {
+          case 1: hipLaunchKernelGGL((rans_encode_pair_kernel<1, false, 2, true>), dim3(grid), dim3(64), 0, st, a); break;
+          case 2: hipLaunchKernelGGL((rans_encode_pair_kernel<2, false, 2, true>), dim3(grid), dim3(128), 0, st, a); break;
+          default: hipLaunchKernelGGL((rans_encode_pair_kernel<4, false, 2, true>), dim3(grid), dim3(256), 0, st, a); break;
+        }
+      } else {
+        switch (w) {
+          case 1: hipLaunchKernelGGL((rans_encode_pair_kernel<1, false>), dim3(grid), dim3(64), 0, st, a); break;
+          case 2: hipLaunchKernelGGL((rans_encode_pair_kernel<2, false>), dim3(grid), dim3(128), 0, st, a); break;
+          default: hipLaunchKernelGGL((rans_encode_pair_kernel<4, false>), dim3(grid), dim3(256), 0, st, a); break;
+        }
       }
     }
   }

@@ -298,3 +298,60 @@ def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
                                    n_tables, counts, status)
         assert int(status.item()) == 0
         assert np.array_equal(u32(counts), oracle.histogram_bucketed(sym, spp, 2, bits, n_tables=n_tables))
+
+
+@pytest.mark.parametrize("n_tables,positions,spp,chunk", [
+    (4, 20, 32, 32),      # units of one group; a workgroup of four wavefronts
+    (4, 43, 96, 512),     # eight full chunks, a shorter last one that ends inside a batch
+    (4, 7, 160, 992),     # one full chunk and a short one; no batch begins where a position does
+    (3, 90, 64, 1024),    # an odd full chunk and a short one, rounds of two batches exactly
+    (2, 36, 32, 1056),    # a chunk of one round and one group more
+    (1, 33, 256, 4096),   # a single table; two full chunks and a short one
+])
+def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk):
+    """Two units per wavefront with a table per depth, against the oracle; word lists at every place inside a line."""
+    O = oracle
+    from paper_2604_15356_amd import plc
+    rng = np.random.default_rng(positions + chunk)
+    S, sps = 2, 3
+    n_streams, N = S * sps, positions * spp
+    bits_np = rng.integers(1, n_tables + 1, (S, positions)).astype(np.uint8)
+    width = 0.3 * 3.0 ** np.repeat(np.repeat(bits_np, sps, 0), spp, 1)   # the first table has an f > 2048
+    sym_np = np.clip(np.round(rng.standard_normal((n_streams, N)) * width + 127), 0, 255).astype(np.uint8)
+    freq_np = O.build_freq_sparse(O.histogram_bucketed(sym_np, spp, sps, bits_np, n_tables=n_tables))
+    sym, bits = torch.from_numpy(sym_np).to(dev), torch.from_numpy(bits_np).to(dev)
+    freq = torch.from_numpy(freq_np.view(np.int16)).to(dev)
+    U, cap = plc.plc_units_per_stream(N, chunk), chunk + 3
+    nu = n_streams * U
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    states = torch.empty((nu, 32), dtype=torch.int32, device=dev)
+    words = torch.full((nu * cap,), -21555, dtype=torch.int16, device=dev)
+    woff = torch.arange(nu, dtype=torch.int64, device=dev) * cap
+    nw = torch.empty(nu, dtype=torch.int32, device=dev)
+    args = (n_streams, N, chunk, spp, sps)
+    plc.plc_rans_encode_bucketed(sym, *args, bits, n_tables, freq, states, words, woff, cap, nw, status)
+    assert int(status.item()) == 0
+    enc = O.rans_encode_bucketed(sym_np, freq_np, spp, sps, bits_np, chunk_syms=chunk, word_cap_per_unit=cap)
+    assert np.array_equal(u32(nw), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+    wd = u16(words)
+    for unit in range(nu):
+        o, k = unit * cap, int(enc["n_words"][unit])
+        assert np.array_equal(wd[o:o + k], enc["words"][o:o + k]), f"unit {unit}"
+        assert (wd[o + k:o + cap] == 0xABCD).all(), f"behind unit {unit}"
+    # what is wrong is reported: a depth of no table, a symbol that its table does not have, lists that are too short
+    for wrong in range(n_tables + 1, n_tables + 3):
+        bad = bits.clone()
+        bad[1, positions // 2] = wrong
+        plc.plc_rans_encode_bucketed(sym, *args, bad, n_tables, freq, states, words, woff, cap, nw, status)
+        assert int(status.item()) == plc.PLC_ERR_INVALID
+        status.zero_()
+    other = sym.clone()
+    other[n_streams - 1, N // 2] = int(np.flatnonzero(freq_np.reshape(n_streams, n_tables, 256)[
+        n_streams - 1, bits_np[S - 1, N // 2 // spp] - 1] == 0)[0])
+    plc.plc_rans_encode_bucketed(other, *args, bits, n_tables, freq, states, words, woff, cap, nw, status)
+    assert int(status.item()) == plc.PLC_ERR_INVALID
+    status.zero_()
+    short = int(nw.max()) - 1
+    if short > 0:
+        plc.plc_rans_encode_bucketed(sym, *args, bits, n_tables, freq, states, words, woff, short, nw, status)
+        assert int(status.item()) == plc.PLC_ERR_CAPACITY
