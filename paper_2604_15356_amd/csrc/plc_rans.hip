@@ -259,6 +259,16 @@ __device__ __forceinline__ uint4 make_enc_entry(EncForm form, uint32_t f, uint32
          : form == kEncPlain ? make_enc_entry<kEncPlain>(f, cum) : make_enc_entry<kEncShort>(f, cum);
 }
 
+// Table entry of 8 bytes, for the coders with a table per bit depth.  .x = m; .y = (4096 - f) | s << 12 | .w << 18, negative for
+// a symbol with f = 0; the threshold follows from f: f * 2^20 - 1 = ~((4096 - f) << 20) mod 2^32.
+__device__ __forceinline__ uint2 pack_enc_entry(const uint4 e) {
+  if (e.w & 0x80000000u) return make_uint2(0u, 0x80000000u);
+  return make_uint2(e.x, (e.z & 0xfffu) | ((e.z >> 24) << 12) | (e.w << 18));
+}
+__device__ __forceinline__ uint4 unpack_enc_entry(const uint2 c) {
+  return make_uint4(c.x, ~(c.y << 20), (c.y & 0xfffu) | ((c.y << 12) & 0x0f000000u), (uint32_t)((int32_t)c.y >> 18));
+}
+
 // One coding step.  Every lane stores its low 16 bits each time -- the emitting lanes into the word
 // list, the others into a scratch slot of their own -- so that the step has no branch; `on` (MASKED
 // only) is false for lanes that hold no symbol in a ragged group.
@@ -340,8 +350,8 @@ __device__ __forceinline__ void enc_step_pinned(uint32_t &x, const uint4 e, uint
   flags |= e.w;
 }
 
-// Many whole streams with one table per bit depth, a unit per wavefront.  (Two units of different streams would need
-// eight tables, 32 KB, in LDS.)
+// Whole streams with one table per bit depth, a unit per wavefront: 22 KB of LDS, seven to a compute unit
+// (encode_depths_in_pairs says when).
 __global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
   __shared__ uint4 table[PLC_MAX_BITS * 256];
   __shared__ uint16_t table_of_group[2][kSuperGroups];  // table offset of each staged group
@@ -550,7 +560,7 @@ __global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
 // ---------------------------------------------------------------------------
 // Encoder for many units: two units per wavefront
 // ---------------------------------------------------------------------------
-// With thousands of units in flight the kernel above is bound by instruction issue, not by latency (measured:
+// With thousands of units in flight a unit per wavefront is bound by instruction issue, not by latency (measured:
 // 83 cycles of a SIMD per step of a unit, the ~21 instructions of a step at 4 cycles each), and half of every
 // instruction's lanes only mirror the other half.  Here lanes 32-63 code a unit of their own: the step's
 // instructions are the same, only the word positions are per half -- a lane ranks itself inside its own
@@ -559,10 +569,11 @@ __global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
 // table), or two consecutive whole streams (TWO_TABLES); a unit without such a partner (an odd count, a
 // shorter last chunk) is coded by the lower half while the upper half shadows it and stores nothing.
 // Symbols and words are staged per half exactly as above.
-// ADAPT, one table per bit depth, chunks only: the stream's four tables serve all of a workgroup's units, and a group's
-// table is looked up per half.  Two batches a round there: beside 16 KB of tables that lets three workgroups share a
-// compute unit.  256 streams of 1,048,576 symbols in units of 4096: 566 us with a unit per wavefront, 342 with two and
-// rounds of four batches, 283 with two, 307 with one; units of 1024 1116 -> 420 us, of 16384 432 -> 259.
+// ADAPT, one table per bit depth: a stream's four tables serve all of a workgroup's units, and a group's table is looked
+// up per half.  LDS decides how many workgroups are resident, so the entries take 8 bytes (the step is four instructions
+// longer: with one table, where that is all it does, 5120 streams take 2455 instead of 2308 us) and a round two batches.
+// 256 streams of 1,048,576 symbols in units of 4096: 566 us with a unit per wavefront; with two 342 (rounds of four
+// batches), 283 (two), 307 (one), with entries of 8 bytes 265; units of 1024 1116 -> 366 us, of 16384 432 -> 250.
 template <bool LONG, bool MASKED>
 __device__ __forceinline__ void enc2_step(uint32_t &x, const uint4 e, uint16_t *&wtop, uint16_t *scratch,
                                           uint32_t &flags, uint32_t below, bool upper, bool on) {
@@ -640,8 +651,9 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
   constexpr int kPairSymStage = kPairGroups * kLanes + 32;     // its symbols at any 16-byte misalignment
   constexpr int kPairPieces = (kPairSymStage + 1023) / 1024;   // 16-byte pieces per lane and round
   static_assert(!TWO_TABLES || W == 1, "whole streams: one pair of streams per workgroup");
-  static_assert(!(TWO_TABLES && ADAPT));
-  __shared__ uint4 table[ADAPT ? PLC_MAX_BITS : TWO_TABLES ? 2 : 1][256];
+  constexpr int kDepths = ADAPT ? PLC_MAX_BITS : 1, kStreams = TWO_TABLES ? 2 : 1;
+  using Entry = std::conditional_t<ADAPT, uint2, uint4>;
+  __shared__ Entry table[kStreams][kDepths * 256];
   __shared__ uint16_t table_of_group[ADAPT ? W : 1][2][2][kPairGroups];  // ADAPT: table offset of each staged group
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage[W][2][2][kPairSymStage];                // [half][buffer]
   __shared__ __attribute__((aligned(16))) uint16_t word_stage[W][2][kBatchSyms + 8 + 64];       // list + carry + scratch slots
@@ -683,26 +695,38 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 
   bool long_form = false;
   {  // table entries: every wavefront scans the frequencies; entry 4*lane + r is built by wavefront (4*lane + r) mod W
-    constexpr int kTables = ADAPT ? PLC_MAX_BITS : TWO_TABLES ? 2 : 1;
-    uint32_t f[kTables][4], cum[kTables];
+    const int n_tables = ADAPT ? a.n_tables : 1;
+    uint32_t f[kStreams][kDepths][4], cum[kStreams][kDepths];
 #pragma unroll
-    for (int t = 0; t < kTables; ++t) {
-      if (ADAPT && t >= a.n_tables) break;
-      const uint16_t *freq = a.freq + (ADAPT ? stream[0] * a.n_tables + t : stream[TWO_TABLES ? t : 0]) * 256;
-      const uint32_t total = load_freq4(freq, lane, f[t], &cum[t]);
-      // (an all-zero table, of a depth the stream does not use, holds only invalid entries)
-      if (total != kScale && !(ADAPT && total == 0) && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
-      long_form = long_form || __ballot(f[t][0] > 2048u || f[t][1] > 2048u || f[t][2] > 2048u || f[t][3] > 2048u) != 0;
+    for (int u = 0; u < kStreams; ++u) {
+#pragma unroll
+      for (int t = 0; t < kDepths; ++t) {
+        if (t >= n_tables) break;
+        const uint32_t total = load_freq4(a.freq + (stream[u] * n_tables + t) * 256, lane, f[u][t], &cum[u][t]);
+        // (an all-zero table, of a depth the stream does not use, holds only invalid entries)
+        if (total != kScale && !(ADAPT && total == 0) && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
+        const uint32_t(&ft)[4] = f[u][t];
+        long_form = long_form || __ballot(ft[0] > 2048u || ft[1] > 2048u || ft[2] > 2048u || ft[3] > 2048u) != 0;
+      }
     }
 #pragma unroll
-    for (int t = 0; t < kTables; ++t) {
-      if (ADAPT && t >= a.n_tables) break;
+    for (int u = 0; u < kStreams; ++u) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int s = lane * 4 + r;
-        if ((s & (W - 1)) == wave)
-          table[t][s] = make_enc_entry(long_form ? kEncLong : kEncShort, f[t][r], cum[t]);
-        cum[t] += f[t][r];
+      for (int t = 0; t < kDepths; ++t) {
+        if (t >= n_tables) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int s = lane * 4 + r;
+          if ((s & (W - 1)) == wave) {
+            const uint4 e = make_enc_entry(long_form ? kEncLong : kEncShort, f[u][t][r], cum[u][t]);
+            if constexpr (ADAPT) {
+              table[u][t * 256 + s] = pack_enc_entry(e);
+            } else {
+              table[u][s] = e;
+            }
+          }
+          cum[u][t] += f[u][t][r];
+        }
       }
     }
   }
@@ -725,20 +749,24 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
   const int rl = 31 - (lane & 31);  // rANS lane carried by this hardware lane
   const uint32_t below = (1u << (lane & 31)) - 1u;
   const bool top_active = (uint32_t)rl < top_syms;
-  const uint4 *mytable = table[TWO_TABLES ? half : 0];
+  const Entry *mytable = table[TWO_TABLES ? half : 0];
   uint32_t x = kLow, flags = 0;
 
   // ADAPT: depth of the group that stage position `lane` will hold (group ghi - kPairGroups + lane), asked for with the
   // symbols; its range is checked when they land, so that nothing waits for it in between.
   bool bad_depth = false;
   const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
-  const uint8_t *const depth_row =
-      ADAPT ? a.bits + (int64_t)((uint32_t)stream[0] / (uint32_t)a.streams_per_session) * ((uint32_t)a.syms_per_stream / spp)
-            : nullptr;
+  const uint8_t *depth_row[2] = {nullptr, nullptr};
+  if (ADAPT) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      depth_row[h] = a.bits + (int64_t)((uint32_t)stream[h] / (uint32_t)a.streams_per_session) *
+                                  ((uint32_t)a.syms_per_stream / spp);
+  }
   auto depth_load = [&](int h, int32_t glo, int32_t ghi) -> uint32_t {
     const int32_t g = ghi - kPairGroups + lane;
     if (!ADAPT || lane >= kPairGroups || g < (glo > 0 ? glo : 0) || g >= ghi) return 1u;
-    return depth_row[((uint32_t)begin[h] + (uint32_t)g * kLanes) / spp];
+    return depth_row[h][((uint32_t)begin[h] + (uint32_t)g * kLanes) / spp];
   };
   auto depth_store = [&](int h, int buf, uint32_t depth) {
     if (!ADAPT) return;
@@ -816,6 +844,13 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
     wave_sync();
   };
 
+  auto entry = [](const Entry &e) {
+    if constexpr (ADAPT) {
+      return unpack_enc_entry(e);
+    } else {
+      return e;
+    }
+  };
   int32_t ghi = G;
   int32_t cnt_groups = G % kPairGroups ? G % kPairGroups : kPairGroups;
   // groups of the first round that do not fill a batch (and the top group if it is ragged) run in a
@@ -850,7 +885,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
     if (head_groups) {
       uint16_t *wtop = wstage + (upper ? fill[1] : fill[0]);
       for (int32_t j = 0; j < head_groups; ++j) {
-        const uint4 e = mytable[sb[kLanes * (kPairGroups - 1 - j)] + (ADAPT ? gt[kPairGroups - 1 - j] : 0u)];
+        const uint4 e = entry(mytable[sb[kLanes * (kPairGroups - 1 - j)] + (ADAPT ? gt[kPairGroups - 1 - j] : 0u)]);
         if (long_form) {
           enc2_step<true, true>(x, e, wtop, scratch, flags, below, upper, j != 0 || top_active);
         } else {
@@ -878,7 +913,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
         for (int j = 0; j < kBatch; ++j) sy[j] += gtb[kBatch - 1 - j];
       }
       // table entries are fetched four groups ahead of the chain, so that their LDS time hides behind it
-      uint4 e[2][4];
+      Entry e[2][4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) e[0][j] = mytable[sy[j]];
 #pragma unroll
@@ -889,10 +924,10 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
         }
         if (long_form) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) enc2_step_pinned<true>(x, e[qt & 1][j], wtop, scratch, flags, below, upper);
+          for (int j = 0; j < 4; ++j) enc2_step_pinned<true>(x, entry(e[qt & 1][j]), wtop, scratch, flags, below, upper);
         } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) enc2_step_pinned<false>(x, e[qt & 1][j], wtop, scratch, flags, below, upper);
+          for (int j = 0; j < 4; ++j) enc2_step_pinned<false>(x, entry(e[qt & 1][j]), wtop, scratch, flags, below, upper);
         }
       }
       if (!landed) {
@@ -1064,23 +1099,6 @@ __device__ __forceinline__ void pipe_batch(uint32_t &x, uint64_t &emit, u32x4 (&
   }
 }
 
-// Table entry of 8 bytes, for the form with a table per bit depth.  .x = m; .y = (4096 - f) | .w << 12 | s << 25, and bit
-// 31 for a symbol with f = 0; the threshold follows from f: f * 2^20 - 1 = -(4096 - f) * 2^20 - 1 mod 2^32.
-__device__ __forceinline__ uint2 pack_enc_entry(const uint4 e) {
-  if (e.w & 0x80000000u) return make_uint2(0u, 0x80000000u);
-  return make_uint2(e.x, (e.z & 0xfffu) | (e.w << 12) | ((e.z >> 24) << 25));
-}
-__device__ __forceinline__ u32x4 unpack_enc_entry(const uint2 c) {
-  u32x4 e;
-  e.x = c.x;
-  e.z = ((c.y >> 1) & 0x0f000000u) | (c.y & 0xfffu);
-  uint32_t thr;
-  asm("v_mad_i32_i24 %0, %1, %2, -1" : "=v"(thr) : "v"(e.z), "s"(-(1 << 20)));  // (of the low 24 bits)
-  e.y = thr;
-  e.w = (c.y >> 12) & 0x1fffu;
-  return e;
-}
-
 // ADAPT: one table per bit depth (the *_bucketed call).  Its entries take 8 bytes where three units are to share a
 // compute unit, and unpacking them costs the feeder what the coder saves; WIDE: whole entries, two units to a compute unit
 // (256 units of 1,048,576 symbols 867 -> 832 us, 512 of 262,144 320 -> 298; 768 need the third).
@@ -1245,7 +1263,8 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
 #pragma unroll
             for (int p = 0; p < kBatch / 2; ++p) {
               any |= c[p].y;
-              e[p] = unpack_enc_entry(c[p]);
+              const uint4 v = unpack_enc_entry(c[p]);
+              e[p] = u32x4{v.x, v.y, v.z, v.w};
             }
           } else {
 #pragma unroll
@@ -1269,7 +1288,7 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
             const Entry c = table[has ? byte : (uint32_t)kIdentity];
             if constexpr (kPacked) {
               bad_symbol = bad_symbol || (c.y & 0x80000000u) != 0;
-              *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = unpack_enc_entry(c);
+              eo[2 * p * kLanes] = unpack_enc_entry(c);
             } else {
               bad_symbol = bad_symbol || (c.w & 0x80000000u) != 0;
               eo[2 * p * kLanes] = c;
@@ -3337,6 +3356,15 @@ int check_depths(int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_p
   return PLC_OK;
 }
 
+// Many whole streams with a table per depth: a compute unit holds seven wavefronts with a stream each, or six with two
+// each, whose steps take longer.  Two each where that is one round instead of two, and where there are so many rounds
+// that the last one's emptiness tells little.  Streams of 131,072 symbols, one and two to a wavefront: 1500 439 and 542 us,
+// 1800 709 and 560, 2560 782 and 645, 3600 1056 and 1172, 5120 1250 and 1187; of 65,536: 3584 452 and 603, 6400 811 and
+// 861, 7200 930 and 885; of 32,768: 9000 591 and 514, 10,800 695 and 629, 16,384 985 and 908.
+bool encode_depths_in_pairs(int64_t n_units) {
+  return (n_units > 7 * kComputeUnits && n_units <= 12 * kComputeUnits) || n_units > 28 * kComputeUnits;
+}
+
 int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
                 const uint16_t *freq, uint32_t *states, uint16_t *words, const uint64_t *word_off,
                 uint64_t word_cap_per_unit, uint32_t *n_words, uint32_t *status, void *stream, RansArgs a,
@@ -3368,8 +3396,10 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
       } else {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       }
-    } else if (a.bits && a.units_per_stream == 1) {
+    } else if (a.bits && a.units_per_stream == 1 && !encode_depths_in_pairs(a.n_units)) {
       hipLaunchKernelGGL(rans_encode_kernel, dim3((unsigned)a.n_units), dim3(64), 0, st, a);
+    } else if (a.bits && a.units_per_stream == 1) {
+      hipLaunchKernelGGL((rans_encode_pair_kernel<1, true, 2, true>), dim3((unsigned)((a.n_units + 1) / 2)), dim3(64), 0, st, a);
     } else if (a.units_per_stream == 1) {
       // many whole streams: two streams per wavefront, one wavefront per workgroup
       const int64_t pairs = (a.n_units + 1) / 2;

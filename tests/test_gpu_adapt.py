@@ -307,13 +307,14 @@ def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
     (3, 90, 64, 1024),    # an odd full chunk and a short one, rounds of two batches exactly
     (2, 36, 32, 1056),    # a chunk of one round and one group more
     (1, 33, 256, 4096),   # a single table; two full chunks and a short one
+    (4, 5, 96, 0),        # whole streams
 ])
 def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk):
     """Two units per wavefront with a table per depth, against the oracle; word lists at every place inside a line."""
     O = oracle
     from paper_2604_15356_amd import plc
     rng = np.random.default_rng(positions + chunk)
-    S, sps = 2, 3
+    S, sps = (2, 3) if chunk else (3, 599)   # (1797 streams, an odd number: two to a wavefront from 1793 on)
     n_streams, N = S * sps, positions * spp
     bits_np = rng.integers(1, n_tables + 1, (S, positions)).astype(np.uint8)
     width = 0.3 * 3.0 ** np.repeat(np.repeat(bits_np, sps, 0), spp, 1)   # the first table has an f > 2048
@@ -321,7 +322,7 @@ def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk
     freq_np = O.build_freq_sparse(O.histogram_bucketed(sym_np, spp, sps, bits_np, n_tables=n_tables))
     sym, bits = torch.from_numpy(sym_np).to(dev), torch.from_numpy(bits_np).to(dev)
     freq = torch.from_numpy(freq_np.view(np.int16)).to(dev)
-    U, cap = plc.plc_units_per_stream(N, chunk), chunk + 3
+    U, cap = plc.plc_units_per_stream(N, chunk), (chunk or N) + 3
     nu = n_streams * U
     status = torch.zeros(1, dtype=torch.int32, device=dev)
     states = torch.empty((nu, 32), dtype=torch.int32, device=dev)
