@@ -86,6 +86,18 @@ def parse():
     return ap.parse_args()
 
 
+def one_kernel_decode(codec, path="mean"):
+    """Whether the single decode call reconstructs inside the entropy decoder for this codec's shape: the bounds that
+    decode_fused_supported() in csrc/plc_rans.hip has."""
+    if codec.chunk_syms or codec.k > 8:
+        return False
+    if codec.restart is not None:   # in pieces: from some size on two calls are faster
+        return path != "adapt" and codec.n_streams * codec.N < (1 << 23 if path == "cond" else 1 << 25)
+    if path == "adapt":
+        return codec.n_streams <= 512
+    return path == "mean" or codec.k <= 4 or codec.n_streams <= 2048
+
+
 class KernelTimer:
     """HIP event pairs that libplc records around the main kernel of each call, on the stream of the call:
     one pair per kernel, timed step and launch of the step (a cache coded in groups launches each kernel
@@ -194,8 +206,7 @@ class Run:
         self.fused = not args.two_call_decode
         self.overlap = not args.no_overlap
         self.fused_counts = self.grouped or not args.separate_histogram
-        # whether the single decode call runs its one-kernel form for this shape (see include/plc.h)
-        self.one_kernel = self.fused and self.chunk_syms == 0 and w.k <= 8
+        self.one_kernel = self.fused and one_kernel_decode(self.codecs()[0])
 
     def step(self, marks=None):
         w, c = self.w, self.codec
@@ -308,11 +319,14 @@ def time_run(run, args, plc, torch, calibrate=False):
     streams_per_launch = w.n_streams // L
     few = run.chunk_syms == 0 and units_per_launch <= 1024      # the whole-stream kernels for few units
     if few:
-        enc_name, dec_name = "rans_encode_pipe_kernel<false>", "rans_decode_chain_kernel<0, false, 4>"
+        points = run.codecs()[0].restart
+        pieces = 0 if points is None else w.n_streams * points.shape[1]
+        enc_name = "rans_encode_pipe_kernel<false, true>"
+        dec_name = "rans_decode_pair_kernel<8, false, true>" if pieces > 1024 else "rans_decode_chain_kernel<0, false, 4>"
     elif run.chunk_syms == 0:                                   # many whole streams: two per wavefront
         pairs = (units_per_launch + 1) // 2
         enc_name = f"rans_encode_pair_kernel<1, true, {2 if 2048 < pairs <= 2816 else 4}>"
-        dec_name = "rans_decode_kernel<1, false, true>"
+        dec_name = "rans_decode_kernel<false>"
     else:
         n_full = w.syms_per_stream // run.chunk_syms
         ups = (w.syms_per_stream + run.chunk_syms - 1) // run.chunk_syms
@@ -321,9 +335,9 @@ def time_run(run, args, plc, torch, calibrate=False):
         while pw < 4 and 2 * pw <= slots:
             pw *= 2
         dw = 1
-        while dw < 8 and 2 * dw <= ups:
+        while dw < 8 and 4 * dw <= ups:
             dw *= 2
-        enc_name, dec_name = f"rans_encode_pair_kernel<{pw}, false, 4>", f"rans_decode_kernel<{dw}, false, true>"
+        enc_name, dec_name = f"rans_encode_pair_kernel<{pw}, false, 4>", f"rans_decode_pair_kernel<{dw}, false, false>"
     dense = streams_per_launch > 512
     if dense and w.k <= 4:              # 4-byte entries, four workgroups per compute unit
         fused_name = f"rans_decode_depths_kernel<{w.k}, 1>"
@@ -441,7 +455,7 @@ def side_paths(run, args, plc, torch, result):
     import numpy as np
     from paper_2604_15356_amd.codec import KVDeltaCodec
     w, dev = run.w, run.w.cand_k.device
-    out_k, out_v, fused, one_kernel = run.out_k, run.out_v, run.fused, run.one_kernel
+    out_k, out_v, fused = run.out_k, run.out_v, run.fused
     codec = run.codec
     E = w.n_streams * w.syms_per_stream
     n_esc = int(codec.esc_cnt.to(torch.int64).sum())
@@ -541,7 +555,7 @@ def side_paths(run, args, plc, torch, result):
         for _ in range(args.warmup):
             step3()
         torch.cuda.synchronize()
-        one_kernel3 = one_kernel and (w.n_streams <= 2048 or w.k <= 4)     # the one-call decode's own bound on this path
+        one_kernel3 = fused and one_kernel_decode(codec3, "cond")
         timer3 = KernelTimer(plc, torch, args.steps, conditional=True, fused=one_kernel3)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -602,7 +616,7 @@ def side_paths(run, args, plc, torch, result):
         for _ in range(args.warmup):
             step4()
         torch.cuda.synchronize()
-        one_kernel4 = one_kernel and w.n_streams <= 512      # the bound of the decoder with one table per depth
+        one_kernel4 = fused and one_kernel_decode(codec4, "adapt")
         timer4 = KernelTimer(plc, torch, args.steps, conditional=True, fused=one_kernel4)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
