@@ -1871,12 +1871,28 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
   const int64_t chunk = ((int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave) * 2 + half;
   const int64_t n_units = PIECES ? (int64_t)a.pieces : a.units_per_stream;
   const bool live = chunk < n_units;
-  auto fail = [&]() {  // every lane of a half alike
-    if (!live || hl != 0) return;
+  // Escapes of each tile: where the caller counts on them, a unit is whole tiles.
+  const int64_t tiles_per_stream = (a.syms_per_stream + kTileSyms - 1) / kTileSyms;
+  // Every lane of a half alike.  A unit that is not decoded still has its tiles counted, as they stand in the symbol
+  // buffer: the escapes of the stream's other units have their places behind them.  (Of pieces the second launch
+  // decodes the whole stream, and what it leaves is counted then.)
+  auto fail = [&]() {
+    if (!live) return;
     if (PIECES) {
-      report_piece(a, stream, (int32_t)chunk, 0, false);
-    } else {
-      raise(a.status, PLC_ERR_CORRUPT);
+      if (hl == 0) report_piece(a, stream, (int32_t)chunk, 0, false);
+      return;
+    }
+    if (hl == 0) raise(a.status, PLC_ERR_CORRUPT);
+    if (!a.tile_cnt) return;
+    const int64_t from = chunk * a.unit_syms;
+    const int64_t to = from + a.unit_syms < a.syms_per_stream ? from + a.unit_syms : a.syms_per_stream;
+    for (int64_t t0 = from; t0 < to; t0 += kTileSyms) {
+      uint32_t n_esc = 0;
+      for (int64_t i = t0 + hl; i < t0 + kTileSyms && i < to; i += kLanes)
+        n_esc += a.sym_out[stream * a.syms_per_stream + i] == PLC_ESCAPE;
+#pragma unroll
+      for (int d = 1; d < kLanes; d <<= 1) n_esc += __shfl_xor(n_esc, d, 64);
+      if (hl == 0) a.tile_cnt[stream * tiles_per_stream + t0 / kTileSyms] = n_esc;
     }
   };
 
@@ -2010,8 +2026,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
   int gbuf = 0;
 
   // Escapes of each tile: a unit's symbols leave 512 at a time, each 512 of one tile.
-  uint32_t *const tile_cnt =
-      a.tile_cnt + stream * ((a.syms_per_stream + kTileSyms - 1) / kTileSyms) + begin / kTileSyms;  // (if a.tile_cnt)
+  uint32_t *const tile_cnt = a.tile_cnt + stream * tiles_per_stream + begin / kTileSyms;  // (if a.tile_cnt)
   uint32_t esc_mine = 0;  // this lane's, of the tile so far
 
   for (int32_t g0 = 0; g0 < n_groups; g0 += 2 * kPairSteps) {

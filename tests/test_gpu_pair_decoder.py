@@ -111,3 +111,42 @@ def test_escapes_counted_by_the_decoder(dev, chunk, n, d, sigma):
         assert torch.equal(codec.dec_symbols, codec.symbols)
         outs.append([o.view(torch.int16) for o in out])
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("path", ["mean", "adapt"])
+@pytest.mark.parametrize("what", ["list", "last_list", "table"])
+def test_units_that_are_refused_leave_the_others_their_escapes(dev, path, what):
+    """A unit whose word list lies outside the words, or whose table is none, is not decoded.  The places of the escapes
+    behind it follow from what the symbol buffer holds there, in one call as in two, and not from old workspace."""
+    from paper_2604_15356_amd import plc
+    w = make_workload("tiny", device=dev, overrides=dict(L=2, H=3, n=300, k=3, d=128, sigma=1.0, seed=5), random_rows=True)
+    codec = codec_for(w, esc_frac=1.0, chunk_syms=2048)
+    vectors, thr = (w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v), plc.surprisal_thresholds(3.0, 3.9)
+    if path == "mean":
+        codec.encode(*vectors)
+    else:
+        codec.encode_adapt(*vectors, torch.zeros((w.S, w.n), dtype=torch.int32, device=dev), thr, 0.32)
+    codec.check_status("encode")
+    stream, ups = 2, codec.units_per_stream
+    if what == "table":
+        (codec.freq if path == "mean" else codec.freq_d[:, 2])[stream, 127] += 1
+    else:
+        codec.n_words[stream * ups + (ups - 1 if what == "last_list" else 4)] = 1 << 30
+    held = torch.randint(0, 256, codec.symbols.shape, dtype=torch.uint8, device=dev)
+    held[:, ::3] = 255
+    outs = []
+    for fused in (True, False):
+        codec.ws.fill_(0xa5)
+        codec.dec_symbols.copy_(held)
+        out = [torch.full_like(w.act_k, 3.0), torch.full_like(w.act_v, 3.0)]
+        args = (w.cand_k, w.cand_v, w.probs, *out)
+        if path == "mean":
+            codec.decode(*args, fused=fused)
+        else:
+            codec.decode_adapt(*args, thr, 0.32, fused=fused)
+        assert int(codec.status.item()) == plc.PLC_ERR_CORRUPT
+        codec.status.zero_()
+        outs.append([codec.dec_symbols.clone()] + [o.view(torch.int16) for o in out])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    assert torch.equal(outs[0][0][:stream], codec.symbols[:stream])
