@@ -173,6 +173,22 @@ def test_records_that_are_not_true_change_nothing(dev, case):
         assert _same(decode(True), whole)
 
 
+@pytest.mark.parametrize("case", list(CASES))
+def test_records_of_other_words_are_told_by_the_first(dev, case):
+    """Record 0 has what the stream starts from: where that is not so, no piece is decoded."""
+    codec, encode, decode = _setup(dev, case)
+    encode()
+    whole, true = decode(False), codec.restart.clone()
+    for word in (0, 31, 32):
+        codec.restart.copy_(true)
+        codec.restart[0, 0, word] ^= 1
+        assert _same(decode(True), whole), word
+        good = _pieces_good(codec, case)
+        assert not bool(good[0]) and bool(good[1:].all())
+        state = codec._restart_scratch.reshape(-1)[:2 * (-(-(len(_geometry(codec)[1]) + 1) // _step(codec, case)))]
+        assert not bool((state[::2] == GOOD).any())
+
+
 @pytest.mark.parametrize("case", ["k8", "k5_d24", "k4_dense", "k20", "k20_tiles", "k20_no_tiles", "cond_k8", "adapt"])
 def test_damaged_words_are_reported(dev, case):
     """What the decoder reports of damage does not depend on the records, nor do the streams that have none."""
