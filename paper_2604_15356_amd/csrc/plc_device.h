@@ -119,27 +119,34 @@ struct ReconView {
 bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart);
 // That decoder: plc_rans_decode with one unit per stream, plus out = prediction + symbol * delta for every
 // component, escapes from their lists.  With recon.bits: plc_rans_decode_bucketed with n_tables tables per
-// stream instead.  The weights must be in place on `st`.  With launch = false the arguments are checked and
-// nothing is enqueued.
+// stream instead.  The weights must be in place on `st`.
+//   kFusedCheck   the arguments are checked and nothing is enqueued;
+//   kFusedDecode  all streams;
+//   kFusedRest    those that rans_decode_counting with `rest` = false has left.
+enum FusedCall { kFusedCheck, kFusedDecode, kFusedRest };
 int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                       const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
-                      const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch);
+                      const plc_restart *restart, uint32_t *status, hipStream_t st, FusedCall call);
 
 // plc_rans_decode_restart (bits = null) and plc_rans_decode_bucketed_restart, which besides may count the escapes of
-// each tile of 2048 symbols into tile_cnt.  counts->counted tells whether it did; then, with counts->piece_state, only
-// for the streams whose pieces are all good -- the others were decoded once more, by a kernel that does not count.
+// each tile of 2048 symbols into tile_cnt, and with `rest` = false leave the streams whose pieces are not all good to the
+// caller.
 struct TileCounts {
-  bool counted;
-  const uint32_t *piece_state;
+  bool counted;                 // tile_cnt is filled in, but for what piece_state tells
+  bool rest_left;               // streams whose pieces are not all good were not decoded again
+  const uint32_t *piece_state;  // non-null: where streams without good pieces may be that were left, or not counted
   int32_t pieces;
 };
+// Such a stream's tile counts once it has been reconstructed by other means than reconstruct_kernel (a tile has at most
+// kTileSyms escapes).
+constexpr uint32_t kTileDone = 0xffffffffu;
 int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                          const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                          int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos,
                          int32_t streams_per_session, const uint8_t *bits, int32_t n_tables,
-                         const plc_restart *restart, uint8_t *symbols, uint32_t *tile_cnt, TileCounts *counts,
-                         uint32_t *status, void *stream);
+                         const plc_restart *restart, bool rest, uint8_t *symbols, uint32_t *tile_cnt,
+                         TileCounts *counts, uint32_t *status, void *stream);
 
 // A stream's two words per piece, as the decoder leaves them: whether all are good (uniform over the wavefront).
 constexpr uint32_t kPieceGood = 0x600du;

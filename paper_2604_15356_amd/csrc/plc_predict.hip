@@ -45,6 +45,7 @@ struct CodecArgs {
   int64_t cs[5], as[4];
   int64_t syms_per_stream;
   float delta, qmax;
+  bool some_done;                 // decode: tiles may be marked kTileDone
 };
 
 // Where a thread's chunk lives.  All threads of a workgroup share (s, l, h).
@@ -415,16 +416,21 @@ __global__ __launch_bounds__(kBlock) void count_escapes_kernel(const CodecArgs a
 }
 
 // Exclusive prefix sum of the tile counts inside each stream; one workgroup per stream.
-// With piece_state: the counts are the decoder's, and those of a stream whose pieces are not all good are taken here first.
+// With piece_state: a stream whose pieces are not all good either has been reconstructed elsewhere (rest_done), and its
+// tiles are marked, or it was decoded again by a kernel that does not count, and its tiles are counted here first.
 __global__ __launch_bounds__(kBlock) void scan_tiles_kernel(uint32_t *tile_cnt, uint32_t *__restrict__ tile_off,
                                                             uint32_t tiles_per_stream,
                                                             uint32_t *__restrict__ esc_cnt,
                                                             const uint32_t *__restrict__ piece_state, int32_t pieces,
-                                                            const uint8_t *__restrict__ symbols,
+                                                            bool rest_done, const uint8_t *__restrict__ symbols,
                                                             int64_t syms_per_stream) {
   __shared__ uint32_t smem[8];
   const int64_t base = (int64_t)blockIdx.x * tiles_per_stream;
   if (piece_state && !pieces_good(piece_state, pieces, blockIdx.x)) {  // uniform; never but for damaged records or words
+    if (rest_done) {
+      for (uint32_t t = threadIdx.x; t < tiles_per_stream; t += kBlock) tile_cnt[base + t] = kTileDone;
+      return;
+    }
     for (uint32_t t = threadIdx.x >> 6; t < tiles_per_stream; t += kBlock / 64)
       count_tile(symbols, syms_per_stream, tiles_per_stream, (uint32_t)base + t, tile_cnt);
     __syncthreads();
@@ -641,6 +647,8 @@ __global__ __launch_bounds__(kBlock) void compact_escapes_kernel(const CodecArgs
 template <int K, bool COND>
 __global__ __launch_bounds__(kBlock) void reconstruct_kernel(const CodecArgs a) {
   __shared__ uint32_t smem[8];
+  // (looked at in front of the loads only where it may be so)
+  if (a.some_done && a.tile_cnt[blockIdx.x] == kTileDone) return;  // uniform
   const Coord q = locate(a);
   const bool tile_has_escapes = a.tile_cnt[blockIdx.x] != 0;  // uniform
   uint2 sv = make_uint2(0u, 0u);
@@ -847,14 +855,18 @@ extern "C" size_t plc_workspace_bytes(const plc_dims *dims) {
 namespace plc {
 namespace {
 
+void launch_weights(const Plan &p, const CodecArgs &a, const float *probs, hipStream_t st) {
+  hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
+                     const_cast<float *>(a.weights), p.rows, a.k, a.status, (uint32_t *)nullptr, (int64_t)0);
+}
+
 // counts: of the decoder, where it took them.
 void launch_scan_tiles(const Plan &p, const CodecArgs &a, uint32_t *tile_off, uint32_t *esc_cnt, const TileCounts &counts,
                        hipStream_t st) {
   hipLaunchKernelGGL(scan_tiles_kernel, dim3((unsigned)p.n_streams), dim3(kBlock), 0, st, a.tile_cnt, tile_off,
-                     (uint32_t)p.tiles_per_stream, esc_cnt, counts.piece_state, counts.pieces, a.symbols,
-                     p.syms_per_stream);
+                     (uint32_t)p.tiles_per_stream, esc_cnt, counts.piece_state, counts.pieces, counts.rest_left,
+                     a.symbols, p.syms_per_stream);
 }
-
 
 int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, const float *probs,
                   const int32_t *chosen, const uint8_t *bits, float range, int trace_id, const void *act_k, const void *act_v, uint8_t *symbols,
@@ -908,6 +920,7 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   return launch_status();
 }
 
+// counts.rest_left: the weights are in place, and the streams left have been reconstructed.
 int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, const float *probs,
                   const int32_t *chosen, const uint8_t *bits, float range, int trace_id, const uint8_t *symbols, const uint16_t *esc_vals,
                   uint64_t esc_len, const uint64_t *esc_off, void *out_k, void *out_v, void *ws, size_t ws_bytes,
@@ -935,11 +948,10 @@ int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   a.chosen = chosen;
   a.bits = bits;
   a.range = range;
-  float *weights = const_cast<float *>(a.weights);
+  a.some_done = counts.rest_left;
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
 
-  hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
-                     weights, p.rows, dims->k, status, (uint32_t *)nullptr, (int64_t)0);
+  if (!counts.rest_left) launch_weights(p, a, probs, st);
   if (!counts.counted)
     hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
                        0, st, a, (uint32_t)p.n_tiles);
@@ -1112,20 +1124,6 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
   if (!aligned(symbols, 8) || !aligned(probs, 4) || !aligned(esc_off, 8)) return PLC_ERR_INVALID;
   if (!aligned(status, 4) || !aligned(ws, 256) || ws_bytes < p.total) return PLC_ERR_INVALID;
   if (esc_len > 0 && !aligned(esc_vals, 2)) return PLC_ERR_INVALID;
-  if (chunk_syms != 0 ||
-      !decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, chosen != nullptr, bits != nullptr,
-                              restart != nullptr)) {
-    CodecArgs a = {};
-    fill_args(dims, p, ws, &a);
-    TileCounts counts;
-    const int rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams,
-                                        p.syms_per_stream, chunk_syms, 2 * dims->d, dims->L * dims->H, bits, n_tables,
-                                        restart, symbols, a.tile_cnt, &counts, status, stream);
-    if (rc) return rc;
-    return decode_floats(dims, cand_k, cand_v, probs, chosen, bits, range,
-                         chosen ? PLC_TRACE_RECONSTRUCT_COND : PLC_TRACE_RECONSTRUCT, symbols, esc_vals, esc_len,
-                         esc_off, out_k, out_v, ws, ws_bytes, status, stream, counts);
-  }
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   CodecArgs a = {};
@@ -1154,13 +1152,35 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
   r.esc_len = esc_len;
   r.esc_off = esc_off;
 
-  const int rc = rans_decode_fused(freq, states, words, words_len, word_off, n_words, p.n_streams,
-                                   p.syms_per_stream, n_tables, symbols, r, restart, status, st, false);
-  if (rc) return rc;  // nothing enqueued
-  hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((p.rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, probs,
-                     const_cast<float *>(a.weights), p.rows, dims->k, status, (uint32_t *)nullptr, (int64_t)0);
-  return rans_decode_fused(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
-                           n_tables, symbols, r, restart, status, st, true);
+  auto fused = [&](FusedCall call) {
+    return rans_decode_fused(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream, n_tables,
+                             symbols, r, restart, status, st, call);
+  };
+  const bool cond = chosen != nullptr, per_depth = bits != nullptr;
+  if (chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, restart != nullptr)) {
+    const int rc = fused(kFusedCheck);
+    if (rc) return rc;  // nothing enqueued
+    launch_weights(p, a, probs, st);
+    return fused(kFusedDecode);
+  }
+  // In two calls.  With restart points the streams whose pieces do not agree go to the one kernel where it takes the
+  // shape, so that records of other words cost no more than it takes to tell them (256 streams of 1,048,576 symbols,
+  // k = 8: 1.55 ms without records, 1.58 with such ones, and 2.35 in two calls to the end).
+  const bool rest_fused =
+      restart && chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, false);
+  TileCounts counts;
+  int rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
+                                chunk_syms, 2 * dims->d, dims->L * dims->H, bits, n_tables, restart, !rest_fused, symbols,
+                                a.tile_cnt, &counts, status, stream);
+  if (rc) return rc;
+  if (counts.rest_left) {
+    launch_weights(p, a, probs, st);
+    rc = fused(kFusedRest);
+    if (rc) return rc;
+  }
+  return decode_floats(dims, cand_k, cand_v, probs, chosen, bits, range,
+                       chosen ? PLC_TRACE_RECONSTRUCT_COND : PLC_TRACE_RECONSTRUCT, symbols, esc_vals, esc_len, esc_off,
+                       out_k, out_v, ws, ws_bytes, status, stream, counts);
 }
 
 }  // namespace

@@ -19,6 +19,7 @@
 // registers.
 #include "plc_device.h"
 
+#include <optional>
 #include <type_traits>
 
 namespace plc {
@@ -2898,10 +2899,10 @@ __global__ __launch_bounds__(depths_threads(RK)) void rans_decode_depths_kernel(
   const uint32_t ring_off = (uint32_t)n_tables * kDepthTableBytes;
   const uint32_t raw_off = ring_off + (uint32_t)n_tables * kDepthRingBytes;
   const uint32_t symtab_off = raw_off + kDepthRawBytes;
-  // (pieces with a table per depth go to the many-unit decoder, what they leave to the form without reconstruction)
+  // (pieces with a table per depth go to the many-unit decoder)
   const bool pieces = MODE && a.pieces > 0;  // uniform: the unit is a piece of the stream
   bool bad = false;
-  if ((MODE || RK == 0) && a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
+  if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
   // (uniform: every wavefront leaves, before any barrier that another might wait at)
   auto give_up = [&]() {
     if (threadIdx.x != 0) return;
@@ -3456,7 +3457,8 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
 int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                 const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams, int64_t syms_per_stream,
                 int32_t chunk_syms, uint8_t *symbols, uint32_t *status, void *stream, RansArgs a,
-                const plc_restart *restart = nullptr, uint32_t *tile_cnt = nullptr, TileCounts *counts = nullptr) {
+                const plc_restart *restart = nullptr, bool rest = true, uint32_t *tile_cnt = nullptr,
+                TileCounts *counts = nullptr) {
   int rc = check_common(n_streams, syms_per_stream, chunk_syms, &a);
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
@@ -3481,12 +3483,17 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
       // (pieces begin at whole tiles if the stream is whole tiles: the encoder's rounds are as long as a tile)
       if (tile_cnt && (a.pieces ? syms_per_stream : a.unit_syms) % kTileSyms == 0) {
         a.tile_cnt = tile_cnt;
-        *counts = TileCounts{true, a.pieces ? a.piece_state : nullptr, a.pieces};
+        counts->counted = true;
       }
       launch_decode_pairs(a, n_streams, st);
     }
+    if (a.pieces && counts && (counts->counted || !rest)) {
+      counts->piece_state = a.piece_state;
+      counts->pieces = a.pieces;
+      counts->rest_left = !rest;
+    }
     if (a.pieces) a = again_args(a);
-    if (a.units_per_stream == 1) launch_decode_streams(a, st);
+    if (a.units_per_stream == 1 && !(a.verified_pieces && !rest)) launch_decode_streams(a, st);
   }
   return launch_status();
 }
@@ -3497,8 +3504,8 @@ int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uin
                          const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                          int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_pos,
                          int32_t streams_per_session, const uint8_t *bits, int32_t n_tables,
-                         const plc_restart *restart, uint8_t *symbols, uint32_t *tile_cnt, TileCounts *counts,
-                         uint32_t *status, void *stream) {
+                         const plc_restart *restart, bool rest, uint8_t *symbols, uint32_t *tile_cnt,
+                         TileCounts *counts, uint32_t *status, void *stream) {
   *counts = TileCounts{};
   RansArgs a = {};
   if (bits) {
@@ -3506,7 +3513,7 @@ int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uin
     if (rc) return rc;
   }
   return decode_impl(freq, states, words, words_len, word_off, n_words, n_streams, syms_per_stream, chunk_syms,
-                     symbols, status, stream, a, restart, tile_cnt, counts);
+                     symbols, status, stream, a, restart, rest, tile_cnt, counts);
 }
 
 bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart) {
@@ -3530,13 +3537,13 @@ bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, b
 int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16_t *words, uint64_t words_len,
                       const uint64_t *word_off, const uint32_t *n_words, int64_t n_streams,
                       int64_t syms_per_stream, int32_t n_tables, uint8_t *symbols, const ReconView &recon,
-                      const plc_restart *restart, uint32_t *status, hipStream_t st, bool launch) {
+                      const plc_restart *restart, uint32_t *status, hipStream_t st, FusedCall call) {
   RansArgs a = {};
   int rc = check_common(n_streams, syms_per_stream, 0, &a);
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr,
-                              restart != nullptr))
+                              restart != nullptr && call != kFusedRest))
     return PLC_ERR_INVALID;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (words_len > 0 && !words) return PLC_ERR_INVALID;
@@ -3548,7 +3555,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
     rc = check_depths(syms_per_stream, 0, 2 * recon.d8 * kChunk, recon.L * recon.H, recon.bits, n_tables, &a);
     if (rc) return rc;
   }
-  if (!launch) return PLC_OK;
+  if (call == kFusedCheck) return PLC_OK;
   a.sym_out = symbols;
   a.freq = freq;
   a.states_in = states;
@@ -3559,10 +3566,15 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
   a.status = status;
   a.recon = recon;
   {
-    TraceScope trace(PLC_TRACE_RANS_DECODE, st);
+    std::optional<TraceScope> trace;  // (the rest: the call has been traced)
+    if (call == kFusedDecode) trace.emplace(PLC_TRACE_RANS_DECODE, st);
     const dim3 block(192);
     const size_t lds = depths_lds_bytes(a.n_tables);
-    merge_pieces(&a, n_streams, recon.k <= kCompactMaxK ? kPiecesPerRoundCompact : kPiecesPerRound);
+    if (call == kFusedRest) {
+      a = again_args(a);
+    } else {
+      merge_pieces(&a, n_streams, recon.k <= kCompactMaxK ? kPiecesPerRoundCompact : kPiecesPerRound);
+    }
     // With pieces: those, then a launch over the streams, in which one whose pieces agree is left alone.
     for (int round = a.pieces ? 0 : 1; round < 2; ++round) {
       const int64_t n_units = a.pieces ? n_streams * a.pieces : n_streams;
