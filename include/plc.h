@@ -240,7 +240,8 @@ int plc_rans_decode(const uint16_t *freq, const uint32_t *states, const uint16_t
  * hints.  Every piece is checked against the record behind it, and a stream whose pieces do not fit
  * together (records of other words, damaged words) is decoded again from its start as if there were
  * no records; status then tells what it would have told.  They need not be stored with the words
- * (136 bytes each): a cache decoded without them takes the time of one chain.
+ * (136 bytes each): a null `restart` decodes without them, in the time of one chain.  Records that belong
+ * to other words take that and a launch: record 0 tells them.
  * A null `restart` makes a call the one of the same name without the suffix.  With restart points
  * n_streams is at most 1024 and chunk_syms 0, else PLC_ERR_INVALID.
  */

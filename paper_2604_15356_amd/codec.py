@@ -80,12 +80,14 @@ class KVDeltaCodec:
         self.words = torch.empty(self.n_units * self.word_cap, dtype=torch.int16, device=dev)
         self.word_off = torch.arange(self.n_units, dtype=torch.int64, device=dev) * self.word_cap
         self.n_words = torch.empty(self.n_units, dtype=torch.int32, device=dev)
-        # restart points, where streams are so few that the decoder gains from them
+        # restart points, where streams are so few that the decoder gains from them; a decode looks at them once an
+        # encode has written them, or set_restart
         points = plc.plc_restart_points(self.n_streams, self.N, self.chunk_syms)
         self.restart = (torch.zeros((self.n_streams, points, plc.RESTART_WORDS), dtype=torch.int32, device=dev)
                         if points else None)
         self._restart_scratch = (torch.empty((self.n_streams, points, 2), dtype=torch.int32, device=dev)
                                  if points else None)
+        self._restart_written = False
         self.pred = (torch.empty((self.n_streams, self.N), dtype=torch.float32, device=dev)
                      if want_pred else None)
         self.dec_symbols = torch.empty_like(self.symbols)
@@ -98,8 +100,24 @@ class KVDeltaCodec:
         self.idx_word_off = torch.arange(S, dtype=torch.int64, device=dev) * self.idx_word_cap
         self.idx_n_words = torch.empty(S, dtype=torch.int32, device=dev)
 
-    def _points(self):
-        return None if self.restart is None else (self.restart, self._restart_scratch)
+    def _points_out(self):
+        self._restart_written = self.restart is not None
+        return None if self.restart is None else (self.restart, None)
+
+    def _points_in(self):
+        return (self.restart, self._restart_scratch) if self.restart is not None and self._restart_written else None
+
+    def set_restart(self, points=None):
+        """For words that come into the buffers from elsewhere, a cache read back from storage for instance: `points` are
+        the records stored with them (Coded.restart), None is that there are none, and then the decode is the one
+        without restart points.  (Records of other words give the same results: it takes a launch to tell them.)"""
+        self._restart_written = False
+        if points is None:
+            return
+        if self.restart is None or points.shape != self.restart.shape:
+            raise ValueError("no restart points of this shape")
+        self.restart.copy_(points)
+        self._restart_written = True
 
     # -- single steps -------------------------------------------------------------------
     def predict_residual(self, cand_k, cand_v, probs, act_k, act_v, with_counts=False):
@@ -122,12 +140,12 @@ class KVDeltaCodec:
     def rans_encode(self, symbols=None):
         plc.plc_rans_encode(self.symbols if symbols is None else symbols, self.n_streams, self.N,
                             self.chunk_syms, self.freq, self.states, self.words, self.word_off,
-                            self.word_cap, self.n_words, self.status, restart=self._points())
+                            self.word_cap, self.n_words, self.status, restart=self._points_out())
 
     def rans_decode(self, out=None):
         out = self.dec_symbols if out is None else out
         plc.plc_rans_decode(self.freq, self.states, self.words, self.word_off, self.n_words,
-                            self.n_streams, self.N, self.chunk_syms, out, self.status, restart=self._points())
+                            self.n_streams, self.N, self.chunk_syms, out, self.status, restart=self._points_in())
         return out
 
     def reconstruct(self, cand_k, cand_v, probs, out_k, out_v, symbols=None):
@@ -153,7 +171,7 @@ class KVDeltaCodec:
             plc.plc_rans_decode_reconstruct(self.dims, self.freq, self.states, self.words, self.word_off,
                                             self.n_words, self.chunk_syms, cand_k, cand_v, probs, self.esc_vals,
                                             self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status,
-                                            restart=self._points())
+                                            restart=self._points_in())
         else:
             self.rans_decode()
             self.reconstruct(cand_k, cand_v, probs, out_k, out_v)
@@ -206,7 +224,7 @@ class KVDeltaCodec:
         plc.plc_build_freq_bucketed(self.counts_d, self.n_streams, B, self.freq_d, self.status)
         plc.plc_rans_encode_bucketed(self.symbols, self.n_streams, self.N, self.chunk_syms, spp, sps, self.bits, B,
                                      self.freq_d, self.states, self.words, self.word_off, self.word_cap,
-                                     self.n_words, self.status, restart=self._points())
+                                     self.n_words, self.status, restart=self._points_out())
         plc.plc_index_encode(probs, self.chosen, self.S, self.n, self.k, self.idx_states, self.idx_words,
                              self.idx_word_off, self.idx_word_cap, self.idx_n_words, self.status)
         c = self.coded(cond=True)
@@ -224,11 +242,11 @@ class KVDeltaCodec:
                                                   self.n_words, self.chunk_syms, B, cand_k, cand_v, probs,
                                                   self.dec_chosen, self.dec_bits, step_range, self.esc_vals,
                                                   self.esc_off, self.dec_symbols, out_k, out_v, self.ws, self.status,
-                                                  restart=self._points())
+                                                  restart=self._points_in())
             return
         plc.plc_rans_decode_bucketed(self.freq_d, self.states, self.words, self.word_off, self.n_words,
                                      self.n_streams, self.N, self.chunk_syms, spp, sps, self.dec_bits, B,
-                                     self.dec_symbols, self.status, restart=self._points())
+                                     self.dec_symbols, self.status, restart=self._points_in())
         plc.plc_reconstruct_adapt(self.dims, cand_k, cand_v, probs, self.dec_chosen, self.dec_bits, step_range,
                                   self.dec_symbols, self.esc_vals, self.esc_off, out_k, out_v, self.ws, self.status)
 
@@ -263,19 +281,20 @@ class KVDeltaCodec:
             plc.plc_rans_decode_reconstruct_cond(self.dims, self.freq, self.states, self.words, self.word_off,
                                                  self.n_words, self.chunk_syms, cand_k, cand_v, probs,
                                                  self.dec_chosen, self.esc_vals, self.esc_off, self.dec_symbols,
-                                                 out_k, out_v, self.ws, self.status, restart=self._points())
+                                                 out_k, out_v, self.ws, self.status, restart=self._points_in())
         else:
             self.rans_decode()
             plc.plc_reconstruct_cond(self.dims, cand_k, cand_v, probs, self.dec_chosen, self.dec_symbols,
                                      self.esc_vals, self.esc_off, out_k, out_v, self.ws, self.status)
 
     def coded(self, cond=False) -> Coded:
+        restart = self.restart if self._restart_written else None
         if cond:
             return Coded(self.symbols, self.esc_vals, self.esc_cnt, self.esc_off, self.counts, self.freq,
                          self.cum, self.states, self.words, self.word_off, self.n_words, self.chosen,
-                         self.idx_states, self.idx_words, self.idx_word_off, self.idx_n_words, restart=self.restart)
+                         self.idx_states, self.idx_words, self.idx_word_off, self.idx_n_words, restart=restart)
         return Coded(self.symbols, self.esc_vals, self.esc_cnt, self.esc_off, self.counts, self.freq,
-                     self.cum, self.states, self.words, self.word_off, self.n_words, restart=self.restart)
+                     self.cum, self.states, self.words, self.word_off, self.n_words, restart=restart)
 
     def check_status(self, where="plc"):
         """Synchronises and raises if a kernel reported a data-dependent error."""

@@ -173,6 +173,29 @@ def test_records_that_are_not_true_change_nothing(dev, case):
         assert _same(decode(True), whole)
 
 
+@pytest.mark.parametrize("case", ["k8", "k20", "cond_k8", "adapt"])
+def test_a_codec_looks_at_records_that_were_written(dev, case):
+    """A codec that takes words from elsewhere decodes without records until it is given theirs."""
+    codec, encode, decode = _setup(dev, case)
+    reader, _, read = _setup(dev, case)
+    encode()
+    whole = decode(False)
+    for x in ("esc_vals", "esc_off", "freq", "states", "words", "n_words", "idx_states", "idx_words", "idx_n_words"):
+        getattr(reader, x).copy_(getattr(codec, x))
+    if case == "adapt":
+        reader._adapt_buffers()
+        reader.freq_d.copy_(codec.freq_d)
+    reader.restart.copy_(codec.restart)
+    untouched = lambda: bool((reader._restart_scratch == -1).all())
+    assert _same(read(True), whole) and untouched() and reader.coded().restart is None
+    reader.set_restart(codec.coded().restart)
+    assert _same(read(True), whole) and bool(_pieces_good(reader, case).all())
+    reader.set_restart(None)
+    assert _same(read(True), whole) and untouched()
+    with pytest.raises(ValueError):
+        reader.set_restart(codec.restart[:, 1:])
+
+
 @pytest.mark.parametrize("case", list(CASES))
 def test_records_of_other_words_are_told_by_the_first(dev, case):
     """Record 0 has what the stream starts from: where that is not so, no piece is decoded."""
