@@ -647,10 +647,9 @@ __global__ __launch_bounds__(kBlock) void compact_escapes_kernel(const CodecArgs
 template <int K, bool COND>
 __global__ __launch_bounds__(kBlock) void reconstruct_kernel(const CodecArgs a) {
   __shared__ uint32_t smem[8];
-  // (looked at in front of the loads only where it may be so)
-  if (a.some_done && a.tile_cnt[blockIdx.x] == kTileDone) return;  // uniform
+  const uint32_t tile_cnt = a.tile_cnt[blockIdx.x];  // uniform; on its way while the place is worked out
   const Coord q = locate(a);
-  const bool tile_has_escapes = a.tile_cnt[blockIdx.x] != 0;  // uniform
+  if (a.some_done && tile_cnt == kTileDone) return;
   uint2 sv = make_uint2(0u, 0u);
   half8 out;
   uint32_t n_esc = 0;
@@ -662,7 +661,7 @@ __global__ __launch_bounds__(kBlock) void reconstruct_kernel(const CodecArgs a) 
     const float step = COND ? position_step(a, q.row) : a.delta;
     out = add_back8(sv, step, pred, &n_esc);
   }
-  if (tile_has_escapes) {
+  if (tile_cnt) {
     uint32_t total;
     const uint32_t rank = block_exclusive_scan(n_esc, smem, &total);
     if (n_esc) {
@@ -920,11 +919,11 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   return launch_status();
 }
 
-// counts.rest_left: the weights are in place, and the streams left have been reconstructed.
+// weights_ready: they are in place.  counts.rest_left: the streams left have been reconstructed.
 int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, const float *probs,
                   const int32_t *chosen, const uint8_t *bits, float range, int trace_id, const uint8_t *symbols, const uint16_t *esc_vals,
                   uint64_t esc_len, const uint64_t *esc_off, void *out_k, void *out_v, void *ws, size_t ws_bytes,
-                  uint32_t *status, void *stream, const TileCounts &counts = TileCounts{}) {
+                  uint32_t *status, void *stream, const TileCounts &counts = TileCounts{}, bool weights_ready = false) {
   Plan p;
   if (!make_plan(dims, &p)) return PLC_ERR_INVALID;
   if (!aligned(cand_k, 16) || !aligned(cand_v, 16) || !aligned(out_k, 16) || !aligned(out_v, 16))
@@ -951,7 +950,7 @@ int decode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   a.some_done = counts.rest_left;
   uint32_t *tile_off = const_cast<uint32_t *>(a.tile_off);
 
-  if (!counts.rest_left) launch_weights(p, a, probs, st);
+  if (!weights_ready) launch_weights(p, a, probs, st);
   if (!counts.counted)
     hipLaunchKernelGGL(count_escapes_kernel, dim3((unsigned)((p.n_tiles + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock),
                        0, st, a, (uint32_t)p.n_tiles);
@@ -1168,19 +1167,18 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
   // k = 8: 1.55 ms without records, 1.58 with such ones, and 2.35 in two calls to the end).
   const bool rest_fused =
       restart && chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, false);
+  int rc = rest_fused ? fused(kFusedCheck) : PLC_OK;
+  if (rc) return rc;  // nothing enqueued
+  if (rest_fused) launch_weights(p, a, probs, st);
   TileCounts counts;
-  int rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
+  rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
                                 chunk_syms, 2 * dims->d, dims->L * dims->H, bits, n_tables, restart, !rest_fused, symbols,
                                 a.tile_cnt, &counts, status, stream);
+  if (!rc && counts.rest_left) rc = fused(kFusedRest);
   if (rc) return rc;
-  if (counts.rest_left) {
-    launch_weights(p, a, probs, st);
-    rc = fused(kFusedRest);
-    if (rc) return rc;
-  }
   return decode_floats(dims, cand_k, cand_v, probs, chosen, bits, range,
                        chosen ? PLC_TRACE_RECONSTRUCT_COND : PLC_TRACE_RECONSTRUCT, symbols, esc_vals, esc_len, esc_off,
-                       out_k, out_v, ws, ws_bytes, status, stream, counts);
+                       out_k, out_v, ws, ws_bytes, status, stream, counts, rest_fused);
 }
 
 }  // namespace

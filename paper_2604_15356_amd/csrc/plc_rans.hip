@@ -3543,7 +3543,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr,
-                              restart != nullptr && call != kFusedRest))
+                              restart != nullptr && call == kFusedDecode))
     return PLC_ERR_INVALID;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (words_len > 0 && !words) return PLC_ERR_INVALID;
