@@ -3311,11 +3311,19 @@ void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), 0, st, a);
   }
 }
-// Two or more units per stream, or pieces.
+// Two or more units per stream, or pieces: a workgroup that holds all of a stream's if eight wavefronts can, so that the
+// table is built once and the last workgroup is not nearly empty.  (Workgroups of the next smaller size, a stream's second
+// one with few units: 4096 streams of three chunks of 1024 37 and 49 us, of five 44 and 58, 1024 of six chunks of 4096 33 and
+// 52, 768 streams of 131,072 symbols in ten pieces, given the tokens, 206 and 250.)  Long units that are fewer than that leaves
+// workgroups for every compute unit are spread over them (64 streams of ten chunks of 65,536: 276 and 261 us; chunks of
+// 8192 are better off together, 45 and 46).
+constexpr int64_t kSpreadSyms = 32768;
 void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
   const int64_t units = a.pieces ? a.pieces : a.units_per_stream;
+  const int64_t unit_syms = a.pieces ? (int64_t)a.piece_batches * kBatchSyms : a.unit_syms;
+  auto wgs = [&](int waves) { return n_streams * ((units + 2 * waves - 1) / (2 * waves)); };
   int w = 1;
-  while (w < kMaxWaves && 4 * w <= units) w *= 2;
+  while (w < kMaxWaves && 2 * w < units && (unit_syms < kSpreadSyms || wgs(2 * w) >= kComputeUnits)) w *= 2;
   a.wgs_per_stream = (uint32_t)((units + 2 * w - 1) / (2 * w));
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
   switch (w) {
