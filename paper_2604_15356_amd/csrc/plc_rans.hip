@@ -1944,8 +1944,10 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
     return;
   }
 
-  // ---- the half's unit; one that does not exist, or whose list is none, is empty
-  const int64_t my_chunk = live ? chunk : 0;
+  // ---- the half's unit; one whose list is none is empty.  An upper half behind the last unit shadows the lower, so that
+  // the steps need no mask, and keeps what it decodes to itself.
+  const bool shadow = half && !live && chunk - 1 < n_units;
+  const int64_t my_chunk = live ? chunk : shadow ? chunk - 1 : 0;
   const int64_t unit = PIECES ? stream : stream * a.units_per_stream + my_chunk;
   const uint64_t off = a.word_off[unit];
   const uint32_t n = a.n_words_in[unit];
@@ -1953,7 +1955,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
   bool list_ok = !(off > a.words_len || (uint64_t)n > a.words_len - off);
   if (PIECES) list_ok = load_piece(a, stream, (int32_t)my_chunk, n, &piece) && list_ok;
   if (!list_ok) fail();
-  const bool runs = live && list_ok;
+  const bool runs = (live || shadow) && list_ok;
   const int64_t begin = PIECES ? (int64_t)piece.begin : my_chunk * a.unit_syms;
   const int64_t rest = a.syms_per_stream - begin;
   const uint32_t len = !runs ? 0u : PIECES ? piece.len : (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
@@ -2078,7 +2080,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
     }
     // the symbols of both batches
     const uint32_t done = (uint32_t)g0 * kLanes, mine = (uint32_t)hl * 16;
-    const uint32_t left = len > done ? len - done : 0u;
+    const uint32_t left = live && len > done ? len - done : 0u;
     if (out_aligned && mine + 16 <= left) {
       const uint4 v = *reinterpret_cast<const uint4 *>(&my_stage[mine]);
       *reinterpret_cast<uint4 *>(ubase + done + mine) = v;
@@ -2100,7 +2102,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
       esc_mine = 0;
 #pragma unroll
       for (int d = 1; d < kLanes; d <<= 1) sum += __shfl_xor(sum, d, 64);
-      if (hl == 0 && done / kTileSyms * kTileSyms < len) tile_cnt[done / kTileSyms] = sum;
+      if (hl == 0 && live && done / kTileSyms * kTileSyms < len) tile_cnt[done / kTileSyms] = sum;
     }
     wave_sync();
   }
@@ -2110,7 +2112,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_pair_kernel(const RansArgs
     if (ptr != stop || x != x_end) bad = true;
   }
   const uint64_t bads = __ballot(bad);
-  if (runs) {
+  if (runs && live) {
     const bool good = (uint32_t)(half ? bads >> 32 : bads) == 0;
     if (PIECES) {
       if (hl < 2) report_piece(a, stream, (int32_t)chunk, hl, good);
