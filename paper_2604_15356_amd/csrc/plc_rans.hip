@@ -355,41 +355,50 @@ __device__ __forceinline__ void enc_step_pinned(uint32_t &x, const uint4 e, uint
   flags |= e.w;
 }
 
-// Whole streams with one table per bit depth, a unit per wavefront: 22 KB of LDS, seven to a compute unit
-// (encode_depths_in_pairs says when).
-__global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
+// One table per bit depth, a unit per wavefront: whole streams, with 22 KB of LDS seven to a compute unit
+// (encode_depths_in_pairs says when), and chunks that are few, W of a stream to a workgroup (kFewChunks).
+template <int W>
+__global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
   __shared__ uint4 table[PLC_MAX_BITS * 256];
-  __shared__ uint16_t table_of_group[2][kSuperGroups];  // table offset of each staged group
-  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
-  __shared__ __attribute__((aligned(16))) uint16_t word_stage[kBatchSyms + 8 + 64];  // list + carry + scratch slots
-  const int lane = threadIdx.x;
-  const int64_t unit = blockIdx.x;  // one unit per stream
+  __shared__ uint16_t table_of_group_of[W][2][kSuperGroups];  // table offset of each staged group
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage_of[W][2][kSymStage];
+  __shared__ __attribute__((aligned(16))) uint16_t word_stage[W][kBatchSyms + 8 + 64];  // list + carry + scratch slots
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t stream = blockIdx.x / a.wgs_per_stream;
+  const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
 
   bool long_form = false;
   {  // one table per bit depth; an all-zero table (a depth the stream does not use) holds only invalid entries
     uint32_t f[PLC_MAX_BITS][4], cum[PLC_MAX_BITS];
     for (int t = 0; t < a.n_tables; ++t) {
-      const uint32_t total = load_freq4(a.freq + (unit * a.n_tables + t) * 256, lane, f[t], &cum[t]);
+      const uint32_t total = load_freq4(a.freq + (stream * a.n_tables + t) * 256, lane, f[t], &cum[t]);
       if (total != kScale && total != 0 && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
       long_form = long_form || __ballot(f[t][0] > 2048u || f[t][1] > 2048u || f[t][2] > 2048u || f[t][3] > 2048u) != 0;
     }
     for (int t = 0; t < a.n_tables; ++t) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        table[t * 256 + lane * 4 + r] = make_enc_entry(long_form ? kEncLong : kEncShort, f[t][r], cum[t]);
+        if ((r & (W - 1)) == wave)
+          table[t * 256 + lane * 4 + r] = make_enc_entry(long_form ? kEncLong : kEncShort, f[t][r], cum[t]);
         cum[t] += f[t][r];
       }
     }
   }
-  wave_sync();
+  __syncthreads();
+  if (chunk >= a.units_per_stream) return;  // no workgroup barrier below
 
-  const uint32_t len = (uint32_t)a.syms_per_stream;
-  const uint8_t *ubase = a.sym_in + unit * a.syms_per_stream;
+  const int64_t unit = stream * a.units_per_stream + chunk;
+  const int64_t begin = chunk * a.unit_syms;
+  const int64_t rest = a.syms_per_stream - begin;
+  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  const uint8_t *ubase = a.sym_in + stream * a.syms_per_stream + begin;
+  auto &table_of_group = table_of_group_of[wave];
+  auto &sym_stage = sym_stage_of[wave];
   const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(ubase) & 15u);
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;  // symbols in the last group, 1..32
   uint16_t *wp = a.words_out + a.word_off[unit];
-  uint16_t *wstage = word_stage;
+  uint16_t *wstage = word_stage[wave];
   uint16_t *scratch = wstage + kBatchSyms + 8 + lane;
 
   const int rl = 31 - (lane & 31);  // rANS lane carried by this hardware lane
@@ -406,7 +415,7 @@ __global__ __launch_bounds__(64) void rans_encode_kernel(const RansArgs a) {
   auto group_load = [&](int32_t glo, int32_t ghi) -> uint32_t {
     const int32_t g = ghi - kSuperGroups + lane;
     if (ghi <= 0 || g < (glo > 0 ? glo : 0) || g >= ghi) return 0u;
-    return group_table(a, unit, 0, g, 256u, &bad_depth);
+    return group_table(a, stream, begin, g, 256u, &bad_depth);
   };
   auto stage_load = [&](int32_t glo, int32_t ghi, uint4 v[kStagePieces], bool take[kStagePieces]) {
     // byte offsets relative to the unit's first symbol; pointers are formed by plain pointer arithmetic
@@ -3394,6 +3403,26 @@ int check_depths(int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_p
 bool encode_depths_in_pairs(int64_t n_units) {
   return (n_units > 7 * kComputeUnits && n_units <= 12 * kComputeUnits) || n_units > 28 * kComputeUnits;
 }
+// Chunks with a table per depth: while few wavefronts are resident a unit to each has the shorter step (chunks of 65,536,
+// one and two to a wavefront: 768 of them 187 and 253 us, 1536 222 and 300, 2048 225 and 270, 2560 265 and 307, 3072 378
+// and 306, 4096 392 and 317; of 4096: 768 25 and 30, 2560 32 and 33, 3072 41 and 34).
+constexpr int64_t kFewChunks = 10 * kComputeUnits;
+template <int W>
+void launch_encode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+  hipLaunchKernelGGL(rans_encode_kernel<W>, dim3(grid), dim3(W * 64), 0, st, a);
+}
+void launch_encode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
+  int w = 1;
+  while (w < kMaxWaves && w < a.units_per_stream) w *= 2;
+  a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
+  const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);  // at most the grid checked before
+  switch (w) {
+    case 1: launch_encode_depths_of<1>(a, grid, st); break;
+    case 2: launch_encode_depths_of<2>(a, grid, st); break;
+    case 4: launch_encode_depths_of<4>(a, grid, st); break;
+    default: launch_encode_depths_of<8>(a, grid, st); break;
+  }
+}
 
 int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms,
                 const uint16_t *freq, uint32_t *states, uint16_t *words, const uint64_t *word_off,
@@ -3426,8 +3455,8 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
       } else {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       }
-    } else if (a.bits && a.units_per_stream == 1 && !encode_depths_in_pairs(a.n_units)) {
-      hipLaunchKernelGGL(rans_encode_kernel, dim3((unsigned)a.n_units), dim3(64), 0, st, a);
+    } else if (a.bits && (a.units_per_stream == 1 ? !encode_depths_in_pairs(a.n_units) : a.n_units <= kFewChunks)) {
+      launch_encode_depths(a, n_streams, st);
     } else if (a.bits && a.units_per_stream == 1) {
       hipLaunchKernelGGL((rans_encode_pair_kernel<1, true, 2, true>), dim3((unsigned)((a.n_units + 1) / 2)), dim3(64), 0, st, a);
     } else if (a.units_per_stream == 1) {

@@ -309,13 +309,17 @@ def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
     (1, 33, 256, 4096),   # a single table; two full chunks and a short one
     (4, 5, 96, 0),        # whole streams
 ])
-def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk):
-    """Two units per wavefront with a table per depth, against the oracle; word lists at every place inside a line."""
+@pytest.mark.parametrize("many", [False, True])
+def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk, many):
+    """A table per depth and one unit per wavefront (up to 2560 chunks; few whole streams: four wavefronts to a unit), or two,
+    against the oracle; word lists at every place inside a line."""
     O = oracle
     from paper_2604_15356_amd import plc
     rng = np.random.default_rng(positions + chunk)
-    S, sps = (2, 3) if chunk else (3, 599)   # (1797 streams, an odd number: two to a wavefront from 1793 on)
-    n_streams, N = S * sps, positions * spp
+    S, sps, N = 2, 3, positions * spp
+    if many:   # (whole streams: 1797, an odd number: two to a wavefront from 1793 on)
+        S, sps = 3, -(-2561 // (3 * plc.plc_units_per_stream(N, chunk))) if chunk else 599
+    n_streams = S * sps
     bits_np = rng.integers(1, n_tables + 1, (S, positions)).astype(np.uint8)
     width = 0.3 * 3.0 ** np.repeat(np.repeat(bits_np, sps, 0), spp, 1)   # the first table has an f > 2048
     sym_np = np.clip(np.round(rng.standard_normal((n_streams, N)) * width + 127), 0, 255).astype(np.uint8)
