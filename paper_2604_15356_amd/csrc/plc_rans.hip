@@ -1612,24 +1612,33 @@ __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const
   }
 }
 
-// Many streams of one unit each: a wavefront, with tables of its own, per workgroup.
-template <bool ADAPT>
-__global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
+// Many streams of one unit each: a wavefront, with tables of its own, per workgroup.  And with a table per depth chunks
+// that are few, W of a stream to a workgroup (kFewChunks).
+template <int W, bool ADAPT>
+__global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   __shared__ uint32_t lut_one[ADAPT ? 1 : kCompactTable];
   extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
   uint32_t *lut = ADAPT ? lut_per_depth : lut_one;
-  __shared__ uint16_t table_of_group[2][kBatch];  // ADAPT: table offset of each group of a batch
-  __shared__ __attribute__((aligned(16))) uint16_t ring[kRingWords + kRingMirror];
-  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[kBatchSyms];
-  const int lane = threadIdx.x;
-  const int64_t stream = blockIdx.x;
+  __shared__ uint16_t table_of_group_of[W][2][kBatch];  // ADAPT: table offset of each group of a batch
+  __shared__ __attribute__((aligned(16))) uint16_t ring[W][kRingWords + kRingMirror];
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage_of[W][kBatchSyms];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t stream = blockIdx.x / a.wgs_per_stream;
+  const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
+  auto sync = [] {
+    if constexpr (W == 1) {
+      wave_sync();
+    } else {
+      __syncthreads();
+    }
+  };
   if (a.verified_pieces && stream_verified(a, stream)) return;  // uniform: nothing to decode again
   bool bad = false;
 
   // One slot table, or one per bit depth: that of a depth the stream does not use is all zero.  The index in the
   // place of a ring.
-  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0]);
-  static_assert(sizeof(ring) >= sizeof(SlotIndex), "room for the index");
+  SlotIndex *const index = reinterpret_cast<SlotIndex *>(&ring[0][0]);
+  static_assert(sizeof(ring[0]) >= sizeof(SlotIndex), "room for the index");
   const int n_tables = ADAPT ? a.n_tables : 1;
   bool ok = true;
   for (int t = 0; t < n_tables; ++t) {
@@ -1637,30 +1646,38 @@ __global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
     const uint32_t total = load_freq4(a.freq + (stream * n_tables + t) * 256, lane, f, &cum);
     ok = ok && (total == kScale || (ADAPT && total == 0));
     uint32_t *lt = lut + t * kCompactTable;
-    if (total == kScale) {  // uniform
+    if (total == kScale && wave == 0) {  // uniform
       build_slot_index(index, f, cum, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         lt[lane * 4 + r] = ((f[r] - 1u) & 0xfffu) | (cum << 16);  // a symbol that does not occur is never looked up
         cum += f[r];
       }
-      wave_sync();
-      for_each_slot<64>(index, [&](uint32_t o, uint32_t row) {
+    }
+    sync();
+    if (total == kScale) {
+      for_each_slot<W * 64>(index, [&](uint32_t o, uint32_t row) {
         reinterpret_cast<uint8_t *>(lt + 256)[o] = (uint8_t)(row >> 24);
       });
     } else {
-      for (uint32_t o = threadIdx.x; o < kCompactTable; o += 64) lt[o] = 0u;
+      for (uint32_t o = threadIdx.x; o < kCompactTable; o += W * 64) lt[o] = 0u;
     }
-    wave_sync();  // before the index serves the next table, or the ring takes its place
+    sync();  // before the index serves the next table, or the ring takes its place
   }
-  const uint64_t off = a.word_off[stream];
-  const uint32_t n = a.n_words_in[stream];
+  if (chunk >= a.units_per_stream) return;  // no workgroup barrier below
+  const int64_t unit = stream * a.units_per_stream + chunk;
+  const uint64_t off = a.word_off[unit];
+  const uint32_t n = a.n_words_in[unit];
   if (!ok || off > a.words_len || (uint64_t)n > a.words_len - off) {  // (not a table: nothing can be decoded)
     if (lane == 0) raise(a.status, PLC_ERR_CORRUPT);
     return;
   }
-  const uint32_t len = (uint32_t)a.syms_per_stream;
-  uint8_t *ubase = a.sym_out + stream * a.syms_per_stream;
+  const int64_t begin = chunk * a.unit_syms;
+  const int64_t rest = a.syms_per_stream - begin;
+  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
+  auto &table_of_group = table_of_group_of[wave];
+  auto &sym_stage = sym_stage_of[wave];
   const bool out_aligned = (reinterpret_cast<uintptr_t>(ubase) & 15u) == 0;
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
   const uint32_t top_syms = len - (uint32_t)(G - 1) * kLanes;
@@ -1670,7 +1687,7 @@ __global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
   const int32_t lo = (int32_t)((reinterpret_cast<uintptr_t>(first_word) & (uintptr_t)(kBlockWords * 2 - 1)) >> 1);
   const uint16_t *aligned_base = first_word - lo;  // pointer arithmetic keeps the loads global, not flat
   const int32_t hi = lo + (int32_t)n;
-  uint16_t *myring = ring;
+  uint16_t *myring = ring[wave];
 
   // one 16-byte piece (eight words) of block blk per lane, if the piece holds a word of this unit
   auto block_load = [&](int32_t blk, uint4 &v) -> bool {
@@ -1705,7 +1722,7 @@ __global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
   const int rl = lane & (kLanes - 1);
   const uint32_t below = (1u << rl) - 1u;
   const bool top_active = (uint32_t)rl < top_syms;
-  uint32_t x = a.states_in[stream * kLanes + rl];
+  uint32_t x = a.states_in[unit * kLanes + rl];
 
   // Full batches of 16 groups are fully unrolled; the groups that do not fill a batch (and the last
   // group if it is ragged) form a tail that runs in a rolled loop.
@@ -1719,7 +1736,7 @@ __global__ __launch_bounds__(64) void rans_decode_kernel(const RansArgs a) {
   auto group_load = [&](int32_t g0) -> uint32_t {
     const int32_t g = g0 + lane;
     if (!ADAPT || lane >= kBatch || g >= G) return 0u;
-    return group_table(a, stream, 0, g, kCompactTable, &bad_depth);
+    return group_table(a, stream, begin, g, kCompactTable, &bad_depth);
   };
   if (ADAPT) {
     const uint32_t gt0 = group_load(0);
@@ -3310,6 +3327,21 @@ RansArgs again_args(RansArgs a) {
   return a;
 }
 
+// Wavefronts of per_wave units each to a workgroup, for units that share a stream's tables: a workgroup holds all of a
+// stream's if eight wavefronts can, so that the tables are built once and the last workgroup is not nearly empty.  (Two
+// units to a wavefront, decoding, and workgroups of the next smaller size, a stream's second one with few units: 4096
+// streams of three chunks of 1024 37 and 49 us, of five 44 and 58, 1024 of six chunks of 4096 33 and 52, 768 streams of
+// 131,072 symbols in ten pieces, given the tokens, 206 and 250.)  Long units that are fewer than that leaves workgroups
+// for every compute unit are spread over them (64 streams of ten chunks of 65,536: 276 and 261 us; chunks of 8192 are
+// better off together, 45 and 46).
+constexpr int64_t kSpreadSyms = 32768;
+int waves_per_workgroup(int64_t n_streams, int64_t units, int per_wave, int64_t unit_syms) {
+  auto wgs = [&](int waves) { return n_streams * ((units + per_wave * waves - 1) / (per_wave * waves)); };
+  int w = 1;
+  while (w < kMaxWaves && per_wave * w < units && (unit_syms < kSpreadSyms || wgs(2 * w) >= kComputeUnits)) w *= 2;
+  return w;
+}
+
 template <int W>  // workgroups of 2 W units of one stream
 void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
   if (a.bits) {
@@ -3322,19 +3354,10 @@ void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(W * 64), 0, st, a);
   }
 }
-// Two or more units per stream, or pieces: a workgroup that holds all of a stream's if eight wavefronts can, so that the
-// table is built once and the last workgroup is not nearly empty.  (Workgroups of the next smaller size, a stream's second
-// one with few units: 4096 streams of three chunks of 1024 37 and 49 us, of five 44 and 58, 1024 of six chunks of 4096 33 and
-// 52, 768 streams of 131,072 symbols in ten pieces, given the tokens, 206 and 250.)  Long units that are fewer than that leaves
-// workgroups for every compute unit are spread over them (64 streams of ten chunks of 65,536: 276 and 261 us; chunks of
-// 8192 are better off together, 45 and 46).
-constexpr int64_t kSpreadSyms = 32768;
+// Two or more units per stream, or pieces.
 void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
   const int64_t units = a.pieces ? a.pieces : a.units_per_stream;
-  const int64_t unit_syms = a.pieces ? (int64_t)a.piece_batches * kBatchSyms : a.unit_syms;
-  auto wgs = [&](int waves) { return n_streams * ((units + 2 * waves - 1) / (2 * waves)); };
-  int w = 1;
-  while (w < kMaxWaves && 2 * w < units && (unit_syms < kSpreadSyms || wgs(2 * w) >= kComputeUnits)) w *= 2;
+  const int w = waves_per_workgroup(n_streams, units, 2, a.pieces ? (int64_t)a.piece_batches * kBatchSyms : a.unit_syms);
   a.wgs_per_stream = (uint32_t)((units + 2 * w - 1) / (2 * w));
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
   switch (w) {
@@ -3342,6 +3365,38 @@ void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
     case 2: launch_decode_pairs_of<2>(a, grid, st); break;
     case 4: launch_decode_pairs_of<4>(a, grid, st); break;
     default: launch_decode_pairs_of<8>(a, grid, st); break;
+  }
+}
+// Encoder of chunks with a table per depth: while few wavefronts are resident a unit to each has the shorter step (chunks of 65,536,
+// one and two to a wavefront: 768 of them 187 and 253 us, 1536 222 and 300, 2048 225 and 270, 2560 265 and 307, 3072 378
+// and 306, 4096 392 and 317; of 4096: 768 25 and 30, 2560 32 and 33, 3072 41 and 34).
+constexpr int64_t kFewChunks = 10 * kComputeUnits;
+// So it is in the decoder (768 chunks of 65,536 351 and 365 us, 1536 366 and 393, 2560 388 and 404, 3072 703 and 399; of
+// 4096: 768 38 and 40, 2560 45 and 47, 3072 65 and 43), but for units that are to have their tiles' escapes counted, which
+// only the other kernel does: there from this length on (to K and V, 512 chunks of 262,144 1431 and 1520 us, 1536 of
+// 65,536 523 and 525).
+constexpr int64_t kFewChunkSymsCounted = 1 << 17;
+bool decode_depths_alone(const RansArgs &a, bool counted) {
+  return a.bits && !a.pieces && a.n_units <= kFewChunks && !(counted && a.unit_syms < kFewChunkSymsCounted);
+}
+template <int W>
+void launch_decode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+  // (split tables: 5 KB per depth instead of 16 lets three times the wavefronts in)
+  const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((rans_decode_kernel<W, true>), dim3(grid), dim3(W * 64), lds, st, a);
+}
+// A table per depth, a unit per wavefront.
+void launch_decode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
+  const int w = waves_per_workgroup(n_streams, a.units_per_stream, 1, a.unit_syms);
+  a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
+  const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
+  switch (w) {
+    case 1: launch_decode_depths_of<1>(a, grid, st); break;
+    case 2: launch_decode_depths_of<2>(a, grid, st); break;
+    case 4: launch_decode_depths_of<4>(a, grid, st); break;
+    default: launch_decode_depths_of<8>(a, grid, st); break;
   }
 }
 // One unit per stream.
@@ -3355,17 +3410,13 @@ void launch_decode_streams(const RansArgs &a, hipStream_t st) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(rans_decode_depths_kernel<0>, grid, dim3(depths_threads(0)), lds, st, a);
   } else if (a.bits) {
-    // (the split tables here too: 5 KB per depth instead of 16 lets three times the wavefronts in)
-    const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(rans_decode_kernel<true>, grid, dim3(64), lds, st, a);
+    launch_decode_depths(a, a.n_units, st);
   } else if (a.n_units <= kChainMaxUnits) {
     hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), grid, dim3(128), 0, st, a);
   } else {
     // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in (twice as many
     // where every one-wavefront workgroup has a table of its own).
-    hipLaunchKernelGGL(rans_decode_kernel<false>, grid, dim3(64), 0, st, a);
+    hipLaunchKernelGGL((rans_decode_kernel<1, false>), grid, dim3(64), 0, st, a);
   }
 }
 
@@ -3403,17 +3454,12 @@ int check_depths(int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_p
 bool encode_depths_in_pairs(int64_t n_units) {
   return (n_units > 7 * kComputeUnits && n_units <= 12 * kComputeUnits) || n_units > 28 * kComputeUnits;
 }
-// Chunks with a table per depth: while few wavefronts are resident a unit to each has the shorter step (chunks of 65,536,
-// one and two to a wavefront: 768 of them 187 and 253 us, 1536 222 and 300, 2048 225 and 270, 2560 265 and 307, 3072 378
-// and 306, 4096 392 and 317; of 4096: 768 25 and 30, 2560 32 and 33, 3072 41 and 34).
-constexpr int64_t kFewChunks = 10 * kComputeUnits;
 template <int W>
 void launch_encode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
   hipLaunchKernelGGL(rans_encode_kernel<W>, dim3(grid), dim3(W * 64), 0, st, a);
 }
 void launch_encode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
-  int w = 1;
-  while (w < kMaxWaves && w < a.units_per_stream) w *= 2;
+  const int w = waves_per_workgroup(n_streams, a.units_per_stream, 1, a.unit_syms);
   a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);  // at most the grid checked before
   switch (w) {
@@ -3520,11 +3566,16 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
       hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3((unsigned)(n_streams * a.pieces)), dim3(128), 0, st, a);
     } else if (a.pieces || a.units_per_stream > 1) {
       // (pieces begin at whole tiles if the stream is whole tiles: the encoder's rounds are as long as a tile)
-      if (tile_cnt && (a.pieces ? syms_per_stream : a.unit_syms) % kTileSyms == 0) {
-        a.tile_cnt = tile_cnt;
-        counts->counted = true;
+      const bool tiles = tile_cnt && (a.pieces ? syms_per_stream : a.unit_syms) % kTileSyms == 0;
+      if (decode_depths_alone(a, tiles)) {
+        launch_decode_depths(a, n_streams, st);
+      } else {
+        if (tiles) {
+          a.tile_cnt = tile_cnt;
+          counts->counted = true;
+        }
+        launch_decode_pairs(a, n_streams, st);
       }
-      launch_decode_pairs(a, n_streams, st);
     }
     if (a.pieces && counts && (counts->counted || !rest)) {
       counts->piece_state = a.piece_state;

@@ -66,11 +66,13 @@ def test_chunks_come_back(dev, kind, N, chunk):
         assert same.all()
 
 
+@pytest.mark.parametrize("many", [False, True])   # up to 2560 units have a wavefront each
 @pytest.mark.parametrize("n_tables,positions,chunk", [(4, 301, 1024), (4, 64, 96), (3, 100, 4096), (1, 77, 512), (2, 40, 32)])
-def test_chunks_come_back_with_a_table_per_depth(dev, n_tables, positions, chunk):
+def test_chunks_come_back_with_a_table_per_depth(dev, n_tables, positions, chunk, many):
     from paper_2604_15356_amd import plc
-    spp, streams, sps, rng = 96, 4, 2, np.random.default_rng(positions)
+    spp, sps, rng = 96, 2, np.random.default_rng(positions)
     N = spp * positions
+    streams = sps * (-(-2561 // (sps * plc.plc_units_per_stream(N, chunk))) if many else 2)
     bits = rng.integers(1, n_tables + 1, (streams // sps, positions)).astype(np.uint8)
     depth = np.repeat(np.repeat(bits, sps, 0), spp, 1)
     data = np.clip(np.round(rng.normal(127, 2.0 ** depth)), 0, 255).astype(np.uint8)
@@ -94,19 +96,29 @@ def test_chunks_come_back_with_a_table_per_depth(dev, n_tables, positions, chunk
     assert int(status.item()) == 0 and torch.equal(out, symbols)
 
 
-@pytest.mark.parametrize("chunk,n,d,sigma", [(2048, 300, 128, 1.0), (4096, 100, 72, 2.0), (1024, 300, 128, 1.0),
-                                             (8192, 33, 40, 3.0), (2048, 8, 128, 3.0)])
-def test_escapes_counted_by_the_decoder(dev, chunk, n, d, sigma):
+@pytest.mark.parametrize("path,chunk,n,d,sigma", [("mean", 2048, 300, 128, 1.0), ("mean", 4096, 100, 72, 2.0),
+                                                  ("mean", 1024, 300, 128, 1.0), ("mean", 8192, 33, 40, 3.0),
+                                                  ("mean", 2048, 8, 128, 3.0), ("adapt", 2048, 300, 128, 1.0),
+                                                  # a unit per wavefront, which leaves the counts to a pass
+                                                  ("adapt", 131072, 1100, 128, 1.0)])
+def test_escapes_counted_by_the_decoder(dev, path, chunk, n, d, sigma):
     """The one call counts each tile's escapes as it decodes (where units are whole tiles), the two calls in a pass."""
+    from paper_2604_15356_amd import plc
     w = make_workload("tiny", device=dev, overrides=dict(L=2, H=3, n=n, k=3, d=d, sigma=sigma, seed=5), random_rows=True)
     codec = codec_for(w, esc_frac=1.0, chunk_syms=chunk)
-    codec.encode(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
+    vectors, adapt = (w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v), path == "adapt"
+    thr = plc.surprisal_thresholds(3.0, 3.9)
+    if adapt:
+        codec.encode_adapt(*vectors, torch.zeros((w.S, w.n), dtype=torch.int32, device=dev), thr, 0.32)
+    else:
+        codec.encode(*vectors)
     assert int(codec.esc_cnt.sum()) > 0
     outs = []
     for fused in (True, False):
         codec.ws.fill_(0xa5)
         out = [torch.full_like(w.act_k, 3.0), torch.full_like(w.act_v, 3.0)]
-        codec.decode(w.cand_k, w.cand_v, w.probs, *out, fused=fused)
+        args = (w.cand_k, w.cand_v, w.probs, *out)
+        codec.decode_adapt(*args, thr, 0.32, fused=fused) if adapt else codec.decode(*args, fused=fused)
         codec.check_status("decode")
         assert torch.equal(codec.dec_symbols, codec.symbols)
         outs.append([o.view(torch.int16) for o in out])
