@@ -1156,7 +1156,8 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
                              symbols, r, restart, status, st, call);
   };
   const bool cond = chosen != nullptr, per_depth = bits != nullptr;
-  if (chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, restart != nullptr)) {
+  const int32_t points = !restart ? 0 : restart->per_stream < 2 ? 2 : restart->per_stream;  // (too few are refused below)
+  if (chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, points)) {
     const int rc = fused(kFusedCheck);
     if (rc) return rc;  // nothing enqueued
     launch_weights(p, a, probs, st);
@@ -1166,15 +1167,16 @@ int decode_and_reconstruct(const plc_dims *dims, const uint16_t *freq, const uin
   // shape, so that records of other words cost no more than it takes to tell them (256 streams of 1,048,576 symbols,
   // k = 8: 1.55 ms without records, 1.58 with such ones, and 2.35 in two calls to the end).
   const bool rest_fused =
-      restart && chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, false);
+      restart && chunk_syms == 0 && decode_fused_supported(p.n_streams, p.syms_per_stream, dims->k, cond, per_depth, 0);
   int rc = rest_fused ? fused(kFusedCheck) : PLC_OK;
   if (rc) return rc;  // nothing enqueued
-  if (rest_fused) launch_weights(p, a, probs, st);
   TileCounts counts;
   rc = rans_decode_counting(freq, states, words, words_len, word_off, n_words, p.n_streams, p.syms_per_stream,
                                 chunk_syms, 2 * dims->d, dims->L * dims->H, bits, n_tables, restart, !rest_fused, symbols,
                                 a.tile_cnt, &counts, status, stream);
-  if (!rc && counts.rest_left) rc = fused(kFusedRest);
+  if (rc) return rc;
+  if (rest_fused) launch_weights(p, a, probs, st);  // (behind the pieces: the host's time for it is hidden there)
+  if (counts.rest_left) rc = fused(kFusedRest);
   if (rc) return rc;
   return decode_floats(dims, cand_k, cand_v, probs, chosen, bits, range,
                        chosen ? PLC_TRACE_RECONSTRUCT_COND : PLC_TRACE_RECONSTRUCT, symbols, esc_vals, esc_len, esc_off,
