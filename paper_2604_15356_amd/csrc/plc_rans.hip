@@ -100,16 +100,14 @@ struct Piece {
   const uint32_t *states;      // at its start
   const uint32_t *end_states;  // at its end; null: the end of the stream
 };
-// Piece i (0 is the last) of a stream whose list has n_words words; false where the records cannot be true (the same in
-// every lane of a wavefront, all of them on).
+// Piece i (0 is the last) of a stream whose list has n_words words; false where the records cannot be true (uniform).
 __device__ __forceinline__ bool load_piece(const RansArgs &a, int64_t stream, int32_t i, uint32_t n_words, Piece *p) {
   const int32_t G = (int32_t)((a.syms_per_stream + kLanes - 1) / kLanes);
   const uint32_t *rec = a.points_in + stream * a.point_stride * PLC_RESTART_WORDS;
   const uint32_t *end = rec + (int64_t)i * a.point_step * PLC_RESTART_WORDS;
   const uint32_t *at = end + (int64_t)a.point_step * PLC_RESTART_WORDS;
   const bool first = i + 1 == a.pieces;
-  const int64_t lane = threadIdx.x & (kLanes - 1);
-  const bool other = __ballot(rec[lane] != a.states_in[stream * kLanes + lane] || rec[kLanes] != n_words) != 0;
+  const uint32_t other = (rec[0] ^ a.states_in[stream * kLanes]) | (rec[kLanes] ^ n_words);  // (these two tell)
   p->begin = (uint32_t)piece_top(G, a.pieces, a.piece_batches, i + 1) * kLanes;
   p->len = (i == 0 ? (uint32_t)a.syms_per_stream : (uint32_t)piece_top(G, a.pieces, a.piece_batches, i) * kLanes) - p->begin;
   p->words = first ? n_words : at[kLanes];
@@ -118,7 +116,7 @@ __device__ __forceinline__ bool load_piece(const RansArgs &a, int64_t stream, in
   p->esc_end = i == 0 ? rec[kLanes + 1] : rec[kLanes + 1] - end[kLanes + 1];
   p->states = first ? a.states_in + stream * kLanes : at;
   p->end_states = i == 0 ? nullptr : end;
-  return !other && p->words <= n_words && p->words_left <= p->words;
+  return (other == 0) & (p->words <= n_words) & (p->words_left <= p->words);
 }
 // What a piece's workgroup found: the decoding wavefront's word and the reconstructing one's (two alike where none is).
 __device__ __forceinline__ void report_piece(const RansArgs &a, int64_t stream, int32_t i, int which, bool good) {
