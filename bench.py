@@ -87,15 +87,10 @@ def parse():
 
 
 def one_kernel_decode(codec, path="mean"):
-    """Whether the single decode call reconstructs inside the entropy decoder for this codec's shape: the bounds that
-    decode_fused_supported() in csrc/plc_rans.hip has."""
-    if codec.chunk_syms or codec.k > 8:
-        return False
-    if codec.restart is not None:   # in pieces: from some size on two calls are faster
-        return path != "adapt" and codec.n_streams * codec.N < (1 << 23 if path == "cond" else 1 << 25)
-    if path == "adapt":
-        return codec.n_streams <= 512
-    return path == "mean" or codec.k <= 4 or codec.n_streams <= 2048
+    """Whether the single decode call reconstructs inside the entropy decoder for this codec's shape."""
+    from paper_2604_15356_amd import plc
+    return plc.plc_decode_one_kernel(codec.n_streams, codec.N, codec.chunk_syms, codec.k, path != "mean", path == "adapt",
+                                     0 if codec.restart is None else codec.restart.shape[1])
 
 
 class KernelTimer:

@@ -256,6 +256,12 @@ typedef struct plc_restart {
  * than a stream).  Host call. */
 int32_t plc_restart_points(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms);
 
+/* Whether plc_rans_decode_reconstruct and its kin reconstruct inside the entropy decoder for this shape (1), or make
+ * the two calls they stand for (0), whichever is faster: k candidates, cond with the token-conditional prediction,
+ * per_depth with a table per bit depth besides, per_stream records of a stream (0: without restart points).  Host call. */
+int32_t plc_decode_one_kernel(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, int32_t k, int32_t cond,
+                              int32_t per_depth, int32_t per_stream);
+
 int plc_rans_encode_restart(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,
                             int32_t chunk_syms, const uint16_t *freq, uint32_t *states,
                             uint16_t *words, const uint64_t *word_off, uint64_t word_cap_per_unit,

@@ -114,9 +114,9 @@ struct ReconView {
   const uint64_t *esc_off;
 };
 // Whether plc_rans.hip has a decoder that reconstructs as it goes for this many streams and candidates
-// (cond: token-conditional prediction; per_depth: with one table per bit depth besides; restart: in pieces between
-// restart points).
-bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart);
+// (cond: token-conditional prediction; per_depth: with one table per bit depth besides; points: in pieces, between so
+// many restart points of a stream, 0: none), and is not slower there than two calls.
+bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, int32_t points);
 // That decoder: plc_rans_decode with one unit per stream, plus out = prediction + symbol * delta for every
 // component, escapes from their lists.  With recon.bits: plc_rans_decode_bucketed with n_tables tables per
 // stream instead.  The weights must be in place on `st`.

@@ -1022,13 +1022,8 @@ constexpr int32_t kPieceMinRounds = 2;
 // streams of 262,144 symbols, 8 pieces each: 117 us, the decoder with two units per wavefront 141; 256 streams: 217 and
 // 143).
 constexpr int64_t kChainMaxPieces = 1024;
-// Symbols altogether from which pieces are decoded in one call and reconstructed in another.  Fewer go to the kernel
-// that does both, in pieces of several records: a round of workgroups (two or, up to kCompactMaxK candidates, four to a
-// compute unit) is best there, whose start is then paid once.  k = 8, 12, 32, 64, 128, 256 million symbols, one kernel
-// and two calls: 100 and 112, 157 and 158, 290 and 280, 577 and 530, 1140 and 1065 us; k = 4: 74 and 87, 112 and 112,
-// 190 and 186, 365 and 347, 716 and 697 us.  Given the tokens (k = 8), 4, 12, 32 million: 53 and 59, 96 and 86, 167 and
-// 126 us.
-constexpr int64_t kTwoCallSymbols = 1ll << 25, kTwoCallSymbolsCond = 1ll << 23;
+// The decoder that reconstructs too takes pieces of several records, so that there is one round of workgroups (two or,
+// up to kCompactMaxK candidates, four to a compute unit), whose start is then paid once.
 constexpr int64_t kPiecesPerRound = 512, kPiecesPerRoundCompact = 1024;
 // From this many streams on (more than two workgroups per compute unit) the decoder that reconstructs takes
 // its three-block ring where k <= 4 lets three workgroups share a compute unit.
@@ -3286,6 +3281,16 @@ int32_t restart_rounds(int64_t syms_per_stream) {
   const int32_t head = G % kBatch ? G % kBatch : kBatch;
   return ((G - head) / kBatch + 1 + 3) / 4;
 }
+// How a stream of so many records is cut: returns the pieces, 0 where it is too short for two.
+int32_t plan_pieces(RansArgs *a, int32_t per_stream) {
+  const int32_t rounds = restart_rounds(a->syms_per_stream);
+  const int32_t per = (rounds + per_stream - 1) / per_stream;
+  a->point_stride = per_stream;
+  a->piece_batches = 4 * per;
+  a->point_step = 1;
+  const int32_t pieces = (rounds + per - 1) / per;
+  return pieces < 2 ? 0 : pieces;
+}
 // Restart points, for a call with one unit per stream (check_common before).
 int check_restart(const plc_restart *r, bool decode, RansArgs *a) {
   if (!r) return PLC_OK;
@@ -3293,16 +3298,11 @@ int check_restart(const plc_restart *r, bool decode, RansArgs *a) {
   if (r->per_stream < 2 || r->per_stream > (1 << 20) || !r->points || reinterpret_cast<uintptr_t>(r->points) % 4)
     return PLC_ERR_INVALID;
   if (decode && (!r->scratch || reinterpret_cast<uintptr_t>(r->scratch) % 4)) return PLC_ERR_INVALID;
-  const int32_t rounds = restart_rounds(a->syms_per_stream);
-  const int32_t per = (rounds + r->per_stream - 1) / r->per_stream;
-  a->point_stride = r->per_stream;
-  a->piece_batches = 4 * per;
-  a->point_step = 1;
+  const int32_t pieces = plan_pieces(a, r->per_stream);
   if (decode) {
     a->points_in = r->points;
     a->piece_state = r->scratch;
-    a->pieces = (rounds + per - 1) / per;
-    if (a->pieces < 2) a->pieces = 0;
+    a->pieces = pieces;
   } else {
     a->points_out = r->points;
   }
@@ -3316,6 +3316,47 @@ void merge_pieces(RansArgs *a, int64_t n_streams, int64_t most) {
   a->piece_batches *= a->point_step;
   a->pieces = (a->pieces + a->point_step - 1) / a->point_step;
   if (a->pieces < 2) a->pieces = 0;
+}
+void merge_pieces_for(RansArgs *a, int64_t n_streams, int k) {
+  merge_pieces(a, n_streams, k <= kCompactMaxK ? kPiecesPerRoundCompact : kPiecesPerRound);
+}
+// Whether streams in pieces are better decoded by one call and reconstructed by another.  The one kernel takes the
+// chain of its longest piece, once per round of workgroups; two calls that of shorter pieces, some 15 to 28 us more of
+// starts and passes, the time of the memory they move, and a stream's tiles are added up by one workgroup.  Fitted to
+// 947 shapes, 1 to 1024 streams of 8192 to 16,777,216 symbols, 4 to 134 million together, both ways timed for each: on
+// average 0.03 % is lost by what it chooses and 4 % at the most (a bound on the symbols altogether lost 2.6 and 46 %).
+// For instance, one kernel and two calls in us: given the tokens, k = 8, 1024 streams of 8192 64 and 73, of 32,768 140
+// and 96; 128 of 65,536 61 and 70; the mean of 4, 1024 of 16,384 65 and 79; of 5, 288 of 65,536 131 and 91, 105 of 124,320
+// 95 and 102; of 8, 512 of 131,072 288 and 278.
+bool pieces_in_two_calls(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, int32_t points) {
+  RansArgs a = {};
+  a.syms_per_stream = syms_per_stream;
+  a.pieces = plan_pieces(&a, points);
+  if (!a.pieces) return false;
+  auto piece_syms = [&] {
+    const int64_t syms = a.pieces ? (int64_t)a.piece_batches * kBatchSyms : syms_per_stream;
+    return syms < syms_per_stream ? syms : syms_per_stream;
+  };
+  const int64_t two_chain = piece_syms();
+  merge_pieces_for(&a, n_streams, k);
+  const int64_t units = n_streams * (a.pieces ? a.pieces : 1);
+  const bool dense = units > kDenseStreams;
+  const int64_t at_once = dense && k <= kCompactMaxK ? 4 * kComputeUnits
+                          : dense && !cond && k <= kDenseMaxK ? 3 * kComputeUnits : 2 * kComputeUnits;
+  // by how much the one kernel's is longer
+  const double chain = (double)(piece_syms() * ((units + at_once - 1) / at_once) - two_chain);
+  double per_step, more, per_symbol;  // ns a symbol of the chain; us; ns a symbol
+  if (cond) {
+    per_step = k <= kCompactMaxK ? 2.22 : 1.45, more = 28.5, per_symbol = 0.6e-3;
+  } else {
+    per_step = k <= kCompactMaxK ? 2.42 + 0.163 * k : k > kDenseMaxK ? 2.05 : dense ? 2.31 : 1.91;
+    more = k <= kCompactMaxK ? 28.6 : k > kDenseMaxK ? 24.5 : 19.5;
+    per_symbol = 0.51e-3 + 0.32e-3 * k;
+  }
+  // (where a stream is no whole tiles, the escapes are counted in a pass of its own)
+  if (syms_per_stream % kTileSyms) more += cond ? 7.0 : 12.0;
+  return 1e-3 * per_step * chain >
+         more + 1e-3 * per_symbol * (double)(n_streams * syms_per_stream) + 2.8e-6 * (double)syms_per_stream;
 }
 // The arguments of the launch behind the pieces', which decodes the streams whose pieces do not agree.
 RansArgs again_args(RansArgs a) {
@@ -3604,8 +3645,8 @@ int rans_decode_counting(const uint16_t *freq, const uint32_t *states, const uin
                      symbols, status, stream, a, restart, rest, tile_cnt, counts);
 }
 
-bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, bool restart) {
-  if (restart && (per_depth || n_streams * syms_per_stream >= (cond ? kTwoCallSymbolsCond : kTwoCallSymbols))) return false;
+bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, bool cond, bool per_depth, int32_t points) {
+  if (points && (per_depth || (k <= 8 && pieces_in_two_calls(n_streams, syms_per_stream, k, cond, points)))) return false;
   // Candidates that fit the registers of one wavefront kRecDepth batches deep, and whole chunks.  As to
   // the number of streams: two or three workgroups per compute unit run at a time, and a round takes its
   // chain's time or the HBM time of its reconstruction, whichever is longer.  With the weighted mean the two
@@ -3616,7 +3657,7 @@ bool decode_fused_supported(int64_t n_streams, int64_t syms_per_stream, int k, b
   // 7.9 ms); with more candidates (two workgroups) the many-unit decoder's shorter total wins from some eight
   // rounds on (16,384 streams, k = 8: 28.4 against 22.5 ms): 2048 streams at most.  With one table per depth a
   // round is 256 workgroups, and the bound of that decoder applies.
-  // (Streams in pieces have a line of their own: kTwoCallSymbols.)
+  // (Streams in pieces have a line of their own besides: pieces_in_two_calls.)
   const int64_t most = per_depth ? kDepthsMaxUnits : (cond && k > 4) ? 2048 : INT64_MAX;
   return n_streams >= 1 && n_streams <= most && k >= 1 && k <= 8 && syms_per_stream >= kChunk &&
          syms_per_stream % kChunk == 0;
@@ -3631,7 +3672,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
   if (!rc) rc = check_restart(restart, true, &a);
   if (rc) return rc;
   if (!decode_fused_supported(n_streams, syms_per_stream, recon.k, recon.chosen != nullptr, recon.bits != nullptr,
-                              restart != nullptr && call == kFusedDecode))
+                              restart && call == kFusedDecode ? restart->per_stream : 0))
     return PLC_ERR_INVALID;
   if (!symbols || !freq || !states || !word_off || !n_words || !status) return PLC_ERR_INVALID;
   if (words_len > 0 && !words) return PLC_ERR_INVALID;
@@ -3661,7 +3702,7 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
     if (call == kFusedRest) {
       a = again_args(a);
     } else {
-      merge_pieces(&a, n_streams, recon.k <= kCompactMaxK ? kPiecesPerRoundCompact : kPiecesPerRound);
+      merge_pieces_for(&a, n_streams, recon.k);
     }
     // With pieces: those, then a launch over the streams, in which one whose pieces agree is left alone.
     for (int round = a.pieces ? 0 : 1; round < 2; ++round) {
@@ -3711,6 +3752,14 @@ extern "C" int32_t plc_restart_points(int64_t n_streams, int64_t syms_per_stream
   int32_t points = (int32_t)(kPiecesWanted / n_streams);
   if (points > most) points = most;
   return points < 2 ? 0 : points;
+}
+
+extern "C" int32_t plc_decode_one_kernel(int64_t n_streams, int64_t syms_per_stream, int32_t chunk_syms, int32_t k,
+                                         int32_t cond, int32_t per_depth, int32_t per_stream) {
+  if (n_streams < 1 || syms_per_stream < 1 || syms_per_stream >= (1ll << 31) - 1024 || chunk_syms != 0 ||
+      (per_stream && (per_stream < 2 || n_streams > kPipeMaxUnits)))
+    return 0;
+  return decode_fused_supported(n_streams, syms_per_stream, k, cond != 0, per_depth != 0, per_stream);
 }
 
 extern "C" int plc_rans_encode_restart(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stream,

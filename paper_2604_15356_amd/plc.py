@@ -30,7 +30,7 @@ EXPORTS = ("plc_version", "plc_strerror", "plc_workspace_bytes", "plc_units_per_
            "plc_surprisal_thresholds", "plc_surprisal_bits", "plc_predict_residual_adapt", "plc_reconstruct_adapt",
            "plc_histogram_bucketed", "plc_build_freq_bucketed", "plc_rans_encode_bucketed",
            "plc_rans_decode_bucketed",
-           "plc_restart_points", "plc_rans_encode_restart", "plc_rans_decode_restart",
+           "plc_restart_points", "plc_decode_one_kernel", "plc_rans_encode_restart", "plc_rans_decode_restart",
            "plc_rans_encode_bucketed_restart", "plc_rans_decode_bucketed_restart",
            "plc_rans_decode_reconstruct_restart", "plc_rans_decode_reconstruct_cond_restart",
            "plc_rans_decode_reconstruct_adapt_restart",
@@ -113,6 +113,8 @@ def lib() -> C.CDLL:
         rp = C.POINTER(plc_restart)
         L.plc_restart_points.restype = i32
         L.plc_restart_points.argtypes = [i64, i64, i32]
+        L.plc_decode_one_kernel.restype = i32
+        L.plc_decode_one_kernel.argtypes = [i64, i64, i32, i32, i32, i32, i32]
         L.plc_rans_encode_restart.argtypes = [p, i64, i64, i32, p, p, p, p, u64, p, rp, p, p]
         L.plc_rans_decode_restart.argtypes = [p, p, p, u64, p, p, i64, i64, i32, rp, p, p, p]
         L.plc_rans_encode_bucketed_restart.argtypes = [p, i64, i64, i32, i32, i32, p, i32, p, p, p, p, u64, p, rp, p,
@@ -175,6 +177,11 @@ def plc_units_per_stream(syms_per_stream: int, chunk_syms: int) -> int:
 
 def plc_restart_points(n_streams: int, syms_per_stream: int, chunk_syms: int) -> int:
     return int(lib().plc_restart_points(int(n_streams), int(syms_per_stream), int(chunk_syms)))
+
+
+def plc_decode_one_kernel(n_streams, syms_per_stream, chunk_syms, k, cond=False, per_depth=False, per_stream=0) -> bool:
+    return bool(lib().plc_decode_one_kernel(int(n_streams), int(syms_per_stream), int(chunk_syms), int(k), int(cond),
+                                            int(per_depth), int(per_stream)))
 
 
 def _ptr(t, dtype=None):

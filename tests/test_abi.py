@@ -40,6 +40,22 @@ def test_host_only_calls():
     assert ws >= 4096 * 8 * 4 + 2 * 4 * tiles and ws % 256 == 0
 
 
+def test_one_kernel_or_two_calls():
+    one = plc.plc_decode_one_kernel
+    assert one(256, 1 << 20, 0, 8) and one(5120, 1 << 17, 0, 4) and not one(256, 1 << 20, 4096, 8)
+    assert not one(256, 1 << 20, 0, 9) and not one(256, 1001, 0, 4)
+    assert one(512, 1 << 16, 0, 8, cond=True, per_depth=True) and not one(513, 1 << 16, 0, 8, cond=True, per_depth=True)
+    assert one(2048, 1 << 16, 0, 8, cond=True) and not one(2049, 1 << 16, 0, 8, cond=True)
+    # in pieces: long ones, and more rounds of them than one, are for two calls
+    points = lambda streams, n: plc.plc_restart_points(streams, n, 0)
+    assert one(8, 1 << 16, 0, 4, per_stream=points(8, 1 << 16))
+    assert one(1024, 1 << 13, 0, 4, cond=True, per_stream=points(1024, 1 << 13))
+    assert not one(256, 1 << 20, 0, 8, per_stream=points(256, 1 << 20))
+    assert not one(300, 1 << 16, 0, 5, per_stream=points(300, 1 << 16))
+    assert not one(8, 1 << 16, 0, 4, cond=True, per_depth=True, per_stream=points(8, 1 << 16))
+    assert not one(1025, 1 << 16, 0, 4, per_stream=8) and not one(8, 1 << 16, 0, 4, per_stream=1)
+
+
 @pytest.mark.parametrize("field,value", [("k", 0), ("k", 33), ("d", 12), ("d", 0), ("n", 0), ("S", 0),
                                          ("delta", 0.0), ("delta", -1.0), ("delta", float("nan")),
                                          ("qmax", 0), ("qmax", 128)])

@@ -37,9 +37,9 @@ CASES = {
     # whole tiles, and where they are not leaves that to a pass of its own
     "k20_tiles": ("mean", dict(L=8, H=16, n=256, k=20, d=64, sigma=0.8), "lhnkd", 16),
     "k20_no_tiles": ("mean", dict(L=8, H=16, n=257, k=20, d=64, sigma=0.8), "lhnkd", 16),
-    # so many symbols that two calls are made
-    "k2_two_calls": ("mean", dict(L=8, H=16, n=1024, k=2, d=128, sigma=0.5), "lhnkd", 11),
-    "cond_k5_two_calls": ("cond", dict(L=8, H=16, n=256, k=5, d=128, sigma=0.4), "lhnkd", 32),
+    # so long pieces that two calls are made
+    "k2_two_calls": ("mean", dict(L=16, H=32, n=320, k=2, d=128, sigma=0.5), "lhnkd", 16),
+    "cond_k5_two_calls": ("cond", dict(L=8, H=16, n=1024, k=5, d=128, sigma=0.4), "lhnkd", 32),
     "cond_k4": ("cond", dict(L=2, H=2, n=300, k=4, d=128, sigma=0.4), "lhnkd", 4),
     "cond_k8": ("cond", dict(L=2, H=2, n=300, k=8, d=80, sigma=0.4), "lnkhd", 7),
     "adapt": ("adapt", dict(L=2, H=2, n=400, k=8, d=64), "lhnkd", 5),
@@ -111,9 +111,11 @@ def _geometry(codec):
 
 def _step(codec, case):
     """Records per piece: the one-kernel decode takes a round of workgroups' worth of pieces."""
-    path, overrides, _, _ = CASES[case]
-    symbols = codec.n_streams * codec.N
-    if path == "adapt" or overrides["k"] > 8 or symbols >= (1 << 25 if path == "mean" else 1 << 23):
+    from paper_2604_15356_amd import plc
+    path, overrides, _, points = CASES[case]
+    one = plc.plc_decode_one_kernel(codec.n_streams, codec.N, 0, overrides["k"], path != "mean", path == "adapt", points)
+    assert one == (path != "adapt" and overrides["k"] <= 8 and "two_calls" not in case)
+    if not one:
         return 1
     most = (1024 if overrides["k"] <= 4 else 512) // codec.n_streams
     return -(-(len(_geometry(codec)[1]) + 1) // most)
