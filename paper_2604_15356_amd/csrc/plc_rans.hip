@@ -3486,12 +3486,15 @@ int check_depths(int64_t syms_per_stream, int32_t chunk_syms, int32_t syms_per_p
 }
 
 // Many whole streams with a table per depth: a compute unit holds seven wavefronts with a stream each, or six with two
-// each, whose steps take longer.  Two each where that is one round instead of two, and where there are so many rounds
-// that the last one's emptiness tells little.  Streams of 131,072 symbols, one and two to a wavefront: 1500 439 and 542 us,
-// 1800 709 and 560, 2560 782 and 645, 3600 1056 and 1172, 5120 1250 and 1187; of 65,536: 3584 452 and 603, 6400 811 and
-// 861, 7200 930 and 885; of 32,768: 9000 591 and 514, 10,800 695 and 629, 16,384 985 and 908.
+// each, whose steps take longer.  Two each where that halves the rounds, and where there are so many that the last one's
+// emptiness tells little.  Streams of 131,072 symbols, one and two to a wavefront: 1536 428 and 550 us, 1900 709 and 554,
+// 3072 813 and 635, 3200 813 and 1076, 4096 1108 and 1160, 5120 1210 and 1174, 5376 1224 and 1236, 5632 1421 and 1243, 6144
+// 1492 and 1250, 6656 1584 and 1690, 7168 1615 and 1705, 7400 1783 and 1715; of 32,768: 5632 391 and 339, 7168 442 and 459,
+// 9216 575 and 504, 12,544 746 and 738, 14,336 848 and 800.
 bool encode_depths_in_pairs(int64_t n_units) {
-  return (n_units > 7 * kComputeUnits && n_units <= 12 * kComputeUnits) || n_units > 28 * kComputeUnits;
+  const int64_t one = (n_units + 7 * kComputeUnits - 1) / (7 * kComputeUnits);
+  const int64_t two = (n_units + 12 * kComputeUnits - 1) / (12 * kComputeUnits);
+  return one > 4 || 2 * two <= one;
 }
 template <int W>
 void launch_encode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
