@@ -361,7 +361,7 @@ __global__ __launch_bounds__(W * 64) void rans_encode_kernel(const RansArgs a) {
   __shared__ uint16_t table_of_group_of[W][2][kSuperGroups];  // table offset of each staged group
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage_of[W][2][kSymStage];
   __shared__ __attribute__((aligned(16))) uint16_t word_stage[W][kBatchSyms + 8 + 64];  // list + carry + scratch slots
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t stream = blockIdx.x / a.wgs_per_stream;
   const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
 
@@ -1606,8 +1606,8 @@ __device__ __forceinline__ void dec_step(uint32_t &x, const uint32_t *lut, const
 }
 
 // Many streams of one unit each: a wavefront, with tables of its own, per workgroup.  And with a table per depth chunks
-// that are few, W of a stream to a workgroup (kFewChunks).
-template <int W, bool ADAPT>
+// that are few, W of a stream to a workgroup (CHUNKS; kFewChunks).
+template <int W, bool ADAPT, bool CHUNKS>
 __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   __shared__ uint32_t lut_one[ADAPT ? 1 : kCompactTable];
   extern __shared__ uint32_t lut_per_depth[];  // ADAPT: n_tables slot tables, sized at launch
@@ -1615,9 +1615,9 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
   __shared__ uint16_t table_of_group_of[W][2][kBatch];  // ADAPT: table offset of each group of a batch
   __shared__ __attribute__((aligned(16))) uint16_t ring[W][kRingWords + kRingMirror];
   __shared__ __attribute__((aligned(16))) uint8_t sym_stage_of[W][kBatchSyms];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t stream = blockIdx.x / a.wgs_per_stream;
-  const int64_t chunk = (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave;
+  const int lane = threadIdx.x & 63, wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t stream = CHUNKS ? blockIdx.x / a.wgs_per_stream : blockIdx.x;
+  const int64_t chunk = CHUNKS ? (int64_t)(blockIdx.x - stream * a.wgs_per_stream) * W + wave : 0;
   auto sync = [] {
     if constexpr (W == 1) {
       wave_sync();
@@ -1657,17 +1657,17 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
     }
     sync();  // before the index serves the next table, or the ring takes its place
   }
-  if (chunk >= a.units_per_stream) return;  // no workgroup barrier below
-  const int64_t unit = stream * a.units_per_stream + chunk;
+  if (CHUNKS && chunk >= a.units_per_stream) return;  // no workgroup barrier below
+  const int64_t unit = CHUNKS ? stream * a.units_per_stream + chunk : stream;
   const uint64_t off = a.word_off[unit];
   const uint32_t n = a.n_words_in[unit];
   if (!ok || off > a.words_len || (uint64_t)n > a.words_len - off) {  // (not a table: nothing can be decoded)
     if (lane == 0) raise(a.status, PLC_ERR_CORRUPT);
     return;
   }
-  const int64_t begin = chunk * a.unit_syms;
+  const int64_t begin = CHUNKS ? chunk * a.unit_syms : 0;
   const int64_t rest = a.syms_per_stream - begin;
-  const uint32_t len = (uint32_t)(rest < a.unit_syms ? rest : a.unit_syms);
+  const uint32_t len = (uint32_t)(CHUNKS && a.unit_syms < rest ? a.unit_syms : rest);
   uint8_t *ubase = a.sym_out + stream * a.syms_per_stream + begin;
   auto &table_of_group = table_of_group_of[wave];
   auto &sym_stage = sym_stage_of[wave];
@@ -3418,15 +3418,15 @@ constexpr int64_t kFewChunkSymsCounted = 1 << 17;
 bool decode_depths_alone(const RansArgs &a, bool counted) {
   return a.bits && !a.pieces && a.n_units <= kFewChunks && !(counted && a.unit_syms < kFewChunkSymsCounted);
 }
-template <int W>
+template <int W, bool CHUNKS = true>
 void launch_decode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
   // (split tables: 5 KB per depth instead of 16 lets three times the wavefronts in)
   const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, CHUNKS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((rans_decode_kernel<W, true>), dim3(grid), dim3(W * 64), lds, st, a);
+  hipLaunchKernelGGL((rans_decode_kernel<W, true, CHUNKS>), dim3(grid), dim3(W * 64), lds, st, a);
 }
-// A table per depth, a unit per wavefront.
+// Chunks with a table per depth, a unit per wavefront.
 void launch_decode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
   const int w = waves_per_workgroup(n_streams, a.units_per_stream, 1, a.unit_syms);
   a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
@@ -3449,13 +3449,13 @@ void launch_decode_streams(const RansArgs &a, hipStream_t st) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(rans_decode_depths_kernel<0>, grid, dim3(depths_threads(0)), lds, st, a);
   } else if (a.bits) {
-    launch_decode_depths(a, a.n_units, st);
+    launch_decode_depths_of<1, false>(a, (unsigned)a.n_units, st);
   } else if (a.n_units <= kChainMaxUnits) {
     hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), grid, dim3(128), 0, st, a);
   } else {
     // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in (twice as many
     // where every one-wavefront workgroup has a table of its own).
-    hipLaunchKernelGGL((rans_decode_kernel<1, false>), grid, dim3(64), 0, st, a);
+    hipLaunchKernelGGL((rans_decode_kernel<1, false, false>), grid, dim3(64), 0, st, a);
   }
 }
 
