@@ -60,3 +60,13 @@ def escape_lists(symbols, act_k, act_v):
     actual values (as 16-bit words) wherever a symbol is 255, in the symbols' order."""
     both = torch.stack([act_k, act_v], dim=4).contiguous().view(torch.int16)   # [S, L, H, n, 2, d]
     return u16(both.reshape(symbols.shape)[symbols == 255])
+
+
+def ways_to_decode(codec):
+    """The fused= arguments under which a codec decodes what it holds by different kernels: in two calls, then, where it
+    has written restart points, without them, in one call (one kernel, where the shape has one) and in two."""
+    yield False
+    if codec.coded().restart is not None:
+        codec.set_restart(None)
+        yield True
+        yield False

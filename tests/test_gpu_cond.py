@@ -13,7 +13,7 @@ import pytest
 import torch
 
 from paper_2604_15356_amd.workloads import make_workload
-from tests.gpu_util import codec_for, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64
+from tests.gpu_util import codec_for, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64, ways_to_decode
 
 pytestmark = pytest.mark.gpu
 
@@ -135,12 +135,13 @@ def test_conditional_encode_decode_matches_oracle(oracle, dev, case):
     assert np.array_equal(u16(out_k).ravel(), rk32) and np.array_equal(u16(out_v).ravel(), rv32)
     # decode_cond() is the single call that reconstructs inside the entropy decoder where the shape allows
     # it; the two calls one after the other must give the same bits
-    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
-    codec.dec_symbols.zero_()
-    codec.decode_cond(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=False)
-    codec.check_status("decode_cond in two calls")
-    assert torch.equal(codec.dec_symbols, coded.symbols)
-    assert np.array_equal(u16(two_k), u16(out_k)) and np.array_equal(u16(two_v), u16(out_v))
+    for fused in ways_to_decode(codec):   # (and either without restart points)
+        two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
+        codec.dec_symbols.zero_()
+        codec.decode_cond(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=fused)
+        codec.check_status("decode_cond in other ways")
+        assert torch.equal(codec.dec_symbols, coded.symbols)
+        assert np.array_equal(u16(two_k), u16(out_k)) and np.array_equal(u16(two_v), u16(out_v))
     # recovery error is the quantiser's: |act - out| <= Delta/2 (+ half an fp16 ulp of the output)
     esc = sym.reshape(codec.n_streams, w.n, 2, w.d) == 255
     delta = float(np.float32(w.delta))

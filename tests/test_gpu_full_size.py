@@ -11,7 +11,7 @@ import pytest
 import torch
 
 from paper_2604_15356_amd.workloads import make_workload
-from tests.gpu_util import codec_for, near_tie_report, u8, u16, u32, u64
+from tests.gpu_util import codec_for, near_tie_report, u8, u16, u32, u64, ways_to_decode
 
 pytestmark = pytest.mark.gpu
 
@@ -32,16 +32,18 @@ def run():
         out_k, out_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
         codec.decode(w.cand_k, w.cand_v, w.probs, out_k, out_v)
         codec.check_status("full size")
-        # every stream, not only the sampled ones: the single decode call (one kernel that also
-        # reconstructs when chunk = 0) against the two calls one after the other
+        # every stream, not only the sampled ones: the single decode call (in pieces when chunk = 0) against the two
+        # calls one after the other, and when chunk = 0 without restart points (one kernel that also reconstructs)
         sym_one = codec.dec_symbols.clone()
         two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
-        codec.dec_symbols.zero_()
-        codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=False)
-        codec.check_status("full size, two calls")
-        assert torch.equal(codec.dec_symbols, sym_one)
-        assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
-        assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
+        for fused in ways_to_decode(codec):
+            two_k.zero_(), two_v.zero_()
+            codec.dec_symbols.zero_()
+            codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=fused)
+            codec.check_status("full size, other ways")
+            assert torch.equal(codec.dec_symbols, sym_one)
+            assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
+            assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
         del two_k, two_v, sym_one
         out[chunk] = (codec, coded, out_k, out_v)
     return w, out
@@ -165,16 +167,18 @@ def test_other_configurations_full_size(oracle, name):
     print(f"{name}: coded, checking", flush=True)
     assert torch.equal(codec.dec_symbols, coded.symbols)
     # every stream, not only the sampled ones: the single decode call (one kernel that also reconstructs where the
-    # shape has one) against the two calls one after the other
+    # shape has one) against the two calls one after the other, and where there are restart points without them
     free, _ = torch.cuda.mem_get_info()
     if free > 2.2 * out_k.numel() * out_k.element_size() * 2:
         two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
-        codec.dec_symbols.zero_()
-        codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=False)
-        codec.check_status(name + ", two calls")
-        assert torch.equal(codec.dec_symbols, coded.symbols)
-        assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
-        assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
+        for fused in ways_to_decode(codec):
+            two_k.zero_(), two_v.zero_()
+            codec.dec_symbols.zero_()
+            codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=fused)
+            codec.check_status(name + ", other ways")
+            assert torch.equal(codec.dec_symbols, coded.symbols)
+            assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
+            assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
         del two_k, two_v
         print(f"{name}: one call and two calls agree on every stream", flush=True)
     freq = coded.freq.to(torch.int32) & 0xffff
@@ -229,13 +233,15 @@ def test_token_conditional_full_size(oracle, name, chunk):
     codec.check_status("token-conditional, full size")
     assert np.array_equal(codec.dec_chosen.cpu().numpy(), ch)
     assert torch.equal(codec.dec_symbols, coded.symbols)
-    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)      # the two calls, on every stream
-    codec.dec_symbols.zero_()
-    codec.decode_cond(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=False)
-    codec.check_status("token-conditional, two calls")
-    assert torch.equal(codec.dec_symbols, coded.symbols)
-    assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
-    assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
+    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
+    for fused in ways_to_decode(codec):    # the two calls and, without restart points, the one kernel, on every stream
+        two_k.zero_(), two_v.zero_()
+        codec.dec_symbols.zero_()
+        codec.decode_cond(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=fused)
+        codec.check_status("token-conditional, other ways")
+        assert torch.equal(codec.dec_symbols, coded.symbols)
+        assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
+        assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
     del two_k, two_v
     probs = w.probs.cpu().numpy()
     ienc = O.index_encode(probs, ch, word_cap=codec.idx_word_cap)
@@ -313,13 +319,15 @@ def test_surprisal_adaptive_full_size(oracle):
     bits = O.surprisal_bits(probs, ch, thr_oracle)
     assert np.array_equal(codec.dec_bits.cpu().numpy(), bits)
     assert torch.equal(codec.dec_symbols, coded.symbols)
-    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)      # the two calls, on every stream
-    codec.dec_symbols.zero_()
-    codec.decode_adapt(w.cand_k, w.cand_v, w.probs, two_k, two_v, thr, step_range, fused=False)
-    codec.check_status("surprisal-adaptive, two calls")
-    assert torch.equal(codec.dec_symbols, coded.symbols)
-    assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
-    assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
+    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
+    for fused in ways_to_decode(codec):    # the two calls and, without restart points, the one kernel, on every stream
+        two_k.zero_(), two_v.zero_()
+        codec.dec_symbols.zero_()
+        codec.decode_adapt(w.cand_k, w.cand_v, w.probs, two_k, two_v, thr, step_range, fused=fused)
+        codec.check_status("surprisal-adaptive, other ways")
+        assert torch.equal(codec.dec_symbols, coded.symbols)
+        assert torch.equal(two_k.view(torch.int16), out_k.view(torch.int16))
+        assert torch.equal(two_v.view(torch.int16), out_v.view(torch.int16))
     del two_k, two_v
     dm = O.make_dims(1, 1, 1, w.n, w.k, w.d, w.delta, w.qmax)
     spp, B = 2 * w.d, plc.MAX_BITS

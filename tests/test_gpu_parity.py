@@ -12,7 +12,8 @@ import pytest
 import torch
 
 from paper_2604_15356_amd.workloads import make_workload, random_bytes
-from tests.gpu_util import (codec_for, escape_lists, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64)
+from tests.gpu_util import (codec_for, escape_lists, near_tie_report, oracle_dims, storage_np, u8, u16, u32, u64,
+                            ways_to_decode)
 
 pytestmark = pytest.mark.gpu
 
@@ -119,13 +120,14 @@ def test_encode_decode_matches_oracle(oracle, dev, case):
                                w.probs.cpu().numpy(), sym, ref32["esc_vals"], ref32["esc_off"], mode=O.F32)
     assert np.array_equal(u16(out_k).ravel(), rk32) and np.array_equal(u16(out_v).ravel(), rv32)
     # decode() is the single call that reconstructs inside the entropy decoder where the shape allows it;
-    # the two calls one after the other must give the same bits
-    two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
-    codec.dec_symbols.zero_()
-    codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=False)
-    codec.check_status("decode in two calls")
-    assert torch.equal(codec.dec_symbols, coded.symbols)
-    assert np.array_equal(u16(two_k), u16(out_k)) and np.array_equal(u16(two_v), u16(out_v))
+    # the two calls one after the other, and either without restart points, must give the same bits
+    for fused in ways_to_decode(codec):
+        two_k, two_v = torch.zeros_like(w.act_k), torch.zeros_like(w.act_v)
+        codec.dec_symbols.zero_()
+        codec.decode(w.cand_k, w.cand_v, w.probs, two_k, two_v, fused=fused)
+        codec.check_status("decode in other ways")
+        assert torch.equal(codec.dec_symbols, coded.symbols)
+        assert np.array_equal(u16(two_k), u16(out_k)) and np.array_equal(u16(two_v), u16(out_v))
     rk64, rv64 = O.reconstruct(oracle_dims(O, w), storage_np(w.cand_k), storage_np(w.cand_v),
                                w.probs.cpu().numpy(), sym, ref32["esc_vals"], ref32["esc_off"], mode=O.F64)
     for got, want in ((u16(out_k).ravel(), rk64), (u16(out_v).ravel(), rv64)):
@@ -784,12 +786,13 @@ def test_one_call_decode_equals_two_calls_on_random_shapes(dev):
         codec.decode(w.cand_k, w.cand_v, w.probs, *ones)
         codec.check_status("decode")
         assert torch.equal(codec.dec_symbols, coded.symbols)
-        codec.dec_symbols.zero_()
-        codec.decode(w.cand_k, w.cand_v, w.probs, *twos, fused=False)
-        codec.check_status("decode in two calls")
-        assert torch.equal(codec.dec_symbols, coded.symbols)
-        for a, b in zip(ones, twos):
-            assert np.array_equal(u16(a), u16(b)), f"trial {trial}"
+        for fused in ways_to_decode(codec):
+            codec.dec_symbols.zero_()
+            codec.decode(w.cand_k, w.cand_v, w.probs, *twos, fused=fused)
+            codec.check_status("decode in other ways")
+            assert torch.equal(codec.dec_symbols, coded.symbols)
+            for a, b in zip(ones, twos):
+                assert np.array_equal(u16(a), u16(b)), f"trial {trial}"
         # token-conditional, a fifth of the positions without a candidate
         ch = w.chosen.to(torch.int32).clone()
         g = torch.Generator(device=ch.device).manual_seed(trial)
@@ -799,11 +802,12 @@ def test_one_call_decode_equals_two_calls_on_random_shapes(dev):
         codec.decode_cond(w.cand_k, w.cand_v, w.probs, *ones)
         codec.check_status("decode_cond")
         assert torch.equal(codec.dec_symbols, coded.symbols)
-        codec.dec_symbols.zero_()
-        codec.decode_cond(w.cand_k, w.cand_v, w.probs, *twos, fused=False)
-        codec.check_status("decode_cond in two calls")
-        for a, b in zip(ones, twos):
-            assert np.array_equal(u16(a), u16(b)), f"trial {trial} (token-conditional)"
+        for fused in ways_to_decode(codec):
+            codec.dec_symbols.zero_()
+            codec.decode_cond(w.cand_k, w.cand_v, w.probs, *twos, fused=fused)
+            codec.check_status("decode_cond in other ways")
+            for a, b in zip(ones, twos):
+                assert np.array_equal(u16(a), u16(b)), f"trial {trial} (token-conditional)"
 
 
 @pytest.mark.parametrize("S,L,groups,layout", [(5, 2, 3, "lhnkd"), (1, 6, 4, "lnkhd"), (2, 5, 4, "lhnkd")])

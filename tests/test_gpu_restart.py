@@ -214,7 +214,7 @@ def test_records_of_other_words_are_told_by_the_first(dev, case):
         assert not bool((state[::2] == GOOD).any())
 
 
-@pytest.mark.parametrize("case", ["k8", "k5_d24", "k4_dense", "k20", "k20_tiles", "k20_no_tiles", "cond_k8", "adapt"])
+@pytest.mark.parametrize("case", list(CASES))
 def test_damaged_words_are_reported(dev, case):
     """What the decoder reports of damage does not depend on the records, nor do the streams that have none."""
     codec, encode, decode = _setup(dev, case)
@@ -223,8 +223,25 @@ def test_damaged_words_are_reported(dev, case):
     codec.words.reshape(codec.n_streams, -1)[0, at[0]] ^= 0x155
     whole, pieces = decode(False), decode(True)
     assert whole[3] == pieces[3] == 3
-    for a, b in zip(whole[:1], pieces[:1]):
+    for a, b in zip(whole[:3], pieces[:3]):   # symbols, K and V, the damaged stream's too
         assert torch.equal(a, b)
+    good = _pieces_good(codec, case)
+    assert not bool(good[0]) and bool(good[1:].all())
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("what", ["table", "list"])
+def test_streams_that_are_refused(dev, case, what):
+    """A stream whose table is none, or whose words lie outside the list: reported, and K and V with and without records
+    the same, for it as for the others."""
+    codec, encode, decode = _setup(dev, case)
+    encode()
+    if what == "table":
+        (codec.freq_d[:, 2] if CASES[case][0] == "adapt" else codec.freq)[0, 127] += 1
+    else:
+        codec.n_words[0] = 1 << 30
+    whole, pieces = decode(False), decode(True)
+    assert whole[3] == 3 and _same(pieces, whole)
     good = _pieces_good(codec, case)
     assert not bool(good[0]) and bool(good[1:].all())
 
