@@ -93,6 +93,12 @@ def one_kernel_decode(codec, path="mean"):
                                      0 if codec.restart is None else codec.restart.shape[1])
 
 
+def restart_bits(codec):
+    """What the restart points add to a codec's output: hints, without which a decode gives the same results."""
+    points = codec.coded().restart
+    return 0 if points is None else 32 * points.numel()
+
+
 class KernelTimer:
     """HIP event pairs that libplc records around the main kernel of each call, on the stream of the call:
     one pair per kernel, timed step and launch of the step (a cache coded in groups launches each kernel
@@ -285,7 +291,8 @@ def time_run(run, args, plc, torch, calibrate=False):
     total_words = sum(int(c.n_words.to(torch.int64).sum()) for c in cs)
     n_esc = sum(int(c.esc_cnt.to(torch.int64).sum()) for c in cs)
     payload = 16 * total_words + 16 * n_esc
-    total_bits = payload + 32 * 32 * n_units + (256 * 16 + 3 * 32) * w.n_streams
+    restart = sum(restart_bits(c) for c in cs)
+    total_bits = payload + 32 * 32 * n_units + (256 * 16 + 3 * 32) * w.n_streams + restart
     roundtrip_exact = all(bool(torch.equal(c.dec_symbols, c.symbols)) for c in cs)
     max_err = run.max_abs_error()
 
@@ -310,38 +317,12 @@ def time_run(run, args, plc, torch, calibrate=False):
     # The roofline object describes the kernel a step spends most time in.  All of them are priced against
     # HBM: the step holds no contraction, and the entropy coder's chains have no tighter ceiling to name.
     # the kernels' names as the profiler prints them (template arguments included), for the traffic lookup
-    units_per_launch = n_units // L
-    streams_per_launch = w.n_streams // L
-    few = run.chunk_syms == 0 and units_per_launch <= 1024      # the whole-stream kernels for few units
-    if few:
-        points = run.codecs()[0].restart
-        pieces = 0 if points is None else w.n_streams * points.shape[1]
-        enc_name = "rans_encode_pipe_kernel<false, true>"
-        dec_name = "rans_decode_pair_kernel<8, false, true>" if pieces > 1024 else "rans_decode_chain_kernel<0, false, 4>"
-    elif run.chunk_syms == 0:                                   # many whole streams: two per wavefront
-        pairs = (units_per_launch + 1) // 2
-        enc_name = f"rans_encode_pair_kernel<1, true, {2 if 2048 < pairs <= 2816 else 4}>"
-        dec_name = "rans_decode_kernel<false>"
-    else:
-        n_full = w.syms_per_stream // run.chunk_syms
-        ups = (w.syms_per_stream + run.chunk_syms - 1) // run.chunk_syms
-        slots = n_full // 2 + (n_full & 1) + (1 if n_full < ups else 0)
-        pw = 1
-        while pw < 4 and 2 * pw <= slots:
-            pw *= 2
-        dw = 1
-        while dw < 8 and 4 * dw <= ups:
-            dw *= 2
-        enc_name, dec_name = f"rans_encode_pair_kernel<{pw}, false, 4>", f"rans_decode_pair_kernel<{dw}, false, false>"
-    dense = streams_per_launch > 512
-    if dense and w.k <= 4:              # 4-byte entries, four workgroups per compute unit
-        fused_name = f"rans_decode_depths_kernel<{w.k}, 1>"
-    else:                               # three-block word ring for k = 5, 6 and many streams
-        fused_name = f"rans_decode_chain_kernel<{w.k}, false, {3 if (dense and w.k <= 6) else 4}>"
+    enc_name = plc.plc_trace_kernel_name(plc.TRACE_RANS_ENCODE)
+    dec_name = plc.plc_trace_kernel_name(plc.TRACE_RANS_DECODE)
     symbol = {"predict_residual": f"predict_residual_hist_kernel<{w.k}>" if run.fused_counts else
               f"predict_residual_kernel<{w.k}>", "reconstruct": f"reconstruct_kernel<{w.k}, false>",
               "histogram": "histogram_kernel", "rans_encode": enc_name, "rans_decode": dec_name,
-              "rans_decode_reconstruct": fused_name}
+              "rans_decode_reconstruct": dec_name}
     dom_name = max(ms, key=lambda nm: ms[nm] * L)
     dom = kernels[dom_name]
     plain = run.layout == "lhnkd" and not args.sessions and run.chunk_syms == 0
@@ -368,6 +349,7 @@ def time_run(run, args, plc, torch, calibrate=False):
                        "decode_ms": round(decode_ms, 4), "decode_GBs": round(w.kv_bytes / decode_ms / 1e6, 1)},
         "kv_GB": round(w.kv_bytes / 1e9, 3),
         "coded_bits_per_token": round(total_bits / (w.S * w.n), 1),
+        "restart_bits_per_token": round(restart / (w.S * w.n), 1),     # part of the coded bits
         "payload_bits_per_symbol": round(payload / E, 4),
         "fp16_bits_per_token": 2 * w.L * w.H * w.d * 16,
         "escape_rate": round(n_esc / E, 6),
@@ -479,7 +461,7 @@ def side_paths(run, args, plc, torch, result):
         timer2.disarm()
         codec2.check_status("chunked steps")
         nw2 = int(codec2.n_words.to(torch.int64).sum())
-        bits2 = 16 * nw2 + 16 * n_esc + 32 * 32 * codec2.n_units + (256 * 16 + 3 * 32) * w.n_streams
+        bits2 = 16 * nw2 + 16 * n_esc + 32 * 32 * codec2.n_units + (256 * 16 + 3 * 32) * w.n_streams + restart_bits(codec2)
         ms2 = timer2.mean_ms()
         result["chunked"] = {
             "workload": run.name, "chunk_syms": args.also_chunked, "rans_units": codec2.n_units,
@@ -564,7 +546,8 @@ def side_paths(run, args, plc, torch, result):
         nw3 = int(codec3.n_words.to(torch.int64).sum())
         esc3 = int(codec3.esc_cnt.to(torch.int64).sum())
         idx_bits = 16 * int(codec3.idx_n_words.to(torch.int64).sum()) + 32 * 32 * w.S
-        bits3 = 16 * nw3 + 16 * esc3 + 32 * 32 * codec3.n_units + (256 * 16 + 3 * 32) * w.n_streams + idx_bits
+        bits3 = 16 * nw3 + 16 * esc3 + 32 * 32 * codec3.n_units + (256 * 16 + 3 * 32) * w.n_streams + idx_bits + \
+            restart_bits(codec3)
         err3 = run.max_abs_error()
         ms3 = timer3.mean_ms()
         k3 = {}
@@ -626,7 +609,8 @@ def side_paths(run, args, plc, torch, result):
         esc4 = int(codec4.esc_cnt.to(torch.int64).sum())
         idx4 = 16 * int(codec4.idx_n_words.to(torch.int64).sum()) + 32 * 32 * w.S
         tables = int((codec4.freq_d.to(torch.int32).abs().sum(-1) > 0).sum())          # tables actually used
-        bits4 = 16 * nw4 + 16 * esc4 + 32 * 32 * codec4.n_units + 256 * 16 * tables + 3 * 32 * w.n_streams + idx4
+        bits4 = 16 * nw4 + 16 * esc4 + 32 * 32 * codec4.n_units + 256 * 16 * tables + 3 * 32 * w.n_streams + idx4 + \
+            restart_bits(codec4)
         depth = codec4.bits.cpu().numpy()
         sq = 0.0
         for s_ in range(w.S):

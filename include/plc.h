@@ -627,6 +627,9 @@ int plc_trie_evict(plc_trie *trie, int64_t id);
 #define PLC_TRACE_RECONSTRUCT_LINEAR 9 /* contraction of plc_reconstruct_linear      */
 #define PLC_TRACE_COUNT 10
 int plc_trace_kernel_events(int kernel_id, void *start, void *stop);
+/* Name, with its template arguments, of the kernel that the last call under such events launched between them; for the
+ * entropy coder's two, whose kernel follows from the shape, else empty. */
+const char *plc_trace_kernel_name(int kernel_id);
 
 #ifdef __cplusplus
 }

@@ -26,3 +26,7 @@ extern "C" int plc_trace_kernel_events(int kernel_id, void *start, void *stop) {
   plc::g_trace[kernel_id].stop = static_cast<hipEvent_t>(stop);
   return PLC_OK;
 }
+
+extern "C" const char *plc_trace_kernel_name(int kernel_id) {
+  return kernel_id < 0 || kernel_id >= PLC_TRACE_COUNT ? "" : plc::g_trace[kernel_id].kernel;
+}

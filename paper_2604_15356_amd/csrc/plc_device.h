@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstdio>
+
 #include "plc.h"
 
 namespace plc {
@@ -32,6 +34,7 @@ __device__ __forceinline__ uint4 load16_stream(const void *p) {
 // Optional event pairs around the main kernel of each call (plc_trace_kernel_events).
 struct TraceEvents {
   hipEvent_t start, stop;
+  char kernel[64];  // plc_trace_kernel_name
 };
 extern TraceEvents g_trace[PLC_TRACE_COUNT];
 
@@ -41,6 +44,11 @@ struct TraceScope {
   TraceScope(int id_, hipStream_t st_) : id(id_), st(st_) {
     if (g_trace[id].start) (void)hipEventRecord(g_trace[id].start, st);
   }
+  template <typename... Args>
+  void kernel(const char *format, Args... args) const {
+    if (g_trace[id].start) (void)std::snprintf(g_trace[id].kernel, sizeof(g_trace[id].kernel), format, args...);
+  }
+  void kernel(const char *name) const { kernel("%s", name); }
   ~TraceScope() {
     if (g_trace[id].stop) (void)hipEventRecord(g_trace[id].stop, st);
   }

@@ -1812,7 +1812,7 @@ __global__ __launch_bounds__(W * 64) void rans_decode_kernel(const RansArgs a) {
 // same stream, so that a workgroup's units share one slot table of whole entries (16 KB, one lookup a step) -- or,
 // with a table per bit depth, one split table per depth.  What is per half: the list of words and the place in it, a
 // lane's rank among its own half's renormalising lanes, and the ends of the units.  The words are staged as
-// above, in blocks of 256 for batches of eight steps, so that a unit needs 1.8 KB of LDS instead of 5.7 and a compute
+// above, in blocks of 256 for batches of eight steps, so that a unit needs 2 KB of LDS instead of 5.7 and a compute
 // unit holds 48 of them: what the wider wavefronts gain in issue they would lose again in latency with fewer.
 // The ring keeps the words in their order, word i at place i mod 512 behind a guard of one block that repeats the
 // upper; a lane's word is the rank-th below the pointer, counted through the lanes that do NOT take one.
@@ -3382,7 +3382,8 @@ int waves_per_workgroup(int64_t n_streams, int64_t units, int per_wave, int64_t 
 }
 
 template <int W>  // workgroups of 2 W units of one stream
-void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st, const TraceScope &trace) {
+  trace.kernel("rans_decode_pair_kernel<%d, %s, %s>", W, a.bits ? "true" : "false", a.pieces ? "true" : "false");
   if (a.bits) {
     const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
     const auto kernel = a.pieces ? &rans_decode_pair_kernel<W, true, true> : &rans_decode_pair_kernel<W, true, false>;
@@ -3394,16 +3395,16 @@ void launch_decode_pairs_of(const RansArgs &a, unsigned grid, hipStream_t st) {
   }
 }
 // Two or more units per stream, or pieces.
-void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st) {
+void launch_decode_pairs(RansArgs a, int64_t n_streams, hipStream_t st, const TraceScope &trace) {
   const int64_t units = a.pieces ? a.pieces : a.units_per_stream;
   const int w = waves_per_workgroup(n_streams, units, 2, a.pieces ? (int64_t)a.piece_batches * kBatchSyms : a.unit_syms);
   a.wgs_per_stream = (uint32_t)((units + 2 * w - 1) / (2 * w));
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
   switch (w) {
-    case 1: launch_decode_pairs_of<1>(a, grid, st); break;
-    case 2: launch_decode_pairs_of<2>(a, grid, st); break;
-    case 4: launch_decode_pairs_of<4>(a, grid, st); break;
-    default: launch_decode_pairs_of<8>(a, grid, st); break;
+    case 1: launch_decode_pairs_of<1>(a, grid, st, trace); break;
+    case 2: launch_decode_pairs_of<2>(a, grid, st, trace); break;
+    case 4: launch_decode_pairs_of<4>(a, grid, st, trace); break;
+    default: launch_decode_pairs_of<8>(a, grid, st, trace); break;
   }
 }
 // Encoder of chunks with a table per depth: while few wavefronts are resident a unit to each has the shorter step (chunks of 65,536,
@@ -3419,7 +3420,8 @@ bool decode_depths_alone(const RansArgs &a, bool counted) {
   return a.bits && !a.pieces && a.n_units <= kFewChunks && !(counted && a.unit_syms < kFewChunkSymsCounted);
 }
 template <int W, bool CHUNKS = true>
-void launch_decode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+void launch_decode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st, const TraceScope *trace) {
+  if (trace) trace->kernel("rans_decode_kernel<%d, true, %s>", W, CHUNKS ? "true" : "false");
   // (split tables: 5 KB per depth instead of 16 lets three times the wavefronts in)
   const size_t lds = (size_t)a.n_tables * kCompactTable * sizeof(uint32_t);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_kernel<W, true, CHUNKS>),
@@ -3427,34 +3429,40 @@ void launch_decode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
   hipLaunchKernelGGL((rans_decode_kernel<W, true, CHUNKS>), dim3(grid), dim3(W * 64), lds, st, a);
 }
 // Chunks with a table per depth, a unit per wavefront.
-void launch_decode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
+void launch_decode_depths(RansArgs a, int64_t n_streams, hipStream_t st, const TraceScope &trace) {
   const int w = waves_per_workgroup(n_streams, a.units_per_stream, 1, a.unit_syms);
   a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);
   switch (w) {
-    case 1: launch_decode_depths_of<1>(a, grid, st); break;
-    case 2: launch_decode_depths_of<2>(a, grid, st); break;
-    case 4: launch_decode_depths_of<4>(a, grid, st); break;
-    default: launch_decode_depths_of<8>(a, grid, st); break;
+    case 1: launch_decode_depths_of<1>(a, grid, st, &trace); break;
+    case 2: launch_decode_depths_of<2>(a, grid, st, &trace); break;
+    case 4: launch_decode_depths_of<4>(a, grid, st, &trace); break;
+    default: launch_decode_depths_of<8>(a, grid, st, &trace); break;
   }
 }
-// One unit per stream.
-void launch_decode_streams(const RansArgs &a, hipStream_t st) {
+// One unit per stream.  trace: null behind pieces, whose kernel is the main one.
+void launch_decode_streams(const RansArgs &a, hipStream_t st, const TraceScope *trace) {
   const dim3 grid((unsigned)a.n_units);
+  auto name = [&](const char *kernel) {
+    if (trace) trace->kernel(kernel);
+  };
   // Few enough units (kChainMaxUnits): time is the length of one unit's chain, so take the variant with the shortest
   // step.  With more units its 60 KB of LDS per workgroup would cost more in occupancy than the shorter step gains.
   if (a.bits && a.n_units <= kDepthsMaxUnits) {
     const size_t lds = depths_lds_bytes(a.n_tables);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&rans_decode_depths_kernel<0>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    name("rans_decode_depths_kernel<0, 0>");
     hipLaunchKernelGGL(rans_decode_depths_kernel<0>, grid, dim3(depths_threads(0)), lds, st, a);
   } else if (a.bits) {
-    launch_decode_depths_of<1, false>(a, (unsigned)a.n_units, st);
+    launch_decode_depths_of<1, false>(a, (unsigned)a.n_units, st, trace);
   } else if (a.n_units <= kChainMaxUnits) {
+    name("rans_decode_chain_kernel<0, false, 4>");
     hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), grid, dim3(128), 0, st, a);
   } else {
     // Many units: LDS decides how many wavefronts fit a compute unit, and the split table lets more in (twice as many
     // where every one-wavefront workgroup has a table of its own).
+    name("rans_decode_kernel<1, false, false>");
     hipLaunchKernelGGL((rans_decode_kernel<1, false, false>), grid, dim3(64), 0, st, a);
   }
 }
@@ -3497,18 +3505,19 @@ bool encode_depths_in_pairs(int64_t n_units) {
   return one > 4 || 2 * two <= one;
 }
 template <int W>
-void launch_encode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st) {
+void launch_encode_depths_of(const RansArgs &a, unsigned grid, hipStream_t st, const TraceScope &trace) {
+  trace.kernel("rans_encode_kernel<%d>", W);
   hipLaunchKernelGGL(rans_encode_kernel<W>, dim3(grid), dim3(W * 64), 0, st, a);
 }
-void launch_encode_depths(RansArgs a, int64_t n_streams, hipStream_t st) {
+void launch_encode_depths(RansArgs a, int64_t n_streams, hipStream_t st, const TraceScope &trace) {
   const int w = waves_per_workgroup(n_streams, a.units_per_stream, 1, a.unit_syms);
   a.wgs_per_stream = (uint32_t)((a.units_per_stream + w - 1) / w);
   const unsigned grid = (unsigned)(n_streams * a.wgs_per_stream);  // at most the grid checked before
   switch (w) {
-    case 1: launch_encode_depths_of<1>(a, grid, st); break;
-    case 2: launch_encode_depths_of<2>(a, grid, st); break;
-    case 4: launch_encode_depths_of<4>(a, grid, st); break;
-    default: launch_encode_depths_of<8>(a, grid, st); break;
+    case 1: launch_encode_depths_of<1>(a, grid, st, trace); break;
+    case 2: launch_encode_depths_of<2>(a, grid, st, trace); break;
+    case 4: launch_encode_depths_of<4>(a, grid, st, trace); break;
+    default: launch_encode_depths_of<8>(a, grid, st, trace); break;
   }
 }
 
@@ -3534,9 +3543,11 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
   {
     TraceScope trace(PLC_TRACE_RANS_ENCODE, st);
     if (a.units_per_stream == 1 && a.n_units <= kPipeMaxUnits) {
+      const bool wide = !a.bits || a.n_units <= 2 * kComputeUnits;
+      trace.kernel("rans_encode_pipe_kernel<%s, %s>", a.bits ? "true" : "false", wide ? "true" : "false");
       // few units (kPipeMaxUnits): the chain of one unit is the time, so give each unit four wavefronts
       // (with more units, four wavefronts per unit cost more in occupancy than the shorter chain gains)
-      if (a.bits && a.n_units <= 2 * kComputeUnits) {
+      if (a.bits && wide) {
         hipLaunchKernelGGL((rans_encode_pipe_kernel<true, true>), dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       } else if (a.bits) {
         hipLaunchKernelGGL(rans_encode_pipe_kernel<true>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
@@ -3544,15 +3555,18 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
         hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
       }
     } else if (a.bits && (a.units_per_stream == 1 ? !encode_depths_in_pairs(a.n_units) : a.n_units <= kFewChunks)) {
-      launch_encode_depths(a, n_streams, st);
+      launch_encode_depths(a, n_streams, st, trace);
     } else if (a.bits && a.units_per_stream == 1) {
+      trace.kernel("rans_encode_pair_kernel<1, true, 2, true>");
       hipLaunchKernelGGL((rans_encode_pair_kernel<1, true, 2, true>), dim3((unsigned)((a.n_units + 1) / 2)), dim3(64), 0, st, a);
     } else if (a.units_per_stream == 1) {
       // many whole streams: two streams per wavefront, one wavefront per workgroup
       const int64_t pairs = (a.n_units + 1) / 2;
       if (pairs > 8 * kComputeUnits && pairs <= 11 * kComputeUnits) {  // all resident at once with the smaller stages
+        trace.kernel("rans_encode_pair_kernel<1, true, 2, false>");
         hipLaunchKernelGGL((rans_encode_pair_kernel<1, true, 2>), dim3((unsigned)pairs), dim3(64), 0, st, a);
       } else {
+        trace.kernel("rans_encode_pair_kernel<1, true, 4, false>");
         hipLaunchKernelGGL((rans_encode_pair_kernel<1, true, 4>), dim3((unsigned)pairs), dim3(64), 0, st, a);
       }
     } else {
@@ -3563,6 +3577,7 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
       while (w < kPairMaxWaves && 2 * w <= slots) w *= 2;
       a.pair_wgs_per_stream = (uint32_t)((slots + w - 1) / w);
       const unsigned grid = (unsigned)(n_streams * a.pair_wgs_per_stream);  // at most the grid checked above
+      trace.kernel("rans_encode_pair_kernel<%d, false, %d, %s>", w, a.bits ? 2 : 4, a.bits ? "true" : "false");
       if (a.bits) {
         switch (w) {
           case 1: hipLaunchKernelGGL((rans_encode_pair_kernel<1, false, 2, true>), dim3(grid), dim3(64), 0, st, a); break;
@@ -3605,18 +3620,19 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
     TraceScope trace(PLC_TRACE_RANS_DECODE, st);
     if (a.pieces && !a.bits && n_streams * a.pieces <= kChainMaxPieces) {
       a.wgs_per_stream = (uint32_t)a.pieces;
+      trace.kernel("rans_decode_chain_kernel<0, false, 4>");
       hipLaunchKernelGGL((rans_decode_chain_kernel<0, false>), dim3((unsigned)(n_streams * a.pieces)), dim3(128), 0, st, a);
     } else if (a.pieces || a.units_per_stream > 1) {
       // (pieces begin at whole tiles if the stream is whole tiles: the encoder's rounds are as long as a tile)
       const bool tiles = tile_cnt && (a.pieces ? syms_per_stream : a.unit_syms) % kTileSyms == 0;
       if (decode_depths_alone(a, tiles)) {
-        launch_decode_depths(a, n_streams, st);
+        launch_decode_depths(a, n_streams, st, trace);
       } else {
         if (tiles) {
           a.tile_cnt = tile_cnt;
           counts->counted = true;
         }
-        launch_decode_pairs(a, n_streams, st);
+        launch_decode_pairs(a, n_streams, st, trace);
       }
     }
     if (a.pieces && counts && (counts->counted || !rest)) {
@@ -3625,7 +3641,7 @@ int decode_impl(const uint16_t *freq, const uint32_t *states, const uint16_t *wo
       counts->rest_left = !rest;
     }
     if (a.pieces) a = again_args(a);
-    if (a.units_per_stream == 1 && !(a.verified_pieces && !rest)) launch_decode_streams(a, st);
+    if (a.units_per_stream == 1 && !(a.verified_pieces && !rest)) launch_decode_streams(a, st, a.verified_pieces ? nullptr : &trace);
   }
   return launch_status();
 }
@@ -3712,6 +3728,15 @@ int rans_decode_fused(const uint16_t *freq, const uint32_t *states, const uint16
       const int64_t n_units = a.pieces ? n_streams * a.pieces : n_streams;
       const dim3 grid((unsigned)n_units);
       if (a.pieces) a.wgs_per_stream = (uint32_t)a.pieces;
+      if (trace && !a.verified_pieces) {
+        const bool compact = recon.k <= kCompactMaxK && n_units > kDenseStreams;
+        if (recon.bits || compact) {
+          trace->kernel("rans_decode_depths_kernel<%d, %d>", (int)recon.k, recon.bits ? 0 : recon.chosen ? 2 : 1);
+        } else {
+          const bool three = !recon.chosen && recon.k <= kDenseMaxK && n_units > kDenseStreams;
+          trace->kernel("rans_decode_chain_kernel<%d, %s, %d>", (int)recon.k, recon.chosen ? "true" : "false", three ? 3 : 4);
+        }
+      }
       switch (recon.k) {
 #define PLC_CASE(K)                                                                              \
     case K:                                                                                        \

@@ -24,7 +24,7 @@ EXPORTS = ("plc_version", "plc_strerror", "plc_workspace_bytes", "plc_units_per_
            "plc_predict_residual", "plc_predict_residual_hist", "plc_predict_residual_noalloc", "plc_histogram", "plc_build_freq", "plc_rans_encode",
            "plc_rans_decode", "plc_reconstruct", "plc_rans_decode_reconstruct", "plc_rans_decode_reconstruct_cond",
            "plc_rans_decode_reconstruct_adapt",
-           "plc_trace_kernel_events",
+           "plc_trace_kernel_events", "plc_trace_kernel_name",
            "plc_predict_residual_cond", "plc_reconstruct_cond", "plc_select_candidate",
            "plc_index_encode", "plc_index_decode",
            "plc_surprisal_thresholds", "plc_surprisal_bits", "plc_predict_residual_adapt", "plc_reconstruct_adapt",
@@ -97,6 +97,8 @@ def lib() -> C.CDLL:
         L.plc_rans_decode_reconstruct_adapt.argtypes = [dp, p, p, p, u64, p, p, i32, i32, p, p, p, p, p, C.c_float, p,
                                                         u64, p, p, p, p, p, sz, p, p]
         L.plc_trace_kernel_events.argtypes = [C.c_int, p, p]
+        L.plc_trace_kernel_name.restype = C.c_char_p
+        L.plc_trace_kernel_name.argtypes = [C.c_int]
         L.plc_predict_residual_cond.argtypes = [dp, p, p, p, p, p, p, p, p, u64, p, p, p, p, sz, p, p]
         L.plc_reconstruct_cond.argtypes = [dp, p, p, p, p, p, p, u64, p, p, p, p, sz, p, p]
         L.plc_select_candidate.argtypes = [dp, p, p, C.c_float, p, p]
@@ -556,3 +558,8 @@ def plc_trace_kernel_events(kernel_id, start=None, stop=None):
     rc = lib().plc_trace_kernel_events(int(kernel_id), C.c_void_p(start) if start else None,
                                        C.c_void_p(stop) if stop else None)
     _check(rc, "plc_trace_kernel_events")
+
+
+def plc_trace_kernel_name(kernel_id) -> str:
+    """Kernel that the last call under trace events launched between them (the entropy coder's two)."""
+    return lib().plc_trace_kernel_name(int(kernel_id)).decode()

@@ -149,6 +149,29 @@ def test_pieces_equal_the_whole_stream(dev, case):
 
 
 @pytest.mark.parametrize("case", list(CASES))
+def test_the_kernel_that_decodes_is_the_one_announced(dev, case):
+    """One kernel that reconstructs, in pieces or not, or the first of two calls."""
+    from paper_2604_15356_amd import plc
+    codec, encode, decode = _setup(dev, case)
+    path, overrides, _, points = CASES[case]
+    encode()
+    around = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in around:
+        e.record()
+    for restart in (True, False):
+        plc.plc_trace_kernel_events(plc.TRACE_RANS_DECODE, *(e.cuda_event for e in around))
+        try:
+            decode(restart)
+        finally:
+            plc.plc_trace_kernel_events(plc.TRACE_RANS_DECODE)
+        one = plc.plc_decode_one_kernel(codec.n_streams, codec.N, 0, overrides["k"], path != "mean", path == "adapt",
+                                        points if restart else 0)
+        name = plc.plc_trace_kernel_name(plc.TRACE_RANS_DECODE)
+        reconstructs = any(name.startswith(f"rans_decode_{x}_kernel<{overrides['k']}, ") for x in ("chain", "depths"))
+        assert bool(one) == reconstructs, name
+
+
+@pytest.mark.parametrize("case", list(CASES))
 def test_records_that_are_not_true_change_nothing(dev, case):
     codec, encode, decode = _setup(dev, case)
     encode()
