@@ -973,41 +973,56 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 }
 
 // ---------------------------------------------------------------------------
-// Encoder for few, long units: four wavefronts per unit
+// Encoder for few, long units: seven wavefronts per unit
 // ---------------------------------------------------------------------------
 // When there are no more units than compute units, time is the length of one unit's chain of steps.  A lone
-// wavefront issues one instruction every 4.64 cycles whether or not it needs the result of the one before
-// (measured on gfx950, v_mul_hi_u32 and the SDWA forms included; s_nop 1 takes 8.6, ds_read_b128 11, ds_write_b32
-// 15), so a step costs its instruction count, wait states included -- and everything that is not the state
-// recurrence moves to three helper wavefronts of the same workgroup, one per SIMD of the compute unit:
-//   mover   brings the symbols from HBM to LDS (64 groups ahead) and the words from LDS to HBM;
-//   feeder  turns every (group, lane) of a batch into its 16-byte table entry at a fixed place of an LDS
+// wavefront issues strictly in order, so a step costs its instructions, wait states included -- and everything that
+// is not the state recurrence moves to helper wavefronts of the same workgroup:
+//   symbols brings the symbols from HBM to LDS (64 groups ahead);
+//   feeder  (two) turns every (group, lane) of a batch into its 16-byte table entry at a fixed place of an LDS
 //           ring; a lane without a symbol (ragged top group, or a step past the unit's first group) gets an
 //           identity entry.  It runs two batches ahead of the coder, so that the coder can ask for the next
 //           batch's first entries before the barrier;
-//   coder   the recurrence alone: six vector instructions a step, five for tables of the plain form (0.76 -> 0.71 ms
-//           for 256 units of 1,048,576 symbols), the entries' reads in the wait states behind the compare, and one
-//           LDS write of the four states of four steps;
-//   packer  recovers from the stored states which lanes emitted (x > thr), ranks them with one ballot per two
-//           steps and packs the 16-bit words into an LDS region per batch.
-// They meet at one workgroup barrier per batch of 16 steps.  The coder writes its last four states of a batch in
-// the batch after (and waits for nothing at a barrier), so the packer works two batches behind it.
-// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer batch it - 4, whose thresholds it has read
-// two iterations earlier: the ring then needs three slots and three units share a compute unit's LDS.  The mover takes in a round
-// of symbols every fourth iteration and sends the words of two batches out in each of the two after it: waiting
-// for symbols is waiting for every store before them as well (one counter), and these are then two iterations
-// old (stores in every iteration held the barrier up every round).
-constexpr int kEntrySlots = 3;  // feeder writes b + 2, coder reads b and b + 1, packer the thresholds of b
-constexpr int kStateSlots = 3;  // coder writes b and the end of b - 1, packer reads b - 2
-constexpr int kListRegion = 2 * kBatchSyms + 8;  // the words of a pair of batches behind up to seven carried ones
-constexpr int kListRegions = 3;  // the packer's, and the up to two in front of it that have not left
-constexpr int kPipeThreads = 256;
+//   coder   the recurrence alone, in all 64 lanes: lanes 32-63 code the same unit a step ahead of lanes 0-31, so that
+//           what one half leaves in LDS of every second step is, for the other, the state behind the one before;
+//   packer  (two) recovers from the states which lanes emitted, ranks them with one ballot per two
+//           steps and packs the 16-bit words into an LDS region per batch;
+//   words   takes the words from LDS to HBM.
+// What a lone wavefront's instructions cost on gfx950, measured: 2.0 ns of four bytes and 2.35 of eight with all lanes
+// on, 2.6 and 3.0 with any lane off, dependent or not; s_nop 1.9; a read of 16 bytes a lane 2.2 in a row with others
+// and 5.6 between vector instructions, a write of as much 10.  Hence all lanes on, the LDS accesses of four steps in one
+// place, one write for eight steps, and one wait state a step (see pipe_step): 13.4 ns a step alone, where a masked
+// lower half, six wait states and two writes took 21.  What the helpers add is LDS traffic: a kilobyte takes 5.7 ns to write, 1.9
+// to read in a row and 4.4 from random places in 16-byte pieces, and the coder waits its turn.  So the packer reads
+// no thresholds, entries are looked up in two halves of 8 bytes (1.7 ns each), and writes do not stand in a row.
+// They meet at one workgroup barrier per batch (150 cycles, the loops' branches included) of B steps: 32 where two units or
+// one share a compute unit, else 16, whose rings take 43 KB of LDS and not 74.  256 units of 1,048,576 symbols
+// 707 -> 565 us, with a table per depth 815 -> 656.
+// The coder writes its last eight steps' states of a batch in the batch after (and waits for nothing at a barrier).
+// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer emissions of batch it - 4 and words of batch
+// it - 5, each packer every second batch.
+constexpr int kEntrySlots = 3;  // feeder writes b + 2, coder reads b and b + 1
+constexpr int kStateSlots = 3;  // coder writes b and the end of b - 1, packer reads b - 2 and the first state behind it
+constexpr int kListRegions = 2;  // batches whose words are being packed and are leaving
+constexpr int kPipeStage = kSuperSyms + 48;  // a round's symbols and the group above them, at any 16-byte misalignment
+enum PipeRole { kFeeder0, kFeeder1, kSymbols, kCoder, kPacker0, kPacker1, kWords, kPipeRoles };  // (wavefronts i and i + 4 share a SIMD)
+constexpr int kPipeThreads = 64 * kPipeRoles;
 // Up to two rounds of 512 units the kernels with one chain per workgroup beat the many-unit kernels.  The encoder's
-// LDS lets three units share a compute unit (768 at a time), the decoder's two, and the more of them do the less
-// each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at 1025:
-// encode 100 / 143 / 190 / 266 and 398 us, with a table per depth 131 / 165 / 201 / 298 and 407 us (with five entry
-// slots, two units to a compute unit, 768 took 229 and 277 us), decode 190 / 199 / 390 / 394 and 621 us.
+// LDS lets two units share a compute unit, three with batches of 16 steps, the decoder's two, and the more of them do
+// the less each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at
+// 1028: encode 85 / 122 / 164 / 214 and 385 us, with a table per depth 91 / 135 / 180 / 240 and 419 us (with four
+// wavefronts a unit and batches of 16: 102 / 140 / 186 / 260 and 110 / 148 / 198 / 282), decode 190 / 199 / 390 / 394 and 621 us.
 constexpr int64_t kPipeMaxUnits = 1024;
+// Beyond, the encoder's further rounds of 768 still win where streams are long: 32,768 symbols, 1028 / 1536 / 1792 / 2048
+// units 77 / 94 / 107 / 130 us and the many-unit kernel 107 / 109 / 123 / 124; 524,288 symbols 1014 / 1242 / 1388 / 1798 and
+// 1537 / 1555 / 1803 / 1860; but 8192 symbols 31 / 38 / 41 / 49 and 33 / 34 / 38 / 38.  The many-unit kernel with a table per
+// depth holds 1792 units at a time: 32,768 symbols, 1028 / 1536 / 1792 / 2048 / 2304 / 2560 units 88 / 118 / 125 / 149 / 166 /
+// 182 us and 116 / 119 / 120 / 172 / 173 / 174.
+__host__ __forceinline__ bool encode_in_pipe(int64_t n_units, int64_t syms_per_stream, bool per_depth) {
+  if (n_units <= kPipeMaxUnits) return true;
+  if (syms_per_stream < 32768) return false;
+  return per_depth ? n_units <= 1536 || (n_units > 1792 && n_units <= 2304) : n_units <= 1792;
+}
 constexpr int64_t kChainMaxUnits = 1024;  // the same bound for the decoder of whole-stream units
 // The decoder with one table per depth holds one unit per compute unit (its tables take 128 KB of LDS): two
 // rounds of 256 are what it may take before the many-unit decoder is as fast.
@@ -1032,109 +1047,116 @@ constexpr int64_t kDenseStreams = 512;
 constexpr int kCompactMaxK = 4;  // up to here four workgroups of the decoder with 4-byte entries fit a compute unit
 constexpr int kDenseMaxK = 6;  // up to here the kernel's registers (156 at k = 6) leave room for three wavefronts per SIMD
 
-// One step from its select on, and the next step's compare: x and the next threshold in, the next x and the mask of its
-// compare out.  Between two of these stand the caller's LDS accesses, two instructions at the least: the wait states that
-// the hardware asks for between a compare and the select that reads its mask.  Written out, because the compiler makes
-// a shift and a select of the one that takes the state's high half as its operand, and puts a wait state behind each
-// piece of assembly whose result the next instruction reads.
+// One step up to the next step's compare.  `y` is the state less the addend of the step before (e.w of this step), which is
+// added here, between the compare and the select that reads its mask: one of the two wait states that the hardware asks for
+// between these (the caller puts an instruction between two of these pieces for the other).  e.z is the step's threshold,
+// less the same addend.  x out: the state in front of the step.  Written out, because the compiler makes a shift and a select
+// of the one that takes the state's high half as its operand, and puts a wait state behind each piece of assembly whose result
+// the next instruction reads.
 template <EncForm FORM>
-__device__ __forceinline__ void pipe_step(uint32_t &x, uint64_t &emit, const u32x4 e, uint32_t thr_next) {
+__device__ __forceinline__ void pipe_step(uint32_t &y, uint32_t &x, uint64_t &emit, const u32x4 e, uint32_t thr_next) {
   register uint64_t mask asm("vcc") = emit;  // (the only place that this form of the select reads its mask from)
-  uint32_t xr, t, xn;
+  uint32_t xr, t, yn, xo;
 #define PLC_PIPE_STEP(QUOTIENT)                                                                                        \
-  asm volatile("v_cndmask_b32_sdwa %0, %4, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t" \
-               "v_mul_hi_u32 %1, %5, %0\n\t" QUOTIENT                                                                \
-               "v_mul_u32_u24 %1, %1, %6\n\t"                                                                        \
-               "v_add3_u32 %2, %0, %7, %1\n\t"                                                                       \
-               "v_cmp_gt_u32_e32 vcc, %2, %8"                                                                          \
-               : "=&v"(xr), "=&v"(t), "=&v"(xn), "+s"(mask)                                                            \
-               : "v"(x), "v"(e.x), "v"(e.z), "v"(e.w), "v"(thr_next))
+  asm volatile("v_add_u32_e32 %4, %5, %8\n\t"                                                                          \
+               "v_cndmask_b32_sdwa %0, %4, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t" \
+               "v_mul_hi_u32 %1, %6, %0\n\t" QUOTIENT                                                                \
+               "v_mad_u32_u24 %2, %1, %7, %0\n\t"                                                                    \
+               "v_cmp_gt_u32_e32 vcc, %2, %9"                                                                          \
+               : "=&v"(xr), "=&v"(t), "=&v"(yn), "+s"(mask), "=&v"(xo)                                                 \
+               : "v"(y), "v"(e.x), "v"(e.y), "v"(e.w), "v"(thr_next))
   if constexpr (FORM == kEncPlain) {
     PLC_PIPE_STEP("");
   } else if constexpr (FORM == kEncShort) {
-    PLC_PIPE_STEP("v_lshrrev_b32_sdwa %1, %6, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
+    PLC_PIPE_STEP("v_lshrrev_b32_sdwa %1, %7, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
   } else {
     PLC_PIPE_STEP("v_add_u32 %1, %1, %0\n\t"
-                  "v_lshrrev_b32_sdwa %1, %6, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
+                  "v_lshrrev_b32_sdwa %1, %7, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
   }
 #undef PLC_PIPE_STEP
-  x = xn;
+  y = yn;
+  x = xo;
   emit = mask;
   PLC_PIN();
 }
 
 // One batch of the coder.  `e` holds the entries of its first eight steps on entry and those of the next
-// batch's first eight (at `next`) on return, `emit` the mask of the first step's compare and of the next batch's.  A
-// lane's states before steps 4 q .. 4 q + 3 leave as one 16-byte vector for xb[q], in the first of the four steps
+// batch's first eight (at `next0` and behind `next`) on return, `emit` the mask of the first step's compare and of the next batch's.  A
+// lane's states before steps 4 q .. 4 q + 3 leave as one 16-byte vector for xb[q], in the four steps
 // after them: `before` holds the last four on return and `held`, where they belong, those of the batch before on
-// entry.  A step asks for entries eight steps ahead (with four the LDS answered late when the helpers were at it: 1.19
-// against 1.11 ms for an encode given the tokens), and one wait a quad leaves those of the quad on their way.
-template <EncForm FORM>
-__device__ __forceinline__ void pipe_batch(uint32_t &x, uint64_t &emit, u32x4 (&e)[kBatch / 4][4], u32x4 &before,
-                                           u32x4 *&held, const u32x4 *eb, const u32x4 *next, u32x4 *xb) {
-  constexpr int kQuads = kBatch / 4;
+// entry.  The LDS accesses of four steps stand in one place: each turn from vector instructions to them costs.
+template <EncForm FORM, int B>
+__device__ __forceinline__ void pipe_batch(uint32_t &y, uint64_t &emit, u32x4 (&e)[4][4], u32x4 &before,
+                                           u32x4 *&held, const u32x4 *eb, const u32x4 *next0, const u32x4 *next,
+                                           u32x4 *xb) {
+  constexpr int kQuads = B / 4;
+  constexpr int kNoWait = 0xcf7f;  // every counter at its most: nothing but an instruction between two steps
 #pragma unroll
   for (int q = 0; q < kQuads; ++q) {
-    u32x4 (&cur)[4] = e[q];
-    u32x4 (&ask)[4] = e[(q + 2) % kQuads];
-    const u32x4 *src = q + 2 < kQuads ? eb + 4 * (q + 2) * kLanes : next + 4 * (q + 2 - kQuads) * kLanes;
-    *held = before;
+    u32x4 (&cur)[4] = e[q % 4];
+    u32x4 (&ask)[4] = e[(q + 2) % 4];
+    const u32x4 *src = (q + 2 < kQuads ? eb + 4 * (q + 2) * kLanes : next + 4 * (q + 2 - kQuads) * kLanes) - kLanes;
+    uint32_t x[4];
+    pipe_step<FORM>(y, x[0], emit, cur[0], cur[1].z);
+    if (q % 2 == 0) *held = before;
     PLC_PIN();
-    ask[0] = src[0];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      ask[j] = q + 2 == kQuads && j == 0 ? *next0 : src[j * kLanes];
+      PLC_PIN();
+    }
+    pipe_step<FORM>(y, x[1], emit, cur[1], cur[2].z);
+    __builtin_amdgcn_s_waitcnt(kNoWait);
     PLC_PIN();
-    before.x = x;
-    pipe_step<FORM>(x, emit, cur[0], cur[1].y);
-    ask[1] = src[kLanes];
+    pipe_step<FORM>(y, x[2], emit, cur[2], cur[3].z);
+    __builtin_amdgcn_s_waitcnt(0xc47f);  // lgkmcnt(4): those of the next quad are there, the one behind it may be on its way
     PLC_PIN();
-    ask[2] = src[2 * kLanes];
+    pipe_step<FORM>(y, x[3], emit, cur[3], e[(q + 1) % 4][0].z);
+    __builtin_amdgcn_s_waitcnt(kNoWait);
     PLC_PIN();
-    ask[3] = src[3 * kLanes];
-    PLC_PIN();
-    before.y = x;
-    pipe_step<FORM>(x, emit, cur[1], cur[2].y);
-    asm volatile("s_nop 1");
-    PLC_PIN();
-    before.z = x;
-    pipe_step<FORM>(x, emit, cur[2], cur[3].y);
-    __builtin_amdgcn_s_waitcnt(0xc57f);  // lgkmcnt(5)
-    PLC_PIN();
-    asm volatile("s_nop 0");
-    PLC_PIN();
-    before.w = x;
-    pipe_step<FORM>(x, emit, cur[3], e[(q + 1) % kQuads][0].y);
-    held = xb + q * kLanes;
+    if (q % 2 == 0) {
+      before.x = x[0];
+      before.y = x[2];
+    } else {
+      before.z = x[0];
+      before.w = x[2];
+      held = xb + (q / 2) * 64;
+    }
   }
 }
 
-// ADAPT: one table per bit depth (the *_bucketed call).  Its entries take 8 bytes where three units are to share a
-// compute unit, and unpacking them costs the feeder what the coder saves; WIDE: whole entries, two units to a compute unit
-// (256 units of 1,048,576 symbols 867 -> 832 us, 512 of 262,144 320 -> 298; 768 need the third).
-template <bool ADAPT, bool WIDE = !ADAPT>
-__global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const RansArgs a) {
+// ADAPT: one table per bit depth (the *_bucketed call).  Its entries take 8 bytes where units are to share a compute
+// unit, and the feeder unpacks them; WIDE: whole entries, one unit to a compute unit with batches of 32 steps (256 units of
+// 1,048,576 symbols 683 -> 662 us).
+template <bool ADAPT, int B, bool WIDE = !ADAPT>
+__global__ __launch_bounds__(kPipeThreads, B == 16 ? 6 : ADAPT && WIDE ? 2 : 4) void rans_encode_pipe_kernel(const RansArgs a) {
   constexpr int kIdentity = (ADAPT ? PLC_MAX_BITS : 1) * 256;  // index of the entry that leaves a state unchanged
   constexpr bool kPacked = ADAPT && !WIDE;
-  using Entry = std::conditional_t<kPacked, uint2, uint4>;
-  __shared__ Entry table[kIdentity + 1];
-  // ADAPT: table of each group of a staging round, in the order in which the feeder's halves want them: a full
-  // batch's eight odd groups from the top, then its eight even ones
-  __shared__ __attribute__((aligned(8))) uint8_t table_of_group[2][kSuperGroups];
-  auto group_at = [](int g) { return (g & ~15) + ((g & 1) ? 0 : 8) + 7 - ((g & 15) >> 1); };
-  __shared__ uint4 entry_ring[kEntrySlots][kBatch][kLanes];
-  __shared__ uint4 state_ring[kStateSlots][kBatch / 4][kLanes];
-  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
+  constexpr int kRoundBatches = kSuperGroups / B;  // batches per staging round
+  constexpr int kListRegion = B * kLanes + 8;      // a batch's words behind up to seven carried ones
+  // Entries of 8 bytes, or their two halves apart (.x and .z of make_enc_entry, and .y and .w): 8 bytes at random places
+  // take LDS 1.7 ns a wavefront, 16 take 4.4.
+  __shared__ uint2 table[(kPacked ? 1 : 2) * (kIdentity + 1)];
+  constexpr int kOther = kPacked ? 0 : kIdentity + 1;
+  // ADAPT: table of each group of a staging round, from its lowest, and of the group above
+  __shared__ __attribute__((aligned(8))) uint8_t table_of_group[2][kSuperGroups + 8];
+  __shared__ uint4 entry_ring[kEntrySlots * B][kLanes];  // by step
+  __shared__ uint4 state_ring[kStateSlots][B / 8][64];
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kPipeStage];
   __shared__ __attribute__((aligned(16))) uint16_t word_list[kListRegions][kListRegion];
-  __shared__ uint16_t spare_word[64];
+  __shared__ uint16_t spare_word;
   __shared__ uint32_t list_fill[kListRegions];  // positions in use of each region of the list
+  __shared__ uint32_t batch_words[2];           // words of the packers' last batches
   static_assert(workgroups_per_cu(sizeof(table) + sizeof(table_of_group) + sizeof(entry_ring) + sizeof(state_ring) +
-                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill)) >=
-                    (ADAPT && WIDE ? 2 : 3),
-                "three units to a compute unit: without the third 513 to 768 units take a second round");
+                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill) +
+                                  sizeof(batch_words)) >= (B == 16 ? 3 : ADAPT && WIDE ? 1 : 2),
+                "so many units to a compute unit");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t unit = blockIdx.x;  // one unit per stream, one workgroup per unit
 
   EncForm form = kEncPlain;  // uniform
-  {  // every wavefront scans the frequencies and builds one of a lane's four entries
+  {  // every wavefront scans the frequencies, and four of them build one of a lane's four entries each
     const int n_tables = ADAPT ? a.n_tables : 1;
     uint32_t f[ADAPT ? PLC_MAX_BITS : 1][4], cum[ADAPT ? PLC_MAX_BITS : 1];
     for (int t = 0; t < n_tables; ++t) {
@@ -1147,21 +1169,26 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       for (int r = 0; r < 4; ++r) {
         if (r == wave) {
           const uint4 e = make_enc_entry(form, f[t][r], cum[t]);
+          const int i = t * 256 + lane * 4 + r;
           if constexpr (kPacked) {
-            table[t * 256 + lane * 4 + r] = pack_enc_entry(e);
+            table[i] = pack_enc_entry(e);
           } else {
-            table[t * 256 + lane * 4 + r] = e;
+            table[i] = make_uint2(e.x, e.z);
+            table[kOther + i] = make_uint2(e.y, e.w);
           }
         }
         cum[t] += f[t][r];
       }
     }
+    if (threadIdx.x < 2) batch_words[threadIdx.x] = 0;
+    if (threadIdx.x < kLanes)  // the step in front of the first
+      entry_ring[kEntrySlots * B - 1][threadIdx.x] = make_uint4(0u, 0u, 0xffffffffu, 0u);
     if (threadIdx.x == 0) {  // never emits, x' = x
-      const uint4 e = make_uint4(0u, 0xffffffffu, 0u, 0u);
       if constexpr (kPacked) {
-        table[kIdentity] = pack_enc_entry(e);
+        table[kIdentity] = pack_enc_entry(make_uint4(0u, 0xffffffffu, 0u, 0u));
       } else {
-        table[kIdentity] = e;
+        table[kIdentity] = make_uint2(0u, 0u);
+        table[kOther + kIdentity] = make_uint2(0xffffffffu, 0u);
       }
     }
   }
@@ -1170,220 +1197,303 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
   const uint8_t *ubase = a.sym_in + unit * a.syms_per_stream;
   const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(ubase) & 15u);
   const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
-  // Batch 0 holds the top G mod 16 groups (a full 16 if that is 0) followed by identity steps; every
-  // later batch is 16 full groups.  Batch b codes groups top(b)-1 down to top(b)-16.
-  const int32_t head = G % kBatch ? G % kBatch : kBatch;
-  const int32_t n_batches = (G - head) / kBatch + 1;
-  auto batch_top = [&](int32_t b) { return b == 0 ? G : G - head - (b - 1) * kBatch; };
-  // Symbol staging rounds of four batches; a round's buffer starts at the 16-byte-aligned address at or
+  // Batch 0 holds the top `head` groups followed by identity steps, and every later batch is B full groups, the last
+  // one possibly half of them and identity steps: pieces end 16 n groups below the top (piece_top), and here a batch
+  // begins there.  Batch b codes groups top(b)-1 down to top(b)-B.
+  const int32_t head16 = G % 16 ? G % 16 : 16, head = B == 16 || G == head16 ? head16 : head16 + 16;
+  const int32_t n_batches = (G - head + B - 1) / B + 1;
+  auto batch_top = [&](int32_t b) { return b == 0 ? G : G - head - (b - 1) * B; };
+  // Symbol staging rounds of 64 groups; a round's buffer starts at the 16-byte-aligned address at or
   // below its lowest symbol, so the symbol at unit offset t sits at  t - 32 * bottom + mis.
   auto round_bottom = [&](int32_t r) {
-    const int32_t g = batch_top(4 * r + 3) - kBatch;
+    const int32_t g = batch_top(kRoundBatches * (r + 1) - 1) - B;
     return g > 0 ? g : 0;
   };
-  const int32_t n_rounds = (n_batches + 3) / 4;
-  const int32_t n_iters = n_batches + 4;
+  const int32_t n_rounds = (n_batches + kRoundBatches - 1) / kRoundBatches;
+  const int32_t n_coded = n_batches + 1;  // as the coder goes: a batch of identity steps behind the last
+  const int32_t n_iters = n_coded + 5;
+  const int32_t piece_batches = a.piece_batches * kBatch / B;
   uint16_t *wp = a.words_out + a.word_off[unit];
   const uint32_t pad = __builtin_amdgcn_readfirstlane((uint32_t)((reinterpret_cast<uintptr_t>(wp) >> 1) & 7u));
-  // Restart points: the packer has a record's states and words at hand, the mover its escapes.
+  // Restart points: the packers have a record's states and words at hand, the symbols' wavefront its escapes.
   uint32_t *const points = a.points_out ? a.points_out + unit * a.point_stride * PLC_RESTART_WORDS : nullptr;
 
-  if (wave == 0) {
-    // ---- coder: batch it - 2
+  if (wave == kCoder) {
+    // ---- batch it - 2
     __syncthreads();  // tables
     __syncthreads();  // first symbols
-    uint32_t x = kLow;
-    u32x4 e[kBatch / 4][4], before = {0u, 0u, 0u, 0u};
-    const u32x4 *const entries = reinterpret_cast<const u32x4 *>(&entry_ring[0][0][lane & 31]);
-    u32x4 *const states = reinterpret_cast<u32x4 *>(&state_ring[0][0][lane & 31]);
-    u32x4 *held = states + (kStateSlots - 1) * (kBatch / 4) * kLanes;  // (read by nobody yet)
+    uint32_t y = kLow;
+    u32x4 e[4][4], before = {0u, 0u, 0u, 0u};
+    constexpr int kEntryStep = B * kLanes, kStateStep = (B / 8) * 64;
+    // the lower half is a step behind the upper: row r - 1 where the other reads row r, the last one for row 0
+    const u32x4 *const entries = reinterpret_cast<const u32x4 *>(&entry_ring[0][0]) + lane;
+    const u32x4 *const wrapped = reinterpret_cast<const u32x4 *>(&entry_ring[lane < kLanes ? kEntrySlots * B - 1 : 0][lane & 31]);
+    u32x4 *const states = reinterpret_cast<u32x4 *>(&state_ring[0][0][lane]);
+    u32x4 *held = states + kStateSlots * kStateStep - 64;  // (read by nobody yet)
     lds_barrier();  // iteration 0
 #pragma unroll
-    for (int j = 0; j < 8; ++j) e[j / 4][j % 4] = entries[j * kLanes];
+    for (int j = 0; j < 8; ++j) e[j / 4][j % 4] = j == 0 ? *wrapped : entries[(j - 1) * kLanes];
     lds_barrier();  // iteration 1
-    auto code = [&](auto form_c) {  // a loop per form, and little in it besides the steps
+    static_assert(kEntrySlots == 3 && kStateSlots == 3, "three batches a turn");
+    auto code = [&](auto form_c) {  // a loop per form, and nothing in it besides the steps
       constexpr EncForm kForm = decltype(form_c)::value;
-      uint64_t emit = __builtin_amdgcn_uicmp(x, e[0][0].y, 34 /* unsigned > */);
-      constexpr int kEntryStep = kBatch * kLanes, kStateStep = (kBatch / 4) * kLanes;
-      int at = 0, sat = 0;  // uniform
-      const u32x4 *eb = entries;
-      for (int32_t b = 0; b < n_batches; ++b) {
-        at = at == (kEntrySlots - 1) * kEntryStep ? 0 : at + kEntryStep;
-        const u32x4 *next = entries + at;
-        pipe_batch<kForm>(x, emit, e, before, held, eb, next, states + sat);
-        sat = sat == (kStateSlots - 1) * kStateStep ? 0 : sat + kStateStep;
-        eb = next;
+      uint64_t emit = __builtin_amdgcn_uicmp(y, e[0][0].z, 34 /* unsigned > */);
+      auto batch = [&](auto slot) {
+        constexpr int kAt = decltype(slot)::value, kNext = (kAt + 1) % 3;
+        pipe_batch<kForm, B>(y, emit, e, before, held, entries + kAt * kEntryStep,
+                          kNext == 0 ? wrapped : entries + kNext * kEntryStep - kLanes, entries + kNext * kEntryStep,
+                          states + kAt * kStateStep);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();  // iteration b + 2
         asm volatile("" ::: "memory");
+      };
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // (lgkmcnt(0): nothing for the loop to wait for in every turn)
+      PLC_PIN();
+      for (int32_t turns = n_coded / 3; turns > 0; --turns) {
+        batch(std::integral_constant<int, 0>{});
+        batch(std::integral_constant<int, 1>{});
+        batch(std::integral_constant<int, 2>{});
       }
+      const int32_t more = n_coded % 3;
+      if (more > 0) batch(std::integral_constant<int, 0>{});
+      if (more > 1) batch(std::integral_constant<int, 1>{});
     };
-    // (the upper half is switched off: it would ask for the same entries once more, 721 instead of 704 us)
-    if (lane < kLanes) {
-      if (form == kEncLong) {
-        code(std::integral_constant<EncForm, kEncLong>{});
-      } else if (form == kEncPlain) {
-        code(std::integral_constant<EncForm, kEncPlain>{});
-      } else {
-        code(std::integral_constant<EncForm, kEncShort>{});
-      }
-      *held = before;  // the last four states, in place before the barrier behind them
+    if (form == kEncLong) {
+      code(std::integral_constant<EncForm, kEncLong>{});
+    } else if (form == kEncPlain) {
+      code(std::integral_constant<EncForm, kEncPlain>{});
+    } else {
+      code(std::integral_constant<EncForm, kEncShort>{});
     }
-    for (int32_t it = n_batches + 2; it < n_iters; ++it) lds_barrier();
-    if (lane < kLanes) {
-      a.states_out[unit * kLanes + lane] = x;
-      if (points) points[lane] = x;
+    *held = before;  // the last states, in place before the barrier behind them, and the one behind them
+    states[(n_coded % kStateSlots) * kStateStep] = u32x4{y, y, y, y};
+    for (int32_t it = n_coded + 2; it < n_iters; ++it) lds_barrier();
+    if (lane < kLanes) {  // (the steps behind the last have added its addend and then nothing)
+      a.states_out[unit * kLanes + lane] = y;
+      if (points) points[lane] = y;
     }
-  } else if (wave == 1) {
-    // ---- feeder: entries of batch it
+  } else if (wave == kFeeder0 || wave == kFeeder1) {
+    // ---- entries of batch it, half of them each: written in the batch's own iteration, looked up in the one before, and
+    // the symbols read two before, so that nothing is waited for.  Lane (half, l) serves kMine steps of rANS lane l from
+    // first on; a step's entry goes with the addend of the step in front of it, whose symbol the lane looks up too.
     __syncthreads();  // tables
     __syncthreads();  // first symbols
-    bool bad_symbol = false;
+    constexpr int kMine = B / 4;
+    const int l = lane & 31, first = ((wave == kFeeder1 ? 2 : 0) + (lane >> 5)) * kMine;
+    uint32_t sy[kMine + 1];     // the step in front, then the lane's own
+    uint32_t own[kMine / 4], above = 0;  // ADAPT: tables of the lane's groups, from the lowest, and of the one in front
+    u32x2 head_of[kMine], tail_of[kMine + 1];  // the entries' halves; the step in front has the first tail
+    uint32_t any = 0;
+    auto ask = [&](int32_t b) __attribute__((always_inline)) {  // symbols of a batch of B full groups
+      const int32_t r = b / kRoundBatches, at = batch_top(b) - round_bottom(r) - first - kMine;  // the lane's lowest group
+      const uint8_t *s0 = sym_stage[r & 1] + (at * kLanes + l + (int32_t)mis);
+#pragma unroll
+      for (int p = 0; p <= kMine; ++p) sy[p] = s0[kLanes * (kMine - p)];
+      if constexpr (ADAPT) {
+        const uint8_t *tg = &table_of_group[r & 1][at];
+#pragma unroll
+        for (int i = 0; i < kMine / 4; ++i) own[i] = reinterpret_cast<const uint32_t *>(tg)[i];
+        above = tg[kMine];
+      }
+    };
+    auto look_up_step = [&](int p, uint32_t i) __attribute__((always_inline)) {
+      if (p) head_of[p - 1] = *reinterpret_cast<const u32x2 *>(&table[i]);
+      if (!kPacked) tail_of[p] = *reinterpret_cast<const u32x2 *>(&table[kOther + i]);
+      if (kPacked && p == 0) tail_of[0].y = table[i].y;
+    };
+    auto look_up = [&](const uint32_t (&i)[kMine + 1]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int p = 0; p <= kMine; ++p) look_up_step(p, i[p]);
+    };
+    auto asked = [&](int32_t b, uint32_t (&i)[kMine + 1]) __attribute__((always_inline)) {
+      i[0] = ADAPT ? sy[0] | above << 8 : sy[0];
+#pragma unroll
+      for (int p = 1; p <= kMine; ++p)  // symbol | table << 8
+        i[p] = ADAPT ? __builtin_amdgcn_perm(own[(kMine - p) / 4], sy[p], 0x0c0c0400u + ((uint32_t)((kMine - p) & 3) << 8)) : sy[p];
+      if (b == 1 && head < B && first == 0) i[0] = kIdentity;  // batch 0 ends in identity steps
+    };
+    auto look_up_ends = [&](int32_t b) {  // the first batch, whose top group may be ragged, and the last
+      uint32_t i[kMine + 1];
+      const int32_t r = b / kRoundBatches, bottom = round_bottom(r), top = batch_top(b);
+#pragma unroll
+      for (int p = 0; p <= kMine; ++p) {
+        const int j = first - 1 + p;  // -1: the batch before's last step
+        const int32_t g = top - 1 - j;
+        const bool step = j < 0 ? b > 1 || (b == 1 && head == B) : b > 0 || j < head;
+        const bool has = step && g >= 0 && (int64_t)g * kLanes + l < (int64_t)len;
+        i[p] = sym_stage[r & 1][has ? (g - bottom) * kLanes + l + (int32_t)mis : 0];
+        if (ADAPT && has) i[p] += (uint32_t)table_of_group[r & 1][g - bottom] << 8;
+        i[p] = has ? i[p] : (uint32_t)kIdentity;
+      }
+      look_up(i);
+    };
+    auto unpack = [&]() __attribute__((always_inline)) {
+      if (kPacked) {
+        tail_of[0].y = (uint32_t)((int32_t)tail_of[0].y >> 18);
+#pragma unroll
+        for (int p = 0; p < kMine; ++p) {
+          const uint4 v = unpack_enc_entry(make_uint2(head_of[p].x, head_of[p].y));
+          head_of[p].y = v.z;
+          tail_of[p + 1] = u32x2{v.y, v.w};
+        }
+      }
+    };
+    auto put_step = [&](int p, uint4 *eo) __attribute__((always_inline)) {
+      any |= tail_of[p + 1].y;
+      tail_of[p].x = tail_of[p + 1].x - tail_of[p].y;  // beside the addend in front already
+      u32x2 *to = reinterpret_cast<u32x2 *>(eo + p * kLanes);
+      to[0] = head_of[p];
+      to[1] = tail_of[p];
+    };
+    look_up_ends(0);
+    if (n_batches > 2) ask(1);
     int slot = 0;
-    for (int32_t it = 0; it < n_iters; ++it) {
-      if (it < n_batches) {
-        const int32_t r = it >> 2;
-        const int32_t top = batch_top(it), bottom = round_bottom(r);
-        const uint8_t *sb = sym_stage[r & 1];
-        // lane (half h, l) serves step 2p + h of the batch: group top - 1 - 2p - h, rANS lane l
-        const int half = lane >> 5, l = lane & 31;
-        uint4 *eo = &entry_ring[slot][half][l];
-        if (it > 0) {
-          // 16 full groups: all symbol reads, then all table reads, then all ring writes, so that the LDS
-          // round trips overlap instead of queueing one behind the other
-          const uint8_t *s0 = sb + ((top - bottom - 2 * (kBatch / 2 - 1) - 1 - half) * kLanes + l + (int32_t)mis);
-          uint32_t sy[kBatch / 2];
-          u32x4 e[kBatch / 2];  // native vectors: each entry moves as one 16-byte LDS access
+    int32_t b = 0;
+    for (; b + 3 < n_batches; ++b) {
+      uint4 *eo = &entry_ring[slot * B + first][l];
+      slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
+      uint32_t i[kMine + 1];
+      asked(b + 1, i);
+      unpack();
+      PLC_PIN();
+      // Writes and look-ups by turns: writes in a row hold the coder's accesses up (256 units of 1,048,576 symbols 620 ->
+      // 586 us).
 #pragma unroll
-          for (int p = 0; p < kBatch / 2; ++p) sy[p] = s0[2 * kLanes * (kBatch / 2 - 1 - p)];
-          uint32_t any = 0;
-          if constexpr (ADAPT) {  // the group of step 2p + half sits at top - bottom - 1 - half - 2p of the round
-            const uint2 tg = *reinterpret_cast<const uint2 *>(&table_of_group[r & 1][top - bottom - kBatch + 8 * half]);
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p)  // symbol | table << 8
-              sy[p] = __builtin_amdgcn_perm(p < 4 ? tg.x : tg.y, sy[p], 0x0c0c0400u + ((uint32_t)(p & 3) << 8));
-          }
-          if constexpr (kPacked) {
-            uint2 c[kBatch / 2];
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p) c[p] = table[sy[p]];
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p) {
-              any |= c[p].y;
-              const uint4 v = unpack_enc_entry(c[p]);
-              e[p] = u32x4{v.x, v.y, v.z, v.w};
-            }
-          } else {
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p) e[p] = *reinterpret_cast<const u32x4 *>(&table[sy[p]]);
-#pragma unroll
-            for (int p = 0; p < kBatch / 2; ++p) any |= e[p].w;
-          }
-#pragma unroll
-          for (int p = 0; p < kBatch / 2; ++p) *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = e[p];
-          bad_symbol = bad_symbol || (any & 0x80000000u) != 0;
-        } else {
-          // the top batch: `head` groups, the first of them possibly ragged, then identity steps
-#pragma unroll
-          for (int p = 0; p < kBatch / 2; ++p) {
-            const int j = 2 * p + half;
-            const int64_t t = (int64_t)(top - 1 - j) * kLanes + l;
-            const bool has = j < head && t < (int64_t)len;
-            const int64_t idx = has ? t - (int64_t)bottom * kLanes + mis : 0;
-            uint32_t byte = sb[idx];
-            if (ADAPT && has) byte += (uint32_t)table_of_group[r & 1][group_at(top - 1 - j - bottom)] << 8;
-            const Entry c = table[has ? byte : (uint32_t)kIdentity];
-            if constexpr (kPacked) {
-              bad_symbol = bad_symbol || (c.y & 0x80000000u) != 0;
-              eo[2 * p * kLanes] = unpack_enc_entry(c);
-            } else {
-              bad_symbol = bad_symbol || (c.w & 0x80000000u) != 0;
-              eo[2 * p * kLanes] = c;
-            }
-          }
-        }
-        slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
+      for (int p = 0; p <= kMine; ++p) {
+        if (p < kMine) put_step(p, eo);
+        PLC_PIN();
+        look_up_step(p, i[p]);
+        PLC_PIN();
       }
-      lds_barrier();
+      ask(b + 2);
+      PLC_PIN();
+      asm volatile("" ::: "memory");
+      // the entries are in the ring; what was asked for behind them may be on its way (tables do not change, and
+      // symbols only rounds later)
+      __builtin_amdgcn_s_waitcnt(kPacked ? 0xc57f : 0xc87f);  // lgkmcnt(5) or (8): of so many reads behind the last write at the least
+      __builtin_amdgcn_s_barrier();  // iteration b
+      asm volatile("" ::: "memory");
     }
-    if (bad_symbol) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0
-  } else if (wave == 2) {
-    // ---- packer: batch it - 4
+    for (; b < n_batches; ++b) {  // the last three
+      uint4 *eo = &entry_ring[slot * B + first][l];
+      slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
+      unpack();
+#pragma unroll
+      for (int p = 0; p < kMine; ++p) put_step(p, eo);
+      if (b + 2 < n_batches) {
+        uint32_t i[kMine + 1];
+        asked(b + 1, i);
+        look_up(i);
+      } else if (b + 1 < n_batches) {
+        look_up_ends(b + 1);
+      }
+      lds_barrier();  // iteration b
+    }
+    {  // the steps behind the last: the first adds what that leaves to add
+      const int32_t r = n_rounds - 1;
+      uint32_t i = sym_stage[r & 1][l + mis];  // group 0, the lowest of the last round
+      if (ADAPT) i += (uint32_t)table_of_group[r & 1][0] << 8;
+      if (n_batches == 1 ? head < B : (G - head) % B != 0) i = kIdentity;
+      uint32_t last = kPacked ? (uint32_t)((int32_t)table[i].y >> 18) : table[kOther + i].y;
+      if (first > 0) last = 0u;
+      uint4 *eo = &entry_ring[slot * B + first][l];
+      eo[0] = make_uint4(0u, 0u, 0xffffffffu - last, last);
+#pragma unroll
+      for (int p = 1; p < kMine; ++p) eo[p * kLanes] = make_uint4(0u, 0u, 0xffffffffu, 0u);
+    }
+    for (int32_t it = n_batches; it < n_iters; ++it) lds_barrier();
+    if (any & 0x80000000u) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0
+  } else if (wave == kPacker0 || wave == kPacker1) {
+    // ---- every second batch each: which lanes emit, and how many, in iteration b + 4, their ranks and words in the one
+    // behind it.
+    // A lane emits in a step iff the state behind the step is below the one in front of it: without a word
+    // x' - x = q * (4096 - f) + cum >= 0, with one x' <= x / (16 f) + 4095 and x >= f * 2^20.
     __syncthreads();  // tables
     __syncthreads();  // first symbols
-    uint32_t fill = pad;  // uniform: positions of the region in use, the first of them not this pair's words
-    int region = 0;
-    uint32_t gone = 0u - pad;  // words of the regions before (the padding in front of the first taken off)
-    int32_t point_at = points ? a.piece_batches : INT32_MAX;  // the batch that the next record stands in front of
+    const int odd = wave == kPacker1 ? 1 : 0;
+    uint32_t total = pad;  // uniform: words in front of the batch, the padding in front of the first among them
+    uint32_t mine = 0;     // and of this packer's last batch
+    int32_t point_at = points ? piece_batches : INT32_MAX;  // the batch that the next record stands in front of
     uint32_t *record = points;
-    // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
-    // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
-    const int half = lane >> 5, rl = 31 - (lane & 31);
-    uint16_t *const spare = &spare_word[lane];
-    // The thresholds are read two batches ahead of the states, while the coder is at their entries, and wait in
-    // registers: three sets, so three iterations a turn.
-    uint32_t thrs[3][kBatch / 2];
-    auto pack = [&](auto turn, int32_t it) {
-      constexpr int kTurn = decltype(turn)::value;  // it mod 3
-      {
-        const uint32_t *ts = &entry_ring[(kTurn + 1) % 3][half][rl].y;  // batch it - 2
+    // Hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first.  A batch here begins with the last
+    // step of the one before: the coder's lower half is a step behind, so that lower lanes have the states in front of
+    // steps -1, 1, .. B - 3 and upper ones those in front of steps 0, 2, .. B - 2, and the states behind are the other
+    // half's.
+    const bool upper = lane >= kLanes;
+    const int at_ring = (lane & 32) + 31 - (lane & 31);
+    constexpr int kPairs = B / 2;  // pairs of steps
+    uint16_t *const spare = &spare_word;
+    int slot = odd;
+    int32_t it = 0;
+    for (; it < 4 + odd; ++it) lds_barrier();
+    for (int32_t b = odd; b < n_coded; b += 2) {
+      const u32x4 *src = reinterpret_cast<const u32x4 *>(&state_ring[slot][0][0]);
+      const uint32_t *behind = &state_ring[slot == kStateSlots - 1 ? 0 : slot + 1][0][at_ring & 31].x;
+      slot = slot == 0 ? 2 : slot - 1;  // two on
+      uint32_t word[kPairs], next[kPairs + 1], at[kPairs];
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) thrs[kTurn][p] = ts[2 * p * kLanes * 4];
+      for (int q = 0; q < B / 8; ++q) {
+        *reinterpret_cast<u32x4 *>(&word[4 * q]) = src[q * 64 + at_ring];
+        *reinterpret_cast<u32x4 *>(&next[4 * q]) = src[q * 64 + (at_ring ^ 32)];
       }
-      const int32_t b = it - 4;
-      if (b >= 0 && b < n_batches) {
-        const uint32_t(&thr)[kBatch / 2] = thrs[(kTurn + 1) % 3];
-        const uint32_t *xs = reinterpret_cast<const uint32_t *>(&state_ring[(kTurn + 2) % 3][0][rl]) + half;
-        uint16_t *list = word_list[region];
-        // In phases, each over all eight step pairs: reads, emit masks, list positions, stores.  A lane without
-        // a word stores into a slot of its own instead of sitting out the store.
-        uint32_t xps[kBatch / 2], at[kBatch / 2];
+      next[kPairs] = *behind;
+      uint32_t n1 = batch_words[odd ^ 1];  // of the batch before
+      PLC_PIN();
+      // (every compare before the first count: a scalar instruction waits for a mask that was only just written)
+      uint64_t emits[kPairs];
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
-        if (b == point_at) {  // uniform; the states in front of the batch's first step
-          point_at += a.piece_batches;
-          record += PLC_RESTART_WORDS;
-          if (half == 0) record[rl] = xps[0];
-          if (lane == 0) record[kLanes] = gone + fill;
-        }
+      for (int p = 0; p < kPairs; ++p) emits[p] = __ballot((upper ? next[p + 1] : next[p]) < word[p]);
+      PLC_PIN();
+      uint32_t n = 0;
+      asm volatile("" : "+v"(n));  // (a vector register: the masks are scalars, and an instruction takes one)
 #pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) {
-          const uint64_t mask = __ballot(xps[p] > thr[p]);
-          at[p] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, fill));
-          fill += (uint32_t)__builtin_popcountll(mask);
-        }
-#pragma unroll
-        for (int p = 0; p < kBatch / 2; ++p) *(xps[p] > thr[p] ? list + at[p] : spare) = (uint16_t)xps[p];
-        if ((b & 1) || b == n_batches - 1) {  // on to the next pair's region
-          if (lane == 0) list_fill[region] = fill;
-          region = region == kListRegions - 1 ? 0 : region + 1;
-          gone += fill & ~7u;
-          fill &= 7u;
-        }
+      for (int p = 0; p < kPairs; ++p) {
+        at[p] = n;
+        n += (uint32_t)__builtin_popcountll(emits[p]);
       }
-      lds_barrier();
-    };
-    static_assert(kEntrySlots == 3 && kStateSlots == 3, "three iterations a turn");
-    for (int32_t it = 0; it < n_iters; it += 3) {
-      pack(std::integral_constant<int, 0>{}, it);
-      if (it + 1 < n_iters) pack(std::integral_constant<int, 1>{}, it + 1);
-      if (it + 2 < n_iters) pack(std::integral_constant<int, 2>{}, it + 2);
+      if (lane == 0) batch_words[odd] = n;
+      n1 = __builtin_amdgcn_readfirstlane(n1);
+      total += mine + n1;
+      mine = __builtin_amdgcn_readfirstlane(n);
+      // a batch has a region, in which its first words stand behind up to seven of the batch before
+      const uint32_t fill = total & 7u;
+      uint16_t *const list = word_list[odd] + fill;
+      PLC_PIN();
+      lds_barrier();  // iteration b + 4
+      // (a lane without a word stores into a slot of its own instead of sitting out the store)
+#pragma unroll
+      for (int p = 0; p < kPairs; ++p) {
+        const uint32_t i = __builtin_amdgcn_mbcnt_hi((uint32_t)(emits[p] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)emits[p], at[p]));
+        *(__builtin_amdgcn_inverse_ballot_w64(emits[p]) ? list + i : spare) = (uint16_t)word[p];
+      }
+      if (lane == 0) list_fill[odd] = fill + mine;
+      if (b >= point_at) {  // uniform; two batches on there is at most one record to be passed
+        record += PLC_RESTART_WORDS;
+        if (b == point_at && b < n_batches) {  // the states in front of the batch's first step
+          if (upper) record[at_ring & 31] = word[0];
+          if (lane == 0) record[kLanes] = total - pad + (uint32_t)__builtin_popcount((uint32_t)emits[0]);
+        }
+        point_at += piece_batches;
+      }
+      lds_barrier();  // iteration b + 5
+      it += 2;
     }
-  } else {
-    // ---- mover: symbols of the coming round, words of batch it - 5
+    for (; it < n_iters; ++it) lds_barrier();
+  } else if (wave == kSymbols) {
+    // ---- symbols of the coming round
     bool bad_depth = false;
     uint4 nv[kStagePieces];         // next round's symbols in flight
     bool ntake[kStagePieces];
     // ADAPT: depth of group bottom + lane of the next round.  It is looked at when the round's symbols land: where it
     // is asked for, its range check would have the wavefront, and at the barrier the others, wait for the answer in
     // every round (964 -> 829 us for 256 units of 1,048,576 symbols).
-    uint32_t next_depth = 1;
+    uint32_t next_depth = 1, table_above = 0;
     const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
     const uint8_t *const depth_row =
         ADAPT ? a.bits + (int64_t)((uint32_t)unit / (uint32_t)a.streams_per_session) * (len / spp) : nullptr;
-    auto round_load = [&](int32_t r) {
+    auto round_load = [&](int32_t r) __attribute__((always_inline)) {  // the round's groups and the one above, whose addends the feeder needs
       const int64_t lo = (int64_t)round_bottom(r) * kLanes;
-      int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
+      int64_t hi = (int64_t)(batch_top(kRoundBatches * r) + 1) * kLanes;
       hi = hi < (int64_t)len ? hi : (int64_t)len;
 #pragma unroll
       for (int i = 0; i < kStagePieces; ++i) {
@@ -1393,82 +1503,45 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
       }
       if (ADAPT) {
         const int32_t g = round_bottom(r) + lane;
-        next_depth = (r < n_rounds && g < batch_top(4 * r)) ? depth_row[(uint32_t)g * kLanes / spp] : 1u;
+        next_depth = (r < n_rounds && g < batch_top(kRoundBatches * r)) ? depth_row[(uint32_t)g * kLanes / spp] : 1u;
       }
     };
-    auto round_store = [&](int buf) {
+    auto round_store = [&](int32_t r) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < kStagePieces; ++i)
-        if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
-      if (ADAPT) {
+        if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[r & 1][(lane + 64 * i) * 16]) = nv[i];
+      if (ADAPT && r < n_rounds) {
         const bool known = next_depth >= 1u && next_depth <= (uint32_t)a.n_tables;
         bad_depth = bad_depth || !known;
-        table_of_group[buf][group_at(lane)] = (uint8_t)(known ? next_depth - 1u : 0u);
+        const uint32_t t = known ? next_depth - 1u : 0u;
+        table_of_group[r & 1][lane] = (uint8_t)t;
+        if (lane == 0 && r > 0)  // the group above is the lowest of the round before
+          table_of_group[r & 1][batch_top(kRoundBatches * r) - round_bottom(r)] = (uint8_t)table_above;
+        table_above = t;
       }
     };
     round_load(0);
     __syncthreads();  // tables
     round_store(0);
     round_load(1);
+    round_store(1);
+    round_load(2);
     __syncthreads();  // first symbols
-    // Words.  Position p of a region stands for the word at 16-byte-aligned address (wp - pad) + vbase + p; the
-    // first `pad` positions of the first are padding in front of the unit's first word.  The complete 16-byte
-    // pieces leave, up to two per lane; the incomplete tail (< 8 words) moves to the front of the next region, in
-    // front of the words that the packer has written or is writing there.
-    const uint32_t cap = a.word_cap < 0x7fffffffull ? (uint32_t)a.word_cap : 0x7fffffffu;  // a unit has < 2^31 symbols
-    uint32_t vbase = 0, rest = pad;
-    const int32_t n_pairs = (n_batches + 1) / 2;
-    int32_t out_pair = 0;  // the next pair of batches whose words leave
-    int region = 0;
-    auto words_out = [&]() {
-      const uint16_t *list = word_list[region];
-      const uint32_t fill = __builtin_amdgcn_readfirstlane(list_fill[region]);
-      region = region == kListRegions - 1 ? 0 : region + 1;
-      const uint32_t full = fill / 8;  // at most 128
-      rest = fill - 8 * full;
-      const uint16_t tail = list[8 * full + (lane & 7)];  // (lanes past the tail read inside the region)
-      if (vbase >= pad && vbase + 8 * full - pad <= cap) {
-        uint16_t *dst = wp + (vbase - pad);  // 16-byte aligned
-        uint4 v[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)  // (a lane past the last piece reads inside the region)
-          v[h] = *reinterpret_cast<const uint4 *>(list + 8 * (lane + 64 * h));
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          if ((uint32_t)(lane + 64 * h) < full) *reinterpret_cast<uint4 *>(dst + 8 * (lane + 64 * h)) = v[h];
-      } else {
-        for (uint32_t q = lane; q < 8 * full; q += 64) {
-          const uint32_t v = vbase + q;
-          if (v >= pad && v - pad < cap) wp[v - pad] = list[q];
-        }
-      }
-      vbase += 8 * full;
-      ++out_pair;
-      if ((uint32_t)lane < rest) {
-        if (out_pair < n_pairs) {
-          word_list[region][lane] = tail;
-        } else {  // the incomplete last piece
-          const uint32_t v = vbase + (uint32_t)lane;
-          if (v >= pad && v - pad < cap) wp[v - pad] = tail;
-        }
-      }
-      wave_sync();  // the next pair's reads come behind the tail's way to its front, from other lanes (no barrier
-                    // stands between them where pairs leave one behind the other at the unit's end)
-    };
     // Escapes, for the restart points: a round's symbols are counted in the stage in the last iteration before others
-    // take their place, in which the mover has nothing else to do.
+    // take their place, in which this wavefront has nothing else to do.
     uint32_t esc_mine = 0;  // this lane's, of the rounds so far
-    int32_t point_at = points ? a.piece_batches / 4 : INT32_MAX;  // the round that the next record stands in front of
+    const int32_t piece_rounds = piece_batches / kRoundBatches;
+    int32_t point_at = points ? piece_rounds : INT32_MAX;  // the round that the next record stands in front of
     uint32_t *record = points;
-    auto count_round = [&](int32_t r) {
+    auto count_round = [&](int32_t r) __attribute__((always_inline)) {
       if (r == point_at) {
-        point_at += a.piece_batches / 4;
+        point_at += piece_rounds;
         record += PLC_RESTART_WORDS;
         const uint32_t total = wave_sum(esc_mine);
         if (lane == 0) record[kLanes + 1] = total;
       }
       const uint8_t *sb = sym_stage[r & 1];
-      const uint32_t lo = (uint32_t)round_bottom(r) * kLanes, top = (uint32_t)batch_top(4 * r) * kLanes;
+      const uint32_t lo = (uint32_t)round_bottom(r) * kLanes, top = (uint32_t)batch_top(kRoundBatches * r) * kLanes;
       const uint32_t n = (top < len ? top : len) - lo;
       if (mis == 0 && n == (uint32_t)kSuperSyms) {  // uniform
 #pragma unroll
@@ -1483,27 +1556,79 @@ __global__ __launch_bounds__(kPipeThreads) void rans_encode_pipe_kernel(const Ra
         for (uint32_t t = lane; t < n; t += 64) esc_mine += sb[t + mis] == PLC_ESCAPE;
       }
     };
+    // The feeders read a round's symbols up to two iterations ahead, the last batch's one ahead.
     for (int32_t it = 0; it < n_iters; ++it) {
-      const int32_t phase = it & 3;
-      if (phase == 3 && points && (it >> 2) < n_rounds) count_round(it >> 2);
-      if (phase == 0 && it < n_batches) {  // the feeder has begun a round: the next one's symbols land
-        const int32_t r = it >> 2;
-        round_store((r + 1) & 1);
-        round_load(r + 2);
+      const int32_t r = it / kRoundBatches, phase = it % kRoundBatches;
+      if (phase == kRoundBatches - 2 && points && r < n_rounds) count_round(r);
+      if (phase == kRoundBatches - 1 && r + 2 < n_rounds) {
+        round_store(r + 2);
+        round_load(r + 3);
       }
-      // (batch it - 5 is packed: in steady state a pair goes out at phase 1 and the next one at phase 2)
-      if ((phase == 1 || phase == 2) && 2 * out_pair + 1 <= it - 5) words_out();
       lds_barrier();
     }
-    while (out_pair < n_pairs) words_out();
+    if (points) {
+      const uint32_t esc_total = wave_sum(esc_mine);
+      if (lane == 0) points[kLanes + 1] = esc_total;
+    }
+    if (bad_depth) raise(a.status, PLC_ERR_INVALID);
+  } else {
+    // ---- words.  Position p of a region stands for the word at 16-byte-aligned address (wp - pad) + vbase + p; the
+    // first `pad` positions of the first are padding in front of the unit's first word.  The complete 16-byte
+    // pieces leave, a batch's in one iteration; the incomplete tail (< 8 words) moves to the front of the next region, in
+    // front of the words that the packer has written or is writing there.
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    const uint32_t cap = a.word_cap < 0x7fffffffull ? (uint32_t)a.word_cap : 0x7fffffffu;  // a unit has < 2^31 symbols
+    uint32_t vbase = 0, rest = pad;
+    auto words_out = [&](int32_t b) __attribute__((always_inline)) {
+      const uint16_t *list = word_list[b & 1];
+      uint32_t fill = list_fill[b & 1];
+      u32x4 v[B / 16];
+#pragma unroll
+      for (int h = 0; h < B / 16; ++h)  // (a lane past the last piece reads inside the region)
+        v[h] = *reinterpret_cast<const u32x4 *>(list + 8 * (lane + 64 * h));
+      fill = __builtin_amdgcn_readfirstlane(fill);
+      const uint32_t full = fill / 8;  // at most 64 to a batch's 512 symbols
+      rest = fill - 8 * full;
+      const uint16_t tail = list[8 * full + (lane & 7)];  // (lanes past the tail read inside the region)
+      if (vbase >= pad && vbase + 8 * full - pad <= cap) {
+        uint16_t *dst = wp + (vbase - pad);  // 16-byte aligned
+#pragma unroll
+        for (int h = 0; h < B / 16; ++h)
+          if ((uint32_t)(lane + 64 * h) < full) *reinterpret_cast<u32x4 *>(dst + 8 * (lane + 64 * h)) = v[h];
+      } else {
+        for (uint32_t q = lane; q < 8 * full; q += 64) {
+          const uint32_t i = vbase + q;
+          if (i >= pad && i - pad < cap) wp[i - pad] = list[q];
+        }
+      }
+      vbase += 8 * full;
+      if ((uint32_t)lane < rest) {
+        if (b + 1 < n_coded) {
+          word_list[(b + 1) & 1][lane] = tail;
+        } else {  // the incomplete last piece
+          const uint32_t i = vbase + (uint32_t)lane;
+          if (i >= pad && i - pad < cap) wp[i - pad] = tail;
+        }
+      }
+    };
+    // The words of batch b are in their region when iteration b + 6 begins; it is written again in iteration b + 7.
+    for (int it = 0; it < 6; ++it) lds_barrier();
+    int32_t b = 0;
+    for (; b + 6 < n_iters; ++b) {
+      words_out(b);
+      lds_barrier();  // iteration b + 6
+    }
+    for (; b < n_coded; ++b) {
+      words_out(b);
+      wave_sync();  // the next batch's reads come behind the tail's way to its front, from other lanes
+    }
     const uint32_t n_words = vbase + rest - pad;
-    const uint32_t esc_total = wave_sum(esc_mine);
     if (lane == 0) {
       a.n_words_out[unit] = n_words;
       if ((uint64_t)n_words > a.word_cap) raise(a.status, PLC_ERR_CAPACITY);
-      if (points) points[kLanes] = n_words, points[kLanes + 1] = esc_total;
+      if (points) points[kLanes] = n_words;
     }
-    if (bad_depth) raise(a.status, PLC_ERR_INVALID);
   }
 }
 
@@ -3542,17 +3667,22 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
   hipStream_t st = static_cast<hipStream_t>(stream);
   {
     TraceScope trace(PLC_TRACE_RANS_ENCODE, st);
-    if (a.units_per_stream == 1 && a.n_units <= kPipeMaxUnits) {
-      const bool wide = !a.bits || a.n_units <= 2 * kComputeUnits;
-      trace.kernel("rans_encode_pipe_kernel<%s, %s>", a.bits ? "true" : "false", wide ? "true" : "false");
-      // few units (kPipeMaxUnits): the chain of one unit is the time, so give each unit four wavefronts
-      // (with more units, four wavefronts per unit cost more in occupancy than the shorter chain gains)
-      if (a.bits && wide) {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, true>), dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
-      } else if (a.bits) {
-        hipLaunchKernelGGL(rans_encode_pipe_kernel<true>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
+    if (a.units_per_stream == 1 && encode_in_pipe(a.n_units, syms_per_stream, a.bits != nullptr)) {
+      const bool wide = !a.bits || a.n_units <= kComputeUnits, few = a.n_units <= 2 * kComputeUnits;
+      trace.kernel("rans_encode_pipe_kernel<%s, %d, %s>", a.bits ? "true" : "false", few ? 32 : 16, wide ? "true" : "false");
+      // few units: the chain of one unit is the time, so give each unit seven wavefronts
+      // (with more units, seven wavefronts per unit cost more in occupancy than the shorter chain gains)
+      const dim3 grid((unsigned)a.n_units), block(kPipeThreads);
+      if (!a.bits && few) {
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 32>), grid, block, 0, st, a);
+      } else if (!a.bits) {
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 16>), grid, block, 0, st, a);
+      } else if (wide) {
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, true>), grid, block, 0, st, a);
+      } else if (few) {
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, false>), grid, block, 0, st, a);
       } else {
-        hipLaunchKernelGGL(rans_encode_pipe_kernel<false>, dim3((unsigned)a.n_units), dim3(kPipeThreads), 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 16, false>), grid, block, 0, st, a);
       }
     } else if (a.bits && (a.units_per_stream == 1 ? !encode_depths_in_pairs(a.n_units) : a.n_units <= kFewChunks)) {
       launch_encode_depths(a, n_streams, st, trace);

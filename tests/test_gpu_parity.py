@@ -373,6 +373,45 @@ def test_few_unit_encoders_side_by_side_on_a_compute_unit(oracle, dev, n_streams
         assert not w[unit, nw:].any()
 
 
+@pytest.mark.parametrize("n_streams,groups", [(260, [1, 16, 17, 31, 32, 33, 48, 49, 64, 80, 81, 113, 145]), (516, [1, 15, 16, 33, 48, 80, 81]),
+                                              (1028, [1024, 1041])])
+@pytest.mark.parametrize("tables", [1, 4])
+def test_few_unit_encoders_of_either_batch_at_the_edges_of_theirs(oracle, dev, n_streams, groups, tables):
+    """Batches of 32 steps and of 16 (more than 512 units, and more than 1024 long ones): heads of up to two times 16
+    groups, a last batch of half its steps, one batch to five and many; every unit against the oracle."""
+    from paper_2604_15356_amd import plc
+    O = oracle
+    for g in groups:
+        N, spp = 32 * g, 32
+        rng = np.random.default_rng(g + tables)
+        bits = rng.integers(1, tables + 1, size=(1, g)).astype(np.uint8)
+        width = 2.0 * 3.0 ** np.repeat(bits, spp, axis=1)
+        sym = np.clip(np.rint(rng.standard_normal((n_streams, N), dtype=np.float32) * width + 127), 0, 254).astype(np.uint8)
+        cap = N + 3
+        i32, i16 = torch.int32, torch.int16
+        sym_t, bits_t = torch.from_numpy(sym).to(dev), torch.from_numpy(bits).to(dev)
+        states, n_words = torch.empty((n_streams, 32), dtype=i32, device=dev), torch.empty(n_streams, dtype=i32, device=dev)
+        words = torch.zeros(n_streams * cap, dtype=i16, device=dev)
+        word_off = torch.arange(n_streams, dtype=torch.int64, device=dev) * cap
+        status = torch.zeros(1, dtype=i32, device=dev)
+        print(f"  {n_streams} units of {N} symbols, {tables} tables", flush=True)
+        if tables > 1:
+            freq = O.build_freq_sparse(O.histogram_bucketed(sym, spp, n_streams, bits, n_tables=tables))
+            enc = O.rans_encode_bucketed(sym, freq, spp, n_streams, bits, word_cap_per_unit=cap)
+            freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+            plc.plc_rans_encode_bucketed(sym_t, n_streams, N, 0, spp, n_streams, bits_t, tables, freq_t, states, words,
+                                         word_off, cap, n_words, status)
+        else:
+            freq, _ = O.build_freq(O.histogram(sym))
+            enc = O.rans_encode(sym, freq, word_cap_per_unit=cap)
+            freq_t = torch.from_numpy(freq.view(np.int16)).to(dev)
+            plc.plc_rans_encode(sym_t, n_streams, N, 0, freq_t, states, words, word_off, cap, n_words, status)
+        assert int(status.item()) == 0
+        assert np.array_equal(u32(n_words), enc["n_words"]) and np.array_equal(u32(states), enc["states"])
+        used = np.arange(cap)[None] < enc["n_words"][:, None]
+        assert np.array_equal(u16(words).reshape(used.shape), np.where(used, enc["words"].reshape(used.shape), 0))
+
+
 @pytest.mark.parametrize("tables", [1, 4])
 def test_few_unit_encoders_with_extreme_frequencies(oracle, dev, tables):
     """Tables of one symbol (f = 4096), of f = 4095 and 1, of two halves (2048 each) and of 256 symbols, each by itself
