@@ -132,6 +132,22 @@ def test_linear_predictor_is_deterministic_and_rejects_bad_shapes(dev):
         plc.plc_expected_embedding(w.probs_full[:100].contiguous(), w.embed_t, codec.ebar[:100].contiguous())
 
 
+@pytest.mark.parametrize("tiles_m,tiles_n", [(16, 16), (4, 72), (9, 32), (32, 8), (15, 18), (64, 4)])
+def test_expected_embedding_tile_orders(dev, tiles_m, tiles_n):
+    """Every tile of the output is written, whatever order the workgroups take them in: blocks of 4 x 8 tiles or row by
+    row, with whole rounds of 256 workgroups and without.  Products of small whole numbers are exact in any order."""
+    from paper_2604_15356_amd import plc
+    rows, m, V = 256 * tiles_m, 256 * tiles_n, 96
+    g = torch.Generator(device="cpu").manual_seed(tiles_m)
+    P = torch.randint(0, 4, (rows, V), generator=g)
+    E = torch.randint(-3, 4, (m, V), generator=g)
+    out = torch.full((rows, m), float("nan"), dtype=torch.float16, device=dev)
+    print(f"expected embedding {rows} x {m}", flush=True)
+    plc.plc_expected_embedding(P.to(torch.float16).to(dev), E.to(torch.float16).to(dev), out)
+    want = P.float() @ E.float().t()   # at most 96 * 9 < 2048: exact in fp32 and in fp16
+    assert torch.equal(out.cpu(), want.to(torch.float16))
+
+
 @pytest.mark.parametrize("V", [32, 64, 96, 416])
 def test_expected_embedding_large_tiles(dev, V):
     """The first contraction at an output that divides into 256 x 256 tiles, one per compute unit (the kernel
