@@ -911,8 +911,11 @@ int encode_floats(const plc_dims *dims, const void *cand_k, const void *cand_v, 
   if (!scan_here)
     hipLaunchKernelGGL(scan_streams_kernel, dim3(1), dim3(kBlock), 0, st, esc_cnt, esc_off, p.n_streams, esc_cap,
                        status);
-  // 64 tiles per wavefront start the fewest wavefronts; where that would leave compute units without one, eight
-  const int32_t per_wave = p.n_tiles >= 64 * 1024 ? 64 : 8;
+  // 64 tiles per wavefront start the fewest wavefronts; where that leaves a SIMD fewer than eight to wait for memory side by
+  // side, fewer (8 / 16 / 32 / 64 tiles, 0.8 % escapes: 65,536 tiles 19 / 22 / 28 / 39 us with the scan in front, 131,072
+  // 27 / 25 / 31 / 43, 262,144 47 / 42 / 38 / 50, 524,288 89 / 76 / 66 / 62).
+  int32_t per_wave = 8;
+  while (per_wave < 64 && per_wave * 8192ll < p.n_tiles) per_wave *= 2;
   const int64_t per_block = (int64_t)per_wave * (kBlock / 64);
   hipLaunchKernelGGL(compact_escapes_kernel, dim3((unsigned)((p.n_tiles + per_block - 1) / per_block)), dim3(kBlock), 0,
                      st, a, esc_vals, esc_cap, esc_off, scan_here ? esc_cnt : nullptr, p.n_tiles, per_wave);

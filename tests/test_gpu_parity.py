@@ -602,6 +602,19 @@ def test_escape_lists_whole_and_cut_short(dev, sigma, layout):
         codec.status.zero_()
 
 
+@pytest.mark.parametrize("L", [33, 66])
+def test_escape_lists_of_many_tiles(dev, L):
+    """More than 65,536 and 131,072 tiles, neither a power of two: 16 and 32 of them to a wavefront of the compaction."""
+    w = make_workload("tiny", device=dev, layout="lhnkd", overrides=dict(L=L, H=3, n=10620, k=1, d=64, sigma=0.9, seed=62))
+    codec = codec_for(w, esc_frac=0.1)
+    codec.predict_residual(w.cand_k, w.cand_v, w.probs, w.act_k, w.act_v)
+    codec.check_status()
+    print(f"  {codec.n_streams * -(-codec.N // 2048)} tiles", flush=True)
+    ref = escape_lists(codec.symbols, w.act_k, w.act_v)
+    assert int(codec.esc_cnt.sum()) == ref.size
+    assert np.array_equal(u16(codec.esc_vals)[:ref.size], ref)
+
+
 @pytest.mark.parametrize("tables", [1, 4])
 @pytest.mark.parametrize("n_streams", [3, 1100])
 def test_word_lists_that_are_too_short(oracle, dev, n_streams, tables):
