@@ -81,8 +81,8 @@ __device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint3
 // of sessions (4096 of 512 positions and 9 candidates: encode 65 us with rows in LDS, 78 in registers for 32, 44 in
 // registers for 16; one session of 4096: 131, 100, 53 us).
 // One session, encode / decode (before: rows in LDS, one load after the other, the decoder's results stored by
-// wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 34 / 51 us (43 / 91),
-// 32,768 of 4 196 / 328 us (246 / 635), 4096 of 20 83 / 93 us (93 / 206), 8192 of 32 235 / 244 us (661 / 655).
+// wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 34 / 41 us (43 / 91),
+// 32,768 of 4 196 / 240 us (246 / 635), 4096 of 20 83 / 93 us (93 / 206), 8192 of 32 235 / 244 us (661 / 655).
 constexpr int kTileGroups = 6;
 constexpr int kTilePos = kTileGroups * kLanes;  // 192 = the three helper wavefronts
 constexpr int kRowWords = (kMaxK + 2) / 2;      // k + 2 cumulative values, two to a word; odd: rows on different banks
@@ -207,7 +207,9 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
                                                            int32_t *__restrict__ chosen, uint32_t *status) {
   // cumulative frequencies cum[0..k+1] of every position of a tile, two to a word, 4096 behind them
   __shared__ uint32_t cums[2][kTilePos][kRowWords];
-  __shared__ int8_t picked[2][kTilePos];  // what a tile's positions decoded to, written out by the helpers
+  // What a tile's positions decoded to, written out by the helpers; up to 8 candidates, their slots: the symbol in which a
+  // slot lies is no part of the chain of steps and found by the helpers, which have made the rows.
+  __shared__ std::conditional_t<MAXK == 8, uint16_t, int8_t> picked[2][kTilePos];
   __shared__ uint16_t wstage[kIdxStageWords];
   const int s = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
   const bool staged = ptr <= (uint64_t)kIdxStageWords;  // uniform
   if (staged)
     for (uint32_t i = threadIdx.x; i < (uint32_t)ptr; i += 256) wstage[i] = words[base + i];
-  uint32_t x = rans_lane ? states[(int64_t)s * kLanes + lane] : kLow;
+  uint32_t x = rans_lane || MAXK == 8 ? states[(int64_t)s * kLanes + (lane & 31)] : kLow;
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
   const int u = threadIdx.x - 64;  // of a helper thread: its place in a tile
@@ -232,63 +234,87 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
   };
   fetch(0);
   __syncthreads();
+  // One tile's steps for up to 8 candidates, in all 64 lanes: the upper half does what the lower does (with it off the
+  // instructions take a third longer).  The row is ten starts, two to a word; the distance from the slot down to the nearest
+  // start at or below it is the smallest of the differences modulo 2^16, and so is the one up to the next.  One start after the
+  // other took twice the instructions: one session of 4096 positions of 8 candidates 43 -> 33 us, of 32,768 of 4 322 -> 234,
+  // 64 sessions of 2048 of 8 24 -> 19.
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  auto code_tile8 = [&](int t, auto from_lds) {
+    constexpr bool kStaged = decltype(from_lds)::value;
+    const int l = lane & 31;
+    const uint32_t below = (1u << l) - 1u;
+    const uint32_t(*tile)[kRowWords] = cums[t & 1];
+    uint32_t v[5];
+#pragma unroll
+    for (int m = 0; m < 5; ++m) v[m] = tile[l][m];
+    for (int gi = 0; gi < kTileGroups; ++gi) {
+      const int g = kTileGroups * t + gi;
+      if (g >= groups) break;  // uniform
+      const bool has = g * kLanes + l < n;
+      uint32_t next_v[5];  // asked for a step ahead
+      const int ahead_gi = gi + 1 < kTileGroups ? gi + 1 : gi;
+#pragma unroll
+      for (int m = 0; m < 5; ++m) next_v[m] = tile[ahead_gi * kLanes + l][m];
+      const uint32_t slot = x & (kScale - 1);
+      const u16x2 at = __builtin_bit_cast(u16x2, slot * 0x10001u), behind = at + (uint16_t)1;
+      u16x2 down = at - __builtin_bit_cast(u16x2, v[0]), up = __builtin_bit_cast(u16x2, v[0]) - behind;
+#pragma unroll
+      for (int m = 1; m < 5; ++m) {
+        const u16x2 c = __builtin_bit_cast(u16x2, v[m]);
+        down = __builtin_elementwise_min(down, (u16x2)(at - c));
+        up = __builtin_elementwise_min(up, (u16x2)(c - behind));
+      }
+      const uint32_t r = down.x < down.y ? down.x : down.y;
+      const uint32_t f = (uint32_t)(up.x < up.y ? up.x : up.y) + r + 1u;
+      picked[t & 1][gi * kLanes + l] = (uint16_t)slot;
+      const uint32_t xn = f * (x >> 12) + r;
+      // Reading lanes are served from the end of the list, lane 0 first.
+      const bool need = has && xn < kLow;
+      const uint32_t mask = (uint32_t)__ballot(need);
+      const uint32_t rank = (uint32_t)__builtin_popcount(mask & below), used = (uint32_t)__builtin_popcount(mask);
+      uint32_t word = 0;
+      if (kStaged) {  // (read by every lane, inside the stage)
+        const uint32_t place = (uint32_t)ptr - 1u - rank;
+        word = wstage[place < (uint32_t)kIdxStageWords ? place : 0u];
+        word = rank < (uint32_t)ptr ? word : 0u;
+      } else if (need && rank < ptr) {
+        word = words[base + ptr - 1 - rank];
+      }
+      corrupt = corrupt || used > ptr;
+      x = need ? (xn << 16) | word : has ? xn : x;
+      ptr = used < ptr ? ptr - used : 0;
+#pragma unroll
+      for (int m = 0; m < 5; ++m) v[m] = next_v[m];
+    }
+  };
   // One tile's steps.  Wavefront 0 touches global memory only where the words are not staged: a wait for a load would
   // also be one for every store before it.
   auto code_tile = [&](int t, auto from_lds) {
     constexpr bool kStaged = decltype(from_lds)::value;
     const uint32_t(*tile)[kRowWords] = cums[t & 1];
-    uint32_t v[5] = {};  // up to 8 candidates: a row whole, asked for a step ahead
-    if (MAXK == 8) {
-#pragma unroll
-      for (int m = 0; m < 5; ++m) v[m] = tile[lane & 31][m];
-    }
     for (int gi = 0; gi < kTileGroups; ++gi) {
       const int g = kTileGroups * t + gi;
       if (g >= groups) break;  // uniform
       const int i = g * kLanes + lane;
       const bool has = rans_lane && i < n;
-      uint32_t next_v[5] = {};
-      if (MAXK == 8) {
-        const int ahead_gi = gi + 1 < kTileGroups ? gi + 1 : gi;
-#pragma unroll
-        for (int m = 0; m < 5; ++m) next_v[m] = tile[ahead_gi * kLanes + (lane & 31)][m];
-      }
       const uint32_t slot = x & (kScale - 1);
       uint32_t sym = 0, cs = 0, next = kScale;
-      if (MAXK == 8) {
-        // the symbol is the number of interval starts cum[1..k] at or below the slot, its start the largest value
-        // at or below the slot and its end the smallest above (what lies behind cum[k+1] = 4096 is taken as that)
-#pragma unroll
-        for (int m = 1; m <= 8; ++m) {
-          uint32_t c = (m & 1) ? v[m >> 1] >> 16 : v[m >> 1] & 0xffffu;
-          c = m <= k ? c : kScale;  // uniform
-          const bool in = c <= slot;
-          cs = in ? c : cs;  // ascending
-          sym += in ? 1u : 0u;
-          const uint32_t above = in ? kScale : c;
-          next = above < next ? above : next;
-        }
-      } else {
-        // the last interval start at or below the slot, by halving; the last one found above it is its end
-        const uint32_t *row = tile[gi * kLanes + (lane & 31)];
-        for (uint32_t half = 32; half; half >>= 1) {
-          if (half > (uint32_t)k) continue;  // uniform
-          const uint32_t at = sym + half, within = at <= (uint32_t)k ? at : (uint32_t)k;
-          const uint32_t w = row[within >> 1];
-          const uint32_t c = at <= (uint32_t)k ? (at & 1 ? w >> 16 : w & 0xffffu) : kScale;
-          const bool in = c <= slot;
-          sym = in ? at : sym;
-          cs = in ? c : cs;
-          next = in ? next : c;
-        }
+      // the last interval start at or below the slot, by halving; the last one found above it is its end
+      const uint32_t *row = tile[gi * kLanes + (lane & 31)];
+      for (uint32_t half = 32; half; half >>= 1) {
+        if (half > (uint32_t)k) continue;  // uniform
+        const uint32_t at = sym + half, within = at <= (uint32_t)k ? at : (uint32_t)k;
+        const uint32_t w = row[within >> 1];
+        const uint32_t c = at <= (uint32_t)k ? (at & 1 ? w >> 16 : w & 0xffffu) : kScale;
+        const bool in = c <= slot;
+        sym = in ? at : sym;
+        cs = in ? c : cs;
+        next = in ? next : c;
       }
       if (has) {
         picked[t & 1][gi * kLanes + lane] = (int8_t)(sym == (uint32_t)k ? -1 : (int)sym);
         x = (next - cs) * (x >> 12) + slot - cs;
-      }
-      if (MAXK == 8) {
-#pragma unroll
-        for (int m = 0; m < 5; ++m) v[m] = next_v[m];
       }
       // Reading lanes are served from the end of the list, lane 0 first.
       const bool need = has && x < kLow;
@@ -313,7 +339,18 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
     if (wave > 0) {
       if (it >= 2) {
         const int64_t i = (int64_t)kTilePos * (it - 2) + u;
-        if (i < n) chosen[(int64_t)s * n + i] = picked[it & 1][u];
+        int32_t sym = (int32_t)picked[it & 1][u];
+        if (MAXK == 8) {  // the number of starts cum[1..k] at or below the slot, in the row of that tile, still in place
+          const uint32_t slot = (uint32_t)sym;
+          sym = 0;
+#pragma unroll
+          for (int m = 1; m <= 8; ++m) {
+            const uint32_t w = cums[it & 1][u][m >> 1], c = (m & 1) ? w >> 16 : w & 0xffffu;
+            sym += m <= k && c <= slot ? 1 : 0;
+          }
+          if (sym == k) sym = -1;
+        }
+        if (i < n) chosen[(int64_t)s * n + i] = sym;
       }
       if (it < tiles) {
         const bool has = (int64_t)kTilePos * it + u < n;
@@ -329,16 +366,23 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
 #pragma unroll
           for (int m = 0; m <= MAXK; m += 2) {
             const uint32_t odd = acc + f[m];
-            if (m <= k + 1) row[m / 2] = acc | (odd << 16);  // uniform
+            if (MAXK == 8 || m <= k + 1) row[m / 2] = acc | (odd << 16);  // uniform (behind the last start: 4096)
             acc = odd + (m < MAXK ? f[m + 1 <= MAXK ? m + 1 : 0] : 0u);
           }
         }
       }
     } else if (it > 0 && it <= tiles) {
-      if (staged)
-        code_tile(it - 1, std::true_type{});
-      else
-        code_tile(it - 1, std::false_type{});
+      if constexpr (MAXK == 8) {
+        if (staged)
+          code_tile8(it - 1, std::true_type{});
+        else
+          code_tile8(it - 1, std::false_type{});
+      } else {
+        if (staged)
+          code_tile(it - 1, std::true_type{});
+        else
+          code_tile(it - 1, std::false_type{});
+      }
     }
     __syncthreads();
   }
