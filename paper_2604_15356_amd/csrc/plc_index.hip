@@ -100,6 +100,7 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
   uint16_t *out = words + word_off[s];
   uint32_t x = kLow;
   uint64_t nw = 0;  // uniform
+  const uint32_t above = ~((2u << (lane & 31)) - 1u);  // the lanes of a half above this one
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
   // tile t holds groups top(t) - 1 down to top(t) - 6, top(t) = groups - 6 t (the encoder walks downwards)
@@ -156,38 +157,33 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
       for (int gi = 0; gi < kTileGroups; ++gi) {
         const int g = groups - kTileGroups * t - 1 - gi;
         if (g < 0) continue;  // uniform
-        const int i = g * kLanes + lane;
-        const bool has = lane < kLanes && i < n;
+        // All 64 lanes: the upper half does what the lower does (with it off the instructions take a third longer) and
+        // stores nothing.
+        const int l = lane & 31;
+        const bool has = g * kLanes + l < n;
         const uint32_t fs = pr[gi].x & 0xffffu, cs = pr[gi].x >> 16;
         // The sequential definition visits lane 31 first: a lane's word comes after those of the
         // emitting lanes above it.
         const bool emit = has && (x >> 20) >= fs;
         const uint32_t mask = (uint32_t)__ballot(emit);
-        if (emit) {
-          const uint32_t above = lane == 31 ? 0u : mask >> (lane + 1);
-          const uint64_t pos = nw + (uint32_t)__builtin_popcount(above);
+        const uint64_t pos = nw + (uint32_t)__builtin_popcount(mask & above);
+        if (emit && lane < kLanes) {
           if (pos < word_cap) {
             out[pos] = (uint16_t)(x & 0xffffu);
           } else {
             raise(status, PLC_ERR_CAPACITY);
           }
-          x >>= 16;
         }
+        x = emit ? x >> 16 : x;
         nw += (uint32_t)__builtin_popcount(mask);
-        if (has) {
-          // x < f * 2^20, so x / f from the reciprocal is less than 2^20 * 4 * 2^-24 off, its whole part one at
-          // most; the remainder puts it right
-          uint32_t q = (uint32_t)((float)x * __uint_as_float(pr[gi].y));
-          int32_t r = (int32_t)(x - q * fs);
-          if (r < 0) {
-            q -= 1;
-            r += (int32_t)fs;
-          } else if (r >= (int32_t)fs) {
-            q += 1;
-            r -= (int32_t)fs;
-          }
-          x = q * kScale + (uint32_t)r + cs;
-        }
+        // x < f * 2^20, so x / f from the reciprocal is less than 2^20 * 4 * 2^-24 off, its whole part one at
+        // most; the remainder puts it right
+        uint32_t q = (uint32_t)((float)x * __uint_as_float(pr[gi].y));
+        int32_t r = (int32_t)(x - q * fs);
+        const int32_t less = r < 0 ? (int32_t)fs : r >= (int32_t)fs ? -(int32_t)fs : 0;
+        q = r < 0 ? q - 1u : r >= (int32_t)fs ? q + 1u : q;
+        r += less;
+        x = has ? q * kScale + (uint32_t)r + cs : x;
       }
     }
     __syncthreads();
