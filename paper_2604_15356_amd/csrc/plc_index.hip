@@ -71,25 +71,28 @@ __device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint3
   return ok;
 }
 
-// Both coders give a session one workgroup of four wavefronts.  The chain of rANS steps is sequential,
+// Both coders give a session one workgroup of four or eight wavefronts.  The chain of rANS steps is sequential,
 // but what a step needs from its position -- the table made from that position's probabilities -- is not:
-// wavefronts 1-3 prepare the tables of the next six groups (192 positions, one per thread, in registers, with the
-// probabilities of the tile after already on their way) while wavefront 0 codes the current six from LDS; one
+// the other wavefronts prepare the tables of the next groups (a position per thread, in registers, with the
+// probabilities of the tile after already on their way) while wavefront 0 codes the current ones from LDS; one
 // barrier per tile.  Bound by latency on both sides.  MAXK, 8, 16 or 32, is the row length the registers are laid out
 // for, and what a position costs whatever its own length: up to 8 candidates, the ordinary case, the search of the
 // decoder runs in registers too; rows of 9 to 16 laid out for 32 took longer than the rows in LDS had with thousands
 // of sessions (4096 of 512 positions and 9 candidates: encode 65 us with rows in LDS, 78 in registers for 32, 44 in
 // registers for 16; one session of 4096: 131, 100, 53 us).
 // One session, encode / decode (before: rows in LDS, one load after the other, the decoder's results stored by
-// wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 34 / 41 us (43 / 91),
-// 32,768 of 4 196 / 240 us (246 / 635), 4096 of 20 83 / 93 us (93 / 206), 8192 of 32 235 / 244 us (661 / 655).
-constexpr int kTileGroups = 6;
-constexpr int kTilePos = kTileGroups * kLanes;  // 192 = the three helper wavefronts
-constexpr int kRowWords = (kMaxK + 2) / 2;      // k + 2 cumulative values, two to a word; odd: rows on different banks
+// wavefront 0, which waited for the stores at every word): 4096 positions of 8 candidates 23 / 31 us (43 / 91),
+// 32,768 of 4 142 / 209 us (246 / 635), 4096 of 20 53 / 78 us (93 / 206), 8192 of 32 204 / 210 us (661 / 655).
+// Where every session can have a compute unit to itself, seven helper wavefronts and tiles of fourteen groups: the tables
+// of a tile took as long as its steps or longer (one session, encode / decode, with three and with seven: 32,768 positions
+// of 4 candidates 157 / 233 and 142 / 209 us, 4096 of 20 87 / 92 and 53 / 78, 8192 of 32 285 / 301 and 204 / 210).  With
+// more sessions the other wavefronts fill the chip, and the larger tiles only cost LDS.
+constexpr int kTileGroupsFew = 14, kTileGroupsMany = 6;
+constexpr int64_t kFewSessions = 256;
 constexpr int kIdxStageWords = 8192;            // decoder: index streams up to this many words are read from LDS
 
-template <int MAXK>
-__global__ __launch_bounds__(256) void index_encode_kernel(const float *__restrict__ probs,
+template <int MAXK, int kTileGroups>
+__global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_encode_kernel(const float *__restrict__ probs,
                                                            const int32_t *__restrict__ chosen, int n, int k,
                                                            uint32_t *__restrict__ states, uint16_t *__restrict__ words,
                                                            const uint64_t *__restrict__ word_off, uint64_t word_cap,
@@ -194,13 +197,16 @@ __global__ __launch_bounds__(256) void index_encode_kernel(const float *__restri
   }
 }
 
-template <int MAXK>
-__global__ __launch_bounds__(256) void index_decode_kernel(const float *__restrict__ probs,
+template <int MAXK, int kTileGroups>
+__global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_decode_kernel(const float *__restrict__ probs,
                                                            const uint32_t *__restrict__ states,
                                                            const uint16_t *__restrict__ words, uint64_t words_len,
                                                            const uint64_t *__restrict__ word_off,
                                                            const uint32_t *__restrict__ n_words, int n, int k,
                                                            int32_t *__restrict__ chosen, uint32_t *status) {
+  constexpr int kTilePos = kTileGroups * kLanes;  // one to a thread of the helper wavefronts
+  constexpr int kRowWords = (MAXK + 2) / 2;       // k + 2 cumulative values, two to a word; odd: rows on different banks
+  static_assert(kRowWords % 2 == 1, "rows on different banks");
   // cumulative frequencies cum[0..k+1] of every position of a tile, two to a word, 4096 behind them
   __shared__ uint32_t cums[2][kTilePos][kRowWords];
   // What a tile's positions decoded to, written out by the helpers; up to 8 candidates, their slots: the symbol in which a
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(256) void index_decode_kernel(const float *__restri
   // renormalising lane does not wait for HBM inside the chain of steps.  A longer one is read in place.
   const bool staged = ptr <= (uint64_t)kIdxStageWords;  // uniform
   if (staged)
-    for (uint32_t i = threadIdx.x; i < (uint32_t)ptr; i += 256) wstage[i] = words[base + i];
+    for (uint32_t i = threadIdx.x; i < (uint32_t)ptr; i += blockDim.x) wstage[i] = words[base + i];
   uint32_t x = rans_lane || MAXK == 8 ? states[(int64_t)s * kLanes + (lane & 31)] : kLow;
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
@@ -441,8 +447,11 @@ extern "C" int plc_index_encode(const float *probs, const int32_t *chosen, int32
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((word_cap > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const auto kernel = k <= 8 ? index_encode_kernel<8> : k <= 16 ? index_encode_kernel<16> : index_encode_kernel<kMaxK>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
+  const bool few = S <= kFewSessions;
+  constexpr int F = kTileGroupsFew, M = kTileGroupsMany;
+  const auto kernel = few ? (k <= 8 ? index_encode_kernel<8, F> : k <= 16 ? index_encode_kernel<16, F> : index_encode_kernel<kMaxK, F>)
+                          : (k <= 8 ? index_encode_kernel<8, M> : k <= 16 ? index_encode_kernel<16, M> : index_encode_kernel<kMaxK, M>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (few ? F : M)), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
                      k, states, words, word_off, word_cap, n_words, status);
   return launch_status();
 }
@@ -453,8 +462,11 @@ extern "C" int plc_index_decode(const float *probs, const uint32_t *states, cons
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((words_len > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const auto kernel = k <= 8 ? index_decode_kernel<8> : k <= 16 ? index_decode_kernel<16> : index_decode_kernel<kMaxK>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(256), 0, static_cast<hipStream_t>(stream), probs, states, words,
+  const bool few = S <= kFewSessions;
+  constexpr int F = kTileGroupsFew, M = kTileGroupsMany;
+  const auto kernel = few ? (k <= 8 ? index_decode_kernel<8, F> : k <= 16 ? index_decode_kernel<16, F> : index_decode_kernel<kMaxK, F>)
+                          : (k <= 8 ? index_decode_kernel<8, M> : k <= 16 ? index_decode_kernel<16, M> : index_decode_kernel<kMaxK, M>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (few ? F : M)), 0, static_cast<hipStream_t>(stream), probs, states, words,
                      words_len, word_off, n_words, n, k, chosen, status);
   return launch_status();
 }

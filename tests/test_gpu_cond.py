@@ -222,6 +222,36 @@ def test_index_coder_at_the_edges_of_rows_and_tiles(oracle, dev, k, n):
     assert int(status.item()) == 0 and np.array_equal(u8(bits).ravel(), O.surprisal_bits(probs, ch, thr).ravel())
 
 
+@pytest.mark.parametrize("S, n", [(1, 447), (2, 448), (256, 449), (3, 897), (257, 191), (260, 192), (257, 385)])
+@pytest.mark.parametrize("k", [8, 9, 32])
+def test_index_coder_with_a_compute_unit_a_session_and_with_more(oracle, dev, S, n, k):
+    """Up to 256 sessions tiles of 448 positions, else of 192, each begun, full and passed; every session against the
+    oracle, and back."""
+    O = oracle
+    from paper_2604_15356_amd import plc
+    rng = np.random.default_rng(1000 * k + n)
+    probs = rng.exponential(size=(S, n, k)).astype(np.float32) ** 2
+    probs /= probs.sum(-1, keepdims=True) * np.float32(1.1)
+    ch = rng.integers(-1, k, size=(S, n)).astype(np.int32)
+    cap = 2 * n + 64
+    ref = O.index_encode(probs, ch, word_cap=cap)
+    dp, dc = torch.from_numpy(probs).to(dev), torch.from_numpy(ch).to(dev)
+    z = lambda count, dt: torch.zeros(count, dtype=dt, device=dev)
+    states, words, n_words, status = z(S * 32, torch.int32), z(S * cap, torch.int16), z(S, torch.int32), z(1, torch.int32)
+    off = torch.arange(S, dtype=torch.int64, device=dev) * cap
+    print(f"{S} sessions k {k} n {n}", flush=True)
+    plc.plc_index_encode(dp, dc, S, n, k, states, words, off, cap, n_words, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(u32(n_words), ref["n_words"])
+    assert np.array_equal(u32(states).ravel(), ref["states"].ravel())
+    for s in range(S):
+        nw, at = int(ref["n_words"][s]), int(ref["word_off"][s])
+        assert np.array_equal(u16(words)[s * cap:s * cap + nw], ref["words"][at:at + nw]), f"session {s}"
+    out = torch.full((S, n), -9, dtype=torch.int32, device=dev)
+    plc.plc_index_decode(dp, states, words, off, n_words, S, n, k, out, status)
+    assert int(status.item()) == 0 and np.array_equal(out.cpu().numpy(), ch)
+
+
 @pytest.mark.parametrize("k", [8, 16, 32])
 @pytest.mark.parametrize("beyond", [False, True])
 def test_index_streams_around_the_words_that_are_staged(oracle, dev, k, beyond):
