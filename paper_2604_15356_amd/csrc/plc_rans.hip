@@ -1007,6 +1007,7 @@ constexpr int kListRegions = 2;  // batches whose words are being packed and are
 constexpr int kPipeStage = kSuperSyms + 48;  // a round's symbols and the group above them, at any 16-byte misalignment
 enum PipeRole { kFeeder0, kFeeder1, kSymbols, kCoder, kPacker0, kPacker1, kWords, kPipeRoles };  // (wavefronts i and i + 4 share a SIMD)
 constexpr int kPipeThreads = 64 * kPipeRoles;
+constexpr int64_t kComputeUnits = 256;  // MI355X
 // Up to two rounds of 512 units the kernels with one chain per workgroup beat the many-unit kernels.  The encoder's
 // LDS lets two units share a compute unit, three with batches of 16 steps, the decoder's two, and the more of them do
 // the less each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at
@@ -1022,6 +1023,16 @@ __host__ __forceinline__ bool encode_in_pipe(int64_t n_units, int64_t syms_per_s
   if (n_units <= kPipeMaxUnits) return true;
   if (syms_per_stream < 32768) return false;
   return per_depth ? n_units <= 1536 || (n_units > 1792 && n_units <= 2304) : n_units <= 1792;
+}
+// Few units below these lengths take the kernel with four wavefronts, which begins and ends sooner (rans_encode_short_kernel).
+// 1 / 256 / 257 / 512 / 768 / 1024 units, four wavefronts and then seven: 2048 symbols 6.2 / 7.1 / 7.1 / 7.6 / 8.7 / 13.6 us and
+// 7.0 / 7.9 / 8.3 / 9.3 / 10.1 / 14.1, 8192 symbols 10.3 / 11.4 / 12.8 / 14.1 / 17.5 / 25.0 and 10.1 / 11.0 / 13.2 / 14.2 / 17.8 /
+// 23.8, 10,240 symbols 11.8 / 13.1 / 15.0 / 16.3 / 20.4 / 29.1 and 11.3 / 12.4 / 15.0 / 16.1 / 19.8 / 27.0.  With four tables:
+// 8192 symbols 15.4 / 16.2 / 18.0 / 18.9 / 23.3 / 34.5 and 15.5 / 16.3 / 19.6 / 20.6 / 25.1 / 34.1, 12,288 symbols 18.3 / 19.2 /
+// 22.2 / 23.3 / 29.3 / 42.7 and 17.8 / 19.0 / 23.4 / 24.5 / 30.0 / 42.0, 20,480 symbols 24.1 / 25.1 / 30.6 / 32.0 / 41.1 / 59.4 and
+// 22.1 / 23.4 / 30.4 / 31.8 / 41.0 / 56.5 (entries of 8 bytes, which the feeders unpack, where a compute unit has more than one).
+__host__ __forceinline__ bool encode_in_short(int64_t n_units, int64_t syms_per_stream, bool per_depth) {
+  return n_units <= kPipeMaxUnits && syms_per_stream < (!per_depth ? 10240 : n_units <= kComputeUnits ? 12288 : 20480);
 }
 constexpr int64_t kChainMaxUnits = 1024;  // the same bound for the decoder of whole-stream units
 // The decoder with one table per depth holds one unit per compute unit (its tables take 128 KB of LDS): two
@@ -1042,7 +1053,6 @@ constexpr int64_t kChainMaxPieces = 1024;
 constexpr int64_t kPiecesPerRound = 512, kPiecesPerRoundCompact = 1024;
 // From this many streams on (more than two workgroups per compute unit) the decoder that reconstructs takes
 // its three-block ring where k <= 4 lets three workgroups share a compute unit.
-constexpr int64_t kComputeUnits = 256;  // MI355X
 constexpr int64_t kDenseStreams = 512;
 constexpr int kCompactMaxK = 4;  // up to here four workgroups of the decoder with 4-byte entries fit a compute unit
 constexpr int kDenseMaxK = 6;  // up to here the kernel's registers (156 at k = 6) leave room for three wavefronts per SIMD
@@ -1631,6 +1641,513 @@ __global__ __launch_bounds__(kPipeThreads, B == 16 ? 6 : ADAPT && WIDE ? 2 : 4) 
     }
   }
 }
+
+// ---------------------------------------------------------------------------
+// Encoder for few, short units: four wavefronts per unit
+// ---------------------------------------------------------------------------
+// Units so short that what comes before the chain of steps and behind it counts as much as the chain: a coder, a feeder, a
+// packer and a mover of symbols and words, one per SIMD of the compute unit.  Against the kernel with seven wavefronts a
+// batch is 16 steps always, no batch of identity steps stands behind the last, the words leave an iteration sooner, and there
+// is less code for the instruction cache to fetch, which every launch begins without.  Its step takes 21 ns where that
+// kernel's takes 15; encode_in_short has the lengths at which one overtakes the other.
+//   mover   brings the symbols from HBM to LDS (64 groups ahead) and the words from LDS to HBM;
+//   feeder  turns every (group, lane) of a batch into its 16-byte table entry at a fixed place of an LDS
+//           ring; a lane without a symbol (ragged top group, or a step past the unit's first group) gets an
+//           identity entry.  It runs two batches ahead of the coder, so that the coder can ask for the next
+//           batch's first entries before the barrier;
+//   coder   the recurrence alone, in the lower half of the lanes, the entries' reads in the wait states behind the compare,
+//           and one LDS write of the four states of four steps;
+//   packer  recovers from the stored states which lanes emitted (x > thr), ranks them with one ballot per two
+//           steps and packs the 16-bit words into an LDS region per batch.
+// They meet at one workgroup barrier per batch of 16 steps.  The coder writes its last four states of a batch in
+// the batch after (and waits for nothing at a barrier), so the packer works two batches behind it.
+// Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer batch it - 4, whose thresholds it has read
+// two iterations earlier: the ring then needs three slots and three units share a compute unit's LDS.  The mover takes in a round
+// of symbols every fourth iteration and sends the words of two batches out in each of the two after it: waiting
+// for symbols is waiting for every store before them as well (one counter), and these are then two iterations
+// old (stores in every iteration held the barrier up every round).
+namespace short_units {
+constexpr int kEntrySlots = 3;  // feeder writes b + 2, coder reads b and b + 1, packer the thresholds of b
+constexpr int kStateSlots = 3;  // coder writes b and the end of b - 1, packer reads b - 2
+constexpr int kListRegion = 2 * kBatchSyms + 8;  // the words of a pair of batches behind up to seven carried ones
+constexpr int kListRegions = 3;  // the packer's, and the up to two in front of it that have not left
+constexpr int kThreads = 256;
+
+// One step from its select on, and the next step's compare: x and the next threshold in, the next x and the mask of its
+// compare out.  Between two of these stand the caller's LDS accesses, two instructions at the least: the wait states that
+// the hardware asks for between a compare and the select that reads its mask.  Written out, because the compiler makes
+// a shift and a select of the one that takes the state's high half as its operand, and puts a wait state behind each
+// piece of assembly whose result the next instruction reads.
+template <EncForm FORM>
+__device__ __forceinline__ void pipe_step(uint32_t &x, uint64_t &emit, const u32x4 e, uint32_t thr_next) {
+  register uint64_t mask asm("vcc") = emit;  // (the only place that this form of the select reads its mask from)
+  uint32_t xr, t, xn;
+#define PLC_PIPE_STEP(QUOTIENT)                                                                                        \
+  asm volatile("v_cndmask_b32_sdwa %0, %4, %4, vcc dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t" \
+               "v_mul_hi_u32 %1, %5, %0\n\t" QUOTIENT                                                                \
+               "v_mul_u32_u24 %1, %1, %6\n\t"                                                                        \
+               "v_add3_u32 %2, %0, %7, %1\n\t"                                                                       \
+               "v_cmp_gt_u32_e32 vcc, %2, %8"                                                                          \
+               : "=&v"(xr), "=&v"(t), "=&v"(xn), "+s"(mask)                                                            \
+               : "v"(x), "v"(e.x), "v"(e.z), "v"(e.w), "v"(thr_next))
+  if constexpr (FORM == kEncPlain) {
+    PLC_PIPE_STEP("");
+  } else if constexpr (FORM == kEncShort) {
+    PLC_PIPE_STEP("v_lshrrev_b32_sdwa %1, %6, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
+  } else {
+    PLC_PIPE_STEP("v_add_u32 %1, %1, %0\n\t"
+                  "v_lshrrev_b32_sdwa %1, %6, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t");
+  }
+#undef PLC_PIPE_STEP
+  x = xn;
+  emit = mask;
+  PLC_PIN();
+}
+
+// One batch of the coder.  `e` holds the entries of its first eight steps on entry and those of the next
+// batch's first eight (at `next`) on return, `emit` the mask of the first step's compare and of the next batch's.  A
+// lane's states before steps 4 q .. 4 q + 3 leave as one 16-byte vector for xb[q], in the first of the four steps
+// after them: `before` holds the last four on return and `held`, where they belong, those of the batch before on
+// entry.  A step asks for entries eight steps ahead (with four the LDS answered late when the helpers were at it: 1.19
+// against 1.11 ms for an encode given the tokens), and one wait a quad leaves those of the quad on their way.
+template <EncForm FORM>
+__device__ __forceinline__ void pipe_batch(uint32_t &x, uint64_t &emit, u32x4 (&e)[kBatch / 4][4], u32x4 &before,
+                                           u32x4 *&held, const u32x4 *eb, const u32x4 *next, u32x4 *xb) {
+  constexpr int kQuads = kBatch / 4;
+#pragma unroll
+  for (int q = 0; q < kQuads; ++q) {
+    u32x4 (&cur)[4] = e[q];
+    u32x4 (&ask)[4] = e[(q + 2) % kQuads];
+    const u32x4 *src = q + 2 < kQuads ? eb + 4 * (q + 2) * kLanes : next + 4 * (q + 2 - kQuads) * kLanes;
+    *held = before;
+    PLC_PIN();
+    ask[0] = src[0];
+    PLC_PIN();
+    before.x = x;
+    pipe_step<FORM>(x, emit, cur[0], cur[1].y);
+    ask[1] = src[kLanes];
+    PLC_PIN();
+    ask[2] = src[2 * kLanes];
+    PLC_PIN();
+    ask[3] = src[3 * kLanes];
+    PLC_PIN();
+    before.y = x;
+    pipe_step<FORM>(x, emit, cur[1], cur[2].y);
+    asm volatile("s_nop 1");
+    PLC_PIN();
+    before.z = x;
+    pipe_step<FORM>(x, emit, cur[2], cur[3].y);
+    __builtin_amdgcn_s_waitcnt(0xc57f);  // lgkmcnt(5)
+    PLC_PIN();
+    asm volatile("s_nop 0");
+    PLC_PIN();
+    before.w = x;
+    pipe_step<FORM>(x, emit, cur[3], e[(q + 1) % kQuads][0].y);
+    held = xb + q * kLanes;
+  }
+}
+
+// ADAPT: one table per bit depth (the *_bucketed call).  Its entries take 8 bytes where three units are to share a
+// compute unit, and unpacking them costs the feeder what the coder saves; WIDE: whole entries, two units to a compute unit
+// (512 units of 262,144 symbols 320 -> 298 us; 768 need the third).
+template <bool ADAPT, bool WIDE = !ADAPT>
+__global__ __launch_bounds__(kThreads) void rans_encode_short_kernel(const RansArgs a) {
+  constexpr int kIdentity = (ADAPT ? PLC_MAX_BITS : 1) * 256;  // index of the entry that leaves a state unchanged
+  constexpr bool kPacked = ADAPT && !WIDE;
+  using Entry = std::conditional_t<kPacked, uint2, uint4>;
+  __shared__ Entry table[kIdentity + 1];
+  // ADAPT: table of each group of a staging round, in the order in which the feeder's halves want them: a full
+  // batch's eight odd groups from the top, then its eight even ones
+  __shared__ __attribute__((aligned(8))) uint8_t table_of_group[2][kSuperGroups];
+  auto group_at = [](int g) { return (g & ~15) + ((g & 1) ? 0 : 8) + 7 - ((g & 15) >> 1); };
+  __shared__ uint4 entry_ring[kEntrySlots][kBatch][kLanes];
+  __shared__ uint4 state_ring[kStateSlots][kBatch / 4][kLanes];
+  __shared__ __attribute__((aligned(16))) uint8_t sym_stage[2][kSymStage];
+  __shared__ __attribute__((aligned(16))) uint16_t word_list[kListRegions][kListRegion];
+  __shared__ uint16_t spare_word[64];
+  __shared__ uint32_t list_fill[kListRegions];  // positions in use of each region of the list
+  static_assert(workgroups_per_cu(sizeof(table) + sizeof(table_of_group) + sizeof(entry_ring) + sizeof(state_ring) +
+                                  sizeof(sym_stage) + sizeof(word_list) + sizeof(spare_word) + sizeof(list_fill)) >=
+                    (ADAPT && WIDE ? 2 : 3),
+                "three units to a compute unit: without the third 513 to 768 units take a second round");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t unit = blockIdx.x;  // one unit per stream, one workgroup per unit
+
+  EncForm form = kEncPlain;  // uniform
+  {  // every wavefront scans the frequencies and builds one of a lane's four entries
+    const int n_tables = ADAPT ? a.n_tables : 1;
+    uint32_t f[ADAPT ? PLC_MAX_BITS : 1][4], cum[ADAPT ? PLC_MAX_BITS : 1];
+    for (int t = 0; t < n_tables; ++t) {
+      const uint32_t total = load_freq4(a.freq + (unit * n_tables + t) * 256, lane, f[t], &cum[t]);
+      if (total != kScale && !(ADAPT && total == 0) && threadIdx.x == 0) raise(a.status, PLC_ERR_INVALID);
+      form = enc_form_for(form, enc_form_of(f[t]));
+    }
+    for (int t = 0; t < n_tables; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (r == wave) {
+          const uint4 e = make_enc_entry(form, f[t][r], cum[t]);
+          if constexpr (kPacked) {
+            table[t * 256 + lane * 4 + r] = pack_enc_entry(e);
+          } else {
+            table[t * 256 + lane * 4 + r] = e;
+          }
+        }
+        cum[t] += f[t][r];
+      }
+    }
+    if (threadIdx.x == 0) {  // never emits, x' = x
+      const uint4 e = make_uint4(0u, 0xffffffffu, 0u, 0u);
+      if constexpr (kPacked) {
+        table[kIdentity] = pack_enc_entry(e);
+      } else {
+        table[kIdentity] = e;
+      }
+    }
+  }
+
+  const uint32_t len = (uint32_t)a.syms_per_stream;
+  const uint8_t *ubase = a.sym_in + unit * a.syms_per_stream;
+  const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(ubase) & 15u);
+  const int32_t G = (int32_t)((len + kLanes - 1) / kLanes);
+  // Batch 0 holds the top G mod 16 groups (a full 16 if that is 0) followed by identity steps; every
+  // later batch is 16 full groups.  Batch b codes groups top(b)-1 down to top(b)-16.
+  const int32_t head = G % kBatch ? G % kBatch : kBatch;
+  const int32_t n_batches = (G - head) / kBatch + 1;
+  auto batch_top = [&](int32_t b) { return b == 0 ? G : G - head - (b - 1) * kBatch; };
+  // Symbol staging rounds of four batches; a round's buffer starts at the 16-byte-aligned address at or
+  // below its lowest symbol, so the symbol at unit offset t sits at  t - 32 * bottom + mis.
+  auto round_bottom = [&](int32_t r) {
+    const int32_t g = batch_top(4 * r + 3) - kBatch;
+    return g > 0 ? g : 0;
+  };
+  const int32_t n_rounds = (n_batches + 3) / 4;
+  const int32_t n_iters = n_batches + 4;
+  uint16_t *wp = a.words_out + a.word_off[unit];
+  const uint32_t pad = __builtin_amdgcn_readfirstlane((uint32_t)((reinterpret_cast<uintptr_t>(wp) >> 1) & 7u));
+  // Restart points: the packer has a record's states and words at hand, the mover its escapes.
+  uint32_t *const points = a.points_out ? a.points_out + unit * a.point_stride * PLC_RESTART_WORDS : nullptr;
+
+  if (wave == 0) {
+    // ---- coder: batch it - 2
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    uint32_t x = kLow;
+    u32x4 e[kBatch / 4][4], before = {0u, 0u, 0u, 0u};
+    const u32x4 *const entries = reinterpret_cast<const u32x4 *>(&entry_ring[0][0][lane & 31]);
+    u32x4 *const states = reinterpret_cast<u32x4 *>(&state_ring[0][0][lane & 31]);
+    u32x4 *held = states + (kStateSlots - 1) * (kBatch / 4) * kLanes;  // (read by nobody yet)
+    lds_barrier();  // iteration 0
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e[j / 4][j % 4] = entries[j * kLanes];
+    lds_barrier();  // iteration 1
+    auto code = [&](auto form_c) {  // a loop per form, and little in it besides the steps
+      constexpr EncForm kForm = decltype(form_c)::value;
+      uint64_t emit = __builtin_amdgcn_uicmp(x, e[0][0].y, 34 /* unsigned > */);
+      constexpr int kEntryStep = kBatch * kLanes, kStateStep = (kBatch / 4) * kLanes;
+      int at = 0, sat = 0;  // uniform
+      const u32x4 *eb = entries;
+      for (int32_t b = 0; b < n_batches; ++b) {
+        at = at == (kEntrySlots - 1) * kEntryStep ? 0 : at + kEntryStep;
+        const u32x4 *next = entries + at;
+        pipe_batch<kForm>(x, emit, e, before, held, eb, next, states + sat);
+        sat = sat == (kStateSlots - 1) * kStateStep ? 0 : sat + kStateStep;
+        eb = next;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();  // iteration b + 2
+        asm volatile("" ::: "memory");
+      }
+    };
+    // (the upper half is switched off: it would ask for the same entries once more, 721 instead of 704 us)
+    if (lane < kLanes) {
+      if (form == kEncLong) {
+        code(std::integral_constant<EncForm, kEncLong>{});
+      } else if (form == kEncPlain) {
+        code(std::integral_constant<EncForm, kEncPlain>{});
+      } else {
+        code(std::integral_constant<EncForm, kEncShort>{});
+      }
+      *held = before;  // the last four states, in place before the barrier behind them
+    }
+    for (int32_t it = n_batches + 2; it < n_iters; ++it) lds_barrier();
+    if (lane < kLanes) {
+      a.states_out[unit * kLanes + lane] = x;
+      if (points) points[lane] = x;
+    }
+  } else if (wave == 1) {
+    // ---- feeder: entries of batch it
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    bool bad_symbol = false;
+    int slot = 0;
+    for (int32_t it = 0; it < n_iters; ++it) {
+      if (it < n_batches) {
+        const int32_t r = it >> 2;
+        const int32_t top = batch_top(it), bottom = round_bottom(r);
+        const uint8_t *sb = sym_stage[r & 1];
+        // lane (half h, l) serves step 2p + h of the batch: group top - 1 - 2p - h, rANS lane l
+        const int half = lane >> 5, l = lane & 31;
+        uint4 *eo = &entry_ring[slot][half][l];
+        if (it > 0) {
+          // 16 full groups: all symbol reads, then all table reads, then all ring writes, so that the LDS
+          // round trips overlap instead of queueing one behind the other
+          const uint8_t *s0 = sb + ((top - bottom - 2 * (kBatch / 2 - 1) - 1 - half) * kLanes + l + (int32_t)mis);
+          uint32_t sy[kBatch / 2];
+          u32x4 e[kBatch / 2];  // native vectors: each entry moves as one 16-byte LDS access
+#pragma unroll
+          for (int p = 0; p < kBatch / 2; ++p) sy[p] = s0[2 * kLanes * (kBatch / 2 - 1 - p)];
+          uint32_t any = 0;
+          if constexpr (ADAPT) {  // the group of step 2p + half sits at top - bottom - 1 - half - 2p of the round
+            const uint2 tg = *reinterpret_cast<const uint2 *>(&table_of_group[r & 1][top - bottom - kBatch + 8 * half]);
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p)  // symbol | table << 8
+              sy[p] = __builtin_amdgcn_perm(p < 4 ? tg.x : tg.y, sy[p], 0x0c0c0400u + ((uint32_t)(p & 3) << 8));
+          }
+          if constexpr (kPacked) {
+            uint2 c[kBatch / 2];
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) c[p] = table[sy[p]];
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) {
+              any |= c[p].y;
+              const uint4 v = unpack_enc_entry(c[p]);
+              e[p] = u32x4{v.x, v.y, v.z, v.w};
+            }
+          } else {
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) e[p] = *reinterpret_cast<const u32x4 *>(&table[sy[p]]);
+#pragma unroll
+            for (int p = 0; p < kBatch / 2; ++p) any |= e[p].w;
+          }
+#pragma unroll
+          for (int p = 0; p < kBatch / 2; ++p) *reinterpret_cast<u32x4 *>(eo + 2 * p * kLanes) = e[p];
+          bad_symbol = bad_symbol || (any & 0x80000000u) != 0;
+        } else {
+          // the top batch: `head` groups, the first of them possibly ragged, then identity steps
+#pragma unroll
+          for (int p = 0; p < kBatch / 2; ++p) {
+            const int j = 2 * p + half;
+            const int64_t t = (int64_t)(top - 1 - j) * kLanes + l;
+            const bool has = j < head && t < (int64_t)len;
+            const int64_t idx = has ? t - (int64_t)bottom * kLanes + mis : 0;
+            uint32_t byte = sb[idx];
+            if (ADAPT && has) byte += (uint32_t)table_of_group[r & 1][group_at(top - 1 - j - bottom)] << 8;
+            const Entry c = table[has ? byte : (uint32_t)kIdentity];
+            if constexpr (kPacked) {
+              bad_symbol = bad_symbol || (c.y & 0x80000000u) != 0;
+              eo[2 * p * kLanes] = unpack_enc_entry(c);
+            } else {
+              bad_symbol = bad_symbol || (c.w & 0x80000000u) != 0;
+              eo[2 * p * kLanes] = c;
+            }
+          }
+        }
+        slot = slot == kEntrySlots - 1 ? 0 : slot + 1;
+      }
+      lds_barrier();
+    }
+    if (bad_symbol) raise(a.status, PLC_ERR_INVALID);  // a symbol with f = 0
+  } else if (wave == 2) {
+    // ---- packer: batch it - 4
+    __syncthreads();  // tables
+    __syncthreads();  // first symbols
+    uint32_t fill = pad;  // uniform: positions of the region in use, the first of them not this pair's words
+    int region = 0;
+    uint32_t gone = 0u - pad;  // words of the regions before (the padding in front of the first taken off)
+    int32_t point_at = points ? a.piece_batches : INT32_MAX;  // the batch that the next record stands in front of
+    uint32_t *record = points;
+    // hardware lane h of a half carries rANS lane 31 - h, which the encoder visits first; a lane serves
+    // step 2p + half, whose state is component 2 * (p & 1) + half of quad p / 2
+    const int half = lane >> 5, rl = 31 - (lane & 31);
+    uint16_t *const spare = &spare_word[lane];
+    // The thresholds are read two batches ahead of the states, while the coder is at their entries, and wait in
+    // registers: three sets, so three iterations a turn.
+    uint32_t thrs[3][kBatch / 2];
+    auto pack = [&](auto turn, int32_t it) {
+      constexpr int kTurn = decltype(turn)::value;  // it mod 3
+      {
+        const uint32_t *ts = &entry_ring[(kTurn + 1) % 3][half][rl].y;  // batch it - 2
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) thrs[kTurn][p] = ts[2 * p * kLanes * 4];
+      }
+      const int32_t b = it - 4;
+      if (b >= 0 && b < n_batches) {
+        const uint32_t(&thr)[kBatch / 2] = thrs[(kTurn + 1) % 3];
+        const uint32_t *xs = reinterpret_cast<const uint32_t *>(&state_ring[(kTurn + 2) % 3][0][rl]) + half;
+        uint16_t *list = word_list[region];
+        // In phases, each over all eight step pairs: reads, emit masks, list positions, stores.  A lane without
+        // a word stores into a slot of its own instead of sitting out the store.
+        uint32_t xps[kBatch / 2], at[kBatch / 2];
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) xps[p] = xs[(p / 2) * kLanes * 4 + 2 * (p & 1)];
+        if (b == point_at) {  // uniform; the states in front of the batch's first step
+          point_at += a.piece_batches;
+          record += PLC_RESTART_WORDS;
+          if (half == 0) record[rl] = xps[0];
+          if (lane == 0) record[kLanes] = gone + fill;
+        }
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) {
+          const uint64_t mask = __ballot(xps[p] > thr[p]);
+          at[p] = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, fill));
+          fill += (uint32_t)__builtin_popcountll(mask);
+        }
+#pragma unroll
+        for (int p = 0; p < kBatch / 2; ++p) *(xps[p] > thr[p] ? list + at[p] : spare) = (uint16_t)xps[p];
+        if ((b & 1) || b == n_batches - 1) {  // on to the next pair's region
+          if (lane == 0) list_fill[region] = fill;
+          region = region == kListRegions - 1 ? 0 : region + 1;
+          gone += fill & ~7u;
+          fill &= 7u;
+        }
+      }
+      lds_barrier();
+    };
+    static_assert(kEntrySlots == 3 && kStateSlots == 3, "three iterations a turn");
+    for (int32_t it = 0; it < n_iters; it += 3) {
+      pack(std::integral_constant<int, 0>{}, it);
+      if (it + 1 < n_iters) pack(std::integral_constant<int, 1>{}, it + 1);
+      if (it + 2 < n_iters) pack(std::integral_constant<int, 2>{}, it + 2);
+    }
+  } else {
+    // ---- mover: symbols of the coming round, words of batch it - 5
+    bool bad_depth = false;
+    uint4 nv[kStagePieces];         // next round's symbols in flight
+    bool ntake[kStagePieces];
+    // ADAPT: depth of group bottom + lane of the next round.  It is looked at when the round's symbols land: where it
+    // is asked for, its range check would have the wavefront, and at the barrier the others, wait for the answer in
+    // every round (964 -> 829 us for 256 units of 1,048,576 symbols).
+    uint32_t next_depth = 1;
+    const uint32_t spp = ADAPT ? (uint32_t)a.syms_per_pos : 1u;
+    const uint8_t *const depth_row =
+        ADAPT ? a.bits + (int64_t)((uint32_t)unit / (uint32_t)a.streams_per_session) * (len / spp) : nullptr;
+    auto round_load = [&](int32_t r) {
+      const int64_t lo = (int64_t)round_bottom(r) * kLanes;
+      int64_t hi = (int64_t)batch_top(4 * r) * kLanes;
+      hi = hi < (int64_t)len ? hi : (int64_t)len;
+#pragma unroll
+      for (int i = 0; i < kStagePieces; ++i) {
+        const int64_t off = lo - (int64_t)mis + (int64_t)(lane + 64 * i) * 16;  // 16-byte aligned in absolute address
+        ntake[i] = r < n_rounds && off < hi;
+        if (ntake[i]) nv[i] = load16_stream(ubase + off);
+      }
+      if (ADAPT) {
+        const int32_t g = round_bottom(r) + lane;
+        next_depth = (r < n_rounds && g < batch_top(4 * r)) ? depth_row[(uint32_t)g * kLanes / spp] : 1u;
+      }
+    };
+    auto round_store = [&](int buf) {
+#pragma unroll
+      for (int i = 0; i < kStagePieces; ++i)
+        if (ntake[i]) *reinterpret_cast<uint4 *>(&sym_stage[buf][(lane + 64 * i) * 16]) = nv[i];
+      if (ADAPT) {
+        const bool known = next_depth >= 1u && next_depth <= (uint32_t)a.n_tables;
+        bad_depth = bad_depth || !known;
+        table_of_group[buf][group_at(lane)] = (uint8_t)(known ? next_depth - 1u : 0u);
+      }
+    };
+    round_load(0);
+    __syncthreads();  // tables
+    round_store(0);
+    round_load(1);
+    __syncthreads();  // first symbols
+    // Words.  Position p of a region stands for the word at 16-byte-aligned address (wp - pad) + vbase + p; the
+    // first `pad` positions of the first are padding in front of the unit's first word.  The complete 16-byte
+    // pieces leave, up to two per lane; the incomplete tail (< 8 words) moves to the front of the next region, in
+    // front of the words that the packer has written or is writing there.
+    const uint32_t cap = a.word_cap < 0x7fffffffull ? (uint32_t)a.word_cap : 0x7fffffffu;  // a unit has < 2^31 symbols
+    uint32_t vbase = 0, rest = pad;
+    const int32_t n_pairs = (n_batches + 1) / 2;
+    int32_t out_pair = 0;  // the next pair of batches whose words leave
+    int region = 0;
+    auto words_out = [&]() {
+      const uint16_t *list = word_list[region];
+      const uint32_t fill = __builtin_amdgcn_readfirstlane(list_fill[region]);
+      region = region == kListRegions - 1 ? 0 : region + 1;
+      const uint32_t full = fill / 8;  // at most 128
+      rest = fill - 8 * full;
+      const uint16_t tail = list[8 * full + (lane & 7)];  // (lanes past the tail read inside the region)
+      if (vbase >= pad && vbase + 8 * full - pad <= cap) {
+        uint16_t *dst = wp + (vbase - pad);  // 16-byte aligned
+        uint4 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)  // (a lane past the last piece reads inside the region)
+          v[h] = *reinterpret_cast<const uint4 *>(list + 8 * (lane + 64 * h));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if ((uint32_t)(lane + 64 * h) < full) *reinterpret_cast<uint4 *>(dst + 8 * (lane + 64 * h)) = v[h];
+      } else {
+        for (uint32_t q = lane; q < 8 * full; q += 64) {
+          const uint32_t v = vbase + q;
+          if (v >= pad && v - pad < cap) wp[v - pad] = list[q];
+        }
+      }
+      vbase += 8 * full;
+      ++out_pair;
+      if ((uint32_t)lane < rest) {
+        if (out_pair < n_pairs) {
+          word_list[region][lane] = tail;
+        } else {  // the incomplete last piece
+          const uint32_t v = vbase + (uint32_t)lane;
+          if (v >= pad && v - pad < cap) wp[v - pad] = tail;
+        }
+      }
+      wave_sync();  // the next pair's reads come behind the tail's way to its front, from other lanes (no barrier
+                    // stands between them where pairs leave one behind the other at the unit's end)
+    };
+    // Escapes, for the restart points: a round's symbols are counted in the stage in the last iteration before others
+    // take their place, in which the mover has nothing else to do.
+    uint32_t esc_mine = 0;  // this lane's, of the rounds so far
+    int32_t point_at = points ? a.piece_batches / 4 : INT32_MAX;  // the round that the next record stands in front of
+    uint32_t *record = points;
+    auto count_round = [&](int32_t r) {
+      if (r == point_at) {
+        point_at += a.piece_batches / 4;
+        record += PLC_RESTART_WORDS;
+        const uint32_t total = wave_sum(esc_mine);
+        if (lane == 0) record[kLanes + 1] = total;
+      }
+      const uint8_t *sb = sym_stage[r & 1];
+      const uint32_t lo = (uint32_t)round_bottom(r) * kLanes, top = (uint32_t)batch_top(4 * r) * kLanes;
+      const uint32_t n = (top < len ? top : len) - lo;
+      if (mis == 0 && n == (uint32_t)kSuperSyms) {  // uniform
+#pragma unroll
+        for (int h = 0; h < kSuperSyms / 1024; ++h) {
+          const uint4 v = *reinterpret_cast<const uint4 *>(&sb[(lane + 64 * h) * 16]);
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)  // a byte is 0xff iff its low seven bits carry into bit 7 and bit 7 is set
+            esc_mine += (uint32_t)__builtin_popcount(((w[i] & 0x7f7f7f7fu) + 0x01010101u) & w[i] & 0x80808080u);
+        }
+      } else {
+        for (uint32_t t = lane; t < n; t += 64) esc_mine += sb[t + mis] == PLC_ESCAPE;
+      }
+    };
+    for (int32_t it = 0; it < n_iters; ++it) {
+      const int32_t phase = it & 3;
+      if (phase == 3 && points && (it >> 2) < n_rounds) count_round(it >> 2);
+      if (phase == 0 && it < n_batches) {  // the feeder has begun a round: the next one's symbols land
+        const int32_t r = it >> 2;
+        round_store((r + 1) & 1);
+        round_load(r + 2);
+      }
+      // (batch it - 5 is packed: in steady state a pair goes out at phase 1 and the next one at phase 2)
+      if ((phase == 1 || phase == 2) && 2 * out_pair + 1 <= it - 5) words_out();
+      lds_barrier();
+    }
+    while (out_pair < n_pairs) words_out();
+    const uint32_t n_words = vbase + rest - pad;
+    const uint32_t esc_total = wave_sum(esc_mine);
+    if (lane == 0) {
+      a.n_words_out[unit] = n_words;
+      if ((uint64_t)n_words > a.word_cap) raise(a.status, PLC_ERR_CAPACITY);
+      if (points) points[kLanes] = n_words, points[kLanes + 1] = esc_total;
+    }
+    if (bad_depth) raise(a.status, PLC_ERR_INVALID);
+  }
+}
+}  // namespace short_units
 
 // ---------------------------------------------------------------------------
 // Decoder
@@ -3667,22 +4184,32 @@ int encode_impl(const uint8_t *symbols, int64_t n_streams, int64_t syms_per_stre
   hipStream_t st = static_cast<hipStream_t>(stream);
   {
     TraceScope trace(PLC_TRACE_RANS_ENCODE, st);
-    if (a.units_per_stream == 1 && encode_in_pipe(a.n_units, syms_per_stream, a.bits != nullptr)) {
+    const dim3 few_grid((unsigned)a.n_units), short_block(short_units::kThreads), pipe_block(kPipeThreads);
+    if (a.units_per_stream == 1 && encode_in_short(a.n_units, syms_per_stream, a.bits != nullptr)) {
+      const bool wide = !a.bits || a.n_units <= 2 * kComputeUnits;
+      trace.kernel("rans_encode_short_kernel<%s, %s>", a.bits ? "true" : "false", wide ? "true" : "false");
+      if (!a.bits) {
+        hipLaunchKernelGGL((short_units::rans_encode_short_kernel<false>), few_grid, short_block, 0, st, a);
+      } else if (wide) {
+        hipLaunchKernelGGL((short_units::rans_encode_short_kernel<true, true>), few_grid, short_block, 0, st, a);
+      } else {
+        hipLaunchKernelGGL((short_units::rans_encode_short_kernel<true, false>), few_grid, short_block, 0, st, a);
+      }
+    } else if (a.units_per_stream == 1 && encode_in_pipe(a.n_units, syms_per_stream, a.bits != nullptr)) {
       const bool wide = !a.bits || a.n_units <= kComputeUnits, few = a.n_units <= 2 * kComputeUnits;
       trace.kernel("rans_encode_pipe_kernel<%s, %d, %s>", a.bits ? "true" : "false", few ? 32 : 16, wide ? "true" : "false");
       // few units: the chain of one unit is the time, so give each unit seven wavefronts
       // (with more units, seven wavefronts per unit cost more in occupancy than the shorter chain gains)
-      const dim3 grid((unsigned)a.n_units), block(kPipeThreads);
       if (!a.bits && few) {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 32>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 32>), few_grid, pipe_block, 0, st, a);
       } else if (!a.bits) {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 16>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<false, 16>), few_grid, pipe_block, 0, st, a);
       } else if (wide) {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, true>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, true>), few_grid, pipe_block, 0, st, a);
       } else if (few) {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 32, false>), few_grid, pipe_block, 0, st, a);
       } else {
-        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 16, false>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((rans_encode_pipe_kernel<true, 16, false>), few_grid, pipe_block, 0, st, a);
       }
     } else if (a.bits && (a.units_per_stream == 1 ? !encode_depths_in_pairs(a.n_units) : a.n_units <= kFewChunks)) {
       launch_encode_depths(a, n_streams, st, trace);
