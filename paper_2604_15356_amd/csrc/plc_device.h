@@ -15,6 +15,7 @@ namespace plc {
 constexpr int kBlock = 256;
 constexpr int kChunk = 8;
 constexpr int kTileSyms = kBlock * kChunk;
+constexpr int64_t kComputeUnits = 256;  // MI355X
 
 constexpr uint32_t kZeroSymbol = 127;
 

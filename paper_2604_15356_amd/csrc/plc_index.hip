@@ -88,7 +88,6 @@ __device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint3
 // of 4 candidates 157 / 233 and 142 / 209 us, 4096 of 20 87 / 92 and 53 / 78, 8192 of 32 285 / 301 and 204 / 210).  With
 // more sessions the other wavefronts fill the chip, and the larger tiles only cost LDS.
 constexpr int kTileGroupsFew = 14, kTileGroupsMany = 6;
-constexpr int64_t kFewSessions = 256;
 constexpr int kIdxStageWords = 8192;            // decoder: index streams up to this many words are read from LDS
 
 template <int MAXK, int kTileGroups>
@@ -436,6 +435,16 @@ int check(const float *probs, int32_t S, int32_t n, int32_t k, const void *state
   return PLC_OK;
 }
 
+// Tiles of fourteen groups or of six (see above).  Up to 192 positions are one tile of six groups, and four wavefronts are
+// sooner at it than eight (256 sessions of 96 positions of 8 candidates, encode 4.06 and 4.18 us).  The decoder of rows of 9
+// to 16 waits longer for the first large tile's tables than for a small one's, two wavefronts to a SIMD, and makes up for it
+// only over many tiles (1 / 256 sessions of 16 candidates, six groups and fourteen: 512 positions 14.5 / 15.3 and 16.4 / 17.0 us,
+// 1024 23.5 / 24.8 and 25.8 / 27.2, 2048 42.3 / 43.6 and 42.7 / 44.9, 4096 78.2 / 80.9 and 77.9 / 80.7, one of 32,768 581 and 555).
+bool large_tiles(int32_t S, int32_t n, int32_t k, bool decode) {
+  const bool late = decode && k > 8 && k <= 16;
+  return S <= kComputeUnits && n >= (late ? 4096 : kTileGroupsMany * kLanes + 1);
+}
+
 }  // namespace
 }  // namespace plc
 
@@ -447,11 +456,11 @@ extern "C" int plc_index_encode(const float *probs, const int32_t *chosen, int32
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((word_cap > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const bool few = S <= kFewSessions;
+  const bool large = large_tiles(S, n, k, false);
   constexpr int F = kTileGroupsFew, M = kTileGroupsMany;
-  const auto kernel = few ? (k <= 8 ? index_encode_kernel<8, F> : k <= 16 ? index_encode_kernel<16, F> : index_encode_kernel<kMaxK, F>)
-                          : (k <= 8 ? index_encode_kernel<8, M> : k <= 16 ? index_encode_kernel<16, M> : index_encode_kernel<kMaxK, M>);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (few ? F : M)), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
+  const auto kernel = large ? (k <= 8 ? index_encode_kernel<8, F> : k <= 16 ? index_encode_kernel<16, F> : index_encode_kernel<kMaxK, F>)
+                            : (k <= 8 ? index_encode_kernel<8, M> : k <= 16 ? index_encode_kernel<16, M> : index_encode_kernel<kMaxK, M>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (large ? F : M)), 0, static_cast<hipStream_t>(stream), probs, chosen, n,
                      k, states, words, word_off, word_cap, n_words, status);
   return launch_status();
 }
@@ -462,11 +471,11 @@ extern "C" int plc_index_decode(const float *probs, const uint32_t *states, cons
   const int rc = check(probs, S, n, k, states, word_off, n_words, chosen, status);
   if (rc) return rc;
   if ((words_len > 0 && !words) || reinterpret_cast<uintptr_t>(words) % 2) return PLC_ERR_INVALID;
-  const bool few = S <= kFewSessions;
+  const bool large = large_tiles(S, n, k, true);
   constexpr int F = kTileGroupsFew, M = kTileGroupsMany;
-  const auto kernel = few ? (k <= 8 ? index_decode_kernel<8, F> : k <= 16 ? index_decode_kernel<16, F> : index_decode_kernel<kMaxK, F>)
-                          : (k <= 8 ? index_decode_kernel<8, M> : k <= 16 ? index_decode_kernel<16, M> : index_decode_kernel<kMaxK, M>);
-  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (few ? F : M)), 0, static_cast<hipStream_t>(stream), probs, states, words,
+  const auto kernel = large ? (k <= 8 ? index_decode_kernel<8, F> : k <= 16 ? index_decode_kernel<16, F> : index_decode_kernel<kMaxK, F>)
+                            : (k <= 8 ? index_decode_kernel<8, M> : k <= 16 ? index_decode_kernel<16, M> : index_decode_kernel<kMaxK, M>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)S), dim3(64 + kLanes * (large ? F : M)), 0, static_cast<hipStream_t>(stream), probs, states, words,
                      words_len, word_off, n_words, n, k, chosen, status);
   return launch_status();
 }

@@ -1007,7 +1007,6 @@ constexpr int kListRegions = 2;  // batches whose words are being packed and are
 constexpr int kPipeStage = kSuperSyms + 48;  // a round's symbols and the group above them, at any 16-byte misalignment
 enum PipeRole { kFeeder0, kFeeder1, kSymbols, kCoder, kPacker0, kPacker1, kWords, kPipeRoles };  // (wavefronts i and i + 4 share a SIMD)
 constexpr int kPipeThreads = 64 * kPipeRoles;
-constexpr int64_t kComputeUnits = 256;  // MI355X
 // Up to two rounds of 512 units the kernels with one chain per workgroup beat the many-unit kernels.  The encoder's
 // LDS lets two units share a compute unit, three with batches of 16 steps, the decoder's two, and the more of them do
 // the less each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at

@@ -252,6 +252,14 @@ def test_index_coder_with_a_compute_unit_a_session_and_with_more(oracle, dev, S,
     assert int(status.item()) == 0 and np.array_equal(out.cpu().numpy(), ch)
 
 
+@pytest.mark.parametrize("S, n", [(3, 192), (256, 193), (2, 4095), (3, 4096), (1, 4513)])
+@pytest.mark.parametrize("k", [9, 16])
+def test_index_coder_on_both_sides_of_the_lengths_for_large_tiles(oracle, dev, S, n, k):
+    """Few sessions take tiles of 448 positions from 193 positions on, the decoder of 9 to 16 candidates from 4096; each
+    session against the oracle, and back."""
+    test_index_coder_with_a_compute_unit_a_session_and_with_more(oracle, dev, S, n, k)
+
+
 @pytest.mark.parametrize("k", [8, 16, 32])
 @pytest.mark.parametrize("beyond", [False, True])
 def test_index_streams_around_the_words_that_are_staged(oracle, dev, k, beyond):
