@@ -1013,15 +1013,18 @@ constexpr int kPipeThreads = 64 * kPipeRoles;
 // 1028: encode 85 / 122 / 164 / 214 and 385 us, with a table per depth 91 / 135 / 180 / 240 and 419 us (with four
 // wavefronts a unit and batches of 16: 102 / 140 / 186 / 260 and 110 / 148 / 198 / 282), decode 190 / 199 / 390 / 394 and 621 us.
 constexpr int64_t kPipeMaxUnits = 1024;
-// Beyond, the encoder's further rounds of 768 still win where streams are long: 32,768 symbols, 1028 / 1536 / 1792 / 2048
-// units 77 / 94 / 107 / 130 us and the many-unit kernel 107 / 109 / 123 / 124; 524,288 symbols 1014 / 1242 / 1388 / 1798 and
-// 1537 / 1555 / 1803 / 1860; but 8192 symbols 31 / 38 / 41 / 49 and 33 / 34 / 38 / 38.  The many-unit kernel with a table per
-// depth holds 1792 units at a time: 32,768 symbols, 1028 / 1536 / 1792 / 2048 / 2304 / 2560 units 88 / 118 / 125 / 149 / 166 /
-// 182 us and 116 / 119 / 120 / 172 / 173 / 174.
+// Beyond, the encoder's further rounds of 768 still win where streams are long, up to seven units for each compute unit: 1028 /
+// 1536 / 1792 / 2048 units of 32,768 symbols 75 / 96 / 105 / 126 us and the many-unit kernel 104 / 106 / 106 / 107, of 524,288
+// 1031 / 1247 / 1426 / 1768 and 1546 / 1658 / 1660 / 1664; but 16,384 symbols 42 / 55 / 60 / 71 and 54 / 56 / 57 / 57.
+// With a table per depth the many-unit kernel holds seven units per compute unit at a time, 1792, so that its second round begins
+// where the third of this one does.  1028 / 1536 / 1537 / 1792 / 1793 / 2304 / 2560 units, four tables, 32,768 symbols 92 / 119 / 122 /
+// 130 / 139 / 175 / 188 us and 108 / 112 / 112 / 115 / 152 / 170 / 171; 49,152 symbols 125 / 164 / 166 / 174 / 191 / 241 / 262 and 157 /
+// 163 / 162 / 164 / 219 / 248 / 249; 131,072 symbols 296 / 375 / 392 / 407 / 454 / 569 / 611 and 403 / 410 / 412 / 415 / 563 / 626 / 626.
 __host__ __forceinline__ bool encode_in_pipe(int64_t n_units, int64_t syms_per_stream, bool per_depth) {
   if (n_units <= kPipeMaxUnits) return true;
-  if (syms_per_stream < 32768) return false;
-  return per_depth ? n_units <= 1536 || (n_units > 1792 && n_units <= 2304) : n_units <= 1792;
+  if (!per_depth) return syms_per_stream >= 32768 && n_units <= 7 * kComputeUnits;
+  return syms_per_stream >= 49152 &&
+         (n_units <= 6 * kComputeUnits || (n_units > 7 * kComputeUnits && n_units <= 9 * kComputeUnits));
 }
 // Few units below these lengths take the kernel with four wavefronts, which begins and ends sooner (rans_encode_short_kernel).
 // 1 / 256 / 257 / 512 / 768 / 1024 units, four wavefronts and then seven: 2048 symbols 6.2 / 7.1 / 7.1 / 7.6 / 8.7 / 13.6 us and
