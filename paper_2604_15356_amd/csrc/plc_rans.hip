@@ -1102,7 +1102,10 @@ __device__ __forceinline__ void pipe_batch(uint32_t &y, uint64_t &emit, u32x4 (&
                                            u32x4 *&held, const u32x4 *eb, const u32x4 *next0, const u32x4 *next,
                                            u32x4 *xb) {
   constexpr int kQuads = B / 4;
-  constexpr int kNoWait = 0xcf7f;  // every counter at its most: nothing but an instruction between two steps
+  // A wait for nothing (every counter at its most): the cheapest instruction to stand between two steps, which has to be
+  // there (see pipe_step).  The steps do not rest on it alone: between two pieces of assembly with nothing in between, the second of
+  // which reads what the first wrote, the compiler puts an s_nop -- as it does behind this wait where that is assembly too.
+  constexpr int kNoWait = 0xcf7f;
 #pragma unroll
   for (int q = 0; q < kQuads; ++q) {
     u32x4 (&cur)[4] = e[q % 4];
@@ -1121,7 +1124,7 @@ __device__ __forceinline__ void pipe_batch(uint32_t &y, uint64_t &emit, u32x4 (&
     __builtin_amdgcn_s_waitcnt(kNoWait);
     PLC_PIN();
     pipe_step<FORM>(y, x[2], emit, cur[2], cur[3].z);
-    __builtin_amdgcn_s_waitcnt(0xc47f);  // lgkmcnt(4): those of the next quad are there, the one behind it may be on its way
+    __builtin_amdgcn_s_waitcnt(0xc47f);  // lgkmcnt(4): the next step needs the next quad's entry; the quad behind it may be on its way
     PLC_PIN();
     pipe_step<FORM>(y, x[3], emit, cur[3], e[(q + 1) % 4][0].z);
     __builtin_amdgcn_s_waitcnt(kNoWait);
