@@ -312,7 +312,7 @@ def test_bucketed_histogram_of_short_streams(oracle, dev, n_tables, spread):
 ])
 @pytest.mark.parametrize("many", [False, True])
 def test_bucketed_encoder_of_chunks(oracle, dev, n_tables, positions, spp, chunk, many):
-    """A table per depth and one unit per wavefront (up to 2560 chunks; few whole streams: seven wavefronts to a unit), or two,
+    """A table per depth and one unit per wavefront (up to 2560 chunks; few whole streams: four or seven wavefronts to a unit), or two,
     against the oracle; word lists at every place inside a line."""
     O = oracle
     from paper_2604_15356_amd import plc

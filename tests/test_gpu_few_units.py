@@ -105,8 +105,8 @@ def test_long_units_beyond_a_round(oracle, dev, n_streams, tables, N, kernel):
 
 
 @pytest.mark.parametrize("n_streams,tables,base,more", [
-    (3, 1, 320, [0, 1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 80, 81, 113, 145]), (516, 1, 320, [0, 1, 15, 16, 33]),
-    (3, 4, 384, [0, 1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 80, 81, 113, 145]), (260, 4, 640, [0, 1, 16, 17, 33]),
+    (17, 1, 320, [0, 1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 80, 81, 113, 145]), (516, 1, 320, [0, 1, 15, 16, 33]),
+    (17, 4, 384, [0, 1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 80, 81, 113, 145]), (260, 4, 640, [0, 1, 16, 17, 33]),
     (516, 4, 640, [0, 1, 15, 16, 33]),
 ])
 def test_long_units_at_the_edges_of_their_batches(oracle, dev, n_streams, tables, base, more):
@@ -116,3 +116,18 @@ def test_long_units_at_the_edges_of_their_batches(oracle, dev, n_streams, tables
         s = Streams(oracle, dev, n_streams, 32 * (base + g), tables, g + tables)
         code, name = s.encode(s.N)
         assert code == 0 and "rans_encode_pipe_kernel" in name, name
+
+
+@pytest.mark.parametrize("n_streams,tables,N", [
+    (3, 1, 10_251), (600, 1, 10_251), (3, 4, 12_320), (300, 4, 20_480), (600, 4, 20_512),  # each form of the long units' kernel
+    (600, 1, 5_728), (300, 4, 5_728), (600, 4, 5_728),                                     # and of the short units'
+])
+def test_word_lists_that_are_too_short_for_few_units(oracle, dev, n_streams, tables, N):
+    """Room for fewer words than a stream has: the first words are in place, what lies between the lists is not touched,
+    states and counts are the whole stream's, and the shortage is reported."""
+    from paper_2604_15356_amd import plc
+    s = Streams(oracle, dev, n_streams, N, tables, N + tables)
+    least = int(s.enc["n_words"].min())
+    for cap in (0, 1, 7, 8, 9, 500, 512, least // 2 // 8 * 8, least // 2 // 8 * 8 + 5, least - 1):
+        code, _ = s.encode(cap)
+        assert code == plc.PLC_ERR_CAPACITY

@@ -377,8 +377,8 @@ def test_few_unit_encoders_side_by_side_on_a_compute_unit(oracle, dev, n_streams
                                               (1028, [1024, 1041])])
 @pytest.mark.parametrize("tables", [1, 4])
 def test_few_unit_encoders_of_either_batch_at_the_edges_of_theirs(oracle, dev, n_streams, groups, tables):
-    """Batches of 32 steps and of 16 (more than 512 units, and more than 1024 long ones): heads of up to two times 16
-    groups, a last batch of half its steps, one batch to five and many; every unit against the oracle."""
+    """Short units, two and three to a compute unit, and more than 1024 long ones: every remainder of a head, one batch to ten
+    and many; every unit against the oracle."""
     from paper_2604_15356_amd import plc
     O = oracle
     for g in groups:
@@ -618,7 +618,7 @@ def test_escape_lists_of_many_tiles(dev, L):
 @pytest.mark.parametrize("tables", [1, 4])
 @pytest.mark.parametrize("n_streams", [3, 1100])
 def test_word_lists_that_are_too_short(oracle, dev, n_streams, tables):
-    """Whole streams (few, and more than the few-unit encoder takes) with room for fewer words than they have, around
+    """Whole streams (few short ones, and more than the few-unit encoders take) with room for fewer words than they have, around
     multiples of 8 in the first pair of batches, in the middle and at the last word, at odd addresses: the first
     words are in place, what lies between the lists is not touched, and the shortage is reported."""
     from paper_2604_15356_amd import plc

@@ -44,6 +44,17 @@ CASES = {
     "cond_k8": ("cond", dict(L=2, H=2, n=300, k=8, d=80, sigma=0.4), "lnkhd", 7),
     "adapt": ("adapt", dict(L=2, H=2, n=400, k=8, d=64), "lhnkd", 5),
     "adapt_many": ("adapt", dict(L=12, H=50, n=70, k=3, d=64), "lhnkd", 2),
+    # the other forms of the encoders of few units, which all write records: see ENCODERS
+    "k20_many": ("mean", dict(L=12, H=50, n=90, k=20, d=64, sigma=0.5), "lhnkd", 2),
+    "k20_short": ("mean", dict(L=3, H=7, n=75, k=20, d=64, sigma=0.5), "lhnkd", 2),
+    "adapt_two": ("adapt", dict(L=10, H=30, n=165, k=3, d=64), "lhnkd", 3),
+    "adapt_three": ("adapt", dict(L=12, H=50, n=169, k=3, d=64), "lhnkd", 3),
+    "adapt_short": ("adapt", dict(L=3, H=7, n=75, k=3, d=64), "lhnkd", 2),
+}
+ENCODERS = {
+    "k8": "pipe_kernel<false, 32, true>", "k20_many": "pipe_kernel<false, 16, true>", "adapt": "pipe_kernel<true, 32, true>",
+    "adapt_two": "pipe_kernel<true, 32, false>", "adapt_three": "pipe_kernel<true, 16, false>",
+    "k20_short": "short_kernel<false, true>", "adapt_short": "short_kernel<true, true>", "adapt_many": "short_kernel<true, false>",
 }
 THR = (3.0, 3.9)
 
@@ -146,6 +157,26 @@ def test_pieces_equal_the_whole_stream(dev, case):
     used = torch.arange(codec.word_cap, device=dev)[None] < codec.n_words[:, None].long()
     assert torch.equal(codec.states, plain["states"]) and torch.equal(codec.n_words, plain["n_words"])
     assert torch.equal(codec.words.reshape(used.shape)[used], plain["words"].reshape(used.shape)[used])
+
+
+@pytest.mark.parametrize("case", list(ENCODERS))
+def test_records_of_every_encoder_fit_together(dev, case):
+    """A record that is not true costs only the time of a second decode, so no other test can tell: every form of the
+    encoders of few units writes records by which the pieces fit together."""
+    from paper_2604_15356_amd import plc
+    codec, encode, decode = _setup(dev, case)
+    around = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in around:
+        e.record()
+    plc.plc_trace_kernel_events(plc.TRACE_RANS_ENCODE, *(e.cuda_event for e in around))
+    try:
+        encode()
+    finally:
+        plc.plc_trace_kernel_events(plc.TRACE_RANS_ENCODE)
+    name = plc.plc_trace_kernel_name(plc.TRACE_RANS_ENCODE)
+    assert ENCODERS[case] in name, name
+    decode(True)
+    assert bool(_pieces_good(codec, case).all())
 
 
 @pytest.mark.parametrize("case", list(CASES))
