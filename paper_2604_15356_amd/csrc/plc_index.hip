@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_encode_kernel
   const uint32_t above = ~((2u << (lane & 31)) - 1u);  // the lanes of a half above this one
   const int groups = (n + kLanes - 1) / kLanes;
   const int tiles = (groups + kTileGroups - 1) / kTileGroups;
-  // tile t holds groups top(t) - 1 down to top(t) - 6, top(t) = groups - 6 t (the encoder walks downwards)
+  // tile t holds the kTileGroups groups below groups - kTileGroups * t (the encoder walks downwards)
   const int u = threadIdx.x - 64, gi_mine = u >> 5, l_mine = u & 31;  // of a helper thread
   auto position = [&](int t) {  // of its symbol in tile t, or -1
     const int g = groups - kTileGroups * t - 1 - gi_mine;
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_encode_kernel
       for (int gi = 0; gi < kTileGroups; ++gi) {
         const int g = groups - kTileGroups * t - 1 - gi;
         if (g < 0) continue;  // uniform
-        // All 64 lanes: the upper half does what the lower does (with it off the instructions take a third longer) and
-        // stores nothing.
+        // All 64 lanes: the upper half does what the lower does and stores nothing.  (With half of the lanes off vector
+        // instructions take a third longer where every compute unit is at work; with one session it makes no difference.)
         const int l = lane & 31;
         const bool has = g * kLanes + l < n;
         const uint32_t fs = pr[gi].x & 0xffffu, cs = pr[gi].x >> 16;
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_decode_kernel
   constexpr int kTilePos = kTileGroups * kLanes;  // one to a thread of the helper wavefronts
   constexpr int kRowWords = (MAXK + 2) / 2;       // k + 2 cumulative values, two to a word; odd: rows on different banks
   static_assert(kRowWords % 2 == 1, "rows on different banks");
-  // cumulative frequencies cum[0..k+1] of every position of a tile, two to a word, 4096 behind them
+  // cumulative frequencies cum[0..k+1] of every position of a tile, two to a word (of rows laid out for 8, 4096 behind them)
   __shared__ uint32_t cums[2][kTilePos][kRowWords];
   // What a tile's positions decoded to, written out by the helpers; up to 8 candidates, their slots: the symbol in which a
   // slot lies is no part of the chain of steps and found by the helpers, which have made the rows.
@@ -235,8 +235,8 @@ __global__ __launch_bounds__(64 + kTileGroups * kLanes) void index_decode_kernel
   };
   fetch(0);
   __syncthreads();
-  // One tile's steps for up to 8 candidates, in all 64 lanes: the upper half does what the lower does (with it off the
-  // instructions take a third longer).  The row is ten starts, two to a word; the distance from the slot down to the nearest
+  // One tile's steps for up to 8 candidates, in all 64 lanes: the upper half does what the lower does (as in the
+  // encoder).  The row is ten starts, two to a word; the distance from the slot down to the nearest
   // start at or below it is the smallest of the differences modulo 2^16, and so is the one up to the next.  One start after the
   // other took twice the instructions: one session of 4096 positions of 8 candidates 43 -> 33 us, of 32,768 of 4 322 -> 234,
   // 64 sessions of 2048 of 8 24 -> 19.

@@ -988,16 +988,19 @@ __global__ __launch_bounds__(W * 64) void rans_encode_pair_kernel(const RansArgs
 //   packer  (two) recovers from the states which lanes emitted, ranks them with one ballot per two
 //           steps and packs the 16-bit words into an LDS region per batch;
 //   words   takes the words from LDS to HBM.
-// What a lone wavefront's instructions cost on gfx950, measured: 2.0 ns of four bytes and 2.35 of eight with all lanes
-// on, 2.6 and 3.0 with any lane off, dependent or not; s_nop 1.9; a read of 16 bytes a lane 2.2 in a row with others
-// and 5.6 between vector instructions, a write of as much 10.  Hence all lanes on, the LDS accesses of four steps in one
-// place, one write for eight steps, and one wait state a step (see pipe_step): 13.4 ns a step alone, where a masked
-// lower half, six wait states and two writes took 21.  What the helpers add is LDS traffic: a kilobyte takes 5.7 ns to write, 1.9
-// to read in a row and 4.4 from random places in 16-byte pieces, and the coder waits its turn.  So the packer reads
-// no thresholds, entries are looked up in two halves of 8 bytes (1.7 ns each), and writes do not stand in a row.
-// They meet at one workgroup barrier per batch (150 cycles, the loops' branches included) of B steps: 32 where two units or
-// one share a compute unit, else 16, whose rings take 43 KB of LDS and not 74.  256 units of 1,048,576 symbols
-// 707 -> 565 us, with a table per depth 815 -> 656.
+// What a lone wavefront's instructions cost on gfx950, one on every compute unit: 1.9 ns a vector instruction of four bytes or
+// of eight, dependent or not, an s_nop 0 and a wait for nothing, 2.65 a select that takes half a register; with the upper half of
+// the lanes off every vector instruction 2.65 (not with one lane off, and not where a single compute unit is at work); a
+// read of 16 bytes a lane 3.9 in a row and 5.1 behind two vector instructions, a write of as much 11.4.  Hence all lanes on, the LDS
+// accesses of four steps in one place, one write for eight steps, and one wait state a step (see pipe_step).  A step
+// takes 14.5 ns where the helpers only stand at the barriers (long reciprocals 16.1) and 18.8 with them at work (20.3); four
+// wavefronts, with a masked lower half, six wait states and two writes, take 23.2 (24.5).  What the helpers add is LDS traffic: a
+// kilobyte takes 5.7 ns to write and 4.4 to read from random places in 16-byte pieces, and the coder waits its turn.  So the
+// packer reads no thresholds, entries are looked up in two halves of 8 bytes (1.7 ns each), and writes do not stand in a row.
+// They meet at one workgroup barrier per batch of B steps: 32 where two units or one share a compute unit, else 16, whose
+// rings and tables take 41 KB of LDS (45 with a table per depth) and not 74 (78, or 86 with whole entries).  256 units of
+// 1,048,576 symbols 707 -> 565 us, with a table per depth 815 -> 656; in a loop of nothing else, at a lower clock, 759 -> 617 and
+// 775 -> 617, with a frequency above 2048 (long reciprocals) 804 -> 665 and 822 -> 661.
 // The coder writes its last eight steps' states of a batch in the batch after (and waits for nothing at a barrier).
 // Iteration `it` of the loop: feeder batch it, coder batch it - 2, packer emissions of batch it - 4 and words of batch
 // it - 5, each packer every second batch.
@@ -1010,8 +1013,8 @@ constexpr int kPipeThreads = 64 * kPipeRoles;
 // Up to two rounds of 512 units the kernels with one chain per workgroup beat the many-unit kernels.  The encoder's
 // LDS lets two units share a compute unit, three with batches of 16 steps, the decoder's two, and the more of them do
 // the less each wavefront issues.  Units of 131,072 symbols, 256 / 512 / 768 / 1024 of them, then the many-unit kernel at
-// 1028: encode 85 / 122 / 164 / 214 and 385 us, with a table per depth 91 / 135 / 180 / 240 and 419 us (with four
-// wavefronts a unit and batches of 16: 102 / 140 / 186 / 260 and 110 / 148 / 198 / 282), decode 190 / 199 / 390 / 394 and 621 us.
+// 1028: encode 85 / 119 / 164 / 222 and 394 us, with four tables 89 / 133 / 184 / 251 and 404 us (with four
+// wavefronts a unit: 102 / 140 / 189 / 266 and 107 / 150 / 198 / 287), decode 190 / 199 / 390 / 394 and 621 us.
 constexpr int64_t kPipeMaxUnits = 1024;
 // Beyond, the encoder's further rounds of 768 still win where streams are long, up to seven units for each compute unit: 1028 /
 // 1536 / 1792 / 2048 units of 32,768 symbols 75 / 96 / 105 / 126 us and the many-unit kernel 104 / 106 / 106 / 107, of 524,288
@@ -1653,8 +1656,9 @@ __global__ __launch_bounds__(kPipeThreads, B == 16 ? 6 : ADAPT && WIDE ? 2 : 4) 
 // Units so short that what comes before the chain of steps and behind it counts as much as the chain: a coder, a feeder, a
 // packer and a mover of symbols and words, one per SIMD of the compute unit.  Against the kernel with seven wavefronts a
 // batch is 16 steps always, no batch of identity steps stands behind the last, the words leave an iteration sooner, and there
-// is less code for the instruction cache to fetch, which every launch begins without.  Its step takes 21 ns where that
-// kernel's takes 15; encode_in_short has the lengths at which one overtakes the other.
+// is less code for the instruction cache to fetch, which every launch begins without.  Its step takes 23 ns where
+// that kernel's takes 19; encode_in_short has the lengths at which one overtakes the other.  (Figures of longer
+// units below are from when this kernel took those too.)
 //   mover   brings the symbols from HBM to LDS (64 groups ahead) and the words from LDS to HBM;
 //   feeder  turns every (group, lane) of a batch into its 16-byte table entry at a fixed place of an LDS
 //           ring; a lane without a symbol (ragged top group, or a step past the unit's first group) gets an
