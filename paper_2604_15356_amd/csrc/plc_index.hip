@@ -86,7 +86,9 @@ __device__ __forceinline__ bool index_table(const float (&p)[MAXK], int k, uint3
 // Where every session can have a compute unit to itself, seven helper wavefronts and tiles of fourteen groups: the tables
 // of a tile took as long as its steps or longer (one session, encode / decode, with three and with seven: 32,768 positions
 // of 4 candidates 157 / 233 and 142 / 209 us, 4096 of 20 87 / 92 and 53 / 78, 8192 of 32 285 / 301 and 204 / 210).  With
-// more sessions the other wavefronts fill the chip, and the larger tiles only cost LDS.
+// more sessions the other wavefronts fill the chip, and the larger tiles cost LDS and registers: 1024 positions, encode / decode, with
+// three and with seven, 256 sessions of 8 candidates 11.7 / 11.9 and 9.6 / 11.7 us, 257 11.8 / 13.0 and 12.9 / 15.3, 512 13.1 / 14.1 and
+// 13.8 / 16.0; 256 of 32 54.6 / 57.2 and 42.5 / 45.0, 257 62.9 / 63.9 and 59.8 / 64.3, 768 of 512 positions 53.2 / 52.9 and 57.2 / 61.5.
 constexpr int kTileGroupsFew = 14, kTileGroupsMany = 6;
 constexpr int kIdxStageWords = 8192;            // decoder: index streams up to this many words are read from LDS
 
